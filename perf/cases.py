@@ -72,7 +72,9 @@ def _log_uniform(rng, lo, hi):
 
 def draw(rng):
     kind = rng.choices(["verify", "merged", "estimate", "rates", "nucleus"], [6, 2, 1, 1, 2])[0]
-    dtype = rng.choices(["bf16", "f32"], [3, 1])[0]
+    # (float32 rows over a large vocabulary have upper sets that differ by less mass than 32-bit sums resolve: which of two
+    # neighbouring thresholds comes out then depends on the order of additions, and masked rows cannot be compared one by one)
+    dtype = "bf16" if kind == "nucleus" else rng.choices(["bf16", "f32"], [3, 1])[0]
     K, L1, L2 = rng.randint(2, 8), rng.choice([0, 0, 1, 2, 3]), rng.randint(2, 5)
     while 1 + L1 + K * L2 > 60:
         K -= 1
@@ -81,7 +83,7 @@ def draw(rng):
     if rng.random() < 0.5:
         V = max(1024, V // 64 * 64)                # padded vocabularies are as common as odd ones
     most = int(_SHARE[kind] * _MOST_BYTES / (2 * N * V * (4 if dtype == "f32" else 2)))
-    B = _log_uniform(rng, 1, max(1, min(256, most)))
+    B = _log_uniform(rng, 1, max(1, min(64 if kind == "nucleus" else 256, most)))
     methods = {"rates": [SPECINFER, NSS, NAIVE, SPECTR]}.get(kind, [SPECINFER, TRAVERSAL, TRAVERSAL, NSS, NAIVE, SPECTR])
     return _case(kind, B, V, K, L1, L2, dtype, rng.choice([0.6, 0.8, 1.0]), rng.choice(methods),
                  rng.choice(["smooth", "peaked", "boosted", "wide"]), top_p=rng.choice([0.9, 0.99]) if kind == "nucleus" else 1.0,
