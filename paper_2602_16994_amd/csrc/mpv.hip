@@ -2709,6 +2709,16 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     return hip_ok(hipGetLastError()) ? MPV_OK : MPV_ERR_HIP;
 }
 
+template <class E>
+static void launch_nucleus(const typename E::T* in, typename E::T* out, int64_t rows, int32_t V, float k32, float top_p,
+                           int keep_all, float* threshold_out, int32_t* kept_out, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(rows));
+    if (V / E::VEC >= kNucleusLongRow)
+        hipLaunchKernelGGL((nucleus_kernel<E, 1024>), grid, dim3(1024), 0, s, in, out, V, k32, top_p, keep_all, threshold_out, kept_out);
+    else
+        hipLaunchKernelGGL((nucleus_kernel<E, 256>), grid, dim3(256), 0, s, in, out, V, k32, top_p, keep_all, threshold_out, kept_out);
+}
+
 // ------------------------------------------------------------------ static scratch
 
 // Scratch of mpv_verify_static: the workspace of one call, held by every device the library
@@ -3168,15 +3178,14 @@ int mpv_nucleus_mask(const void* logits, void* out, int32_t logit_dtype, int64_t
     const float k32 = static_cast<float>(1.4426950408889634 / static_cast<double>(temperature));
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
-    const dim3 grid(static_cast<unsigned>(rows)), block(mpv::kNucleusBlock);
     // top_p = 1 keeps every token: a threshold no mass can miss
     const float p = top_p < 1.0f ? top_p : 0.0f;
     if (logit_dtype == MPV_DTYPE_F32)
-        hipLaunchKernelGGL((mpv::nucleus_kernel<mpv::ElemF32>), grid, block, 0, s, static_cast<const float*>(logits),
-                           static_cast<float*>(out), rows, V, k32, p, top_p < 1.0f ? 0 : 1, threshold_out, kept_out);
+        mpv::launch_nucleus<mpv::ElemF32>(static_cast<const float*>(logits), static_cast<float*>(out), rows, V, k32, p,
+                                          top_p < 1.0f ? 0 : 1, threshold_out, kept_out, s);
     else
-        hipLaunchKernelGGL((mpv::nucleus_kernel<mpv::ElemBF16>), grid, block, 0, s, static_cast<const uint16_t*>(logits),
-                           static_cast<uint16_t*>(out), rows, V, k32, p, top_p < 1.0f ? 0 : 1, threshold_out, kept_out);
+        mpv::launch_nucleus<mpv::ElemBF16>(static_cast<const uint16_t*>(logits), static_cast<uint16_t*>(out), rows, V, k32, p,
+                                           top_p < 1.0f ? 0 : 1, threshold_out, kept_out, s);
     return mpv::hip_ok(hipGetLastError()) ? MPV_OK : MPV_ERR_HIP;
 }
 

@@ -6,18 +6,30 @@
 // whatever reads the row afterwards sees the renormalised truncated distribution.  Tokens with
 // equal logits are kept or dropped together.
 //
-// One workgroup per row:
-//   1. the row's maximum m (the one read from memory that computes next to nothing);
-//   2. tau by bisection over the order-preserving integer keys of float values.  One probe per
-//      step: the mass of {z >= cut} together with the nearest row values on either side of the
-//      cut, to which the bracket then snaps, so a step never lands between two row values
-//      twice (at most 33 steps for float rows, 18 for bfloat16 rows).  A first sweep adds up the
-//      whole row (masses are 2^((z - m) log2(e)/T): the largest is 1) and copies the tokens whose
-//      probability is within 2^-12 of the largest into LDS; if they reach top_p and fit, the
-//      probes run over that copy, else over the row itself (which stays in the caches);
-//   3. the row is written out, masked.
-// The masses are float sums in a fixed order (bitwise reproducible); "reaches top_p" is decided
-// against the sum of the whole row computed the same way, by the same sweep.
+// One workgroup per row.  Masses are 2^((z - m) log2(e)/T), m the row's maximum: the largest is 1.
+//   1. One sweep over the row adds up its mass and copies the tokens that can matter, those
+//      whose probability is within 2^-12 of the largest, into a list in LDS (value and position).
+//   2. If they reach top_p and fit, the row is never looked at again: it is filled with -inf while
+//      tau is found among the listed tokens by bisection over the order-preserving integer keys of
+//      float values (each probe returns the mass of {z >= cut} and the nearest values on either
+//      side of the cut, to which the bracket snaps), and the kept tokens are put back: the row is read
+//      once and written once.
+//   3. Otherwise (flat rows, top_p close to 1) the mass of the row is sorted into bins of 1/32
+//      binary order by logit (a second sweep); the bin that contains tau is known then, and a third
+//      sweep writes the row, keeping what lies above the bin, dropping what lies below, and
+//      listing the bin's own tokens, among which tau is found as in 2.
+//   4. Where a bin holds more tokens than the list (thousands of nearly equal logits), the probes of
+//      the bisection run over the row in memory.
+// What bounds it: traffic, at the rate of a device copy.  10 496 rows of 151 936 bf16 logits, top_p 0.9 held by
+// a few dozen tokens: 1.25 ms = 5.1 TB/s read and written (a large copy reaches 5.1); it was 2.11 ms with a read for
+// the maximum, one for the list and one for the masked copy.  960 rows of 128 256: 115 us, was 350.  Flat rows
+// (top_p 0.99, 40 000 tokens kept; 3): 190 us, was 925 with every probe a pass over the row.
+// The list is filled best if the first cut is good: from the maximum of the workgroup's first 4 vectors per lane
+// (32 768 bf16 logits), which are in registers anyway; from one vector per lane the same rows took 143 us.
+//
+// The list's masses and the bins are added as integers (units of 2^-40), and each wave measures its
+// part of the row's mass against a reference that depends on its own part alone, so the results do
+// not depend on the order in which waves run (bitwise reproducible).
 
 #pragma once
 
@@ -25,8 +37,12 @@
 
 namespace mpv {
 
-constexpr int kNucleusBlock = 512;
 constexpr int kNucleusUnroll = 4;     // 16-byte loads in flight per lane
+// Rows of this many vectors or more get a workgroup of 1024 lanes (two per compute unit), shorter ones 256
+// (eight).  Measured, 1024 / 256 lanes: 960 rows of 16 032 vectors 115 / 177 us, 300 of 8 000 40 / 53, 30 of
+// 16 032 22 / 93; 960 of 4 000 69 / 56, 2 000 of 125 54 / 18, 64 of 128 12 / 9: the line is drawn where few
+// rows still gain (a row's own time counts) and many do not lose much.
+constexpr int kNucleusLongRow = 2048;
 
 // ascending unsigned key of a float (no NaN): negative values reversed, sign bit flipped
 __device__ __forceinline__ uint32_t float_key(float f) {
@@ -37,148 +53,192 @@ __device__ __forceinline__ float key_float(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-template <class E>
-struct NucleusProbeF {
-    float k32, nA;          // p_v = 2^(z_v k32 + nA), up to a factor common to the row
-    float cut;
-    float acc0, acc1;       // mass of {z >= cut}
+
+// Barrier between waves that hand each other values through LDS only: row loads and stores in
+// flight are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// What one probe of the bisection finds out about a cut.
+struct NucleusProbe {
+    double mass;            // of {z >= cut}
     float below, above;     // largest z < cut, smallest z >= cut
     int count;              // |{z >= cut}|
-    __device__ __forceinline__ void init(float k, float na, float c) {
-        k32 = k; nA = na; cut = c; acc0 = 0.f; acc1 = 0.f; below = -INFINITY; above = INFINITY; count = 0;
-    }
-    __device__ __forceinline__ void item(float z, float& acc) {
-        const float e = fast_exp2(fmaf(z, k32, nA));
-        const bool in = z >= cut;
-        acc += in ? e : 0.f;
-        below = in ? below : fmaxf(below, z);
-        above = in ? fminf(above, z) : above;
-        count += in ? 1 : 0;
-    }
-    __device__ __forceinline__ void one(float z) { item(z, acc0); }
-    __device__ __forceinline__ void vec(const float (&z)[E::VEC]) {
-#pragma unroll
-        for (int i = 0; i < E::VEC; i += 2) { item(z[i], acc0); item(z[i + 1], acc1); }
-    }
 };
 
-struct NucleusProbeResult { double mass; float below, above; int count; double whole; };
+// The list has room for this many tokens per wave, 2 KB each: 33 KB for 16 waves.  (With twice the room only
+// one workgroup of 1024 lanes ran per compute unit: 143 against 118 us on the rows above.)
+constexpr int kNucleusPerWave = 256;
+constexpr float kNucleusSpan = 12.f;                   // listed: within this many binary orders of the largest
+constexpr double kNucleusUnit = 1099511627776.0;       // 2^40
+constexpr int kNucleusBins = 1280;                     // of 1/32 binary order; the last one takes the rest
+constexpr float kBinsPerOctave = 32.f;
 
-// One value per workgroup of each of the numbers of a probe (`whole`: a second sum that goes along,
-// scratch has room for both); the same values in every lane.
-__device__ __forceinline__ NucleusProbeResult nucleus_reduce(double mass, float below, float above, int count,
-                                                             double* scratch, float* fscratch, int* iscratch,
-                                                             double whole = 0.0) {
-    constexpr int NW = kNucleusBlock / kWave;
+template <int BLOCK>
+struct NucleusShared {
+    static constexpr int NW = BLOCK / kWave;
+    static constexpr int CAP = NW * kNucleusPerWave;
+    union {
+        struct { float z[CAP]; int at[CAP]; } list;
+        unsigned long long bin[kNucleusBins];
+    };
+    double mass[NW];
+    float lo[NW], hi[NW];
+    int count[NW];
+    int listed;                                        // third sweep: tokens listed
+    uint32_t max_key;                                  // key of the largest logit seen so far
+    int tau_bin;
+    double above_bin, want;                            // mass of the bins above that one; top_p of all of them
+    float tau;
+    int kept;
+};
+
+// mass of a token in units of 2^-40, relative to the largest
+__device__ __forceinline__ double nucleus_units(float z, float k32, float nA) {
+    return floor(static_cast<double>(fast_exp2(fmaf(z, k32, nA))) * kNucleusUnit);
+}
+
+// A probe over the listed tokens by `LANES` lanes (a wave, or the whole workgroup).
+template <int LANES>
+__device__ __forceinline__ NucleusProbe probe_listed(const float* z, int n, float cut, float k32, float nA) {
+    NucleusProbe p;
+    p.mass = 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = 0;
+    for (int i = static_cast<int>(threadIdx.x) % LANES; i < n; i += LANES) {
+        const float v = z[i];
+        const bool in = v >= cut;
+        p.mass += in ? nucleus_units(v, k32, nA) : 0.0;
+        p.below = in ? p.below : fmaxf(p.below, v);
+        p.above = in ? fminf(p.above, v) : p.above;
+        p.count += in ? 1 : 0;
+    }
+    return p;
+}
+__device__ __forceinline__ int wave_sum_i32(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);
+    return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+           (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+__device__ __forceinline__ NucleusProbe wave_total(NucleusProbe p) {
+    p.mass = wave_sum(p.mass);
+    p.below = wave_max(p.below);
+    p.above = -wave_max(-p.above);
+    p.count = wave_sum_i32(p.count);
+    return p;
+}
+template <int BLOCK>
+__device__ __forceinline__ NucleusProbe block_total(NucleusProbe p, NucleusShared<BLOCK>& sh) {
+    constexpr int NW = BLOCK / kWave;
+    p = wave_total(p);
     const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const double m = wave_sum(mass);
-    const double wh = wave_sum(whole);
-    const float lo = wave_max(below);
-    const float hi = -wave_max(-above);
-    const int c = wave_inclusive_scan_i32(count);            // lane 63 holds the wave's total
-    __syncthreads();                                          // the previous probe's results have been read
-    if (lane == kWave - 1) { scratch[w] = m; scratch[NW + w] = wh; fscratch[2 * w] = lo; fscratch[2 * w + 1] = hi; iscratch[w] = c; }
-    __syncthreads();
-    NucleusProbeResult r;
-    r.mass = scratch[0]; r.whole = scratch[NW]; r.below = fscratch[0]; r.above = fscratch[1]; r.count = iscratch[0];
+    lds_barrier();                                     // the previous results have been read
+    if (lane == 0) { sh.mass[w] = p.mass; sh.lo[w] = p.below; sh.hi[w] = p.above; sh.count[w] = p.count; }
+    lds_barrier();
+    p.mass = sh.mass[0]; p.below = sh.lo[0]; p.above = sh.hi[0]; p.count = sh.count[0];
 #pragma unroll
     for (int i = 1; i < NW; ++i) {
-        r.mass += scratch[i];
-        r.whole += scratch[NW + i];
-        r.below = fmaxf(r.below, fscratch[2 * i]);
-        r.above = fminf(r.above, fscratch[2 * i + 1]);
-        r.count += iscratch[i];
+        p.mass += sh.mass[i];
+        p.below = fmaxf(p.below, sh.lo[i]);
+        p.above = fminf(p.above, sh.hi[i]);
+        p.count += sh.count[i];
     }
-    return r;
+    return p;
 }
 
-// the largest value of a row
-template <class E>
-struct RowMaxF {
-    float m0, m1;
-    __device__ __forceinline__ void init() { m0 = -INFINITY; m1 = -INFINITY; }
-    __device__ __forceinline__ void one(float z) { m0 = fmaxf(m0, z); }
-    __device__ __forceinline__ void vec(const float (&z)[E::VEC]) {
-#pragma unroll
-        for (int i = 0; i < E::VEC; i += 2) { m0 = fmaxf(m0, z[i]); m1 = fmaxf(m1, z[i + 1]); }
-    }
-};
-
-// Probe over the whole row in memory.
-template <class E>
-__device__ __forceinline__ NucleusProbeResult nucleus_probe(const typename E::T* z, int V, float k32, float nA, float cut,
-                                                            double* scratch, float* fscratch, int* iscratch) {
-    NucleusProbeF<E> f;
-    f.init(k32, nA, cut);
-    sweep_row<E, kNucleusBlock, kNucleusUnroll>(z, V, f);
-    return nucleus_reduce(static_cast<double>(f.acc0) + static_cast<double>(f.acc1), f.below, f.above, f.count,
-                          scratch, fscratch, iscratch);
-}
-
-// The tokens that can matter are usually few: those whose probability is within 2^-kNucleusSpan of
-// the largest.  One sweep copies them (value and mass) into LDS; if they hold enough mass and fit,
-// tau is found among them without touching the row again.
-constexpr int kNucleusCap = 8192;
-constexpr float kNucleusSpan = 12.f;
-// candidate masses are added as integers (units of 2^-40, exact in a double): the order in which
-// the waves append their candidates does not change any sum
-constexpr double kNucleusUnit = 1099511627776.0;
-
-template <class E>
-struct NucleusCollectF {
-    float k32, nA, cut;
-    float* cand_z;
-    float* cand_e;
-    int* cand_n;
-    float acc0, acc1, below, above;
-    float all0, all1;       // the mass of the whole row
-    int count;
-    __device__ __forceinline__ void init(float k, float na, float c, float* cz, float* ce, int* cn) {
-        k32 = k; nA = na; cut = c; cand_z = cz; cand_e = ce; cand_n = cn;
-        acc0 = 0.f; acc1 = 0.f; all0 = 0.f; all1 = 0.f; below = -INFINITY; above = INFINITY; count = 0;
-    }
-    __device__ __forceinline__ void item(float z, float& acc, float& all) {
-        const float e = fast_exp2(fmaf(z, k32, nA));
-        const bool in = z >= cut;
-        all += e;
-        acc += in ? e : 0.f;
-        below = in ? below : fmaxf(below, z);
-        above = in ? fminf(above, z) : above;
-        count += in ? 1 : 0;
-        const unsigned long long m = __ballot(in);            // lanes of this wave that are here and have one
-        if (m) {
-            const int lane = threadIdx.x & (kWave - 1);
-            const int leader = __ffsll(static_cast<long long>(m)) - 1;
-            int base = 0;
-            if (lane == leader) base = atomicAdd(cand_n, __popcll(m));
-            base = __shfl(base, leader, kWave);
-            const int idx = base + __popcll(m & ((1ull << lane) - 1ull));
-            if (in && idx < kNucleusCap) { cand_z[idx] = z; cand_e[idx] = e; }
+// Bisection: the smallest upper set of row values whose mass reaches `want`, between the set of
+// lo_key (which does, given by tau and kept) and hi_key (from which on nothing is left).
+template <class PROBE>
+__device__ __forceinline__ void nucleus_bisect(uint32_t lo_key, uint32_t hi_key, double want, float& tau, int& kept, PROBE probe) {
+    for (int step = 0; step < 40 && hi_key - lo_key > 1u; ++step) {
+        const NucleusProbe p = probe(key_float(lo_key + (hi_key - lo_key) / 2u));
+        if (p.mass >= want) {
+            tau = p.above;                             // the same upper set, named by its smallest value
+            kept = p.count;
+            lo_key = float_key(tau);
+        } else {
+            hi_key = float_key(p.below) + 1u;          // every cut above `below` has this upper set or less
         }
     }
-    __device__ __forceinline__ void one(float z) { item(z, acc0, all0); }
-    __device__ __forceinline__ void vec(const float (&z)[E::VEC]) {
+}
+// ... among the listed tokens.  Up to 16 per lane the first wave does it alone: a probe is then
+// a few hundred cycles without a barrier, and the other waves' stores of the row go on meanwhile.
+template <int BLOCK>
+__device__ __forceinline__ void bisect_listed(NucleusShared<BLOCK>& sh, int n, uint32_t lo_key, uint32_t hi_key, double want,
+                                              float k32, float nA, float& tau, int& kept) {
+    if (n <= 16 * kWave) {
+        if (threadIdx.x < kWave) {
+            nucleus_bisect(lo_key, hi_key, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+                return wave_total(probe_listed<kWave>(sh.list.z, n, cut, k32, nA));
+            });
+            if (threadIdx.x == 0) { sh.tau = tau; sh.kept = kept; }
+        }
+        lds_barrier();
+        tau = sh.tau;
+        kept = sh.kept;
+    } else {
+        nucleus_bisect(lo_key, hi_key, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+            return block_total<BLOCK>(probe_listed<BLOCK>(sh.list.z, n, cut, k32, nA), sh);
+        });
+    }
+}
+
+// A row of `V` elements: `head` elements before the first 16-byte boundary, nvec vectors, the rest.
+template <class E>
+struct NucleusRow {
+    const typename E::T* z;
+    typename E::T* o;
+    int V, head, nvec, tail0;
+    __device__ __forceinline__ NucleusRow(const typename E::T* z_, typename E::T* o_, int V_) : z(z_), o(o_), V(V_) {
+        const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(z) & 15u) / sizeof(typename E::T));
+        head = mis ? min(E::VEC - mis, V) : 0;
+        nvec = (V - head) / E::VEC;
+        tail0 = head + nvec * E::VEC;
+    }
+    // Calls f(values, position of the first, raw vector, inside) for every vector, all lanes of a wave
+    // together (lanes past the end: inside = false, -inf values), then edge(value, position, inside) for
+    // the elements before and after.  U loads per lane are in flight: with four workgroups per compute unit
+    // (64 registers per lane) the other workgroups' work covers their latency.  begin(vectors) sees the
+    // first U vectors of every lane before any of them is used.
+    struct Nothing { template <class R> __device__ __forceinline__ void operator()(const R&) const {} };
+    template <int BLOCK, int U, class F, class G, class H = Nothing>
+    __device__ __forceinline__ void sweep(F f, G edge, H begin = H()) const {
+        const int tid = threadIdx.x;
+        const typename E::T* const base = z + head;
+        for (int i0 = 0; i0 < nvec; i0 += BLOCK * U) {
+            uint4 raw[U];
 #pragma unroll
-        for (int i = 0; i < E::VEC; i += 2) { item(z[i], acc0, all0); item(z[i + 1], acc1, all1); }
+            for (int u = 0; u < U; ++u) raw[u] = load_raw_at(base, min(i0 + u * BLOCK + tid, nvec - 1));
+            if (i0 == 0) begin(raw);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * BLOCK + tid;
+                const bool inside = i < nvec;
+                if (!inside) raw[u] = NegInfVec<E>::v();
+                float a[E::VEC];
+                E::unpack(raw[u], a);
+                f(a, head + i * E::VEC, raw[u], inside);
+            }
+        }
+        if (head > 0) {
+            const bool inside = tid < head;
+            edge(inside ? E::load_one_global(z + tid) : -INFINITY, tid, inside);
+        }
+        if (tail0 < V) {
+            const bool inside = tail0 + tid < V;
+            edge(inside ? E::load_one_global(z + tail0 + tid) : -INFINITY, tail0 + tid, inside);
+        }
+    }
+    __device__ __forceinline__ void store_vec(int e, const uint4& v) const {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        const v4u t = {v.x, v.y, v.z, v.w};
+        *as_global(reinterpret_cast<v4u*>(o + e)) = t;
     }
 };
-
-// Probe over the n candidates in LDS; masses in units of 2^-40.
-__device__ __forceinline__ NucleusProbeResult nucleus_probe_candidates(const float* cand_z, const float* cand_e, int n, float cut,
-                                                                       double* scratch, float* fscratch, int* iscratch) {
-    double mass = 0.0;
-    float below = -INFINITY, above = INFINITY;
-    int count = 0;
-    for (int i = threadIdx.x; i < n; i += kNucleusBlock) {
-        const float z = cand_z[i];
-        const bool in = z >= cut;
-        mass += in ? floor(static_cast<double>(cand_e[i]) * kNucleusUnit) : 0.0;
-        below = in ? below : fmaxf(below, z);
-        above = in ? fminf(above, z) : above;
-        count += in ? 1 : 0;
-    }
-    return nucleus_reduce(mass, below, above, count, scratch, fscratch, iscratch);
-}
 
 template <class E> struct MaskedStore;
 template <> struct MaskedStore<ElemF32> {
@@ -190,6 +250,9 @@ template <> struct MaskedStore<ElemF32> {
         return o;
     }
     __device__ static __forceinline__ float to_elem(float v) { return v; }
+    __device__ static __forceinline__ uint4 pack(const float (&v)[4]) {
+        return make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+    }
 };
 template <> struct MaskedStore<ElemBF16> {
     static constexpr uint32_t kNegInf = 0xff80u;
@@ -204,118 +267,328 @@ template <> struct MaskedStore<ElemBF16> {
         return o;
     }
     __device__ static __forceinline__ uint16_t to_elem(float v) { return static_cast<uint16_t>(__float_as_uint(v) >> 16); }
+    __device__ static __forceinline__ uint32_t two(float lo, float hi) {       // (values that are bf16 numbers already)
+        return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
+    }
+    __device__ static __forceinline__ uint4 pack(const float (&v)[8]) {
+        return make_uint4(two(v[0], v[1]), two(v[2], v[3]), two(v[4], v[5]), two(v[6], v[7]));
+    }
+};
+
+
+// Per-wave part of the first sweep: the mass of what the wave has seen, against a reference that is
+// the largest logit it has seen (or the largest of the workgroup's first vectors), and the wave's
+// own run of the list (no atomic, no wait: a listed token costs a few instructions).
+template <class E, int BLOCK>
+struct NucleusCollect {
+    NucleusShared<BLOCK>& sh;
+    float k32, span;        // span: of what is listed, in units of the logits
+    int first;              // the wave's run of the list starts here
+    float mz, mk;           // the reference: mk = mz * k32 (the same in every lane of the wave)
+    float cut, thr;         // listed: logits >= cut; a vector whose terms add up to less than thr has none
+    float s;                // this lane's mass, in units of the reference
+    int n;                  // tokens listed by this wave (more than fit: too many)
+    __device__ __forceinline__ void init(float k, float top, int wave) {
+        k32 = k; span = kNucleusSpan / k; first = wave * kNucleusPerWave;
+        mz = top; mk = top > -INFINITY ? top * k : OnlineLse::kFloor;
+        s = 0.f; n = 0;
+        set_cut(top);
+    }
+    // what to list depends on the largest logit any wave has seen (asked for now and then: an old one
+    // only means that more is listed than need be; what is within the span is sorted out at the end)
+    __device__ __forceinline__ void refresh() {
+        set_cut(uniform_f32(key_float(__hip_atomic_load(&sh.max_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))));
+    }
+    __device__ __forceinline__ void set_cut(float top) {
+        const bool none = !(top > -INFINITY) || n > kNucleusPerWave;     // nothing but -inf so far, or no room left
+        cut = none ? INFINITY : top - span;
+        // (0.98: the rounding of the terms; 0.9: a logit above the reference must always be noticed)
+        thr = none ? 0.9f : fminf(0.9f, 0.98f * fast_exp2(fmaf(cut, k32, -mk)));
+    }
+    template <int COUNT>
+    __device__ __forceinline__ float terms(const float (&a)[COUNT]) const {
+        float t0 = fast_exp2(fmaf(a[0], k32, -mk)), t1 = COUNT > 1 ? fast_exp2(fmaf(a[COUNT > 1 ? 1 : 0], k32, -mk)) : 0.f;
+#pragma unroll
+        for (int i = 2; i + 1 < COUNT; i += 2) {
+            t0 += fast_exp2(fmaf(a[i], k32, -mk));
+            t1 += fast_exp2(fmaf(a[i + 1], k32, -mk));
+        }
+        return t0 + t1;
+    }
+    template <int COUNT>
+    __device__ __forceinline__ void add(const float (&a)[COUNT], int e0) {
+        float v = terms(a);
+        if (__builtin_amdgcn_ballot_w64(!(v < thr)) != 0ull) {
+            float lm = a[0];
+#pragma unroll
+            for (int i = 1; i < COUNT; ++i) lm = fmaxf(lm, a[i]);
+            if (__builtin_amdgcn_ballot_w64(lm > mz) != 0ull) {        // a new largest logit
+                const float nz = wave_max(lm), nmk = nz * k32;
+                s *= fast_exp2(mk - nmk);
+                mz = nz; mk = nmk;
+                v = terms(a);
+                if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&sh.max_key, float_key(nz));
+                set_cut(fmaxf(nz, cut + span));
+            }
+#pragma unroll
+            for (int i = 0; i < COUNT; ++i) {
+                const unsigned long long hit = __builtin_amdgcn_ballot_w64(a[i] >= cut);
+                if (hit) {
+                    const int mine = n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(hit >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(hit), 0u)));
+                    if (a[i] >= cut && mine < kNucleusPerWave) { sh.list.z[first + mine] = a[i]; sh.list.at[first + mine] = e0 + i; }
+                    n += __popcll(hit);
+                }
+            }
+        }
+        s += v;
+    }
 };
 
 // top_p in (0, 1): see the file header; keep_all: top_p = 1, nothing is dropped (tau = the row's
 // minimum).  threshold_out / kept_out may be null.
-template <class E>
-__global__ __launch_bounds__(kNucleusBlock) void nucleus_kernel(const typename E::T* in, typename E::T* out, int64_t rows,
-                                                                int V, float k32, float top_p, int keep_all,
-                                                                float* threshold_out, int32_t* kept_out) {
+template <class E, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in, typename E::T* out, int V, float k32,
+                                                        float top_p, int keep_all, float* threshold_out, int32_t* kept_out) {
     using T = typename E::T;
-    constexpr int NW = kNucleusBlock / kWave;
-    __shared__ double scratch[2 * NW];
-    __shared__ float fscratch[2 * NW];
-    __shared__ int iscratch[NW];
-    __shared__ float cand_z[kNucleusCap], cand_e[kNucleusCap];
-    __shared__ int cand_n;
+    __shared__ NucleusShared<BLOCK> sh;
     const int64_t r = blockIdx.x;
-    const T* z = in + r * V;
-    T* o = out + r * V;
+    const NucleusRow<E> row(in + r * V, out + r * V, V);
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
 
     float tau = -INFINITY;                                    // so far: everything is kept
     int kept = V;
-    // 1. the maximum (the same value in every lane)
+    bool written = false;
     float row_max = -INFINITY;
+    double want = 0.0;                                        // top_p of the row's mass, in units
     if (!keep_all) {
-        RowMaxF<E> mf;
-        mf.init();
-        sweep_row<E, kNucleusBlock, kNucleusUnroll>(z, V, mf);
-        const NucleusProbeResult top = nucleus_reduce(0.0, fmaxf(mf.m0, mf.m1), INFINITY, 0, scratch, fscratch, iscratch);
-        row_max = top.below;
-    }
-    // 2. tau.  The masses a probe adds up are 2^(z k32 + nA) = 2^((z - m) k32); over the whole row
-    //    they add up to S.  (A row of -inf only has nothing to drop.)
-    if (!keep_all && row_max > -INFINITY) {
+        // ---- first sweep: the row's mass, its maximum, the list
+        if (tid == 0) sh.max_key = float_key(-INFINITY);
+        lds_barrier();
+        NucleusCollect<E, BLOCK> c{sh};
+        c.init(k32, -INFINITY, wave);
+        int countdown = 0;
+        row.template sweep<BLOCK, kNucleusUnroll>(
+            [&](const float (&a)[E::VEC], int e0, const uint4&, bool) __attribute__((always_inline)) {
+                if (countdown == 0) { c.refresh(); countdown = kNucleusUnroll; }
+                --countdown;
+                c.add(a, e0);
+            },
+            [&](float z, int e, bool) __attribute__((always_inline)) {
+                const float a[1] = {z};
+                c.add(a, e);
+            },
+            [&](const uint4 (&raw)[kNucleusUnroll]) __attribute__((always_inline)) {
+                // every wave starts from the largest of the workgroup's first vectors
+                float m = -INFINITY;
+#pragma unroll
+                for (int u = 0; u < kNucleusUnroll; ++u) {
+                    float a[E::VEC];
+                    E::unpack(raw[u], a);
+#pragma unroll
+                    for (int i = 0; i < E::VEC; ++i) m = fmaxf(m, a[i]);
+                }
+                m = wave_max(m);
+                if (lane == 0) atomicMax(&sh.max_key, float_key(m));
+                lds_barrier();
+                c.init(k32, uniform_f32(key_float(sh.max_key)), wave);
+                lds_barrier();                                // everybody starts from the same maximum
+            });
+        lds_barrier();                                        // the list and the maximum are complete
+        row_max = uniform_f32(key_float(sh.max_key));
         const float nA = -row_max * k32;
-        if (threadIdx.x == 0) cand_n = 0;
-        __syncthreads();
-        const float cut0 = row_max - kNucleusSpan / k32;
-        NucleusCollectF<E> cf;
-        cf.init(k32, nA, cut0, cand_z, cand_e, &cand_n);
-        sweep_row<E, kNucleusBlock, kNucleusUnroll>(z, V, cf);
-        const NucleusProbeResult first = nucleus_reduce(static_cast<double>(cf.acc0) + static_cast<double>(cf.acc1),
-                                                        cf.below, cf.above, cf.count, scratch, fscratch, iscratch,
-                                                        static_cast<double>(cf.all0) + static_cast<double>(cf.all1));
-        const double want = static_cast<double>(top_p) * first.whole;
-        uint32_t lo_key, hi_key = float_key(row_max) + 1u;    // cuts from hi_key on leave nothing above them
-        bool in_lds = false;
-        if (first.mass >= want) {                             // tau >= cut0
-            tau = first.above;                                // the upper set of cut0, named by its smallest value
-            kept = first.count;
-            lo_key = float_key(tau);
-            in_lds = first.count <= kNucleusCap;
-        } else {                                              // tau < cut0: the candidates are not enough
-            lo_key = float_key(-INFINITY);
-            hi_key = float_key(first.below) + 1u;
+        {   // the row's mass: each wave's part, brought to the row's maximum
+            const double part = wave_sum(static_cast<double>(c.s)) * exp2(static_cast<double>(c.mk) + static_cast<double>(nA));
+            NucleusProbe p;
+            p.mass = lane == 0 ? part : 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = 0;
+            want = static_cast<double>(top_p) * block_total<BLOCK>(p, sh).mass * kNucleusUnit;
         }
-        if (in_lds) {
-            const int n = first.count;
-            const double want_units = want * kNucleusUnit;
-            // everything at or above cut0 is in LDS; is it still enough counted in units?
-            const NucleusProbeResult c0 = nucleus_probe_candidates(cand_z, cand_e, n, cut0, scratch, fscratch, iscratch);
-            if (c0.mass >= want_units) {
-                for (int step = 0; step < 40 && hi_key - lo_key > 1u; ++step) {
-                    const float cut = key_float(lo_key + (hi_key - lo_key) / 2u);      // tau < cut <= maximum
-                    const NucleusProbeResult p = nucleus_probe_candidates(cand_z, cand_e, n, cut, scratch, fscratch, iscratch);
-                    if (p.mass >= want_units) {
-                        tau = p.above;                        // the same upper set, named by its smallest value
-                        kept = p.count;
-                        lo_key = float_key(tau);
-                    } else {
-                        hi_key = float_key(p.below) + 1u;     // every cut above `below` has this upper set or less
+        if (row_max > -INFINITY) {                            // (a row of -inf only has nothing to drop)
+            // what is within the span of the maximum moves to the front of the list
+            const float cut0 = row_max - kNucleusSpan / k32;
+            int listed = 0;
+            bool complete = true;
+            {
+                constexpr int PER = kNucleusPerWave / kWave;
+                float z[PER];
+                int at[PER], within = 0;
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    const int j = i * kWave + lane;
+                    z[i] = -INFINITY; at[i] = 0;
+                    if (j < min(c.n, kNucleusPerWave)) { z[i] = sh.list.z[wave * kNucleusPerWave + j]; at[i] = sh.list.at[wave * kNucleusPerWave + j]; }
+                    within += __popcll(__builtin_amdgcn_ballot_w64(z[i] >= cut0));
+                }
+                if (lane == 0) sh.count[wave] = c.n > kNucleusPerWave ? -1 : within;
+                lds_barrier();                                // (and the runs have been read)
+                int before = 0;
+                for (int w = 0; w < NucleusShared<BLOCK>::NW; ++w) {
+                    const int k = __builtin_amdgcn_readfirstlane(sh.count[w]);
+                    if (k < 0) complete = false;
+                    if (w < wave) before += k;
+                    listed += k;
+                }
+                if (complete) {
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) {
+                        const unsigned long long in = __builtin_amdgcn_ballot_w64(z[i] >= cut0);
+                        if (in) {
+                            const int mine = before + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(in >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(in), 0u)));
+                            if (z[i] >= cut0) { sh.list.z[mine] = z[i]; sh.list.at[mine] = at[i]; }
+                            before += __popcll(in);
+                        }
                     }
                 }
-                hi_key = lo_key;                              // done
-            } else {                                          // within rounding of top_p at cut0: decide in memory
-                tau = -INFINITY;
-                kept = V;
-                lo_key = float_key(-INFINITY);
-                hi_key = float_key(row_max) + 1u;
+                lds_barrier();
             }
-        }
-        for (int step = 0; step < 40 && hi_key - lo_key > 1u; ++step) {
-            const float cut = key_float(lo_key + (hi_key - lo_key) / 2u);
-            const NucleusProbeResult p = nucleus_probe<E>(z, V, k32, nA, cut, scratch, fscratch, iscratch);
-            if (p.mass >= want) {
-                tau = p.above;
-                kept = p.count;
-                lo_key = float_key(tau);
+            NucleusProbe all;
+            all.mass = -1.0;
+            if (complete) all = block_total<BLOCK>(probe_listed<BLOCK>(sh.list.z, listed, cut0, k32, nA), sh);
+            if (all.mass >= want) {
+                // ---- tau is among the listed tokens: fill the row, find tau, put the kept tokens back
+                const uint4 fill = NegInfVec<E>::v();
+                for (int i = tid; i < row.nvec; i += BLOCK) row.store_vec(row.head + i * E::VEC, fill);
+                if (tid < row.head) *as_global(row.o + tid) = MaskedStore<E>::to_elem(-INFINITY);
+                if (row.tail0 + tid < V) *as_global(row.o + row.tail0 + tid) = MaskedStore<E>::to_elem(-INFINITY);
+                tau = all.above;
+                kept = all.count;
+                bisect_listed<BLOCK>(sh, listed, float_key(tau), float_key(row_max) + 1u, want, k32, nA, tau, kept);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's share of the fill has been performed
+                lds_barrier();                                        // ... and everybody's
+                for (int i = tid; i < listed; i += BLOCK) {
+                    const float z = sh.list.z[i];
+                    if (z >= tau) *as_global(row.o + sh.list.at[i]) = MaskedStore<E>::to_elem(z);
+                }
+                written = true;
             } else {
-                hi_key = float_key(p.below) + 1u;
+                // ---- second sweep: the mass of every bin (bins are ordered as the logits are)
+                lds_barrier();                                        // the list has been read
+                for (int i = tid; i < kNucleusBins; i += BLOCK) sh.bin[i] = 0ull;
+                lds_barrier();
+                auto into_bin = [&](float z) __attribute__((always_inline)) {
+                    const float y = fmaf(z, k32, nA);
+                    const int b = static_cast<int>(fminf(fmaxf(-kBinsPerOctave * y, 0.f), kNucleusBins - 1.f));
+                    const unsigned long long units = static_cast<unsigned long long>(fast_exp2(y) * static_cast<float>(kNucleusUnit));
+                    if (units) atomicAdd(&sh.bin[b], units);
+                };
+                row.template sweep<BLOCK, 2>(
+                    [&](const float (&a)[E::VEC], int, const uint4&, bool) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int i = 0; i < E::VEC; ++i) into_bin(a[i]);
+                    },
+                    [&](float z, int, bool) __attribute__((always_inline)) { into_bin(z); });
+                lds_barrier();
+                if (wave == 0) {                              // the bin that takes the running mass to `want`
+                    constexpr int PER = kNucleusBins / kWave;
+                    static_assert(kNucleusBins % kWave == 0, "whole bins per lane");
+                    double mine = 0.0;
+                    for (int i = 0; i < PER; ++i) mine += static_cast<double>(sh.bin[lane * PER + i]);
+                    const double incl = wave_inclusive_scan(mine);
+                    // (of the row's mass as the bins have it: added up from the very same terms)
+                    want = static_cast<double>(top_p) * lane_f64(incl, kWave - 1);
+                    if (lane == 0) sh.want = want;
+                    const unsigned long long reach = __builtin_amdgcn_ballot_w64(incl >= want);
+                    if (lane == 0) sh.tau_bin = -1;
+                    if (reach != 0ull && lane == __ffsll(static_cast<long long>(reach)) - 1) {
+                        double run = incl - mine;
+                        for (int i = 0; i < PER; ++i) {
+                            const double m = static_cast<double>(sh.bin[lane * PER + i]);
+                            if (run + m >= want || i == PER - 1) { sh.tau_bin = lane * PER + i; sh.above_bin = run; break; }
+                            run += m;
+                        }
+                    }
+                }
+                lds_barrier();
+                const int tb = __builtin_amdgcn_readfirstlane(sh.tau_bin);
+                const double above_bin = sh.above_bin;
+                want = sh.want;
+                // how many tokens the bin holds at most: its mass over the smallest a token of it can have
+                // (one unit less for each token's rounding down)
+                bool fits = tb >= 0 && tb < kNucleusBins - 1;
+                if (fits) {
+                    const double least = floor(static_cast<double>(fast_exp2(-(static_cast<float>(tb) + 1.01f) / kBinsPerOctave)) * kNucleusUnit) - 1.0;
+                    fits = least >= 1.0 && static_cast<double>(sh.bin[tb]) <= least * NucleusShared<BLOCK>::CAP;
+                }
+                lds_barrier();                                // the bins have been read
+                if (fits) {
+                    // ---- third sweep: write the row, list the bin's tokens (dropped for now)
+                    if (tid == 0) sh.listed = 0;
+                    lds_barrier();
+                    const float lo_y = tb > 0 ? static_cast<float>(tb) : -INFINITY, hi_y = static_cast<float>(tb) + 1.f;
+                    int above = 0;
+                    auto place = [&](float z, int e, bool inside) __attribute__((always_inline)) -> bool {      // true: kept
+                        const float y = -kBinsPerOctave * fmaf(z, k32, nA);
+                        const bool in_bin = inside && y >= lo_y && y < hi_y;
+                        if (in_bin) {
+                            const int at = atomicAdd(&sh.listed, 1);
+                            if (at < NucleusShared<BLOCK>::CAP) { sh.list.z[at] = z; sh.list.at[at] = e; }
+                        }
+                        const bool keep = inside && y < lo_y;
+                        above += keep ? 1 : 0;
+                        return keep;
+                    };
+                    row.template sweep<BLOCK, 2>(
+                        [&](const float (&a)[E::VEC], int e0, const uint4& raw, bool inside) __attribute__((always_inline)) {
+                            float m[E::VEC];
+#pragma unroll
+                            for (int i = 0; i < E::VEC; ++i) m[i] = place(a[i], e0 + i, inside) ? a[i] : -INFINITY;
+                            if (inside) row.store_vec(e0, MaskedStore<E>::pack(m));
+                            (void)raw;
+                        },
+                        [&](float z, int e, bool inside) __attribute__((always_inline)) {
+                            const bool keep = place(z, e, inside);
+                            if (inside) *as_global(row.o + e) = MaskedStore<E>::to_elem(keep ? z : -INFINITY);
+                        });
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    NucleusProbe p;
+                    p.mass = 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = above;
+                    const int count_above = block_total<BLOCK>(p, sh).count;      // (its barriers also complete the list)
+                    const int n = min(__builtin_amdgcn_readfirstlane(sh.listed), NucleusShared<BLOCK>::CAP);
+                    const NucleusProbe bin = block_total<BLOCK>(probe_listed<BLOCK>(sh.list.z, n, -INFINITY, k32, nA), sh);
+                    tau = bin.above;
+                    kept = bin.count;
+                    bisect_listed<BLOCK>(sh, n, float_key(tau), float_key(row_max) + 1u, want - above_bin, k32, nA, tau, kept);
+                    kept += count_above;
+                    for (int i = tid; i < n; i += BLOCK) {
+                        const float z = sh.list.z[i];
+                        if (z >= tau) *as_global(row.o + sh.list.at[i]) = MaskedStore<E>::to_elem(z);
+                    }
+                    written = true;
+                } else if (tb >= 0) {
+                    // ---- too many tokens in one bin: probe the row in memory
+                    nucleus_bisect(float_key(-INFINITY), float_key(row_max) + 1u, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+                        NucleusProbe p;
+                        p.mass = 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = 0;
+                        auto item = [&](float z, bool inside) __attribute__((always_inline)) {
+                            const bool in = inside && z >= cut;
+                            p.mass += in ? nucleus_units(z, k32, nA) : 0.0;
+                            p.below = in ? p.below : fmaxf(p.below, z);
+                            p.above = in ? fminf(p.above, z) : p.above;
+                            p.count += in ? 1 : 0;
+                        };
+                        row.template sweep<BLOCK, 2>(
+                            [&](const float (&a)[E::VEC], int, const uint4&, bool inside) __attribute__((always_inline)) {
+#pragma unroll
+                                for (int i = 0; i < E::VEC; ++i) item(a[i], inside);
+                            },
+                            [&](float z, int, bool inside) __attribute__((always_inline)) { item(z, inside); });
+                        return block_total<BLOCK>(p, sh);
+                    });
+                }
+                // (tb < 0: the mass of the whole row rounds to less than top_p of it: everything is kept)
             }
         }
     }
-
-    // 3. masked copy (in place if out == in: every element is read and written by the same lane)
-    const int tid = threadIdx.x;
-    const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(z) & 15u) / sizeof(T));
-    const int head = mis ? min(E::VEC - mis, V) : 0;
-    const int nvec = (V - head) / E::VEC;
-    const int tail0 = head + nvec * E::VEC;
-    if (tid < head) o[tid] = MaskedStore<E>::to_elem(MaskedStore<ElemF32>::one(E::load_one(z + tid), tau));
-    if (tail0 + tid < V) o[tail0 + tid] = MaskedStore<E>::to_elem(MaskedStore<ElemF32>::one(E::load_one(z + tail0 + tid), tau));
-    const uint4* zv = reinterpret_cast<const uint4*>(z + head);
-    uint4* ov = reinterpret_cast<uint4*>(o + head);
-    int i = tid;
-    for (; i + 3 * kNucleusBlock < nvec; i += 4 * kNucleusBlock) {       // four loads in flight per lane
-        const uint4 a0 = zv[i], a1 = zv[i + kNucleusBlock], a2 = zv[i + 2 * kNucleusBlock], a3 = zv[i + 3 * kNucleusBlock];
-        ov[i] = MaskedStore<E>::vec(a0, tau);
-        ov[i + kNucleusBlock] = MaskedStore<E>::vec(a1, tau);
-        ov[i + 2 * kNucleusBlock] = MaskedStore<E>::vec(a2, tau);
-        ov[i + 3 * kNucleusBlock] = MaskedStore<E>::vec(a3, tau);
+    if (!written) {
+        // ---- masked copy (in place if out == in: every element is read and written by the same lane)
+        row.template sweep<BLOCK, kNucleusUnroll>(
+            [&](const float (&)[E::VEC], int e0, const uint4& raw, bool inside) __attribute__((always_inline)) {
+                if (inside) row.store_vec(e0, MaskedStore<E>::vec(raw, tau));
+            },
+            [&](float z, int e, bool inside) __attribute__((always_inline)) {
+                if (inside) *as_global(row.o + e) = MaskedStore<E>::to_elem(z >= tau ? z : -INFINITY);
+            });
     }
-    for (; i < nvec; i += kNucleusBlock) ov[i] = MaskedStore<E>::vec(zv[i], tau);
     if (tid == 0) {
         if (threshold_out) threshold_out[r] = tau;
         if (kept_out) kept_out[r] = kept;

@@ -183,3 +183,38 @@ def test_benchmark_batch_rows_sampled():
     near = check_rows(flat[rows], cfg.T, 0.9, masked.view(-1, cfg.V)[rows], thr.view(-1)[rows], kept.view(-1)[rows])
     assert near <= 1
     assert int(kept.min()) >= 1 and int(kept.max()) < cfg.V
+
+
+# Row lengths around the switch of the workgroup size (2048 vectors) and around whole chunks of a sweep; row shapes that
+# lead through each way of finding the threshold: "few" tokens hold the mass (the list suffices), "flat" rows (the list is
+# not enough or overflows: bins), "level" rows (thousands of nearly equal logits: one bin holds more than the list).
+@pytest.mark.parametrize("shape", ["few", "flat", "level"])
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 8), (torch.bfloat16, 65), (torch.bfloat16, 8192), (torch.bfloat16, 16383), (torch.bfloat16, 16391),
+                                     (torch.bfloat16, 32768), (torch.bfloat16, 40961), (torch.float32, 3), (torch.float32, 8195), (torch.float32, 16384),
+                                     (torch.float32, 20481)])
+def test_ways_of_finding_the_threshold(shape, dtype, V):
+    announce("nucleus ways", shape, dtype, "V", V)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V + len(shape))
+    rows = 6
+    z = torch.randn(rows, V, generator=gen, device="cuda") * {"few": 4.0, "flat": 0.5, "level": 1e-3}[shape]
+    if shape == "few":
+        z[:, V // 2] += 12.0
+        z[1, : V - 1] = -float("inf")                 # one token, at the end of a row that starts with -inf
+        z[2] = -float("inf")                          # nothing to drop
+    z = z.to(dtype)
+    use = z[[r for r in range(rows) if shape != "few" or r != 2]]
+    for T, top_p in ((1.0, 0.9), (0.7, 0.999)):
+        masked, thr, kept = mpv.mpv_nucleus_mask(z, T, top_p)
+        place = z.clone()
+        mpv.mpv_nucleus_mask(place, T, top_p, inplace=True)
+        torch.cuda.synchronize()
+        same = torch.int16 if dtype == torch.bfloat16 else torch.int32
+        assert torch.equal(place.view(same), masked.view(same))
+        if shape == "few":
+            assert torch.equal(masked[2].view(same), z[2].view(same)) and int(kept[2]) == V
+        sel = [r for r in range(rows) if shape != "few" or r != 2]
+        near = check_rows(use, T, top_p, masked[sel], thr[sel], kept[sel])
+        # float32 rows without a head: neighbouring upper sets differ by about 1/V of mass, which the band of 1e-6 resolves
+        # at these lengths except where it happens to straddle one
+        assert near <= 1
