@@ -137,8 +137,8 @@ def other_configs(mpv, torch, workloads, skip, steps=10):
 def merged_trees(mpv, torch, workloads, names=("v128k_delayed", "v152k_root"), steps=3):
     """mpv_verify_merged (draft trees whose nodes are distinct contexts, Def. 3.1) on batches whose
     rows are functions of the context: time per call with the trees as drafted and with trees of
-    equal shape laid next to each other (one launch per run of equal shapes), next to the plain call
-    on the same batch, and what merging does to the accepted length."""
+    equal shape laid next to each other (one launch pair and a little set-up either way), next to the
+    plain call on the same batch, and what merging does to the accepted length."""
     import numpy as np
     res = {}
     for name in names:
@@ -177,8 +177,8 @@ def merged_trees(mpv, torch, workloads, names=("v128k_delayed", "v152k_root"), s
             del moved
             entry["methods"][METHOD_LABEL[method]] = {
                 "plain_call_ms": sec_plain * 1e3,
-                "merged_as_drafted": {"launches": runs(merged_parent), "ms_per_step": sec_drafted * 1e3},
-                "merged_sorted_by_shape": {"launches": runs(merged_parent[order]), "ms_per_step": sec_sorted * 1e3},
+                "merged_as_drafted": {"runs_of_equal_shapes": runs(merged_parent), "ms_per_step": sec_drafted * 1e3},
+                "merged_sorted_by_shape": {"runs_of_equal_shapes": runs(merged_parent[order]), "ms_per_step": sec_sorted * 1e3},
                 "mean_accept_len_plain": float(out_plain.accept_len.float().mean().item()),
                 "mean_accept_len_merged": float(out_merged.accept_len.float().mean().item())}
         res[name] = entry

@@ -228,10 +228,10 @@ int mpv_merge_duplicates(const int32_t* parent, const int32_t* tokens, int32_t B
  * [B,N], what mpv_merge_duplicates wrote (copied to the device by the caller), borrowed like the
  * buffers; an entry outside [0,N) is ignored (the walk stays at the accepted entry); with the other
  * methods the argument is not read and may be NULL.
- * Cost: the kernels share one shape per launch, so the call makes one mpv_verify launch per run of
- * consecutive trees with equal rows in merged_parent, one after the other on `hip_stream`; lay trees
- * of equal shape next to each other (the shapes are known before the target pass writes its rows).
- * Nothing is launched unless every run is a valid problem. */
+ * Cost: that of mpv_verify, plus a set-up launch per 3584 / N trees.  With per-node outputs (stats,
+ * edge_probs, accept_prob under SPECINFER and TRAVERSAL) the call instead makes one mpv_verify launch
+ * per run of consecutive trees with equal rows in merged_parent, one after the other on `hip_stream`.
+ * Nothing is launched unless every tree is a valid problem. */
 int mpv_verify_merged(const mpv_problem* problem, const int32_t* merged_parent, const int32_t* context_node,
                       const mpv_buffers* buffers, void* workspace, size_t workspace_bytes, void* hip_stream);
 
@@ -324,8 +324,8 @@ int mpv_fill_uniforms(uint64_t seed, int64_t count, float* d_u, void* hip_stream
  * and destroys the events.  mpv_timing_read, called after the caller has
  * synchronised that stream, writes the elapsed milliseconds and the MPV_KERNEL_*
  * id of each recorded launch (HOST arrays of `capacity` entries), sets *count and
- * clears the record.  One call is two launches: MPV_KERNEL_INIT (counters, queue) and
- * MPV_KERNEL_NODE_TASK, whose persistent workgroups run every node task (softmax
+ * clears the record.  One call is two launches: MPV_KERNEL_INIT (counters, queue; mpv_verify_merged: the
+ * launches that set up the trees' shapes have this id too) and MPV_KERNEL_NODE_TASK, whose persistent workgroups run every node task (softmax
  * statistics, per-child test probabilities, residual masses) and every sampling task
  * (accept/reject walk, bonus token) of the batch (Sec. 2, step 3); MPV_KERNEL_DEBUG_STATS
  * follows when `stats` is requested. */

@@ -21,6 +21,7 @@
 //                            tree: the uniform-dependent walk, then the team draws the bonus
 //                            token by inverse CDF from the residual of the stopping node.
 //                            (NSS, Naive, SpecTr: one per draw of the token-following walk.)
+// mpv_verify_merged (a shape per tree) adds shape_kernel, which works out every tree's tables.
 // mpv_block_efficiency and mpv_acceptance_rates run the same kernels with every node task and
 // no uniforms (see Args::estimate); mpv_nucleus_mask is a kernel of its own (mpv_nucleus.h).
 //
@@ -49,6 +50,12 @@ namespace mpv {
 // workgroups of a compute unit have 53 KB each).
 struct TreeDesc {
     int32_t N;
+    // Traversal, only what is needed, no team to spare: the node where the tree branches
+    // (-1: not used) first handles its first child only; the rest of its work (a second task:
+    // "resumed") is started when that child's subtree, split_mask in postorder positions, turns
+    // out to be rejected as a whole.
+    int32_t split_node;
+    unsigned long long split_mask;
     int8_t parent[MPV_MAX_NODES];
     int8_t nchild[MPV_MAX_NODES];
     int8_t child_off[MPV_MAX_NODES];     // start of the node's children in child_list
@@ -58,10 +65,17 @@ struct TreeDesc {
     int8_t rank[MPV_MAX_NODES];          // position of the node in postorder
     int8_t sub_lo[MPV_MAX_NODES];        // the node's subtree is postorder[sub_lo[n] .. rank[n]]
     int8_t cls[MPV_MAX_NODES];           // priority class of the node's task (see QueuePlan)
-    int8_t pad[MPV_MAX_NODES];
     int32_t class_off[8];                // QueuePlan::off again, for the kernels that read the tables from memory
 };
-static_assert(MPV_MAX_NODES <= 127 && sizeof(TreeDesc) % 4 == 0, "node numbers must fit a signed byte");
+static_assert(MPV_MAX_NODES <= 127 && sizeof(TreeDesc) % 8 == 0, "node numbers must fit a signed byte");
+
+// The tables of one tree of a batch in which every tree has a shape of its own: one 64-bit word per
+// node (a wave reads a tree's tables in one load, a lane a word), the fields of node n in word n except
+// for child_list and postorder, which are lists: entry n.
+constexpr int kShapeParent = 0, kShapeNChild = 6, kShapeChildOff = 11, kShapeChildList = 17, kShapeDepth = 23,
+              kShapePostorder = 29, kShapeRank = 35, kShapeSubLo = 41, kShapeCls = 47, kShapeSplit = 48;
+constexpr int kShapeNoSplit = 127;        // (7 bits in kShapeSplit: split_node, the same in every word)
+static_assert(MPV_MAX_NODES <= 64 && MPV_MAX_CHILDREN < 32, "the fields of a shape word are too narrow");
 
 constexpr int kMaxClasses = 4;
 static_assert(kMaxClasses + 1 <= 8, "TreeDesc::class_off is too short");
@@ -84,13 +98,6 @@ struct QueuePlan {
     int32_t team_size;                   // G: workgroups that share one task
     int32_t part_vecs;                   // 16-byte vectors of a row per member (a multiple of 64)
     int32_t same_xcd;                    // members of a team are 8 workgroup numbers apart (one chiplet, its L2)
-    // Traversal, only what is needed, no team to spare: the node where the tree branches
-    // (-1: not used) first handles its first child only; the rest of its work (a second task:
-    // "resumed") is started when that child's subtree, split_mask in postorder positions, turns
-    // out to be rejected as a whole.
-    int32_t split_node;
-    unsigned long long split_mask;
-
 };
 
 constexpr int kMaxTeam = 16;                          // workgroups per team, at most
@@ -102,7 +109,8 @@ struct Workspace {
     double* At;      // log2-partition of the target row (internal nodes)
     double* Ad;      // same for the draft row
     double* cfin;    // c of the node's final state (all children rejected); SpecTr: the division factor rho* (the token is drawn from (p - rho* q)_+)
-    double* aux;     // block-efficiency estimate, Naive and SpecTr: p_res at the node's token (see estimate_wave)
+    double* aux;     // block-efficiency estimate, Naive and SpecTr: p_res at the node's token (see estimate_wave);
+                     // verification of trees that each have a shape of their own: the shape words (see load_shape)
     double* a0;      // Traversal: weight the node starts with (kNotReady until its parent's task publishes it)
     double* atest;   // probability the node is tested with
     int32_t* queue;      // entry = tree * N + node (node task) or B * N + tree (sampling task), -1 = not written yet
@@ -160,7 +168,7 @@ struct Args {
     // number of children alone; no tokens are read, nothing follows the node tasks.  alpha [B,N].
     int32_t estimate = 0;
     int32_t keep_counters = 0;   // the call continues an earlier one: init_kernel leaves the counters as they are
-    int32_t reserved = 0;
+    int32_t per_tree = 0;        // every tree has a shape of its own: its tables are in Workspace::aux
     float* reach_prob = nullptr;
     float* expected = nullptr;
     float* alpha = nullptr;
@@ -222,6 +230,8 @@ __shared__ uint4 g_rows[2 * kLdsVecs * kTaskBlock];
 static_assert(sizeof(g_rows) >= kMaxTiles * sizeof(float), "tile masses do not fit in the kept-row LDS");
 // the tree tables (copied from the workspace at the start of node_task_kernel)
 __shared__ TreeDesc g_tree;
+// Args::per_tree: the tree whose tables g_tree holds (-1: none yet); the first wave's business
+__shared__ int g_tree_of;
 
 // A value that is the same in every lane, for the compiler to keep in scalar registers.  Needed
 // wherever a function that is not inlined receives it: arguments arrive in vector registers.
@@ -242,6 +252,114 @@ __device__ __forceinline__ S uniform_struct(const S& s) {
 #pragma unroll
     for (int i = 0; i < static_cast<int>(sizeof(S) / 4); ++i) dst[i] = __builtin_amdgcn_readfirstlane(src[i]);
     return out;
+}
+
+// ------------------------------------------------------------------ trees that each have a shape of their own
+
+// First wave of a workgroup, when nobody else reads the tables (the other waves wait at a barrier):
+// puts the tables of tree b into g_tree.  One load per tree change, about a microsecond; between
+// tasks of one tree nothing is read.
+__device__ __forceinline__ void load_shape(const unsigned long long* shapes, int N, int b) {
+    if (uniform_i32(g_tree_of) == b) return;
+    const int lane = threadIdx.x;
+    const unsigned long long w = lane < N ? as_global(shapes)[static_cast<size_t>(b) * N + lane] : 0ull;
+    const unsigned lo = static_cast<unsigned>(w), hi = static_cast<unsigned>(w >> 32);
+    auto bits = [&](int at, int width) { return static_cast<int>((w >> at) & ((1ull << width) - 1ull)); };
+    if (lane < N) {
+        g_tree.parent[lane] = static_cast<int8_t>(lane ? bits(kShapeParent, 6) : -1);
+        g_tree.nchild[lane] = static_cast<int8_t>(bits(kShapeNChild, 5));
+        g_tree.child_off[lane] = static_cast<int8_t>(bits(kShapeChildOff, 6));
+        g_tree.child_list[lane] = static_cast<int8_t>(bits(kShapeChildList, 6));
+        g_tree.depth[lane] = static_cast<int8_t>(bits(kShapeDepth, 6));
+        g_tree.postorder[lane] = static_cast<int8_t>(bits(kShapePostorder, 6));
+        g_tree.rank[lane] = static_cast<int8_t>(bits(kShapeRank, 6));
+        g_tree.sub_lo[lane] = static_cast<int8_t>(bits(kShapeSubLo, 6));
+        g_tree.cls[lane] = static_cast<int8_t>(bits(kShapeCls, 1));
+    }
+    // the word of one node, the same in every lane
+    auto word = [&](int n) {
+        const unsigned long long l = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(lo), n));
+        const unsigned long long h = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(hi), n));
+        return (h << 32) | l;
+    };
+    const int split = static_cast<int>((word(0) >> kShapeSplit) & 127ull);
+    unsigned long long mask = 0ull;
+    if (split != kShapeNoSplit) {                      // the subtree of the first child, in postorder positions
+        const int at = static_cast<int>((word(split) >> kShapeChildOff) & 63ull);
+        const unsigned long long first = word(static_cast<int>((word(at) >> kShapeChildList) & 63ull));
+        const int r_hi = static_cast<int>((first >> kShapeRank) & 63ull), r_lo = static_cast<int>((first >> kShapeSubLo) & 63ull);
+        mask = ((r_hi >= 63) ? ~0ull : ((1ull << (r_hi + 1)) - 1ull)) & ~((1ull << r_lo) - 1ull);
+    }
+    if (lane == 0) {
+        g_tree.split_node = split != kShapeNoSplit ? split : -1;
+        g_tree.split_mask = mask;
+        g_tree_of = b;
+    }
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// Before, a batch was one launch pair per run of consecutive equal shapes, each a dependent chain of
+// tasks with most of the chip idle: 64 trees of 22 shapes, V = 128256, SpecInfer 3.6 ms, now 0.112 ms;
+// 256 trees of 162 shapes, V = 151936, Traversal 22.2 ms, now 0.515 ms.
+//
+// Parent arrays travel to the device as kernel arguments (a byte per node): no copy that could
+// synchronise, no host memory that has to outlive the call, and a captured graph holds them.
+constexpr int kShapeChunkBytes = 3584;               // (kernel arguments: 4 KB in all)
+struct ShapeChunk { unsigned char parent[kShapeChunkBytes]; };
+
+// The tables of the trees [first, first + gridDim.x) from their parent arrays: one wave per tree, lane n
+// looks after node n; the two loops over the nodes are scalar steps over the wave's registers (about 2 us
+// for 41 nodes).  The host has checked the arrays (0 <= parent[n] < n, depth, number of children).
+__global__ __launch_bounds__(kWave) void shape_kernel(ShapeChunk chunk, unsigned long long* shapes, int first, int N, int split) {
+    __shared__ int sh_child[MPV_MAX_NODES], sh_post[MPV_MAX_NODES];
+    const int lane = threadIdx.x;
+    const bool live = lane < N;
+    const int par = (live && lane > 0) ? chunk.parent[blockIdx.x * N + lane] : 0;
+    unsigned long long sub = live ? 1ull << lane : 0ull, kids = 0ull;
+    for (int m = N - 1; m > 0; --m) {                  // descendants and children, as masks of nodes
+        const int p = __builtin_amdgcn_readlane(par, m);
+        const unsigned long long of_m = (static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(sub >> 32), m))) << 32)
+                                      | static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(sub), m));
+        if (lane == p) { sub |= of_m; kids |= 1ull << m; }
+    }
+    const int nchild = __popcll(kids), size = __popcll(sub);
+    const int off = wave_inclusive_scan_i32(nchild) - nchild;
+    int depth = 0, start = 0, next = 0;                // start: postorder position of the subtree's first node
+    for (int m = 1; m < N; ++m) {
+        const int p = __builtin_amdgcn_readlane(par, m);
+        const int at = __builtin_amdgcn_readlane(next, p), d = __builtin_amdgcn_readlane(depth, p);
+        const int sz = __builtin_amdgcn_readlane(size, m);
+        if (lane == p) next += sz;
+        if (lane == m) { start = at; next = at; depth = d + 1; }
+    }
+    const int rank = start + size - 1;
+    const unsigned long long siblings = __shfl(kids, par, kWave);
+    const int par_off = __shfl(off, par, kWave);
+    if (lane == 0) sh_child[N - 1] = 0;                // (N - 1 entries: the root is nobody's child)
+    __builtin_amdgcn_wave_barrier();
+    if (live) {
+        if (lane > 0) sh_child[par_off + __popcll(siblings & ((1ull << lane) - 1ull))] = lane;
+        sh_post[rank] = lane;
+    }
+    __syncthreads();
+    // the first node from the root down that does not have exactly one child
+    int branch = 0;
+    while (__builtin_amdgcn_readlane(nchild, branch) == 1) branch = sh_child[__builtin_amdgcn_readlane(off, branch)];
+    branch = uniform_i32(branch);
+    const int branch_depth = __builtin_amdgcn_readlane(depth, branch), branch_kids = __builtin_amdgcn_readlane(nchild, branch);
+    int split_node = kShapeNoSplit;
+    if (split && branch_kids >= 2) {
+        const int c0 = uniform_i32(sh_child[__builtin_amdgcn_readlane(off, branch)]);
+        if (__builtin_amdgcn_readlane(nchild, c0) > 0) split_node = branch;
+    }
+    auto field = [](int v, int at) { return static_cast<unsigned long long>(v) << at; };
+    if (live)
+        shapes[static_cast<size_t>(first + static_cast<int>(blockIdx.x)) * N + lane] =
+            field(par, kShapeParent) | field(nchild, kShapeNChild) | field(off, kShapeChildOff) |
+            field(sh_child[lane], kShapeChildList) | field(depth, kShapeDepth) | field(sh_post[lane], kShapePostorder) |
+            field(rank, kShapeRank) | field(start, kShapeSubLo) | field(depth <= branch_depth ? 0 : 1, kShapeCls) |
+            field(split_node, kShapeSplit);
 }
 
 // ------------------------------------------------------------------ init
@@ -924,12 +1042,16 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         NodeView v;
         v.resumed = t >= B * N + B;
         v.b = uniform_i32(v.resumed ? t - (B * N + B) : t / N);
-        v.n = uniform_i32(v.resumed ? q.split_node : t % N);
+        v.n = uniform_i32(v.resumed ? tree.split_node : t % N);
         v.bn = static_cast<size_t>(v.b) * N + v.n;
         v.zt = uniform_ptr(static_cast<const T*>(a.zt)) + v.bn * V;
         v.zd = uniform_ptr(static_cast<const T*>(a.zd)) + v.bn * V;
         v.k = uniform_i32(tree.nchild[v.n]);
         return v;
+    };
+
+    auto tree_of = [&](int t) __attribute__((always_inline)) -> int {
+        return uniform_i32(t >= B * N + B ? t - (B * N + B) : (t >= B * N ? t - B * N : t / N));
     };
 
     // ---- the part of the pair this member keeps on chip while a task runs
@@ -1037,6 +1159,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // branches): no way back through the task loop, no queue in between.
     for (;;) {
     {
+    // (a task that is under way already belongs to the tree of the task before)
+    if (!ACCEPT && started != task && uniform_i32(a.per_tree)) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), N, tree_of(task));
     const NodeView nv = view_of(task);
     const bool resumed = nv.resumed;
     const int b = nv.b, n = nv.n, k = nv.k;
@@ -1075,7 +1199,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // are teams idle?  Asked now, needed when this task hands on to the next (the leader's business)
     int idle_now = 0;
     if (lead) idle_now = ld_relaxed(&ws.qctl[4 + 2 * kMaxClasses]);
-    const bool split_here = METHOD == MPV_METHOD_TRAVERSAL && a.lazy && !resumed && n == q.split_node;
+    const bool split_here = METHOD == MPV_METHOD_TRAVERSAL && a.lazy && !resumed && n == tree.split_node;
     const bool idle_seen = (flags & kFlagIdle) != 0;
 
     // Traversal, only what is needed, and idle teams about: an only child's task is queued
@@ -1525,7 +1649,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         }
     }
     {
-        const int start_now = likely >= 0 ? likely : ((taken >= 0 && !(taken >= B * N && taken < B * N + B)) ? taken : -1);
+        // (trees of different shapes: the tables in LDS are still this tree's)
+        const int start_now = likely >= 0 ? likely
+                            : ((taken >= 0 && !(taken >= B * N && taken < B * N + B) && (!a.per_tree || tree_of(taken) == b)) ? taken : -1);
         if (start_now >= 0) {
             start_task(view_of(start_now), start_now);
             started = start_now;
@@ -1627,9 +1753,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             // The subtree that was explored first has just turned out to be rejected as a whole
             // (this task supplied its last missing outcome): time for the rest of the node
             // where the tree branches.
-            if (METHOD == MPV_METHOD_TRAVERSAL && a.lazy && q.split_node >= 0 && !settled_tree &&
-                ((q.split_mask >> tree.rank[n]) & 1ull) != 0ull) {          // this node lies in that subtree
-                const unsigned long long m = q.split_mask;
+            if (METHOD == MPV_METHOD_TRAVERSAL && a.lazy && tree.split_node >= 0 && !settled_tree &&
+                ((tree.split_mask >> tree.rank[n]) & 1ull) != 0ull) {          // this node lies in that subtree
+                const unsigned long long m = tree.split_mask;
                 resume = (known & m) == m && (known_before & m) != m && (acc & m) == 0ull;
             }
         }
@@ -1769,6 +1895,7 @@ void node_task_kernel(const Launch* __restrict__ launch) {
             g_loop.own_task = leader ? -1 : kNothingHeard;
             g_loop.own_flags = 0;
             g_loop.previous_task = -4;            // none yet
+            g_tree_of = -1;
             // the last member to arrive opens the team's mailbox: from then on the dispatcher may hand it tasks
             const int n_arrived = atomicAdd(&ws.arrived[team.id], 1) + 1;
             if (n_arrived == team.size) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
@@ -2111,6 +2238,7 @@ __device__ __attribute__((noinline)) int sample_task(int b_in) {
     const bool leader = team.member == 0;
     const bool lead = leader && threadIdx.x == 0;
     if (wave == 0) {
+        if (a.per_tree) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), a.N, b);
         // where the token is drawn: the node the rule stops in, or the node a token-following
         // walk has reached
         const int stop = a.walk ? ld_relaxed(&ws.cur[b]) : walk_wave<METHOD>(tree, ws, a, b, leader);
@@ -2465,7 +2593,48 @@ struct Plan {
     int max_tree_depth;
     int n_internal;
     int nclass;
+    int64_t class_tasks[kMaxClasses];      // tasks a class can ever hold, over the batch
+    const int32_t* shapes;                 // HOST [B,N]: a parent array per tree, checked; null: every tree is `tree`
 };
+
+// What the checks of one parent array find out.
+struct TreeScan {
+    int nch[MPV_MAX_NODES], depth[MPV_MAX_NODES];
+    int max_depth, internal, trunk;        // trunk: internal nodes from the root down to the first that branches
+    bool branches;
+};
+
+static int scan_tree(const int32_t* parent, int N, int max_depth, TreeScan* t) {
+    if (parent[0] != -1) return MPV_ERR_BAD_TREE;
+    memset(t->nch, 0, sizeof(int) * static_cast<size_t>(N));
+    t->depth[0] = 0;
+    for (int n = 1; n < N; ++n) {
+        const int par = parent[n];
+        if (par < 0 || par >= n) return MPV_ERR_BAD_TREE;
+        t->depth[n] = t->depth[par] + 1;
+        ++t->nch[par];
+    }
+    t->max_depth = t->internal = t->trunk = 0;
+    for (int n = 0; n < N; ++n) {
+        if (t->nch[n] > MPV_MAX_CHILDREN) return MPV_ERR_UNSUPPORTED;
+        if (t->depth[n] > t->max_depth) t->max_depth = t->depth[n];
+        if (t->nch[n]) ++t->internal;
+    }
+    // (the nodes of a trunk come in ascending order, each the only one of its depth)
+    int branch = 0;
+    for (int n = 1; n < N && t->nch[branch] == 1; ++n)
+        if (parent[n] == branch) branch = n;
+    t->branches = t->nch[branch] > 0;
+    t->trunk = t->depth[branch] + (t->branches ? 1 : 0);
+    return t->max_depth > max_depth ? MPV_ERR_BAD_SHAPE : MPV_OK;
+}
+
+// Queue space: class 0 holds the trunk's tasks and the sampling task, class 1 the other nodes' and the resumed one.
+static void count_tasks(const TreeScan& t, int64_t trees, Plan* plan) {
+    plan->class_tasks[0] += trees * (t.trunk + 1);
+    if (t.branches) plan->class_tasks[1] += trees * (t.internal - t.trunk + 1);
+    if (t.branches) plan->nclass = 2;
+}
 
 static int validate(const mpv_problem* p, Plan* plan) {
     if (!p) return MPV_ERR_NULL;
@@ -2477,27 +2646,21 @@ static int validate(const mpv_problem* p, Plan* plan) {
     if (p->logit_dtype != MPV_DTYPE_F32 && p->logit_dtype != MPV_DTYPE_BF16) return MPV_ERR_BAD_DTYPE;
     if (!(p->temperature > 0.0f) || !isfinite(p->temperature)) return MPV_ERR_BAD_TEMPERATURE;
     if (!p->parent) return MPV_ERR_NULL;
-    if (p->parent[0] != -1) return MPV_ERR_BAD_TREE;
+    TreeScan scan;
+    const int rc = scan_tree(p->parent, p->N, p->max_depth, &scan);
+    if (rc != MPV_OK) return rc;
     TreeDesc& t = plan->tree;
-    memset(&t, 0, sizeof(t));
+    memset(plan, 0, sizeof(*plan));
     t.N = p->N;
     t.parent[0] = -1;
-    int nch[MPV_MAX_NODES] = {0};
-    for (int n = 1; n < p->N; ++n) {
-        const int par = p->parent[n];
-        if (par < 0 || par >= n) return MPV_ERR_BAD_TREE;
-        t.parent[n] = par;
-        t.depth[n] = t.depth[par] + 1;
-        ++nch[par];
-    }
-    int off = 0, maxd = 0, internal = 0;
+    t.split_node = -1;
+    int off = 0;
     for (int n = 0; n < p->N; ++n) {
-        if (nch[n] > MPV_MAX_CHILDREN) return MPV_ERR_UNSUPPORTED;
-        t.nchild[n] = nch[n];
-        t.child_off[n] = off;
-        off += nch[n];
-        if (t.depth[n] > maxd) maxd = t.depth[n];
-        if (nch[n]) ++internal;
+        if (n) t.parent[n] = static_cast<int8_t>(p->parent[n]);
+        t.depth[n] = static_cast<int8_t>(scan.depth[n]);
+        t.nchild[n] = static_cast<int8_t>(scan.nch[n]);
+        t.child_off[n] = static_cast<int8_t>(off);
+        off += scan.nch[n];
     }
     int fill[MPV_MAX_NODES] = {0};
     for (int n = 1; n < p->N; ++n) {
@@ -2526,11 +2689,11 @@ static int validate(const mpv_problem* p, Plan* plan) {
         int branch = 0;
         while (t.nchild[branch] == 1) branch = t.child_list[t.child_off[branch]];
         for (int n = 0; n < p->N; ++n) t.cls[n] = (t.depth[n] <= t.depth[branch]) ? 0 : 1;
-        plan->nclass = t.nchild[branch] ? 2 : 1;
     }
-    plan->max_tree_depth = maxd;
-    plan->n_internal = internal;
-    if (p->max_depth < maxd) return MPV_ERR_BAD_SHAPE;
+    plan->nclass = 1;
+    count_tasks(scan, p->B, plan);
+    plan->max_tree_depth = scan.max_depth;
+    plan->n_internal = scan.internal;
     return MPV_OK;
 }
 
@@ -2644,11 +2807,7 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     QueuePlan q;
     memset(&q, 0, sizeof(q));
     q.nclass = plan.nclass;
-    int in_class[kMaxClasses] = {0};
-    for (int n = 0; n < p->N; ++n)
-        if (tree.nchild[n]) ++in_class[tree.cls[n]];
-    for (int c = 0; c < q.nclass; ++c)
-        q.off[c + 1] = q.off[c] + p->B * (in_class[c] + 1);     // class 0 also holds the sampling tasks, class 1 the resumed ones
+    for (int c = 0; c < q.nclass; ++c) q.off[c + 1] = q.off[c] + static_cast<int>(plan.class_tasks[c]);
     int prequeued[kMaxClasses] = {0};
     for (int n = 0; n < p->N; ++n) q.init_slot[n] = -1;
     const bool all_up_front = (p->method != MPV_METHOD_TRAVERSAL && !a.lazy);
@@ -2675,8 +2834,18 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
     q.same_xcd = shape.same_xcd;
-    q.split_node = -1;
-    if (p->method == MPV_METHOD_TRAVERSAL && a.lazy && p->B >= q.teams) {
+    const bool split = p->method == MPV_METHOD_TRAVERSAL && a.lazy && p->B >= q.teams;
+    if (a.per_tree) {
+        // (the root of every tree is an inner node, N > 1: what is prequeued is the same for all of them)
+        const int per_chunk = kShapeChunkBytes / p->N;
+        for (int b0 = 0; b0 < p->B; b0 += per_chunk) {
+            const int trees = min(per_chunk, p->B - b0);
+            ShapeChunk chunk;
+            const int32_t* rows = plan.shapes + static_cast<size_t>(b0) * p->N;
+            for (int i = 0; i < trees * p->N; ++i) chunk.parent[i] = static_cast<unsigned char>(rows[i]);
+            launch(MPV_KERNEL_INIT, shape_kernel, dim3(trees), dim3(kWave), s, chunk, reinterpret_cast<unsigned long long*>(ws.aux), b0, p->N, split ? 1 : 0);
+        }
+    } else if (split) {
         int branch = 0;
         while (tree.nchild[branch] == 1) branch = tree.child_list[tree.child_off[branch]];
         if (tree.nchild[branch] >= 2) {
@@ -2684,8 +2853,8 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
             if (tree.nchild[first] > 0) {
                 const int hi = tree.rank[first], lo = tree.sub_lo[first];
                 const unsigned long long upto = (hi >= 63) ? ~0ull : ((1ull << (hi + 1)) - 1ull);
-                q.split_node = branch;
-                q.split_mask = upto & ~((1ull << lo) - 1ull);
+                tree.split_node = branch;
+                tree.split_mask = upto & ~((1ull << lo) - 1ull);
             }
         }
     }
@@ -2786,9 +2955,17 @@ int mpv_workspace_bytes(const mpv_problem* problem, size_t* out) {
 // bytes, which is what the kernels rely on; the caller has checked the batch's own pointers);
 // keep_counters: add to the counters instead of starting them at zero.
 // context_node: see Args (device pointer, already moved on to the run's first tree).
+// shapes: HOST [B,N], a parent array per tree, all of them checked (problem->parent is the first); null: one shape.
 static int verify_with_workspace(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                                  size_t workspace_bytes, void* hip_stream, bool part_of_batch = false,
-                                 bool keep_counters = false, const int32_t* context_node = nullptr);
+                                 bool keep_counters = false, const int32_t* context_node = nullptr,
+                                 const int32_t* shapes = nullptr);
+
+// Only what the rule needs is computed: nobody has asked for per-node outputs.
+static bool only_what_is_needed(const mpv_problem* p, const mpv_buffers* buf) {
+    return (p->method != MPV_METHOD_SPECINFER && p->method != MPV_METHOD_TRAVERSAL) ||
+           (!buf->edge_probs && !buf->accept_prob && !buf->stats);
+}
 
 int mpv_verify(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                size_t workspace_bytes, void* hip_stream) {
@@ -2808,10 +2985,20 @@ int mpv_verify_static(const mpv_problem* problem, const mpv_buffers* buf, void* 
 
 static int verify_with_workspace(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                                  size_t workspace_bytes, void* hip_stream, bool part_of_batch, bool keep_counters,
-                                 const int32_t* context_node) {
+                                 const int32_t* context_node, const int32_t* shapes) {
     mpv::Plan plan;
     const int rc = mpv::validate(problem, &plan);
     if (rc != MPV_OK) return rc;
+    if (shapes) {
+        memset(plan.class_tasks, 0, sizeof(plan.class_tasks));
+        mpv::TreeScan scan;
+        mpv::for_each_run(shapes, problem->B, problem->N, [&](int32_t b0, int32_t b1) {
+            (void)mpv::scan_tree(shapes + static_cast<size_t>(b0) * problem->N, problem->N, problem->max_depth, &scan);
+            mpv::count_tasks(scan, b1 - b0, &plan);
+            return true;
+        });
+        plan.shapes = shapes;
+    }
     if (!buf) return MPV_ERR_NULL;
     if (problem->B == 0) return MPV_OK;
     if (!buf->target_logits || !buf->draft_logits || !buf->tokens || !buf->uniforms || !buf->accept_len ||
@@ -2839,7 +3026,8 @@ static int verify_with_workspace(const mpv_problem* problem, const mpv_buffers* 
     a.dbg_stats = buf->stats; a.dbg_edge = buf->edge_probs; a.dbg_accept = buf->accept_prob; a.dbg_resid = buf->final_residual;
     a.B = problem->B; a.N = problem->N; a.V = problem->V; a.max_depth = problem->max_depth;
     a.k32 = static_cast<float>(1.4426950408889634 / static_cast<double>(problem->temperature));
-    a.lazy = (walk || (buf->edge_probs == nullptr && buf->accept_prob == nullptr && buf->stats == nullptr)) ? 1 : 0;
+    a.lazy = only_what_is_needed(problem, buf) ? 1 : 0;
+    a.per_tree = shapes ? 1 : 0;
     a.estimate = 0; a.reach_prob = nullptr; a.expected = nullptr;
     a.keep_counters = keep_counters ? 1 : 0;
     a.context_node = context_node;
@@ -2895,19 +3083,32 @@ int mpv_verify_merged(const mpv_problem* problem, const int32_t* merged_parent, 
     // (its size depends on the number of trees and of nodes only, and grows with both)
     mpv_problem run = *problem;
     int rc = MPV_OK;
+    int64_t runs = 0;
+    mpv::TreeScan scan;
     mpv::for_each_run(merged_parent, B, N, [&](int32_t b0, int32_t b1) {
         run.B = b1 - b0;
         run.parent = merged_parent + static_cast<size_t>(b0) * N;
-        mpv::Plan plan;
-        rc = mpv::validate(&run, &plan);
+        if (runs++ == 0) {                             // the sizes are the same for all: checked once
+            mpv::Plan plan;
+            rc = mpv::validate(&run, &plan);
+        } else {
+            rc = static_cast<int64_t>(run.B) * (N + 2) > (1ll << 30) ? MPV_ERR_UNSUPPORTED
+                                                                      : mpv::scan_tree(run.parent, N, run.max_depth, &scan);
+        }
         return rc == MPV_OK;
     });
     if (rc != MPV_OK) return rc;
     run.B = B;
+    run.parent = merged_parent;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < mpv::carve(&run, nullptr, nullptr))
         return MPV_ERR_WORKSPACE;
     if ((reinterpret_cast<uintptr_t>(buf->target_logits) & 15u) || (reinterpret_cast<uintptr_t>(buf->draft_logits) & 15u))
         return MPV_ERR_ALIGNMENT;
+    // One launch for the whole batch, every tree with its own tables.  Per-node outputs want every node's
+    // task, which the top-down rules queue up front by node number: there (and beyond what one launch can
+    // number) each run of equal shapes is a launch of its own.
+    if (runs > 1 && only_what_is_needed(problem, buf) && static_cast<int64_t>(B) * (N + 2) <= (1ll << 30))
+        return verify_with_workspace(&run, buf, workspace, workspace_bytes, hip_stream, false, false, context_node, merged_parent);
     const size_t elem = problem->logit_dtype == MPV_DTYPE_F32 ? 4 : 2;
     const size_t V = static_cast<size_t>(problem->V), D = static_cast<size_t>(problem->max_depth);
     auto moved = [](const void* p, size_t bytes) -> const void* { return p ? static_cast<const char*>(p) + bytes : nullptr; };

@@ -166,6 +166,66 @@ def test_without_repeats_the_merged_call_is_the_plain_call():
             assert np.array_equal(a[key], b[key]), key
 
 
+def shapes_of(N, rng):
+    """Parent arrays at the edges of the per-tree tables: a chain, a star, a broom, a binary heap, a
+    branch whose first child is a leaf, random ones."""
+    k = min(16, N - 1)
+    out = [[-1] + list(range(N - 1)),
+           [-1] + [0] * k + [1 + i % k for i in range(N - 1 - k)],
+           [-1] + list(range(N - 1 - k)) + [N - 1 - k] * k,
+           [-1] + [(n - 1) // 2 for n in range(1, N)],
+           [-1, 0] + [0 if n == 2 else n - 1 for n in range(2, N)]]
+    for _ in range(3):
+        parent = [-1]
+        for n in range(1, N):
+            at = int(rng.integers(max(0, n - 6), n))
+            parent.append(at if parent.count(at) < 16 else n - 1)
+        out.append(parent)
+    return out
+
+
+@pytest.mark.parametrize("method", [SI, TV, NSS, NAIVE, SPECTR])
+@pytest.mark.parametrize("B,N,V,dtype", [
+    (800, 64, 40, "f32"),         # the widest tables, 15 chunks of parent arrays, more trees than teams
+    (400, 7, 30000, "bf16"),      # teams of two members, more trees than teams
+    (9, 2, 16, "bf16"),           # the smallest tree: one shape, a plain call
+    (57, 63, 1001, "f32"),        # a chunk and one tree, rows at any address
+])
+def test_a_shape_per_tree_gives_what_one_call_per_shape_gives(method, B, N, V, dtype):
+    rng = np.random.default_rng(8600 + N)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8600 + N)
+    shapes = shapes_of(N, rng)
+    which = rng.integers(0, len(shapes), B)
+    rows = np.array([shapes[w] for w in which], dtype=np.int32)
+    announce("a shape per tree", NAMES[method], f"B={B} N={N} V={V} {dtype} runs={len(runs_of(rows))}")
+    draft = torch.randn(B, N, V, generator=gen, device="cuda") * 2.0
+    target = (draft + torch.randn(B, N, V, generator=gen, device="cuda") * 0.7)
+    if dtype == "bf16":
+        draft, target = draft.bfloat16(), target.bfloat16()
+    # few distinct tokens, likely ones: equal siblings and long walks
+    tokens = draft[:, 0].float().topk(6, dim=1).indices.gather(1, torch.randint(0, 6, (B, N), generator=gen, device="cuda")).int()
+    uniforms, draws = (torch.rand(B, N, generator=gen, device="cuda") for _ in range(2))
+    own = torch.arange(N, dtype=torch.int32, device="cuda").repeat(B, 1)
+    D = N - 1
+    kw = dict(max_depth=D, draw_uniforms=draws)
+    got = mpv.mpv_verify(shapes[0], tokens, target, draft, 1.0, uniforms, method, merged_parent=rows, context_node=own, **kw)
+    torch.cuda.synchronize()
+    got = result_to_host(got)
+    assert got["counters"][4] == 0
+    for w in sorted({tuple(s) for s in rows.tolist()}):
+        idx = np.flatnonzero((rows == np.array(w)).all(axis=1))
+        at = torch.as_tensor(idx, device="cuda")
+        one = mpv.mpv_verify(list(w), tokens[at], target[at], draft[at], 1.0, uniforms[at], method, max_depth=D,
+                             draw_uniforms=draws[at])
+        torch.cuda.synchronize()
+        one = result_to_host(one)
+        # (whole numbers: the same unless a uniform lies within the rounding of a row sum, 1e-7, of its
+        # probability, which teams of another size may add up in another order)
+        for key in ("accept_len", "path_nodes", "path_tokens", "bonus_token"):
+            assert np.array_equal(got[key][idx], one[key]), (key, w)
+
+
 def test_large_vocabulary_sorted_and_unsorted():
     """Config 3's vocabulary and tree (trunk 2, then 4 paths of depth 3) with a draft that repeats
     itself often; the batch as drafted and the same batch with trees of equal shape laid next to
