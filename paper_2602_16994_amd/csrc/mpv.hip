@@ -2771,17 +2771,19 @@ static int resident_per_cu(K kernel) {
 }
 
 template <class E>
-static Shape launch_shape(const mpv_problem* p, int tasks, int per_cu) {
+static Shape launch_shape(const mpv_problem* p, int tasks, int64_t width, int per_cu) {
     Shape s;
     const int nvec = (p->V + E::VEC - 1) / E::VEC;
     const int slots = per_cu * compute_units() < kMaxGrid ? per_cu * compute_units() : kMaxGrid;      // workgroups that can be resident
     // The fewest members whose kept parts (plus the one overflow slot a sweep hides) hold a row:
-    // the most teams, which is what counts when there are more trees than teams.  With fewer
-    // trees a task's own time counts: more members, parts of about 2048 vectors (measured: shorter
-    // parts no longer pay for the larger exchange), as long as every tree still has a team.
+    // the most teams, which is what counts when more tasks can run at once (width) than there are teams.
+    // With fewer a task's own time counts: more members, parts of about 2048 vectors (measured: shorter
+    // parts no longer pay for the larger exchange), as long as there is a team for each.
+    // (64 trees of 33 inner nodes, V = 151936: block efficiency with 72 teams of 10 526 us, with 128 of 6
+    // 410; acceptance rates 670 and 497: a task spends less than half its time in sweeps.)
     int g = 1;
     while (g < kMaxTeam && static_cast<long long>(g) * (kPartCapacity + kTaskBlock / 2) < nvec) ++g;
-    while (g < kMaxTeam && slots / (g + 1) >= p->B && static_cast<long long>(g) * 2048 < nvec) ++g;
+    while (g < kMaxTeam && slots / (g + 1) >= width && static_cast<long long>(g) * 2048 < nvec) ++g;
     int teams = slots / g;
     if (teams > kMaxTeams) teams = kMaxTeams;
     if (teams > tasks) teams = tasks;
@@ -2829,7 +2831,19 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     static const int per_cu[3] = {resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>),
                                   resident_per_cu(node_task_kernel<E, MPV_METHOD_TRAVERSAL>),
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
-    const Shape shape = launch_shape<E>(p, tasks, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
+    // Node tasks that can run at the same time: one per tree where the rule follows one path at a time, every
+    // node's where all are queued up front, and where every task runs top-down (Traversal) one per chain.
+    int64_t width = p->B;
+    if (!a.lazy) {
+        int at_once = 0;
+        for (int n = 0; n < p->N; ++n) {
+            bool inner_child = false;
+            for (int j = 0; j < tree.nchild[n]; ++j) inner_child |= tree.nchild[tree.child_list[tree.child_off[n] + j]] > 0;
+            if (tree.nchild[n] && (all_up_front || !inner_child)) ++at_once;
+        }
+        width *= max(at_once, 1);
+    }
+    const Shape shape = launch_shape<E>(p, tasks, width, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
     q.teams = shape.teams;
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
