@@ -129,14 +129,13 @@ struct Workspace {
     unsigned long long* acc;
     int32_t* decided;
     int32_t* cur;        // [B] token-following walks: the node the walk has reached
-    TreeDesc* tree;      // the tree tables, written by init_kernel for the kernel that follows
     // Teams.  exch: [team][2][member][kExchWords] words of (sequence number << 32 | 32 bits of payload);
     // team_task: [team][2] the task the leader has taken and its flags, same packing; arrived: members
     // of the team that have started.
     unsigned long long* exch;
     unsigned long long* team_task;
     int32_t* arrived;
-    struct Launch* launch;   // what node_task_kernel is launched with, written by init_kernel
+    struct LaunchBlock* launch;   // what node_task_kernel is launched with, written by init_kernel
 };
 
 // Every field has a default (null / 0): what a call does not set stays off.
@@ -185,7 +184,13 @@ struct Launch {
     Workspace ws;
     Args a;
 };
+struct LaunchBlock {
+    Launch l;
+    TreeDesc tree;
+};
+static_assert(sizeof(Launch) % 8 == 0, "the launch block is copied in whole words, the tree tables follow at once");
 
+constexpr int kInitBlock = 256;
 constexpr int kTaskBlock = 256;
 constexpr int kTaskWaves = kTaskBlock / kWave;
 constexpr int kTaskUnroll = 4;
@@ -366,41 +371,33 @@ __global__ __launch_bounds__(kWave) void shape_kernel(ShapeChunk chunk, unsigned
 
 // Grid: x covers the trees (and the few per-launch words), y the nodes, so that every table
 // lookup by node has a workgroup-uniform index.
-__global__ void init_kernel(QueuePlan q, TreeDesc tree, Workspace ws, Args a) {
+//
+// Latency only: every word is written once and nothing is read but the arguments, so what counts is
+// that no thread does one thing after another.  The launch block goes over a word per lane, straight
+// from the argument segment (a structure passed by value and indexed by the lane would first be
+// copied to private memory; a word per workgroup, through scalar loads, was a chain of 40 loads on a
+// small tree), and only the words of the teams that are launched are cleared.
+// Median of this kernel 7.2 -> 5.4 us; with the tree tables next to the launch block, so that the kernel
+// that follows asks for both at once, a call on one tree of 7 nodes takes 35.6 us (41.3).
+__global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
+    const QueuePlan& q = block.l.q;
+    const Workspace& ws = block.l.ws;
+    const Args& a = block.l.a;
+    const TreeDesc& tree = block.tree;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;      // tree, or word number
     const int n = blockIdx.y;
-    {   // the tree tables for the next kernel, a few words per workgroup (the word number is the
-        // same in every lane: scalar loads from the kernel arguments)
-        const int* src = reinterpret_cast<const int*>(&tree);
-        int* dst = reinterpret_cast<int*>(ws.tree);
-        const int groups = gridDim.x * gridDim.y;
-        for (int w = blockIdx.y * gridDim.x + blockIdx.x; w < static_cast<int>(sizeof(TreeDesc) / sizeof(int)); w += groups) {
-            const int v = src[w];
-            if (threadIdx.x == 0) dst[w] = v;
-        }
-    }
-    {   // the launch block of the next kernel
-        struct Words { Launch l; };
-        const int groups = gridDim.x * gridDim.y;
+    const int stride = gridDim.x * gridDim.y * blockDim.x;
+    const int me = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+    {   // the launch block of the next kernel (the only argument: it starts the argument segment)
+        const auto* src = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
         int* dst = reinterpret_cast<int*>(ws.launch);
-        const int me = blockIdx.y * gridDim.x + blockIdx.x;
-        const int nq = static_cast<int>(sizeof(QueuePlan) / sizeof(int)), nw = static_cast<int>(sizeof(Workspace) / sizeof(int));
-        const int na = static_cast<int>(sizeof(Args) / sizeof(int));
-        static_assert(sizeof(QueuePlan) % 8 == 0 && sizeof(Workspace) % 8 == 0 && sizeof(Args) % 8 == 0, "Launch has no padding between its members");
-        for (int w = me; w < nq + nw + na; w += groups) {
-            int v;
-            if (w < nq) v = reinterpret_cast<const int*>(&q)[w];
-            else if (w < nq + nw) v = reinterpret_cast<const int*>(&ws)[w - nq];
-            else v = reinterpret_cast<const int*>(&a)[w - nq - nw];
-            if (threadIdx.x == 0) dst[w] = v;
-        }
+        for (int w = me; w < static_cast<int>(sizeof(LaunchBlock) / sizeof(int)); w += stride) dst[w] = src[w];
     }
     {   // team words: every sequence number starts at 0, nobody has arrived
-        const int stride = gridDim.x * gridDim.y * blockDim.x;
-        const int me = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-        for (int w = me; w < kMaxGrid * 2 * kExchWords; w += stride) ws.exch[w] = 0ull;
-        for (int w = me; w < kMaxTeams * 2; w += stride) ws.team_task[w] = 0ull;
-        for (int w = me; w < kMaxTeams; w += stride) { ws.arrived[w] = 0; ws.mailbox[w] = kMailboxAbsent; }
+        const int exch_words = q.teams * q.team_size * 2 * kExchWords;
+        for (int w = me; w < exch_words; w += stride) ws.exch[w] = 0ull;
+        for (int w = me; w < q.teams * 2; w += stride) ws.team_task[w] = 0ull;
+        for (int w = me; w < q.teams; w += stride) { ws.arrived[w] = 0; ws.mailbox[w] = kMailboxAbsent; }
     }
     if (n == 0) {
         if (i < MPV_COUNTER_COUNT && !a.keep_counters) a.counters[i] = 0u;
@@ -1847,7 +1844,7 @@ task_end:
 // all of them, would save and restore dozens per call in private memory)
 template <class E, int KIND>
 __global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
-void node_task_kernel(const Launch* __restrict__ launch) {
+void node_task_kernel(const LaunchBlock* __restrict__ launch) {
     // KIND: MPV_METHOD_SPECINFER (all top-down rules) or MPV_METHOD_TRAVERSAL, or kKindAcceptance: the
     // top-down kernel reduced to what the acceptance rates need (an instantiation of its own, so that
     // its extra sweeps do not weigh on the register allocation of the verification kernels)
@@ -1861,7 +1858,7 @@ void node_task_kernel(const Launch* __restrict__ launch) {
     for (int w = threadIdx.x; w < static_cast<int>(sizeof(Launch) / sizeof(int)); w += kTaskBlock)
         g_launch_words[w] = reinterpret_cast<const int*>(launch)[w];
     for (int w = threadIdx.x; w < static_cast<int>(sizeof(TreeDesc) / sizeof(int)); w += kTaskBlock)
-        reinterpret_cast<int*>(&g_tree)[w] = reinterpret_cast<const int*>(launch->ws.tree)[w];
+        reinterpret_cast<int*>(&g_tree)[w] = reinterpret_cast<const int*>(&launch->tree)[w];
     __syncthreads();
     const QueuePlan& q = lds_launch().q;
     const Workspace& ws = lds_launch().ws;
@@ -2717,13 +2714,12 @@ static size_t carve(const mpv_problem* p, void* base, Workspace* ws) {
     unsigned long long* ac = static_cast<unsigned long long*>(take(static_cast<size_t>(p->B) * 8));
     int32_t* de = static_cast<int32_t*>(take(static_cast<size_t>(p->B) * 4));
     int32_t* cu = static_cast<int32_t*>(take(static_cast<size_t>(p->B) * 4));
-    TreeDesc* tr = static_cast<TreeDesc*>(take(sizeof(TreeDesc)));
     unsigned long long* ex = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxGrid) * 2 * kExchWords * 8));
     unsigned long long* tt = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxTeams) * 2 * 8));
     int32_t* ar = static_cast<int32_t*>(take(kMaxTeams * 4));
-    Launch* la = static_cast<Launch*>(take(sizeof(Launch)));
+    LaunchBlock* la = static_cast<LaunchBlock*>(take(sizeof(LaunchBlock)));
     if (ws) { ws->exch = ex; ws->team_task = tt; ws->arrived = ar; ws->launch = la; }
-    if (ws) { ws->At = At; ws->Ad = Ad; ws->cfin = cf; ws->aux = ax; ws->a0 = a0; ws->atest = at; ws->queue = qu; ws->qctl = qc; ws->mailbox = mb; ws->known = kn; ws->acc = ac; ws->decided = de; ws->cur = cu; ws->tree = tr; }
+    if (ws) { ws->At = At; ws->Ad = Ad; ws->cfin = cf; ws->aux = ax; ws->a0 = a0; ws->atest = at; ws->queue = qu; ws->qctl = qc; ws->mailbox = mb; ws->known = kn; ws->acc = ac; ws->decided = de; ws->cur = cu; }
     return off < 256 ? 256 : off;
 }
 
@@ -2873,18 +2869,20 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
         }
     }
     {
-        const int threads = 256;
+        const int threads = kInitBlock;
         const int blocks = (max(p->B, 64) + threads - 1) / threads;
-        launch(MPV_KERNEL_INIT, init_kernel, dim3(blocks, p->N), dim3(threads), s, q, tree, ws, a);
+        LaunchBlock block;
+        block.l.q = q; block.l.ws = ws; block.l.a = a; block.tree = tree;
+        launch(MPV_KERNEL_INIT, init_kernel, dim3(blocks, p->N), dim3(threads), s, block);
     }
     if (tasks > 0) {
         const dim3 grid(static_cast<unsigned>(q.teams * q.team_size)), block(kTaskBlock);
         if (a.estimate == 2) {
-            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, kKindAcceptance>, grid, block, s, const_cast<const Launch*>(ws.launch));
+            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, kKindAcceptance>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         } else if (p->method != MPV_METHOD_TRAVERSAL) {      // NSS, Naive and SpecTr are variants of the top-down kernel
-            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_SPECINFER>, grid, block, s, const_cast<const Launch*>(ws.launch));
+            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_SPECINFER>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         } else {
-            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_TRAVERSAL>, grid, block, s, const_cast<const Launch*>(ws.launch));
+            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_TRAVERSAL>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         }
     }
     if (a.dbg_stats) {
