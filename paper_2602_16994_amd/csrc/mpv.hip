@@ -2775,8 +2775,8 @@ static Shape launch_shape(const mpv_problem* p, int tasks, int64_t width, int pe
     // the most teams, which is what counts when more tasks can run at once (width) than there are teams.
     // With fewer a task's own time counts: more members, parts of about 2048 vectors (measured: shorter
     // parts no longer pay for the larger exchange), as long as there is a team for each.
-    // (64 trees of 33 inner nodes, V = 151936: block efficiency with 72 teams of 10 526 us, with 128 of 6
-    // 410; acceptance rates 670 and 497: a task spends less than half its time in sweeps.)
+    // (64 trees of 33 inner nodes, V = 151936, acceptance rates: 670 us with 72 teams of 10, 497 with 128 of 6: a
+    // task spends less than half its time in sweeps.)
     int g = 1;
     while (g < kMaxTeam && static_cast<long long>(g) * (kPartCapacity + kTaskBlock / 2) < nvec) ++g;
     while (g < kMaxTeam && slots / (g + 1) >= width && static_cast<long long>(g) * 2048 < nvec) ++g;
@@ -2827,18 +2827,13 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     static const int per_cu[3] = {resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>),
                                   resident_per_cu(node_task_kernel<E, MPV_METHOD_TRAVERSAL>),
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
-    // Node tasks that can run at the same time: one per tree where the rule follows one path at a time, every
-    // node's where all are queued up front, and where every task runs top-down (Traversal) one per chain.
-    int64_t width = p->B;
-    if (!a.lazy) {
-        int at_once = 0;
-        for (int n = 0; n < p->N; ++n) {
-            bool inner_child = false;
-            for (int j = 0; j < tree.nchild[n]; ++j) inner_child |= tree.nchild[tree.child_list[tree.child_off[n] + j]] > 0;
-            if (tree.nchild[n] && (all_up_front || !inner_child)) ++at_once;
-        }
-        width *= max(at_once, 1);
-    }
+    // Node tasks that can run at the same time: every node's for the acceptance rates, which do not depend on each other.
+    // (A rate is 1 less a mass: with other parts, so sums in another order, it moves by 3e-7 at most.)  All else is sized
+    // by the trees, block efficiency too, although its nodes could be counted like that (64 trees of 33 inner nodes,
+    // V = 151936, Traversal: 526 us, 410 with teams of 6): probabilities further down a tree are quotients of
+    // differences, p - c q over what is left of p, and sums in another order then move single ones by 1e-5 (against 64
+    // bits both are equally far off, up to 5e-5 over 71 such batches, but callers compare estimates of one tree).
+    const int64_t width = a.estimate == 2 ? tasks : p->B;
     const Shape shape = launch_shape<E>(p, tasks, width, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
     q.teams = shape.teams;
     q.team_size = shape.team_size;
