@@ -2767,26 +2767,42 @@ static int resident_per_cu(K kernel) {
 }
 
 template <class E>
-static Shape launch_shape(const mpv_problem* p, int tasks, int64_t width, int per_cu) {
+static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, int per_cu) {
     Shape s;
     const int nvec = (p->V + E::VEC - 1) / E::VEC;
     const int slots = per_cu * compute_units() < kMaxGrid ? per_cu * compute_units() : kMaxGrid;      // workgroups that can be resident
     // The fewest members whose kept parts (plus the one overflow slot a sweep hides) hold a row:
-    // the most teams, which is what counts when more tasks can run at once (width) than there are teams.
+    // the most teams, which is what counts when there are more trees than teams.
     // With fewer a task's own time counts: more members, parts of about 2048 vectors (measured: shorter
     // parts no longer pay for the larger exchange), as long as there is a team for each.
-    // (64 trees of 33 inner nodes, V = 151936, acceptance rates: 670 us with 72 teams of 10, 497 with 128 of 6: a
-    // task spends less than half its time in sweeps.)
     int g = 1;
     while (g < kMaxTeam && static_cast<long long>(g) * (kPartCapacity + kTaskBlock / 2) < nvec) ++g;
-    while (g < kMaxTeam && slots / (g + 1) >= width && static_cast<long long>(g) * 2048 < nvec) ++g;
-    int teams = slots / g;
-    if (teams > kMaxTeams) teams = kMaxTeams;
-    if (teams > tasks) teams = tasks;
-    if (teams < 1) teams = 1;
-    // workgroup i runs on chiplet i % 8: with a multiple of 8 teams every team can stay on one chiplet
+    const int fewest = g;
+    while (g < kMaxTeam && slots / (g + 1) >= p->B && static_cast<long long>(g) * 2048 < nvec) ++g;
+    auto teams_of = [&](int size) {
+        int teams = slots / size;
+        if (teams > kMaxTeams) teams = kMaxTeams;
+        if (teams > tasks) teams = tasks;
+        if (teams < 1) teams = 1;
+        // workgroup i runs on chiplet i % 8: with a multiple of 8 teams every team can stay on one chiplet
+        return size > 1 && teams >= 8 ? teams - teams % 8 : teams;
+    };
+    // Tasks that do not depend on each other: the size whose rounds take the least time.  A task's own time is
+    // a part that no team shortens (exchanges, scalar steps) and one that goes with a member's vectors; the two
+    // are equal at about 1900 vectors (22 us a task with parts of 1 900, 30 with 3 165).  64 trees of 33 inner
+    // nodes, V = 151936: 670 us with 72 teams of 10, 497 with 128 of 6; but 4 such trees of V = 262144 are three
+    // rounds either way, 91 us with teams of 16, 97 with teams of 11.
+    if (independent > 0) {
+        double least = 0.0;
+        for (int size = g; size >= fewest; --size) {
+            const int64_t teams = teams_of(size);
+            const double time = static_cast<double>((independent + teams - 1) / teams) * (1.0 + nvec / (1900.0 * size));
+            if (size == g || time < least) { least = time; s.team_size = size; }
+        }
+        g = s.team_size;
+    }
+    const int teams = teams_of(g);
     s.same_xcd = (g > 1 && teams >= 8) ? 1 : 0;
-    if (s.same_xcd) teams -= teams % 8;
     s.team_size = g;
     s.teams = teams;
     const int tiles = (nvec + kWave - 1) / kWave;                 // wave tiles of 64 vectors
@@ -2827,14 +2843,13 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     static const int per_cu[3] = {resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>),
                                   resident_per_cu(node_task_kernel<E, MPV_METHOD_TRAVERSAL>),
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
-    // Node tasks that can run at the same time: every node's for the acceptance rates, which do not depend on each other.
-    // (A rate is 1 less a mass: with other parts, so sums in another order, it moves by 3e-7 at most.)  All else is sized
-    // by the trees, block efficiency too, although its nodes could be counted like that (64 trees of 33 inner nodes,
-    // V = 151936, Traversal: 526 us, 410 with teams of 6): probabilities further down a tree are quotients of
-    // differences, p - c q over what is left of p, and sums in another order then move single ones by 1e-5 (against 64
-    // bits both are equally far off, up to 5e-5 over 71 such batches, but callers compare estimates of one tree).
-    const int64_t width = a.estimate == 2 ? tasks : p->B;
-    const Shape shape = launch_shape<E>(p, tasks, width, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
+    // Tasks that do not depend on each other: every node's for the acceptance rates.  (A rate is 1 less a mass: with other
+    // parts, so sums in another order, it moves by 7e-7 at most.)  Block efficiency keeps the size that the trees give,
+    // although its tasks could be counted too (64 trees of 33 inner nodes, V = 151936, Traversal: 526 us, 410 with teams of
+    // 6): probabilities further down a tree are quotients of differences, p - c q over what is left of p, and sums in
+    // another order then move single ones by 1e-5 (against 64 bits both are equally far off, up to 5e-5 over 71 such batches).
+    const int64_t independent = a.estimate == 2 ? static_cast<int64_t>(p->B) * plan.n_internal : 0;
+    const Shape shape = launch_shape<E>(p, tasks, independent, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
     q.teams = shape.teams;
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
