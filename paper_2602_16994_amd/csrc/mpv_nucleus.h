@@ -285,6 +285,7 @@ struct NucleusCollect {
     float k32, span;        // span: of what is listed, in units of the logits
     int first;              // the wave's run of the list starts here
     float mz, mk;           // the reference: mk = mz * k32 (the same in every lane of the wave)
+    float top;              // the largest logit of any wave, as far as this one knows
     float cut, thr;         // listed: logits >= cut; a vector whose terms add up to less than thr has none
     float s;                // this lane's mass, in units of the reference
     int n;                  // tokens listed by this wave (more than fit: too many)
@@ -299,7 +300,8 @@ struct NucleusCollect {
     __device__ __forceinline__ void refresh() {
         set_cut(uniform_f32(key_float(__hip_atomic_load(&sh.max_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))));
     }
-    __device__ __forceinline__ void set_cut(float top) {
+    __device__ __forceinline__ void set_cut(float largest) {
+        top = largest;
         const bool none = !(top > -INFINITY) || n > kNucleusPerWave;     // nothing but -inf so far, or no room left
         cut = none ? INFINITY : top - span;
         // (0.98: the rounding of the terms; 0.9: a logit above the reference must always be noticed)
@@ -328,7 +330,7 @@ struct NucleusCollect {
                 mz = nz; mk = nmk;
                 v = terms(a);
                 if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&sh.max_key, float_key(nz));
-                set_cut(fmaxf(nz, cut + span));
+                set_cut(fmaxf(nz, top));
             }
 #pragma unroll
             for (int i = 0; i < COUNT; ++i) {

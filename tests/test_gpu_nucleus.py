@@ -218,3 +218,32 @@ def test_ways_of_finding_the_threshold(shape, dtype, V):
         # float32 rows without a head: neighbouring upper sets differ by about 1/V of mass, which the band of 1e-6 resolves
         # at these lengths except where it happens to straddle one
         assert near <= 1
+
+
+# Rows whose leading logits are all -inf (a masked vocabulary).  The sweep takes whole chunks of 4 vectors per lane (1024 lanes
+# for rows of 2048 vectors or more, 256 for shorter ones); the -inf run covers one or two chunks, or ends a few logits before
+# or after the edge of one.  Behind it: the most likely token, alone less than 1 - top_p of the mass; then dozens of likely
+# tokens, which reach top_p without it; and eight tokens of equal logit, far enough apart to fall to several waves.
+@pytest.mark.parametrize("dtype,V,chunk", [(torch.bfloat16, 151936, 32768), (torch.bfloat16, 100003, 32768), (torch.bfloat16, 16383, 8192),
+                                           (torch.bfloat16, 15000, 8192), (torch.float32, 70000, 16384), (torch.float32, 50001, 16384),
+                                           (torch.float32, 8191, 4096)])
+def test_rows_that_begin_with_minus_infinity(dtype, V, chunk):
+    announce("nucleus leading -inf", dtype, "V", V)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    leads = [lead for lead in (chunk, 2 * chunk, chunk - 3, chunk + 5) if lead + 2000 <= V]
+    z = torch.full((3 * len(leads), V), -float("inf"), device="cuda")
+    for i, lead in enumerate(leads):
+        room = V - lead - 200
+        step = max(1, room // 48)
+        z[3 * i, lead + 57] = 2.25
+        z[3 * i, lead + 200: lead + 200 + 40 * step: step] = torch.linspace(1.0, 2.0, 40, device="cuda")
+        z[3 * i + 1, lead + 3: lead + 11] = 2.0
+        z[3 * i + 1, lead + 200: lead + 200 + 40 * step: step] = 2.0
+        z[3 * i + 2, lead:] = torch.randn(V - lead, generator=gen, device="cuda") * 3.0
+    z = z.to(dtype)
+    for T, top_p in ((1.0, 0.9), (0.8, 0.7)):
+        masked, thr, kept = mpv.mpv_nucleus_mask(z, T, top_p)
+        torch.cuda.synchronize()
+        near = check_rows(z, T, top_p, masked, thr, kept)
+        assert near <= (0 if dtype == torch.bfloat16 else 1)        # (float32 rows of noise: see MASS_BAND)
