@@ -261,6 +261,10 @@ __device__ __forceinline__ S uniform_struct(const S& s) {
 
 // ------------------------------------------------------------------ trees that each have a shape of their own
 
+__device__ __forceinline__ int tree_of_task(int t, int B, int N) {      // (node, sampling and resumed tasks)
+    return uniform_i32(t >= B * N + B ? t - (B * N + B) : (t >= B * N ? t - B * N : t / N));
+}
+
 // First wave of a workgroup, when nobody else reads the tables (the other waves wait at a barrier):
 // puts the tables of tree b into g_tree.  One load per tree change, about a microsecond; between
 // tasks of one tree nothing is read.
@@ -1019,6 +1023,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     using T = typename E::T;
     constexpr bool ACCEPT = KIND == kKindAcceptance;
     constexpr int METHOD = ACCEPT ? MPV_METHOD_SPECINFER : KIND;
+    // Trees with shapes of their own: a task of another tree has its tables loaded here (Traversal), or it goes back to the
+    // task loop, which loads them.  The top-down rules run this function through its whole length for SpecTr, and the loads
+    // within it made plain batches of many trees slower (Naive, 204 trees of V = 7872: 246 us, 237 without); Traversal
+    // has no such cost, and going back would make 256 trees of V = 151936 slower (538 us, 531).
+    constexpr bool kShapeInTask = !ACCEPT && METHOD == MPV_METHOD_TRAVERSAL;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
     const QueuePlan& q = lds_launch().q;
@@ -1047,9 +1056,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         return v;
     };
 
-    auto tree_of = [&](int t) __attribute__((always_inline)) -> int {
-        return uniform_i32(t >= B * N + B ? t - (B * N + B) : (t >= B * N ? t - B * N : t / N));
-    };
+    auto tree_of = [&](int t) __attribute__((always_inline)) -> int { return tree_of_task(t, B, N); };
 
     // ---- the part of the pair this member keeps on chip while a task runs
     RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs> pair;
@@ -1157,7 +1164,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     for (;;) {
     {
     // (a task that is under way already belongs to the tree of the task before)
-    if (!ACCEPT && started != task && uniform_i32(a.per_tree)) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), N, tree_of(task));
+    if (kShapeInTask && started != task && uniform_i32(a.per_tree)) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), N, tree_of(task));
     const NodeView nv = view_of(task);
     const bool resumed = nv.resumed;
     const int b = nv.b, n = nv.n, k = nv.k;
@@ -1814,7 +1821,8 @@ task_end:
     } else {
         next = team_listen(team, next_flags, ws);
     }
-    const bool node_next = next >= 0 && !(next >= B * N && next < B * N + B) && !team.dead;
+    const bool node_next = next >= 0 && !(next >= B * N && next < B * N + B) && !team.dead &&
+                           (kShapeInTask || !a.per_tree || tree_of(next) == uniform_i32(g_tree_of));
     if (started >= 0 && (!node_next || next != started)) {
         // taken up in vain (the tree was settled meanwhile, or the task went elsewhere): the other
         // waves finish their sweep, this wave's loads land, and the slots are free again
@@ -1950,6 +1958,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             task = team_listen(team, flags, ws);
         }
         const bool sampling = task != kTaskExit && task >= a.B * a.N && task < a.B * a.N + a.B && !(ACCEPT || a.estimate);
+        if (!ACCEPT && a.per_tree && task != kTaskExit) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), a.N, tree_of_task(task, a.B, a.N));
         if (sampling && leader && !asked) {
             // the walk and the bonus token come next: one sweep or two, then the team is free
             if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
@@ -2235,7 +2244,6 @@ __device__ __attribute__((noinline)) int sample_task(int b_in) {
     const bool leader = team.member == 0;
     const bool lead = leader && threadIdx.x == 0;
     if (wave == 0) {
-        if (a.per_tree) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), a.N, b);
         // where the token is drawn: the node the rule stops in, or the node a token-following
         // walk has reached
         const int stop = a.walk ? ld_relaxed(&ws.cur[b]) : walk_wave<METHOD>(tree, ws, a, b, leader);
