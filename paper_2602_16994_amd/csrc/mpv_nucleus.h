@@ -27,9 +27,12 @@
 // The list is filled best if the first cut is good: from the maximum of the workgroup's first 4 vectors per lane
 // (32 768 bf16 logits), which are in registers anyway; from one vector per lane the same rows took 143 us.
 //
-// The list's masses and the bins are added as integers (units of 2^-40), and each wave measures its
-// part of the row's mass against a reference that depends on its own part alone, so the results do
-// not depend on the order in which waves run (bitwise reproducible).
+// Whether the list suffices depends on when the waves hear of each other's maxima (a list that fills up
+// before the largest logit is known is given up), the results do not (bitwise reproducible): all of these
+// ways compare the same two numbers.  top_p of the row's mass comes from the first sweep, whose sums are
+// added in a fixed order against references that do not depend on timing.  The mass of an upper set is a sum of
+// whole units (2^-40), exact in any order where the list could have been used: 4096 terms or less of 24 bits
+// within 2^-12 of the largest.
 
 #pragma once
 
@@ -151,12 +154,13 @@ __device__ __forceinline__ NucleusProbe block_total(NucleusProbe p, NucleusShare
 }
 
 // Bisection: the smallest upper set of row values whose mass reaches `want`, between the set of
-// lo_key (which does, given by tau and kept) and hi_key (from which on nothing is left).
+// lo_key (which does, given by tau and kept) and hi_key (from which on nothing is left).  `base`: the
+// mass of the tokens above those that the probes look at.
 template <class PROBE>
-__device__ __forceinline__ void nucleus_bisect(uint32_t lo_key, uint32_t hi_key, double want, float& tau, int& kept, PROBE probe) {
+__device__ __forceinline__ void nucleus_bisect(uint32_t lo_key, uint32_t hi_key, double base, double want, float& tau, int& kept, PROBE probe) {
     for (int step = 0; step < 40 && hi_key - lo_key > 1u; ++step) {
         const NucleusProbe p = probe(key_float(lo_key + (hi_key - lo_key) / 2u));
-        if (p.mass >= want) {
+        if (base + p.mass >= want) {
             tau = p.above;                             // the same upper set, named by its smallest value
             kept = p.count;
             lo_key = float_key(tau);
@@ -168,11 +172,11 @@ __device__ __forceinline__ void nucleus_bisect(uint32_t lo_key, uint32_t hi_key,
 // ... among the listed tokens.  Up to 16 per lane the first wave does it alone: a probe is then
 // a few hundred cycles without a barrier, and the other waves' stores of the row go on meanwhile.
 template <int BLOCK>
-__device__ __forceinline__ void bisect_listed(NucleusShared<BLOCK>& sh, int n, uint32_t lo_key, uint32_t hi_key, double want,
+__device__ __forceinline__ void bisect_listed(NucleusShared<BLOCK>& sh, int n, uint32_t lo_key, uint32_t hi_key, double base, double want,
                                               float k32, float nA, float& tau, int& kept) {
     if (n <= 16 * kWave) {
         if (threadIdx.x < kWave) {
-            nucleus_bisect(lo_key, hi_key, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+            nucleus_bisect(lo_key, hi_key, base, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
                 return wave_total(probe_listed<kWave>(sh.list.z, n, cut, k32, nA));
             });
             if (threadIdx.x == 0) { sh.tau = tau; sh.kept = kept; }
@@ -181,7 +185,7 @@ __device__ __forceinline__ void bisect_listed(NucleusShared<BLOCK>& sh, int n, u
         tau = sh.tau;
         kept = sh.kept;
     } else {
-        nucleus_bisect(lo_key, hi_key, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+        nucleus_bisect(lo_key, hi_key, base, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
             return block_total<BLOCK>(probe_listed<BLOCK>(sh.list.z, n, cut, k32, nA), sh);
         });
     }
@@ -454,7 +458,7 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
                 if (row.tail0 + tid < V) *as_global(row.o + row.tail0 + tid) = MaskedStore<E>::to_elem(-INFINITY);
                 tau = all.above;
                 kept = all.count;
-                bisect_listed<BLOCK>(sh, listed, float_key(tau), float_key(row_max) + 1u, want, k32, nA, tau, kept);
+                bisect_listed<BLOCK>(sh, listed, float_key(tau), float_key(row_max) + 1u, 0.0, want, k32, nA, tau, kept);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's share of the fill has been performed
                 lds_barrier();                                        // ... and everybody's
                 for (int i = tid; i < listed; i += BLOCK) {
@@ -485,14 +489,15 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
                     static_assert(kNucleusBins % kWave == 0, "whole bins per lane");
                     double mine = 0.0;
                     for (int i = 0; i < PER; ++i) mine += static_cast<double>(sh.bin[lane * PER + i]);
-                    const double incl = wave_inclusive_scan(mine);
-                    // (of the row's mass as the bins have it: added up from the very same terms)
-                    want = static_cast<double>(top_p) * lane_f64(incl, kWave - 1);
-                    if (lane == 0) sh.want = want;
+                    const double incl = wave_inclusive_scan(mine), up_to = __shfl_up(incl, 1, kWave);
+                    // The same sum as with the list decides.  (Only if top_p is so close to 1 that it is out of reach by its
+                    // rounding, then there is no list that reaches it either: top_p of what the bins hold.)
+                    const double whole = lane_f64(incl, kWave - 1);
+                    if (!(whole >= want)) want = static_cast<double>(top_p) * whole;
                     const unsigned long long reach = __builtin_amdgcn_ballot_w64(incl >= want);
-                    if (lane == 0) sh.tau_bin = -1;
-                    if (reach != 0ull && lane == __ffsll(static_cast<long long>(reach)) - 1) {
-                        double run = incl - mine;
+                    if (lane == 0) sh.want = want;
+                    if (lane == __ffsll(static_cast<long long>(reach)) - 1) {
+                        double run = lane > 0 ? up_to : 0.0;
                         for (int i = 0; i < PER; ++i) {
                             const double m = static_cast<double>(sh.bin[lane * PER + i]);
                             if (run + m >= want || i == PER - 1) { sh.tau_bin = lane * PER + i; sh.above_bin = run; break; }
@@ -506,7 +511,7 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
                 want = sh.want;
                 // how many tokens the bin holds at most: its mass over the smallest a token of it can have
                 // (one unit less for each token's rounding down)
-                bool fits = tb >= 0 && tb < kNucleusBins - 1;
+                bool fits = tb < kNucleusBins - 1;
                 if (fits) {
                     const double least = floor(static_cast<double>(fast_exp2(-(static_cast<float>(tb) + 1.01f) / kBinsPerOctave)) * kNucleusUnit) - 1.0;
                     fits = least >= 1.0 && static_cast<double>(sh.bin[tb]) <= least * NucleusShared<BLOCK>::CAP;
@@ -549,16 +554,16 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
                     const NucleusProbe bin = block_total<BLOCK>(probe_listed<BLOCK>(sh.list.z, n, -INFINITY, k32, nA), sh);
                     tau = bin.above;
                     kept = bin.count;
-                    bisect_listed<BLOCK>(sh, n, float_key(tau), float_key(row_max) + 1u, want - above_bin, k32, nA, tau, kept);
+                    bisect_listed<BLOCK>(sh, n, float_key(tau), float_key(row_max) + 1u, above_bin, want, k32, nA, tau, kept);
                     kept += count_above;
                     for (int i = tid; i < n; i += BLOCK) {
                         const float z = sh.list.z[i];
                         if (z >= tau) *as_global(row.o + sh.list.at[i]) = MaskedStore<E>::to_elem(z);
                     }
                     written = true;
-                } else if (tb >= 0) {
+                } else {
                     // ---- too many tokens in one bin: probe the row in memory
-                    nucleus_bisect(float_key(-INFINITY), float_key(row_max) + 1u, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
+                    nucleus_bisect(float_key(-INFINITY), float_key(row_max) + 1u, 0.0, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
                         NucleusProbe p;
                         p.mass = 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = 0;
                         auto item = [&](float z, bool inside) __attribute__((always_inline)) {
@@ -577,7 +582,6 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
                         return block_total<BLOCK>(p, sh);
                     });
                 }
-                // (tb < 0: the mass of the whole row rounds to less than top_p of it: everything is kept)
             }
         }
     }

@@ -247,3 +247,47 @@ def test_rows_that_begin_with_minus_infinity(dtype, V, chunk):
         torch.cuda.synchronize()
         near = check_rows(z, T, top_p, masked, thr, kept)
         assert near <= (0 if dtype == torch.bfloat16 else 1)        # (float32 rows of noise: see MASS_BAND)
+
+
+# Logits and temperature with exact masses: the scale of the exponent, log2(e) / T in float32, is 1, and a token of logit -n has
+# 2^-n of the largest one's mass.  Every sum below has few enough bits that its order does not matter.
+EXACT_T = float(np.float32(1.4426950408889634))
+
+
+def test_the_threshold_does_not_depend_on_where_the_tokens_are():
+    """The same tokens in two orders: with the likely ones in front, the list of likely tokens suffices; behind 65536 tokens of
+    equal logit it overflows.  top_p lies where the mass of the two million least likely tokens decides: their 2^-20 of the
+    largest one's makes the most likely token alone fall short of it."""
+    V = 1 << 21
+    assert np.float32(1.4426950408889634 / np.float64(np.float32(EXACT_T))) == np.float32(1.0)
+    z = torch.full((2, V), -41.0, device="cuda")
+    z[0, 0], z[0, 1], z[0, 2: 2 + 65536] = 0.0, -1.0, -30.0
+    z[1, :65536], z[1, V - 2], z[1, V - 9] = -30.0, 0.0, -1.0
+    head = 1.5 + 65536 * 2.0 ** -30
+    tail = (V - 65538) * 2.0 ** -41
+    top_p = float(np.float32(0.5 * (1.0 / head + 1.0 / (head + tail))))
+    # 1 / head - 1 / (head + tail) is 4e-7; float32 sums in any order and the rounding of top_p move the line by 6e-8 each
+    assert top_p * (head + tail) > 1.0 + 2e-7 and top_p * head < 1.0 - 2e-7
+    for dtype in (torch.bfloat16, torch.float32):
+        announce("nucleus order of tokens", dtype)
+        _, thr, kept = mpv.mpv_nucleus_mask(z.to(dtype), EXACT_T, top_p)
+        torch.cuda.synchronize()
+        assert thr.tolist() == [-1.0, -1.0] and kept.tolist() == [2, 2]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_repeated_calls_agree(dtype):
+    """Rows whose largest logits rise along the row, so that what a wave lists depends on when it hears of the others' maxima."""
+    announce("nucleus repeated calls", dtype)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+    V = 131072
+    z = torch.randn(48, V, generator=gen, device="cuda") * 1.5 + torch.linspace(0.0, 6.0, V, device="cuda")
+    z = z.to(dtype)
+    for top_p in (0.3, 0.9):
+        first = mpv.mpv_nucleus_mask(z, 1.0, top_p)
+        for _ in range(8):
+            again = mpv.mpv_nucleus_mask(z, 1.0, top_p)
+            torch.cuda.synchronize()
+            assert torch.equal(again[1], first[1]) and torch.equal(again[2], first[2])
+            assert torch.equal(again[0], first[0])
