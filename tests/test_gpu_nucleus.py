@@ -291,3 +291,30 @@ def test_repeated_calls_agree(dtype):
             torch.cuda.synchronize()
             assert torch.equal(again[1], first[1]) and torch.equal(again[2], first[2])
             assert torch.equal(again[0], first[0])
+
+
+# Rows on which one bin (a 32nd of a binary order) holds more tokens than the list: equal logits, two or a few distinct ones,
+# nearly equal ones far from zero, and around zero, where the keys of neighbouring values lie far apart.  Both sizes of the
+# workgroup (2048 vectors or more, and less), rows that start at any address.
+@pytest.mark.parametrize("shape", ["equal", "two", "steps", "level", "around_zero", "negative"])
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 9001), (torch.bfloat16, 16392), (torch.bfloat16, 40961), (torch.float32, 6003),
+                                     (torch.float32, 8196), (torch.float32, 20481)])
+def test_rows_of_few_or_nearly_equal_logits(shape, dtype, V):
+    announce("nucleus few or nearly equal logits", shape, dtype, "V", V)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    z = torch.randn(5, V, generator=gen, device="cuda")
+    z = {"equal": torch.full_like(z, -1.25), "two": -1.0 * (z > 0.3), "steps": torch.round(z * 1.5) * 2.0, "level": 9.0 + z * 0.004,
+         "around_zero": z * 0.002, "negative": -30.0 + z * 0.02}[shape].to(dtype)
+    z[3, : V // 3] = -float("inf")
+    z[4, ::7] = -float("inf")
+    same = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    for T, top_p in ((1.0, 0.9), (0.7, 0.3), (1.3, 0.999)):
+        masked, thr, kept = mpv.mpv_nucleus_mask(z, T, top_p)
+        place = z.clone()
+        mpv.mpv_nucleus_mask(place, T, top_p, inplace=True)
+        torch.cuda.synchronize()
+        assert torch.equal(place.view(same), masked.view(same))
+        # float32 rows: upper sets of neighbouring values differ by 1/V or so, 5e-5 and more; the sums are within MASS_BAND, so
+        # at most a few in a hundred of such rows have one that close to top_p
+        assert check_rows(z, T, top_p, masked, thr, kept) <= (1 if dtype == torch.float32 else 0)
