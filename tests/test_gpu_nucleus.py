@@ -318,3 +318,27 @@ def test_rows_of_few_or_nearly_equal_logits(shape, dtype, V):
         # float32 rows: upper sets of neighbouring values differ by 1/V or so, 5e-5 and more; the sums are within MASS_BAND, so
         # at most a few in a hundred of such rows have one that close to top_p
         assert check_rows(z, T, top_p, masked, thr, kept) <= (1 if dtype == torch.float32 else 0)
+
+
+# The largest token comes behind thousands of tokens that filled the list while the cut was too low.  It reaches top_p alone, or with
+# a few of the others, or not with any list; its equals, if any, are kept with it.  (7.5 and 15 above a background of standard
+# deviation 2: shares of the mass from 0.4 to 0.999.)
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 16385), (torch.bfloat16, 50001), (torch.float32, 8000), (torch.float32, 50001),
+                                     (torch.float32, 131072)])
+def test_the_largest_token_comes_late(dtype, V):
+    announce("nucleus late largest token", dtype, "V", V)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V + 1)
+    z = torch.randn(8, V, generator=gen, device="cuda") * 2.0
+    for r in range(8):
+        z[r, V - 7 - r] = 8.0 + (7.5, 15.0)[r % 2] - r / 8
+    z[4, V - 2] = z[4, V - 11]                           # the largest twice
+    z[5, V - 500: V - 20] = 9.0                          # hundreds of equals below it
+    z[6, V - 6000: V - 900] = z[6].max()                 # thousands of equals: more than any list
+    z = z.to(dtype)
+    for T, top_p in ((1.0, 0.9), (1.0, 0.98), (1.1, 0.7)):
+        masked, thr, kept = mpv.mpv_nucleus_mask(z, T, top_p)
+        again = mpv.mpv_nucleus_mask(z, T, top_p)
+        torch.cuda.synchronize()
+        assert torch.equal(again[1], thr) and torch.equal(again[2], kept) and torch.equal(again[0], masked)
+        assert check_rows(z, T, top_p, masked, thr, kept) <= (1 if dtype == torch.float32 else 0)
