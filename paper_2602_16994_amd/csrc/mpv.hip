@@ -1821,8 +1821,8 @@ task_end:
     } else {
         next = team_listen(team, next_flags, ws);
     }
-    const bool node_next = next >= 0 && !(next >= B * N && next < B * N + B) && !team.dead &&
-                           (kShapeInTask || !a.per_tree || tree_of(next) == uniform_i32(g_tree_of));
+    bool node_next = next >= 0 && !(next >= B * N && next < B * N + B) && !team.dead;
+    if constexpr (!kShapeInTask && !ACCEPT) node_next = node_next && (!a.per_tree || tree_of(next) == uniform_i32(g_tree_of));
     if (started >= 0 && (!node_next || next != started)) {
         // taken up in vain (the tree was settled meanwhile, or the task went elsewhere): the other
         // waves finish their sweep, this wave's loads land, and the slots are free again
