@@ -351,3 +351,44 @@ def test_acceptance_rates_of_merged_trees(method):
     assert cnt[4] == 0 and cnt[5] == internal
     with pytest.raises(mpv.MpvError):
         mpv.mpv_acceptance_rates(cfg.parent, inputs["target"], inputs["draft"], cfg.T, TV, merged_parent=mp)
+
+
+@pytest.mark.parametrize("method", [SI, TV, NAIVE])
+def test_merged_call_captured_in_a_graph(method):
+    """A captured call holds the shapes of its trees: the host's parent arrays are overwritten after the capture, the inputs
+    between the replays; every replay gives what the eager call gives on the same inputs."""
+    cfg = workloads.Config("merged_graph", B=300, V=2003, K=4, L1=1, L2=3, dtype="bf16", T=0.9, methods=[method],
+                           draft_sigma=2.5, target_sigma=1.0, top_boost_k=3, top_boost=6.0, seed=8701)
+    inputs = workloads.make_context_inputs(cfg, "cuda")
+    mp, _ = merged_arrays(cfg, inputs)
+    announce("merged call under graph capture", NAMES[method], f"B={cfg.B} N={cfg.N} V={cfg.V} runs={len(runs_of(mp))}")
+    assert len(runs_of(mp)) > 8 and cfg.B * cfg.N > 3584         # shapes in more than one launch's arguments
+    args = (cfg.parent, inputs["tokens"], inputs["target"], inputs["draft"], cfg.T, inputs["uniforms"], method)
+    draws = inputs["draw_uniforms"]
+    held = mp.copy()
+    out = mpv.mpv_verify(*args, draw_uniforms=draws, merged_parent=held)           # outputs and workspace exist before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        mpv.mpv_verify(*args, draw_uniforms=draws, merged_parent=held, out=out)
+    held[:] = -1
+    torch.cuda.synchronize()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+    for replay in range(4):
+        if replay:
+            inputs["uniforms"].copy_(torch.rand(cfg.B, cfg.N, generator=gen, device="cuda"))
+            draws.copy_(torch.rand(cfg.B, cfg.N, generator=gen, device="cuda"))
+        want = result_to_host(mpv.mpv_verify(*args, draw_uniforms=draws, merged_parent=mp))
+        torch.cuda.synchronize()
+        out.accept_len.fill_(-7)
+        out.bonus_token.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = result_to_host(out)
+        assert got["counters"][4] == 0
+        for key in ("accept_len", "path_nodes", "path_tokens", "bonus_token"):
+            assert np.array_equal(got[key], want[key]), (replay, key)
