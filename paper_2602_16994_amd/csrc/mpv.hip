@@ -985,7 +985,7 @@ __device__ __forceinline__ void run_sweep(PAIR& pair, const SweepCmd& cmd, float
         pair.replay(f);
         s0 = static_cast<double>(f.acc0) + static_cast<double>(f.acc1);
     } else {
-        ResidualMassRawF<E> f;
+        ResidualMassRawF<E, ACCEPT> f;
         f.init(k32, cmd.nAt, cmd.nAd, cmd.rho);
         pair.replay(f);
         s0 = f.total();
@@ -1112,9 +1112,10 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 if (asked_for != t) take_up(t);
                 asked_for = -1;
                 const int kk = uniform_i32(tree.nchild[view_of(t).n]);
-                PairStatsRawF<E> f;
+                PairStatsRawF<E, ACCEPT> f;
                 f.t.init(); f.d.init(); f.k32 = k32;
                 pair.first_pass(f);
+                f.t.finish(); f.d.finish();
                 if (wave == 1) {
                     if (lane < kk) { ch_tok[lane] = pf_x; ch_u[lane] = pf_u; ch_zt[lane] = E::load_one(&pf_t); ch_zd[lane] = E::load_one(&pf_d); }
                     if (lane == MPV_MAX_CHILDREN) ch_u[MPV_MAX_CHILDREN] = pf_u;
@@ -1231,9 +1232,10 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         const bool wants_a0 = lead && METHOD == MPV_METHOD_TRAVERSAL && n != 0 && !(a0_known >= 0.0);
         unsigned long long bits = kNotReady;
         if (wants_a0) bits = ld_relaxed(reinterpret_cast<const unsigned long long*>(&ws.a0[bn]));
-        PairStatsRawF<E> f;
+        PairStatsRawF<E, ACCEPT> f;
         f.t.init(); f.d.init(); f.k32 = k32;
         pair.first_pass(f);
+        f.t.finish(); f.d.finish();
         double a0 = 1.0;
         if (wants_a0) {
             for (int spin = 0; spin < kMaxSpins && bits == kNotReady; ++spin) {

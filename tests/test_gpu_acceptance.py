@@ -122,3 +122,26 @@ def test_benchmark_batch_sampled():
     # the paper's observation (Sec. 5): with i.i.d. rows there is no trend with depth here, but the
     # root (k = 8) must accept more often than the chain nodes (k = 1)
     assert got[:, 0].mean() > got[:, 1].mean()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_small_terms_are_not_lost_beside_a_large_one(dtype):
+    """Equal target and draft rows: Naive's rate is sum min(p, q) = 1.  One token has almost all of the mass; a lane meets it in
+    its first vector of a later sweep, and each of its other tokens is less than half a unit in the last place of the large term
+    (2^-25): added one by one next to it they leave no trace (about 50 of them: 1.3e-6).  Added to each other first, a vector at
+    a time, each of at most 7 vectors next to the large term is rounded by 2^-25 at most: 2.1e-7; the exponentials and the
+    factors of p add 1e-7."""
+    V, B = 151936, 64 if dtype == torch.bfloat16 else 24
+    parent = mpv.delayed_tree(8, 0, 5)
+    N = len(parent)
+    print("[case] acceptance, one large term", dtype, f"B={B} N={N} V={V}", flush=True)
+    row = torch.zeros(V, device="cuda")
+    row[6 * 256 * (8 if dtype == torch.bfloat16 else 4)] = 17.5           # (the sweeps begin with the seventh slot of a lane)
+    assert 2.0 ** -26 < 1.0 / (float(torch.tensor(17.5).exp()) + V) < 2.0 ** -25
+    rows = row.to(dtype).expand(B, N, V).contiguous()
+    alpha, counters = mpv.mpv_acceptance_rates(parent, rows, rows, 1.0, mpv.MPV_METHOD_NAIVE)
+    torch.cuda.synchronize()
+    inner = sorted(set(parent[1:]))
+    err = float((alpha[:, inner].double() - 1.0).abs().max())
+    print("[report] largest error:", err, flush=True)
+    assert int(counters[4]) == 0 and err <= 3.1e-7
