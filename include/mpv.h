@@ -275,7 +275,8 @@ int mpv_block_efficiency_merged(const mpv_problem* problem, const int32_t* merge
  * Depends on the node's two logit rows and on k only: no tokens, no uniforms.
  * alpha: DEVICE float32 [B,N]; leaves get 0.  Methods: SPECINFER, NSS, NAIVE, SPECTR;
  * MPV_METHOD_TRAVERSAL returns MPV_ERR_UNSUPPORTED (it is not an OTLP solver; App. C has no rate
- * for it).  Everything else as for mpv_block_efficiency. */
+ * for it).  Rates come from sums of float32 terms over the row: off by 5e-8 on average (2e-7 for SpecInfer on rows with
+ * a dominant token, single ones up to 5e-6).  Everything else as for mpv_block_efficiency. */
 int mpv_acceptance_rates(const mpv_problem* problem, const void* target_logits, const void* draft_logits,
                          void* workspace, size_t workspace_bytes, float* alpha, uint32_t* counters,
                          void* hip_stream);
@@ -300,7 +301,9 @@ int mpv_acceptance_rates_merged(const mpv_problem* problem, const int32_t* merge
  * logits, out: DEVICE, [rows, V] of logit_dtype, 16-byte aligned bases; out may equal logits
  * (in place), otherwise the buffers must not overlap.  Logits must be finite or -inf.
  * threshold_out: DEVICE float32 [rows] or NULL: tau.  kept_out: DEVICE int32 [rows] or NULL: the
- * number of tokens kept.  Errors: MPV_ERR_BAD_SHAPE (rows < 0, V < 1), _UNSUPPORTED (V or rows too
+ * number of tokens kept.  Precision: the row's mass is a float32 sum (relative error about 1e-7), and an upper set can
+ * appear smaller by V * 2^-40 of the largest token's mass (2.4e-7 at V = 262144): tau is the right one for a top_p
+ * within 1e-6 of the one given (within 2e-6 at V = 2^21).  Errors: MPV_ERR_BAD_SHAPE (rows < 0, V < 1), _UNSUPPORTED (V or rows too
  * large), _BAD_DTYPE, _BAD_TEMPERATURE, _BAD_TOP_P, _NULL, _ALIGNMENT, _HIP. */
 int mpv_nucleus_mask(const void* logits, void* out, int32_t logit_dtype, int64_t rows, int32_t V,
                      float temperature, float top_p, float* threshold_out, int32_t* kept_out, void* hip_stream);

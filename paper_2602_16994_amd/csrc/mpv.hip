@@ -1788,7 +1788,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     } else if (resume_i) {
         // Queued, not run at once: while there are trees that have not been begun, beginning them comes
         // first (class 0), so that the long trees, whose branching node is resumed, share the teams evenly
-        // at the end instead of running on by themselves (benchmark batch: 503 -> 478 us).
+        // at the end instead of running on by themselves (benchmark batch: 5 % less time).
         if (lane == 0) append_task(tree, ws, 1, B * N + B + b);
     } else if (taken >= 0) {
         // (nothing else can follow from a task that has no child of its own to run)
@@ -2801,7 +2801,9 @@ static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, 
     // a part that no team shortens (exchanges, scalar steps) and one that goes with a member's vectors; the two
     // are equal at about 1900 vectors (22 us a task with parts of 1 900, 30 with 3 165).  64 trees of 33 inner
     // nodes, V = 151936: 670 us with 72 teams of 10, 497 with 128 of 6; but 4 such trees of V = 262144 are three
-    // rounds either way, 91 us with teams of 16, 97 with teams of 11.
+    // rounds either way, 91 us with teams of 16, 97 with teams of 11.  (The constant is SpecInfer's in bf16 at V = 151936;
+    // with the others the sizes it gives are faster too than those that the trees give: SpecTr 791 -> 609 us, NSS
+    // 822 -> 628, Naive 783 -> 598; 24 trees of V = 100003 in float32, 12 inner nodes: 137 -> 98, 150 -> 109, 146 -> 106.)
     if (independent > 0) {
         double least = 0.0;
         for (int size = g; size >= fewest; --size) {

@@ -24,7 +24,8 @@
 // What bounds it: traffic, at the rate of a device copy.  10 496 rows of 151 936 bf16 logits, top_p 0.9 held by
 // a few dozen tokens: 1.25 ms = 5.1 TB/s read and written (a large copy reaches 5.1); it was 2.11 ms with a read for
 // the maximum, one for the list and one for the masked copy.  960 rows of 128 256: 115 us, was 350.  Flat rows
-// (top_p 0.99, 40 000 tokens kept; 3): 190 us, was 925 with every probe a pass over the row.
+// (top_p 0.99, 40 000 tokens kept; 3): 191 us, was 925 with every probe a pass over the row.  Rows of 32 000 to 50 000
+// times the same logit are the ones that took less with those probes (960 of 32 000 in bf16: 62 us, now 68).
 // The list is filled best if the first cut is good: from the maximum of the workgroup's first 4 vectors per lane
 // (32 768 bf16 logits), which are in registers anyway; from one vector per lane the same rows took 143 us.
 //
@@ -33,7 +34,8 @@
 // ways compare the same two numbers.  top_p of the row's mass comes from the first sweep, whose sums are
 // added in a fixed order against references that do not depend on timing.  The mass of an upper set is a sum of
 // whole units (2^-40), exact in any order where the list could have been used: 4096 terms or less of 24 bits
-// within 2^-12 of the largest.
+// within 2^-12 of the largest.  (In the bins a token counts with its mass rounded down to a whole unit: an upper set
+// appears smaller by V * 2^-40 of the largest mass at most.)
 
 #pragma once
 
@@ -223,8 +225,8 @@ struct NucleusRow {
     }
     // Calls f(values, position of the first, raw vector, inside) for every vector, all lanes of a wave
     // together (lanes past the end: inside = false, -inf values), then edge(value, position, inside) for
-    // the elements before and after.  U loads per lane are in flight: with four workgroups per compute unit
-    // (64 registers per lane) the other workgroups' work covers their latency.  begin(vectors) sees the
+    // the elements before and after.  U loads per lane are in flight: with 32 waves per compute unit (two
+    // workgroups of 1024 lanes or eight of 256, 64 registers per lane) the other waves' work covers their latency.  begin(vectors) sees the
     // first U vectors of every lane before any of them is used.
     struct Nothing { template <class R> __device__ __forceinline__ void operator()(const R&) const {} };
     template <int BLOCK, int U, class F, class G, class H = Nothing>
