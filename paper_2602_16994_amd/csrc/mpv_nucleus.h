@@ -191,10 +191,13 @@ __device__ __forceinline__ void nucleus_bisect(uint32_t lo_key, uint32_t hi_key,
 }
 // ... among the listed tokens.  Up to 16 per lane the first wave does it alone: a probe is then
 // a few hundred cycles without a barrier, and the other waves' stores of the row go on meanwhile.
+// Four waves share more than 8 per lane while the compute units have idle slots (flat float32 rows of 1000: 8 rows
+// 22.7 us by the first wave alone, 15.0 shared, 1024 rows 29.5 and 26.2; but 2000 with a few raised tokens 35.1 and 40.7).
 template <int BLOCK>
 __device__ __forceinline__ void bisect_listed(NucleusShared<BLOCK>& sh, int n, uint32_t lo_key, uint32_t hi_key, double base, double want,
                                               float k32, float nA, float& tau, int& kept) {
-    if (n <= 16 * kWave) {
+    const int alone = BLOCK == 256 && gridDim.x <= 1024u ? 8 : 16;
+    if (n <= alone * kWave) {
         if (threadIdx.x < kWave) {
             nucleus_bisect(lo_key, hi_key, base, want, tau, kept, [&](float cut) __attribute__((always_inline)) {
                 return wave_total(probe_listed<kWave>(sh.list.z, n, cut, k32, nA));
