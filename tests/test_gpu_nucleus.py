@@ -342,3 +342,19 @@ def test_the_largest_token_comes_late(dtype, V):
         torch.cuda.synchronize()
         assert torch.equal(again[1], thr) and torch.equal(again[2], kept) and torch.equal(again[0], masked)
         assert check_rows(z, T, top_p, masked, thr, kept) <= (1 if dtype == torch.float32 else 0)
+
+
+def test_one_wave_or_four_find_the_same_threshold():
+    """Up to 1024 short rows share the bisection of more than 512 listed tokens among four waves, more rows leave it to one."""
+    announce("nucleus, rows of 1000 listed tokens")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(41)
+    z = torch.randn(1025, 1000, generator=gen, device="cuda")
+    for top_p in (0.9, 0.4):
+        many = mpv.mpv_nucleus_mask(z, 1.0, top_p)
+        few = mpv.mpv_nucleus_mask(z[:1024], 1.0, top_p)
+        torch.cuda.synchronize()
+        for a, b in zip(many, few):
+            assert torch.equal(a[:1024], b)
+        # (upper sets of neighbouring values differ by 1e-3 of the mass)
+        assert check_rows(z[:12], 1.0, top_p, few[0][:12], few[1][:12], few[2][:12]) == 0
