@@ -78,6 +78,7 @@ constexpr int kShapeNoSplit = 127;        // (7 bits in kShapeSplit: split_node,
 static_assert(MPV_MAX_NODES <= 64 && MPV_MAX_CHILDREN < 32, "the fields of a shape word are too narrow");
 
 constexpr int kMaxClasses = 4;
+constexpr int kCtlIdle = 4 + 2 * kMaxClasses, kCtlFirst = kCtlIdle + 1, kCtlTreesDone = kCtlIdle + 2, kCtlWords = kCtlIdle + 3;
 static_assert(kMaxClasses + 1 <= 8, "TreeDesc::class_off is too short");
 
 // The task queue is one first-in-first-out queue per priority class; a free team is
@@ -90,10 +91,11 @@ static_assert(kMaxClasses + 1 <= 8, "TreeDesc::class_off is too short");
 struct QueuePlan {
     int32_t nclass;
     int32_t off[kMaxClasses + 1];        // class c owns queue[off[c] .. off[c+1])
-    int32_t init_tail[kMaxClasses];      // entries of class c written by init_kernel
-    int32_t init_slot[MPV_MAX_NODES];    // -1, or the node's index among the prequeued nodes of its class
-    int32_t init_total;                  // prequeued tasks
-    int32_t root_is_leaf;                // no node task at all: the sampling tasks are prequeued
+    // First tasks: the nodes whose tasks can run from the start, lowest class first; first task number h
+    // is that of node init_node[h / B] of tree h % B.  They are never queued, the teams count them off.
+    int8_t init_node[MPV_MAX_NODES];
+    int32_t init_total;                  // first tasks
+    int32_t root_is_leaf;                // no node task at all: the first tasks are the sampling tasks
     int32_t teams;                       // teams of the launch (the grid is teams * team_size workgroups)
     int32_t team_size;                   // G: workgroups that share one task
     int32_t part_vecs;                   // 16-byte vectors of a row per member (a multiple of 64)
@@ -117,9 +119,10 @@ struct Workspace {
     // [0] appended: tasks ever queued or started directly, [1] completed: tasks finished or cancelled,
     // [2] exit: set when nothing is left, [3] lock: held by the team leader that is dispatching,
     // [4 + c] tail of class c: entries appended, [4 + kMaxClasses + c] head of class c: entries handed out,
-    // [4 + 2 kMaxClasses] teams left waiting after the last round of dispatching (a hint)
+    // [kCtlIdle] teams left waiting after the last round of dispatching (a hint), [kCtlFirst] first tasks
+    // counted off, [kCtlTreesDone] trees whose outputs are written
     int32_t* qctl;
-    int32_t* mailbox;    // [teams] kMailboxAbsent until every member has started, then kMailboxWaiting /
+    int32_t* mailbox;    // [teams] kMailboxAbsent until the team has asked for a task, then kMailboxWaiting /
                          // kMailboxSoon, or the task handed to that team
     // Per tree, one bit per node at the node's position in postorder: `known` = the outcome of
     // the node's test is settled, `acc` = it is "accepted" (valid once known).  `decided` = the
@@ -130,11 +133,11 @@ struct Workspace {
     int32_t* decided;
     int32_t* cur;        // [B] token-following walks: the node the walk has reached
     // Teams.  exch: [team][2][member][kExchWords] words of (sequence number << 32 | 32 bits of payload);
-    // team_task: [team][2] the task the leader has taken and its flags, same packing; arrived: members
-    // of the team that have started.
+    // team_task: [team][2] the task the leader has taken and its flags, same packing.  The first line of a
+    // team's area also serves its start (it is first written by exchange 2): word 0 counts the members that
+    // have started, words 1 and 2 announce the first task.
     unsigned long long* exch;
     unsigned long long* team_task;
-    int32_t* arrived;
     struct LaunchBlock* launch;   // what node_task_kernel is launched with, written by init_kernel
 };
 
@@ -210,8 +213,9 @@ constexpr int kMaxTiles = MPV_MAX_VOCAB / (kWave * 4);
 // task hand-over between the dispatcher and the teams (see "task queue")
 constexpr int kMailboxWaiting = -1;                  // the team is idle
 constexpr int kMailboxSoon = -2;                     // the team has asked ahead: it will be free shortly
-constexpr int kMailboxAbsent = -3;                   // not every member of the team has started yet
+constexpr int kMailboxAbsent = -3;                   // the team has not asked for anything yet
 constexpr int kTaskExit = -1;                         // what a leader's wait returns when all is done
+constexpr int kTaskNone = -2;                         // announced to a team that came too late for a first task
 constexpr int kWorkerSlots = 8;                       // mailboxes per dispatcher lane
 constexpr int kMaxTeams = kWave * kWorkerSlots;
 constexpr int kKindAcceptance = 100;                   // node_task_kernel instantiation for the acceptance rates (see there)
@@ -387,7 +391,6 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
     const QueuePlan& q = block.l.q;
     const Workspace& ws = block.l.ws;
     const Args& a = block.l.a;
-    const TreeDesc& tree = block.tree;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;      // tree, or word number
     const int n = blockIdx.y;
     const int stride = gridDim.x * gridDim.y * blockDim.x;
@@ -401,16 +404,11 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
         const int exch_words = q.teams * q.team_size * 2 * kExchWords;
         for (int w = me; w < exch_words; w += stride) ws.exch[w] = 0ull;
         for (int w = me; w < q.teams * 2; w += stride) ws.team_task[w] = 0ull;
-        for (int w = me; w < q.teams; w += stride) { ws.arrived[w] = 0; ws.mailbox[w] = kMailboxAbsent; }
+        for (int w = me; w < q.teams; w += stride) ws.mailbox[w] = kMailboxAbsent;
     }
     if (n == 0) {
         if (i < MPV_COUNTER_COUNT && !a.keep_counters) a.counters[i] = 0u;
-        if (i == 0) { ws.qctl[0] = q.init_total; ws.qctl[1] = 0; ws.qctl[2] = 0; ws.qctl[3] = 0; ws.qctl[4 + 2 * kMaxClasses] = 0; }
-        for (int c = 0; c < kMaxClasses; ++c)
-            if (i == 0) {
-                ws.qctl[4 + c] = (c < q.nclass) ? q.init_tail[c] : 0;
-                ws.qctl[4 + kMaxClasses + c] = 0;
-            }
+        if (i < kCtlWords) ws.qctl[i] = i == 0 ? q.init_total : 0;
         if (i < a.B) {
             // the root is never tested: it counts as accepted from the start
             ws.known[i] = 1ull << (a.N - 1);
@@ -421,7 +419,6 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
                 a.dbg_edge[static_cast<size_t>(i) * a.N * 2] = 1.f;
                 a.dbg_edge[static_cast<size_t>(i) * a.N * 2 + 1] = 1.f;
             }
-            if (q.root_is_leaf) ws.queue[q.off[0] + i] = a.B * a.N + i;
         }
     }
     if (i >= a.B) return;
@@ -432,27 +429,24 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
     // a node no task ever reaches is tested with probability 0
     ws.atest[bn] = (n == 0) ? 1.0 : 0.0;
     ws.cfin[bn] = 0.0;
-    // queue: the prequeued node tasks, node-major inside their class (the same node of
-    // consecutive trees next to each other); everything else "not written yet"
-    const int at = n * a.B + b;                               // this thread's share of the queue words
-    if (at < q.off[q.nclass]) {
-        int c = 0;
-        while (c + 1 < q.nclass && at >= q.off[c + 1]) ++c;
-        if (at - q.off[c] >= q.init_tail[c]) ws.queue[at] = -1;
-    }
-    if (q.init_slot[n] >= 0) {
-        const int slot = q.init_slot[n] * a.B + b;
-        ws.queue[q.off[tree.cls[n]] + slot] = b * a.N + n;
-    }
+    const int at = n * a.B + b;                               // this thread's share of the queue words: "not written yet"
+    if (at < q.off[q.nclass]) ws.queue[at] = -1;
 }
 
 // ------------------------------------------------------------------ task queue
 //
 // node_task_kernel is launched with three workgroups per compute unit at most, grouped in teams;
 // each team runs tasks until told to exit.  A team takes part only once every member has
-// started (the last to arrive opens the team's mailbox), so a task is only ever handed to
+// started (the last to arrive counts off its first task), so a task is only ever handed to
 // workgroups that are running, whatever else occupies the device.  A task is appended only when
 // everything it needs has been published, so every queued task can run at once, on any team.
+//   first:    the tasks that can run from the start are counted off by the teams (one atomic add each,
+//             see claim_first), asked for ahead of time like the others.  Only what follows from them is
+//             queued, and only a team for which no first task is left turns to the dispatcher.
+//             (Through the dispatcher, as all tasks were before, a single team had its first task 5.6 us
+//             after the start of the kernel and 768 workgroups theirs after 7 to 20; now 2.0 and 2.8.  The
+//             counts of a team's arrivals and its first announcement are in a line of their own: next to
+//             other teams' they took 9.6 us.)
 //   append:   appended++, then slot = tail++ of the class, then the entry is written.
 //   request:  mailbox[team] = "soon" when a team asks ahead, before the last sweep of its
 //             current task (the answer is then usually there when it is done), "waiting" once
@@ -511,6 +505,21 @@ __device__ __forceinline__ void append_task(const TreeDesc& tree, const Workspac
     if (slot < end - first) st_relaxed(&ws.queue[first + slot], entry);
 }
 
+// First task number h, or kTaskNone when there are not that many.
+__device__ __forceinline__ int first_task(const QueuePlan& q, const Args& a, int h) {
+    if (h >= q.init_total) return kTaskNone;
+    if (q.root_is_leaf) return a.B * a.N + h;
+    return (h % a.B) * a.N + q.init_node[h / a.B];
+}
+// Counts off one first task (one lane).
+__device__ __forceinline__ int claim_first(const Workspace& ws) { return atomicAdd(&ws.qctl[kCtlFirst], 1); }
+
+// A tree's outputs are written (one lane): with the last one the launch is over, whatever is still
+// queued belongs to settled trees.
+__device__ __forceinline__ void tree_done(const Workspace& ws, const Args& a) {
+    if (atomicAdd(&ws.qctl[kCtlTreesDone], 1) + 1 == a.B) st_relaxed(&ws.qctl[2], 1);
+}
+
 // One round of dispatching, by a whole wave that holds the lock.  Lane c keeps the head of
 // class c in `head`; lane l looks after the teams l, l + 64, ...  Returns true when
 // everything is finished (the exit flag has been set).
@@ -530,7 +539,8 @@ __device__ __forceinline__ bool dispatch_round(const QueuePlan& q, const TreeDes
             if (m == kMailboxSoon) soon |= 1u << sl;
         }
     }
-    const int tail = (lane < q.nclass) ? ld_relaxed(&ws.qctl[4 + lane]) : 0;
+    const int tail = (lane <= kMaxClasses) ? ld_relaxed(&ws.qctl[lane < kMaxClasses ? 4 + lane : 2]) : 0;
+    if (__builtin_amdgcn_readlane(tail, kMaxClasses) != 0) return true;               // (the exit flag)
     const int avail = (lane < q.nclass) ? tail - head : 0;
     const int my_waiting = __popc(waiting), my_soon = __popc(soon);
     const int waiting_incl = wave_inclusive_scan_i32(my_waiting);
@@ -562,7 +572,7 @@ __device__ __forceinline__ bool dispatch_round(const QueuePlan& q, const TreeDes
     }
     // how many will still be waiting after this round: tasks look at it to decide whether work
     // that may turn out useless is worth queueing
-    if (lane == 0) st_relaxed(&ws.qctl[4 + 2 * kMaxClasses], max(0, total_idle - total_avail));
+    if (lane == 0) st_relaxed(&ws.qctl[kCtlIdle], max(0, total_idle - total_avail));
     if (total_avail == 0 || total_waiting == 0) {
         __builtin_amdgcn_s_sleep(8);
         return false;
@@ -703,14 +713,18 @@ struct Team {
 // whoever needs it takes a copy into registers.
 struct LoopState {
     Team team;
-    int asked;            // the leader has asked for its next task (mailbox says waiting or soon)
+    int asked;            // the leader has asked for its next task (mailbox says waiting or soon, or it has one: claimed)
     int own_task;         // leader: a task the team produced for itself, already announced (-1: none);
                           // member: the task it has already heard of (kNothingHeard: none)
     int own_flags;
     int previous_task;    // last task taken from the mailbox
+    int claims;           // leader: there may be first tasks left to count off
+    int claimed;          // leader: the first task the team has counted off ahead of time (kTaskNone: none)
+    int want_claim;       // leader: the second wave is to count off a first task while the team samples
 };
 __shared__ LoopState g_loop;
 constexpr int kNothingHeard = -4;
+constexpr int kNotStarted = -5;           // own_task, every member: the team's first announcement is still to come
 
 // First wave only.  Lane w < kExchWords brings `mine`, its 32 bits of payload.  On return
 // g_sh.words[m * kExchWords + w] holds member m's word w (visible to the other waves after the
@@ -812,16 +826,22 @@ __device__ __forceinline__ void team_announce(Team& t, int task, int flags) {
     }
 }
 // The others wait for it (first wave; returns the same in every lane).  kTaskExit on a timeout.
+// first: the team's first task, which its last member to arrive announces to all of them; a team that
+// is still incomplete when the launch ends leaves by the exit flag (it has no task).
+template <bool FIRST = false>
 __device__ __forceinline__ int team_listen(Team& t, int& flags, const Workspace& ws) {
     t.tseq++;
     unsigned long long v = 0ull;
     int ok = 1;
     if (threadIdx.x < 2) {
-        for (;;) {
-            v = ld_relaxed(t.task_word + threadIdx.x);
+        const unsigned long long* const word = (FIRST ? t.area + 1 : t.task_word) + threadIdx.x;
+        for (unsigned spin = 1;; ++spin) {
+            // (the exit flag is looked at rarely: its line is the one that the first tasks are counted on)
+            const int leave = FIRST && (spin & 31u) == 0u ? ld_relaxed(&ws.qctl[2]) : 0;
+            v = ld_relaxed(word);
             if ((v >> 32) == t.tseq) break;
-            if (wall_clock64() - t.t_start > kLaunchTimeoutTicks) { ok = 0; break; }
-            __builtin_amdgcn_s_sleep(2);
+            if (leave != 0 || wall_clock64() - t.t_start > kLaunchTimeoutTicks) { ok = 0; break; }
+            __builtin_amdgcn_s_sleep(FIRST ? 1 : 2);
         }
     }
     const int all_ok = __ballot(!ok) == 0ull;
@@ -1138,10 +1158,47 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
 
     // ================================================================ the first wave
     Team team = uniform_struct(g_loop.team);           // in registers while the tasks run
-    bool asked = uniform_i32(g_loop.asked) != 0;
+    bool asked = uniform_i32(g_loop.asked) != 0, claims = uniform_i32(g_loop.claims) != 0, claim_pending = false;
+    int claimed = uniform_i32(g_loop.claimed), claim_number = 0;
     int own_task = -1, own_flags = 0;
     const bool leader = team.member == 0;
     const bool lead = leader && lane == 0;            // the one lane that talks to the rest of the launch
+    // The leader asks for the team's next task ahead of time: a first task, while there are any, else
+    // the dispatcher.
+    auto ask_ahead = [&]() __attribute__((always_inline)) {
+        if (claims) {
+            if (lane == 0) claim_number = claim_first(ws);       // (looked at in answer())
+            claim_pending = true;
+        } else if (lane == 0) {
+            st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+        }
+        asked = true;
+    };
+    auto settle_claim = [&]() __attribute__((always_inline)) {
+        if (!claim_pending) return;
+        claim_pending = false;
+        claimed = first_task(q, a, uniform_i32(claim_number));
+        if (claimed == kTaskNone) {
+            claims = false;
+            if (lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+        }
+    };
+    // the task that was asked for, if it is there (-1); it is the team's then
+    auto answer = [&]() __attribute__((always_inline)) -> int {
+        settle_claim();
+        int t = claimed;
+        if (t == kTaskNone) {
+            if (claims) return -1;
+            const int previous = uniform_i32(g_loop.previous_task);
+            if (lane == 0) t = ld_relaxed(&ws.mailbox[team.id]);
+            t = uniform_i32(t);
+            if (t < 0 || t == previous) return -1;
+            if (lane == 0) g_loop.previous_task = t;
+        }
+        claimed = kTaskNone;
+        asked = false;
+        return t;
+    };
     // Takes a task up: the other waves are told, this wave's share of the pair is asked for.
     auto start_task = [&](const NodeView& v, int t) __attribute__((always_inline)) {
         if (lane == 0) { g_cmd.kind = kCmdTask; g_cmd.m = t; }
@@ -1203,7 +1260,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     if (lead) atomicAdd(&a.counters[resumed ? MPV_COUNTER_NODE_TASKS_RESUMED : MPV_COUNTER_NODE_TASKS_RUN], 1u);
     // are teams idle?  Asked now, needed when this task hands on to the next (the leader's business)
     int idle_now = 0;
-    if (lead) idle_now = ld_relaxed(&ws.qctl[4 + 2 * kMaxClasses]);
+    if (lead) idle_now = ld_relaxed(&ws.qctl[kCtlIdle]);
     const bool split_here = METHOD == MPV_METHOD_TRAVERSAL && a.lazy && !resumed && n == tree.split_node;
     const bool idle_seen = (flags & kFlagIdle) != 0;
 
@@ -1406,10 +1463,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         //   NSS        sum_t p (1 - (1-q)^k)                                    (one sweep)
         //   Naive      sum_t min(p,q) + sum_t (p-q)_+ (1 - (1-q)^(k-1))         (one sweep)
         // (nothing follows from such a task: the team asks for its next one right away)
-        if (leader && !asked) {
-            if (lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
-            asked = true;
-        }
+        if (leader && !asked) ask_ahead();
         double alpha;
         if (a.walk == 3) {
             const double D = fmin(fmax((sp_W + sp_rho - 1.0) / sp_rho, 0.0), 1.0);
@@ -1432,13 +1486,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         }
         // the answer may be there already: then the team goes straight on (see the end of the other tasks)
         if (leader && asked && !team.dead) {
-            const int previous = uniform_i32(g_loop.previous_task);
-            int t = -1;
-            if (lane == 0) t = ld_relaxed(&ws.mailbox[team.id]);
-            t = uniform_i32(t);
-            if (t >= 0 && t != previous) {
-                asked = false;
-                if (lane == 0) g_loop.previous_task = t;
+            const int t = answer();
+            if (t >= 0) {
                 team_announce(team, t, 0);
                 if (!(t >= B * N && t < B * N + B)) {
                     start_task(view_of(t), t);
@@ -1449,7 +1498,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         }
         if (lead) {
             as_global(a.alpha)[bn] = static_cast<float>(fmin(fmax(alpha, 0.0), 1.0));
-            atomicAdd(&ws.qctl[1], 1);
+            // (the team that finishes the last task has found no further first task)
+            if (claims) (void)atomicAdd(&ws.qctl[1], 1);
+            else if (atomicAdd(&ws.qctl[1], 1) + 1 == q.init_total) st_relaxed(&ws.qctl[2], 1);
         }
         goto task_end;
     }
@@ -1516,10 +1567,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // One more sweep to go at most: time to ask for the next task, unless this team
         // already knows what it will run next (a child's task).
         if (leader && j == k - 1 && !asked && (own_child < 0 || own_given) &&
-            !(METHOD == MPV_METHOD_SPECINFER && a.lazy && child_accepted && tree.nchild[cn] > 0)) {
-            if (lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
-            asked = true;
-        }
+            !(METHOD == MPV_METHOD_SPECINFER && a.lazy && child_accepted && tree.nchild[cn] > 0))
+            ask_ahead();
         if (lead && !redone) {
             if (METHOD == MPV_METHOD_TRAVERSAL) {
                 if (tree.nchild[cn] == 0) {
@@ -1643,16 +1692,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // tree can need several draws, the queue has room for one.)
     int taken = -1;
     if (leader && likely < 0 && !paused && asked && !team.dead && a.walk == 0) {
-        const int previous = uniform_i32(g_loop.previous_task);
-        int t = -1;
-        if (lane == 0) t = ld_relaxed(&ws.mailbox[team.id]);
-        t = uniform_i32(t);
-        if (t >= 0 && t != previous) {
-            taken = t;
-            asked = false;
-            if (lane == 0) g_loop.previous_task = t;
-            team_announce(team, t, uniform_i32(idle_now) != 0 ? kFlagIdle : 0);
-        }
+        taken = answer();
+        if (taken >= 0) team_announce(team, taken, uniform_i32(idle_now) != 0 ? kFlagIdle : 0);
     }
     {
         // (trees of different shapes: the tables in LDS are still this tree's)
@@ -1780,6 +1821,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             // the expected block efficiency instead of a walk: scalar work over the tree's
             // per-node results, done here and now by this wave (there are no uniforms to walk with)
             estimate_wave<METHOD>(tree, ws, a, b);
+            if (lane == 0) tree_done(ws, a);
         } else if (taken >= 0) {
             if (lane == 0) append_task(tree, ws, 0, B * N + b);      // (the results were waited for above)
         } else {
@@ -1833,11 +1875,14 @@ task_end:
         started = -1;
     }
     if (!node_next) {
+        settle_claim();
         if (lane == 0) g_cmd.kind = kCmdDone;
         task_barrier();                                    // B: the other waves leave
         if (lane == 0) {
             g_loop.team = team;
             g_loop.asked = asked ? 1 : 0;
+            g_loop.claims = claims ? 1 : 0;
+            g_loop.claimed = claimed;
             g_loop.own_task = next;                       // (already announced to, or heard by, the team)
             g_loop.own_flags = next_flags;
         }
@@ -1896,16 +1941,34 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         team.task_word = ws.team_task + static_cast<size_t>(team.id) * 2;
         team.t_start = wall_clock64();
         leader = team.member == 0;
-        if (threadIdx.x == 0) {
-            g_loop.team = team;
-            g_loop.asked = 1;                     // the team starts out waiting
-            g_loop.own_task = leader ? -1 : kNothingHeard;
-            g_loop.own_flags = 0;
-            g_loop.previous_task = -4;            // none yet
-            g_tree_of = -1;
-            // the last member to arrive opens the team's mailbox: from then on the dispatcher may hand it tasks
-            const int n_arrived = atomicAdd(&ws.arrived[team.id], 1) + 1;
-            if (n_arrived == team.size) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
+        if (wave == 0) {
+            const int lane = threadIdx.x;
+            // The last member to arrive counts off the team's first task and tells the others; if there is
+            // none left it opens the team's mailbox: from then on the dispatcher may hand it tasks.
+            const int flags = q.teams > q.init_total ? kFlagIdle : 0;
+            int task = kNotStarted, n_arrived = 1;
+            if (team.size > 1) {
+                if (lane == 0) n_arrived = atomicAdd(reinterpret_cast<int*>(team.area), 1) + 1;
+                n_arrived = uniform_i32(n_arrived);
+            }
+            if (n_arrived == team.size) {
+                int number = 0;
+                if (lane == 0) number = claim_first(ws);
+                const int t = first_task(q, a, uniform_i32(number));
+                if (t == kTaskNone && lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
+                if (team.size == 1) task = t == kTaskNone ? -1 : t;
+                else if (lane < 2) st_relaxed(team.area + 1 + lane, (1ull << 32) | static_cast<unsigned>(lane == 0 ? t : flags));
+            }
+            if (lane == 0) {
+                g_loop.team = team;
+                g_loop.own_task = task;
+                g_loop.own_flags = flags;
+                g_loop.asked = task == -1;
+                g_loop.claims = task != -1;
+                g_loop.claimed = kTaskNone;
+                g_loop.previous_task = -4;            // none yet
+                g_tree_of = -1;
+            }
         }
     }
     // The first wave's scalar steps are the critical path of every task and few in number: they
@@ -1919,25 +1982,46 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         bool asked = uniform_i32(g_loop.asked) != 0;
         int own_task = uniform_i32(g_loop.own_task), own_flags = uniform_i32(g_loop.own_flags);
         int previous_task = uniform_i32(g_loop.previous_task);
+        bool claims = uniform_i32(g_loop.claims) != 0;
+        int claimed = uniform_i32(g_loop.claimed);
         int task = kTaskExit, flags = 0;
         if (team.dead) {
             task = kTaskExit;
         } else if (leader) {
             for (;;) {
+                if (own_task == kNotStarted) {
+                    own_task = -1;
+                    task = team_listen<true>(team, flags, ws);
+                    if (task == kTaskExit) team_announce(team, task, 0);      // (for one that heard "none" just before)
+                    if (task != kTaskNone) break;
+                    claims = false;
+                    asked = true;
+                }
                 if (own_task >= 0) {
                     task = own_task;
                     flags = own_flags;
                     own_task = -1;
                     break;
                 }
-                if (!asked) {
-                    if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
-                    wait_memory();
+                if (claims && claimed == kTaskNone) {
+                    int number = 0;
+                    if (threadIdx.x == 0) number = claim_first(ws);
+                    claimed = first_task(q, a, uniform_i32(number));
+                    if (claimed == kTaskNone) claims = false;
                 }
-                task = acquire_task(team.id, previous_task, drop_settled, team.t_start);
+                if (claimed != kTaskNone) {
+                    task = claimed;
+                    claimed = kTaskNone;
+                } else {
+                    if (!asked) {
+                        if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
+                        wait_memory();
+                    }
+                    task = acquire_task(team.id, previous_task, drop_settled, team.t_start);
+                    previous_task = task;
+                }
                 // are teams idle (as of the last round of dispatching)?
-                flags = uniform_i32(ld_relaxed(&ws.qctl[4 + 2 * kMaxClasses])) != 0 ? kFlagIdle : 0;
-                previous_task = task;
+                flags = uniform_i32(ld_relaxed(&ws.qctl[kCtlIdle])) != 0 ? kFlagIdle : 0;
                 asked = false;
                 // tasks without any V-wide work are the leader's alone; everything else is announced
                 const bool solo = task != kTaskExit && task >= a.B * a.N && task < a.B * a.N + a.B && (ACCEPT || a.estimate);
@@ -1945,6 +2029,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                     if (!ACCEPT) estimate_wave<METHOD>(tree, ws, a, task - a.B * a.N);
                     if (threadIdx.x == 0) {
                         wait_memory();
+                        tree_done(ws, a);
                         atomicAdd(&ws.qctl[1], 1);
                     }
                     continue;
@@ -1952,22 +2037,30 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 team_announce(team, task, flags);
                 break;
             }
-        } else if (own_task != kNothingHeard) {
+        } else if (own_task >= 0 || own_task == kTaskExit) {
             task = own_task;
             flags = own_flags;
             own_task = kNothingHeard;
         } else {
-            task = team_listen(team, flags, ws);
+            task = kTaskNone;
+            if (own_task == kNotStarted) task = team_listen<true>(team, flags, ws);
+            if (task == kTaskNone) task = team_listen(team, flags, ws);
+            own_task = kNothingHeard;
         }
         const bool sampling = task != kTaskExit && task >= a.B * a.N && task < a.B * a.N + a.B && !(ACCEPT || a.estimate);
         if (!ACCEPT && a.per_tree && task != kTaskExit) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), a.N, tree_of_task(task, a.B, a.N));
+        bool want_claim = false;
         if (sampling && leader && !asked) {
             // the walk and the bonus token come next: one sweep or two, then the team is free
-            if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+            want_claim = claims;
+            if (!claims && threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
             asked = true;
         }
         if (threadIdx.x == 0) {
             g_loop.team = team;
+            g_loop.claims = claims ? 1 : 0;
+            g_loop.claimed = claimed;
+            g_loop.want_claim = want_claim ? 1 : 0;
             g_loop.asked = asked ? 1 : 0;
             g_loop.own_task = own_task;
             g_loop.own_flags = own_flags;
@@ -1986,10 +2079,18 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 if (!ACCEPT) estimate_wave<METHOD>(tree, ws, a, task - a.B * a.N);
                 if (threadIdx.x == 0) {
                     wait_memory();
+                    tree_done(ws, a);
                     atomicAdd(&ws.qctl[1], 1);
                 }
             }
             continue;
+        }
+        if (leader && threadIdx.x == kWave && g_loop.want_claim) {          // (the first wave is busy with the walk)
+            g_loop.claimed = first_task(q, a, claim_first(ws));
+            if (g_loop.claimed == kTaskNone) {
+                g_loop.claims = 0;
+                st_relaxed(&ws.mailbox[g_loop.team.id], kMailboxSoon);
+            }
         }
         // the tree's outcome is settled: walk and bonus token
         const int next = sample_task<E, METHOD>(task - a.B * a.N);
@@ -2007,6 +2108,8 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 if (next >= 0) {
                     (void)atomicAdd(&ws.qctl[0], 1);
                     wait_memory();                    // counted (and the walk's position written) first
+                } else {
+                    tree_done(ws, a);
                 }
                 atomicAdd(&ws.qctl[1], 1);
             }
@@ -2718,7 +2821,7 @@ static size_t carve(const mpv_problem* p, void* base, Workspace* ws) {
     double* a0 = static_cast<double*>(take(bn * 8));
     double* at = static_cast<double*>(take(bn * 8));
     int32_t* qu = static_cast<int32_t*>(take(bn * 4));
-    int32_t* qc = static_cast<int32_t*>(take((5 + 2 * kMaxClasses) * 4));
+    int32_t* qc = static_cast<int32_t*>(take(kCtlWords * 4));
     int32_t* mb = static_cast<int32_t*>(take(kMaxTeams * 4));
     unsigned long long* kn = static_cast<unsigned long long*>(take(static_cast<size_t>(p->B) * 8));
     unsigned long long* ac = static_cast<unsigned long long*>(take(static_cast<size_t>(p->B) * 8));
@@ -2726,9 +2829,9 @@ static size_t carve(const mpv_problem* p, void* base, Workspace* ws) {
     int32_t* cu = static_cast<int32_t*>(take(static_cast<size_t>(p->B) * 4));
     unsigned long long* ex = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxGrid) * 2 * kExchWords * 8));
     unsigned long long* tt = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxTeams) * 2 * 8));
-    int32_t* ar = static_cast<int32_t*>(take(kMaxTeams * 4));
+    (void)take(kMaxTeams * 4);                        // (unused: the workspace keeps its size)
     LaunchBlock* la = static_cast<LaunchBlock*>(take(sizeof(LaunchBlock)));
-    if (ws) { ws->exch = ex; ws->team_task = tt; ws->arrived = ar; ws->launch = la; }
+    if (ws) { ws->exch = ex; ws->team_task = tt; ws->launch = la; }
     if (ws) { ws->At = At; ws->Ad = Ad; ws->cfin = cf; ws->aux = ax; ws->a0 = a0; ws->atest = at; ws->queue = qu; ws->qctl = qc; ws->mailbox = mb; ws->known = kn; ws->acc = ac; ws->decided = de; ws->cur = cu; }
     return off < 256 ? 256 : off;
 }
@@ -2829,25 +2932,21 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     // Queue layout and initial tasks.  Computing only what is needed, both rules start from the
     // root: SpecInfer queues the accepted child, Traversal the children of positive weight.
     // Computing everything (debug outputs), SpecInfer's node tasks are independent and all
-    // queued up front, nodes with many children (the long tasks) first.
+    // there from the start, nodes with many children (the long tasks) first.
     QueuePlan q;
     memset(&q, 0, sizeof(q));
     q.nclass = plan.nclass;
     for (int c = 0; c < q.nclass; ++c) q.off[c + 1] = q.off[c] + static_cast<int>(plan.class_tasks[c]);
-    int prequeued[kMaxClasses] = {0};
-    for (int n = 0; n < p->N; ++n) q.init_slot[n] = -1;
     const bool all_up_front = (p->method != MPV_METHOD_TRAVERSAL && !a.lazy);
-    for (int kk = MPV_MAX_CHILDREN; kk >= 1; --kk)
-        for (int n = 0; n < p->N; ++n)
-            if (tree.nchild[n] == kk && (all_up_front || n == 0) && (a.walk != 1 || !a.lazy))      // NSS verification has no node tasks
-                q.init_slot[n] = prequeued[tree.cls[n]]++;
-    for (int c = 0; c < q.nclass; ++c) {
-        q.init_tail[c] = prequeued[c] * p->B;
-        q.init_total += q.init_tail[c];
-    }
+    int first_nodes = 0;
+    for (int c = 0; c < q.nclass; ++c)
+        for (int kk = MPV_MAX_CHILDREN; kk >= 1; --kk)
+            for (int n = 0; n < p->N; ++n)
+                if (tree.cls[n] == c && tree.nchild[n] == kk && (all_up_front || n == 0) && (a.walk != 1 || !a.lazy))      // NSS verification has no node tasks
+                    q.init_node[first_nodes++] = static_cast<int8_t>(n);
+    q.init_total = first_nodes * p->B;
     if (tree.nchild[0] == 0 || (a.walk == 1 && a.lazy)) {
         q.root_is_leaf = 1;
-        q.init_tail[0] = p->B;
         q.init_total = p->B;
     }
     for (int c = 0; c <= q.nclass; ++c) tree.class_off[c] = q.off[c];
