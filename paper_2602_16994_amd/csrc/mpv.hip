@@ -511,8 +511,13 @@ __device__ __forceinline__ int first_task(const QueuePlan& q, const Args& a, int
     if (q.root_is_leaf) return a.B * a.N + h;
     return (h % a.B) * a.N + q.init_node[h / a.B];
 }
-// Counts off one first task (one lane).
-__device__ __forceinline__ int claim_first(const Workspace& ws) { return atomicAdd(&ws.qctl[kCtlFirst], 1); }
+// Counts off one first task (one lane).  The address is made a lane's own: for one that is the same in every lane the
+// compiler adds the lanes up first and waits for the result at once; here it is waited for where it is used.
+__device__ __forceinline__ int claim_first(const Workspace& ws) {
+    unsigned long long at = reinterpret_cast<unsigned long long>(&ws.qctl[kCtlFirst]);
+    asm volatile("" : "+v"(at));
+    return atomicAdd(reinterpret_cast<int32_t*>(at), 1);
+}
 
 // A tree's outputs are written (one lane): with the last one the launch is over, whatever is still
 // queued belongs to settled trees.
@@ -762,6 +767,71 @@ __device__ __forceinline__ void exchange_words(const Team& t, unsigned mine) {
     }
 }
 
+// The lane number, for numbers derived from it that are not worth keeping: computed where they are used
+// instead of ahead of the task loop (there they took so many registers that others went to memory).
+__device__ __forceinline__ int lane_here() {
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// The node task's exchanges (first wave only) stay in registers: lane 16 r + m looks after member m, so that
+// the members' numbers meet in reductions along a row of 16 lanes, and a member's own numbers do not travel.
+// (Through LDS, one member after the other, as the other tasks' still do, the statistics of a team of 8 took
+// 1.15 us from the last word's arrival to the logarithms, now 0.3.)
+static_assert(kMaxTeam <= 16, "a row of lanes holds a team");
+
+// Lane l < count sends word l; every lane with `wants` set receives the words at[] of member lane & 15 into
+// got[] (its own are there already).  Returns whether a partner failed to answer.
+template <int COUNT>
+__device__ __forceinline__ int swap_words(const Team& t, unsigned mine, int count, bool wants, const int (&at)[COUNT], unsigned (&got)[COUNT]) {
+    const int lane = lane_here();
+    unsigned long long* const base = t.area + static_cast<size_t>(t.seq & 1u) * t.size * kExchWords;
+    if (lane < count) st_relaxed(base + t.member * kExchWords + lane, (static_cast<unsigned long long>(t.seq) << 32) | mine);
+    int dead = t.dead;
+    if (wants && (lane & 15) != t.member) {
+        const unsigned long long* const line = base + (lane & 15) * kExchWords;
+        for (unsigned spin = 1; !dead; ++spin) {
+            unsigned long long v[COUNT];
+            bool there = true;
+#pragma unroll
+            for (int i = 0; i < COUNT; ++i) v[i] = ld_relaxed(line + at[i]);
+#pragma unroll
+            for (int i = 0; i < COUNT; ++i) {
+                there = there && static_cast<unsigned>(v[i] >> 32) == t.seq;
+                got[i] = static_cast<unsigned>(v[i]);
+            }
+            if (there) break;
+            if ((spin & 31u) == 0u && wall_clock64() - t.t_start > kLaunchTimeoutTicks) dead = 1;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    return __ballot(dead != 0) != 0ull;
+}
+
+// a partner has not answered: counted once, and everybody leaves at the next occasion
+__device__ __forceinline__ void note_dead(Team& t, int dead) {
+    if (dead && !t.dead && threadIdx.x == 0) {
+        atomicAdd(&lds_launch().a.counters[MPV_COUNTER_DEPENDENCY_TIMEOUT], 1u);
+        st_relaxed(&lds_launch().ws.qctl[2], 1);
+    }
+    t.dead = dead;
+}
+
+// reductions along the rows of 16 lanes (every lane gets its row's result, in a fixed order)
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, dpp_f32<0xB1>(v));
+    v = fmaxf(v, dpp_f32<0x4E>(v));
+    v = fmaxf(v, dpp_f32<0x124>(v));
+    return fmaxf(v, dpp_f32<0x128>(v));
+}
+__device__ __forceinline__ double row_sum(double v) {
+    v += dpp_f64<0xB1>(v);
+    v += dpp_f64<0x4E>(v);
+    v += dpp_f64<0x124>(v);
+    return v + dpp_f64<0x128>(v);
+}
+
 // All lanes of the workgroup: one exchange of raw words (lane w < kExchWords of the first wave
 // brings `mine`); afterwards every lane may read g_sh.words.
 __device__ __forceinline__ void team_exchange(Team& t, unsigned mine) {
@@ -866,6 +936,8 @@ __device__ __forceinline__ double probability_exp2(double x) {
 }
 __device__ __forceinline__ double cold_log2(double x) { return log2(x); }
 __device__ __forceinline__ ResidualConsts cold_residual_consts(double At, double Ad, double c) { return residual_consts(At, Ad, c); }
+// a comparison of numbers that are the same in every lane: a scalar branch, not a masked one
+__device__ __forceinline__ bool all_alike(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
 // x^k for a small whole k
 __device__ __forceinline__ double int_power(double x, int k) {
     double r = 1.0;
@@ -980,11 +1052,14 @@ struct SweepCmd {
     float nAt, nAd, rho;             // constants of the residual sweeps
     float sp, sq;                    // acceptance sweep: scale factors of p and q
     int m, naive;                    // acceptance sweep: exponent, which formula (kCmdTask: m = the task)
+    int claim;                       // a sweep: the second wave counts off a first task meanwhile (g_claim_number)
+    int b, n;                        // kCmdTask: its tree and node;  a sweep: n = the node of `next`, in the same tree
     int next;                        // a sweep: the task this team goes on with when the sweep was the
                                      // current task's last (-1: not known); each wave asks for its share
                                      // of that task's rows as soon as it is done with its share of the sweep
 };
 __shared__ SweepCmd g_cmd;
+__shared__ int g_claim_number;
 
 // One sweep over the part on chip as the command says; the wave's partial sums go to g_sh.part.
 template <class E, int KIND, class PAIR>
@@ -1015,27 +1090,63 @@ __device__ __forceinline__ void run_sweep(PAIR& pair, const SweepCmd& cmd, float
     if (lane == 0) { g_sh.part[wave][0] = s0; g_sh.part[wave][1] = s1; }
 }
 
-// First wave, after barrier A: the workgroup's sums of the last sweep, exchanged and added over the
-// team in member order.  Every lane of the first wave of every member gets the same bits.
+// First wave, after barrier A: the workgroup's sums of the last sweep (one or two), exchanged and added
+// over the team.  Every lane of the first wave of every member gets the same bits.
+template <bool TWO>
 __device__ __forceinline__ void collect_sums(Team& t, double& s0, double& s1) {
-    const int lane = threadIdx.x;
+    const int lane = lane_here(), row = lane >> 4, m = lane & 15;
     t.seq++;
-    unsigned mine = 0u;
-    if (lane < 4) {
-        const int i = lane >> 1;
-        double b = g_sh.part[0][i];
-#pragma unroll
-        for (int w = 1; w < kTaskWaves; ++w) b += g_sh.part[w][i];
-        mine = half_of(b, lane & 1);
+    // row 0 of the lanes looks after the first sum, row 1 after the second; each quad adds up the four waves
+    double v = g_sh.part[lane & 3][TWO ? row & 1 : 0];
+    v += dpp_f64<0xB1>(v);
+    v += dpp_f64<0x4E>(v);
+    if (t.size > 1) {
+        const double other = TWO ? lane_f64(v, 16) : 0.0, one = TWO ? lane_f64(v, 0) : v;
+        const unsigned mine = half_of(TWO && (lane & 2) ? other : one, lane & 1);
+        unsigned got[2] = {half_of(v, 0), half_of(v, 1)};
+        const int at[2] = {2 * row, 2 * row + 1};
+        note_dead(t, swap_words(t, mine, TWO ? 4 : 2, row < (TWO ? 2 : 1) && m < t.size, at, got));
+        v = row_sum(m < t.size && !t.dead ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) : 0.0);
     }
-    exchange_words(t, mine);
-    __builtin_amdgcn_wave_barrier();
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the wave's own LDS writes, before its reads
-    t.dead = g_sh.dead;
-    double a = 0.0, b = 0.0;
-    for (int m = 0; m < t.size; ++m) { a += double_at(g_sh.words, m, 0); b += double_at(g_sh.words, m, 1); }
-    s0 = uniform_f64(a);
-    s1 = uniform_f64(b);
+    s0 = lane_f64(v, 0);
+    s1 = TWO ? lane_f64(v, 16) : 0.0;
+}
+
+// First wave, after barrier A of the statistics sweep: the waves' partials (g_sh.part, partf) become the log2-partitions of the
+// two rows; a0 is the leader's starting weight (WEIGHT; what the other members bring is ignored).
+template <bool WEIGHT>
+__device__ __forceinline__ void collect_stats(Team& t, double& a0, double& At, double& Ad) {
+    const int lane = lane_here(), row = lane >> 4, m = lane & 15;
+    t.seq++;
+    // row 0: target, row 1: draft; each quad brings the four waves to the largest reference
+    const float Mw = g_sh.partf[lane & 3][row & 1];
+    double s = g_sh.part[lane & 3][row & 1];
+    float M = fmaxf(Mw, dpp_f32<0xB1>(Mw));
+    M = fmaxf(M, dpp_f32<0x4E>(M));
+    s *= static_cast<double>(fast_exp2(Mw - M));
+    s += dpp_f64<0xB1>(s);
+    s += dpp_f64<0x4E>(s);
+    if (t.size > 1) {
+        // words: the two references, the two sums, the weight
+        const float Mt = lane_f32(M, 0), Md = lane_f32(M, 16);
+        const double st = lane_f64(s, 0), sd = lane_f64(s, 16);
+        const double of_pair = lane < 4 ? st : lane < 6 ? sd : a0;
+        unsigned mine = half_of(of_pair, lane & 1);
+        if (lane < 2) mine = __float_as_uint(lane ? Md : Mt);
+        unsigned got[3] = {half_of(s, 0), __float_as_uint(M), half_of(s, 1)};
+        if (WEIGHT && row == 2) { got[0] = half_of(a0, 0); got[2] = half_of(a0, 1); }
+        const bool wants = (row < 2 && m < t.size) || (WEIGHT && lane == 32);
+        const int at[3] = {2 * row + 2, row < 2 ? row : 6, 2 * row + 3};
+        note_dead(t, swap_words(t, mine, WEIGHT ? 8 : 6, wants, at, got));
+        const bool live = m < t.size && !t.dead;
+        const float Mm = live ? __uint_as_float(got[1]) : OnlineLse::kFloor;
+        M = row_max(Mm);
+        s = row_sum(live ? __hiloint2double(static_cast<int>(got[2]), static_cast<int>(got[0])) * static_cast<double>(fast_exp2(Mm - M)) : 0.0);
+        if (WEIGHT) a0 = __hiloint2double(__builtin_amdgcn_readlane(static_cast<int>(got[2]), 32), __builtin_amdgcn_readlane(static_cast<int>(got[0]), 32));
+    }
+    const double A = static_cast<double>(M) + cold_log2(s);          // both logarithms in one go, a row of lanes each
+    At = lane_f64(A, 0);
+    Ad = lane_f64(A, 16);
 }
 
 template <class E, int KIND>
@@ -1063,59 +1174,44 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
 
     // what a task number stands for (tree, node: made scalar explicitly, so that the table lookups
     // that follow have uniform addresses)
-    struct NodeView { int b, n, k; bool resumed; size_t bn; const T* zt; const T* zd; };
-    auto view_of = [&](int t) __attribute__((always_inline)) -> NodeView {
+    const T* const zt0 = uniform_ptr(static_cast<const T*>(a.zt));
+    const T* const zd0 = uniform_ptr(static_cast<const T*>(a.zd));
+    const int part_vecs = uniform_i32(q.part_vecs);
+    struct NodeView { int b, n; bool resumed; size_t bn; const T* zt; const T* zd; };
+    auto view_at = [&](int b, int n, bool resumed) __attribute__((always_inline)) -> NodeView {
         NodeView v;
-        v.resumed = t >= B * N + B;
-        v.b = uniform_i32(v.resumed ? t - (B * N + B) : t / N);
-        v.n = uniform_i32(v.resumed ? tree.split_node : t % N);
+        v.resumed = resumed;
+        v.b = uniform_i32(b);
+        v.n = uniform_i32(n);
         v.bn = static_cast<size_t>(v.b) * N + v.n;
-        v.zt = uniform_ptr(static_cast<const T*>(a.zt)) + v.bn * V;
-        v.zd = uniform_ptr(static_cast<const T*>(a.zd)) + v.bn * V;
-        v.k = uniform_i32(tree.nchild[v.n]);
+        v.zt = zt0 + v.bn * V;
+        v.zd = zd0 + v.bn * V;
         return v;
     };
+    auto view_of = [&](int t) __attribute__((always_inline)) -> NodeView {
+        if (t >= B * N + B) return view_at(t - (B * N + B), tree.split_node, true);
+        int nodes_per_tree = N;                           // (its reciprocal is not kept across tasks)
+        asm volatile("" : "+s"(nodes_per_tree));
+        return view_at(t / nodes_per_tree, t % nodes_per_tree, false);
+    };
 
-    auto tree_of = [&](int t) __attribute__((always_inline)) -> int { return tree_of_task(t, B, N); };
+    auto tree_of = [&](int t) __attribute__((always_inline)) -> int {
+        int nodes_per_tree = N;
+        asm volatile("" : "+s"(nodes_per_tree));
+        return tree_of_task(t, B, nodes_per_tree);
+    };
 
     // ---- the part of the pair this member keeps on chip while a task runs
     RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs> pair;
-    // the children's tokens, their two logits and the uniforms, for the first wave's scalar steps
-    __shared__ int ch_tok[MPV_MAX_CHILDREN];
-    __shared__ float ch_zt[MPV_MAX_CHILDREN], ch_zd[MPV_MAX_CHILDREN];
-    __shared__ float ch_u[MPV_MAX_CHILDREN + 1];      // last: the node's own uniform
 
     if (wave != 0) {
         // ---- a sweeping wave does what the first wave commands: it takes up a task (loads its
         //      share of the pair and runs the statistics sweep) or sweeps once more
-        // what the second wave fetches of the children (kept as stored until the sweep is over)
-        int pf_x = -1;
-        float pf_u = 2.f;
-        T pf_t = 0, pf_d = 0;
         int asked_for = -1;                               // the task whose rows this wave has asked for already
-        // Asks for this wave's share of task t.  The second wave also fetches what the scalar steps
-        // need of the children (lane j looks after child j): the tokens, then the two logits at each
-        // token, and only then its row loads.  (Loads that depend on loads: issued after the row
-        // loads they would wait for every one of them, the compiler cannot count past the
-        // conditional ones; before them they wait for the tokens alone.)
-        auto take_up = [&](int t) __attribute__((always_inline)) {
-            const NodeView nv = view_of(t);
-            pf_x = -1; pf_u = 2.f; pf_t = 0; pf_d = 0;
-            if (wave == 1) {
-                if (lane < nv.k && a.tokens) {
-                    const size_t bc = static_cast<size_t>(nv.b) * N + tree.child_list[tree.child_off[nv.n] + lane];
-                    pf_x = as_global(a.tokens)[bc];
-                    if (!a.estimate) pf_u = as_global(a.uniforms)[bc];
-                }
-                if (lane == MPV_MAX_CHILDREN && !a.estimate) pf_u = as_global(a.uniforms)[nv.bn];
-                if (pf_x >= 0 && pf_x < V) {
-                    pf_t = as_global(nv.zt)[pf_x];
-                    pf_d = as_global(nv.zd)[pf_x];
-                }
-            }
+        auto take_up = [&](int t, const NodeView& nv) __attribute__((always_inline)) {
             int tid_l = threadIdx.x;
             asm volatile("" : "+v"(tid_l));     // per-task copy: nothing derived from it is kept across tasks
-            pair.setup(nv.zt, nv.zd, V, lds_t, lds_d, tid_l, member, team_size, uniform_i32(q.part_vecs));
+            pair.setup(nv.zt, nv.zd, V, lds_t, lds_d, tid_l, member, team_size, part_vecs);
             pair.issue_loads();
             asked_for = t;
         };
@@ -1129,17 +1225,12 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             }
             if (kind == kCmdTask) {
                 const int t = uniform_i32(cmd.m);
-                if (asked_for != t) take_up(t);
+                if (asked_for != t) take_up(t, view_at(cmd.b, cmd.n, false));
                 asked_for = -1;
-                const int kk = uniform_i32(tree.nchild[view_of(t).n]);
                 PairStatsRawF<E, ACCEPT> f;
                 f.t.init(); f.d.init(); f.k32 = k32;
                 pair.first_pass(f);
                 f.t.finish(); f.d.finish();
-                if (wave == 1) {
-                    if (lane < kk) { ch_tok[lane] = pf_x; ch_u[lane] = pf_u; ch_zt[lane] = E::load_one(&pf_t); ch_zd[lane] = E::load_one(&pf_d); }
-                    if (lane == MPV_MAX_CHILDREN) ch_u[MPV_MAX_CHILDREN] = pf_u;
-                }
                 const float Mt_w = wave_max(f.t.mk), Md_w = wave_max(f.d.mk);
                 const double st_w = wave_sum((f.t.s > 0.f) ? static_cast<double>(f.t.s * fast_exp2(f.t.mk - Mt_w)) : 0.0);
                 const double sd_w = wave_sum((f.d.s > 0.f) ? static_cast<double>(f.d.s * fast_exp2(f.d.mk - Md_w)) : 0.0);
@@ -1148,9 +1239,13 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     g_sh.part[wave][0] = st_w; g_sh.part[wave][1] = sd_w;
                 }
             } else {
+                const bool claims_now = wave == 1 && uniform_i32(cmd.claim) != 0;
+                int claim_number = 0;
+                if (claims_now && lane == 0) claim_number = claim_first(ws);
                 run_sweep<E, KIND>(pair, cmd, k32, wave, lane);
+                if (claims_now && lane == 0) g_claim_number = claim_number;
                 const int nx = uniform_i32(cmd.next);
-                if (nx >= 0) take_up(nx);                 // this wave's slots are free again: the next task's rows
+                if (nx >= 0) take_up(nx, view_at(cmd.b, cmd.n, false));     // this wave's slots are free again: the next task's rows
             }
             task_barrier();                                // A: this wave's partial sums are there
         }
@@ -1158,8 +1253,10 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
 
     // ================================================================ the first wave
     Team team = uniform_struct(g_loop.team);           // in registers while the tasks run
-    bool asked = uniform_i32(g_loop.asked) != 0, claims = uniform_i32(g_loop.claims) != 0, claim_pending = false;
-    int claimed = uniform_i32(g_loop.claimed), claim_number = 0;
+    bool asked = uniform_i32(g_loop.asked) != 0, claims = uniform_i32(g_loop.claims) != 0;
+    int claimed = uniform_i32(g_loop.claimed);
+    // a first task to be counted off, or being counted off by the second wave while it sweeps
+    bool claim_wanted = false, claim_pending = false;
     int own_task = -1, own_flags = 0;
     const bool leader = team.member == 0;
     const bool lead = leader && lane == 0;            // the one lane that talks to the rest of the launch
@@ -1167,17 +1264,19 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // the dispatcher.
     auto ask_ahead = [&]() __attribute__((always_inline)) {
         if (claims) {
-            if (lane == 0) claim_number = claim_first(ws);       // (looked at in answer())
-            claim_pending = true;
+            claim_wanted = true;
         } else if (lane == 0) {
             st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
         }
         asked = true;
     };
     auto settle_claim = [&]() __attribute__((always_inline)) {
-        if (!claim_pending) return;
-        claim_pending = false;
-        claimed = first_task(q, a, uniform_i32(claim_number));
+        if (!claim_wanted && !claim_pending) return;
+        int number = 0;
+        if (claim_pending) number = g_claim_number;
+        else if (lane == 0) number = claim_first(ws);
+        claim_wanted = claim_pending = false;
+        claimed = first_task(q, a, uniform_i32(number));
         if (claimed == kTaskNone) {
             claims = false;
             if (lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
@@ -1199,14 +1298,58 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         asked = false;
         return t;
     };
-    // Takes a task up: the other waves are told, this wave's share of the pair is asked for.
+    // What the scalar steps look up is kept in registers, a node (or a child) per lane: read from LDS or memory
+    // one after the other, when needed, it was most of the time between the sweeps.
+    const int lazy = uniform_i32(a.lazy), walk = uniform_i32(a.walk);
+    unsigned nodes = 0u;                              // the tree's tables, lane n: see below
+    int tokens = -1;                                  // lane n: token and uniform of node n
+    float uniforms = 2.f;
+    int tree_in_regs = -1;                            // the tree they belong to
+    unsigned children = 0u;                           // lane j (and 32 + j): node word of child j of the task's node, its number instead of the list entry
+    unsigned long long token_ok = 0ull;               // bit j: child j's token is in range
+    T logits = 0;                                     // lane j: child j's target logit, lane 32 + j: draft logit
+    constexpr int kOff = 5, kEntry = 11, kRank = 17, kLow = 23, kClass = 29;      // nchild: bits 0..4
+    auto field = [](unsigned word, int at, unsigned mask) __attribute__((always_inline)) { return static_cast<int>((word >> at) & mask); };
+    auto node_word = [&](int node) __attribute__((always_inline)) { return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(nodes), node)); };
+    auto n_children = [&](int node) __attribute__((always_inline)) { return field(node_word(node), 0, 31u); };
+    auto load_tables = [&]() __attribute__((always_inline)) {
+        nodes = 0u;
+        const int own = lane_here();
+        if (own < N)
+            nodes = static_cast<unsigned>(tree.nchild[own]) | static_cast<unsigned>(tree.child_off[own]) << kOff |
+                    static_cast<unsigned>(tree.child_list[own]) << kEntry | static_cast<unsigned>(tree.rank[own]) << kRank |
+                    static_cast<unsigned>(tree.sub_lo[own]) << kLow | static_cast<unsigned>(tree.cls[own]) << kClass;
+    };
+    load_tables();
+    auto gather = [&](int from_lane, int v) __attribute__((always_inline)) { return __builtin_amdgcn_ds_bpermute(from_lane << 2, v); };
+    // Takes a task up: the other waves are told, this wave's share of the pair is asked for, then the children's logits
+    // (tokens and uniforms once per tree, so that nothing waits for a load that depends on a load).
     auto start_task = [&](const NodeView& v, int t) __attribute__((always_inline)) {
-        if (lane == 0) { g_cmd.kind = kCmdTask; g_cmd.m = t; }
+        if (lane == 0) { g_cmd.kind = kCmdTask; g_cmd.m = t; g_cmd.b = v.b; g_cmd.n = v.n; }
         task_barrier();                                    // B: the other waves take the task up
         int tid_l = threadIdx.x;
         asm volatile("" : "+v"(tid_l));     // per-task copy: nothing derived from it is kept across tasks
-        pair.setup(v.zt, v.zd, V, lds_t, lds_d, tid_l, member, team_size, uniform_i32(q.part_vecs));
+        pair.setup(v.zt, v.zd, V, lds_t, lds_d, tid_l, member, team_size, part_vecs);
+        if (ACCEPT) {
+            pair.issue_loads();
+            return;
+        }
+        const bool new_tree = tree_in_regs != v.b;
+        tree_in_regs = v.b;
+        if (new_tree) {
+            const size_t at = static_cast<size_t>(v.b) * N + min(lane_here(), N - 1);
+            tokens = as_global(a.tokens)[at];
+            if (!a.estimate) uniforms = as_global(a.uniforms)[at];
+        }
         pair.issue_loads();
+        // (lanes read each other's registers here, not LDS: the compiler would wait for the loads that go there)
+        const int own = lane_here(), j = own & 31, k = n_children(v.n);
+        const int child = field(static_cast<unsigned>(gather(field(node_word(v.n), kOff, 63u) + j, static_cast<int>(nodes))), kEntry, 63u);
+        children = (static_cast<unsigned>(gather(child, static_cast<int>(nodes))) & ~(63u << kEntry)) | static_cast<unsigned>(child) << kEntry;
+        const int x = gather(child, tokens);
+        const bool ok = j < k && x >= 0 && x < V;
+        token_ok = __ballot(ok);
+        logits = as_global(own < 32 ? v.zt : v.zd)[ok ? x : 0];
     };
     // A task taken up before it was certain (the task this team is most likely to run next,
     // started while the leader still settles what follows from the last one), -1: none.
@@ -1216,16 +1359,23 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // starts with (Traversal), known here without asking memory; negative: not known.
     unsigned long long chain_settled = 0ull, chain_accepted = 0ull;
     double a0_known = -1.0;
+    int chained = -1;                                 // the node of the task handed on to (same tree)
     // One node task after the other, for as long as the team knows its next one itself (the task
     // a node task hands to its own team: a child's, or the rest of the node where the tree
     // branches): no way back through the task loop, no queue in between.
     for (;;) {
     {
     // (a task that is under way already belongs to the tree of the task before)
-    if (kShapeInTask && started != task && uniform_i32(a.per_tree)) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), N, tree_of(task));
-    const NodeView nv = view_of(task);
+    if (kShapeInTask && started != task && uniform_i32(a.per_tree)) {
+        load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), N, tree_of(task));
+        load_tables();
+    }
+    const NodeView nv = chained >= 0 ? view_at(tree_in_regs, chained, false) : view_of(task);
+    chained = -1;
     const bool resumed = nv.resumed;
-    const int b = nv.b, n = nv.n, k = nv.k;
+    const int b = nv.b, n = nv.n, k = n_children(n), off = field(node_word(n), kOff, 63u);
+    auto child_of = [&](int j) __attribute__((always_inline)) { return field(node_word(off + j), kEntry, 63u); };
+    (void)child_of;
     const size_t bn = nv.bn;
     const T* const zt = nv.zt;
     const T* const zd = nv.zd;
@@ -1234,20 +1384,26 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     if (started != task) start_task(nv, task);            // (else: under way since the end of the task before)
     started = -1;
     double At_ = 0.0, Ad_ = 0.0, wa = 1.0;            // log2-partitions of the two rows; the node's weight
+    int next_hint_node = 0;
     int next_hint = -1;                               // goes out with a sweep command (SweepCmd::next)
     // one more sweep by all four waves; the team's sums come back
     auto sweep = [&](int kind, const ResidualConsts& rc, float sp, float sq, int m, int naive, double& s0, double& s1) __attribute__((always_inline)) {
         if (lane == 0) {
             g_cmd.kind = kind; g_cmd.nAt = rc.nAt; g_cmd.nAd = rc.nAd; g_cmd.rho = rc.rho;
             g_cmd.sp = sp; g_cmd.sq = sq; g_cmd.m = m; g_cmd.naive = naive; g_cmd.next = next_hint;
+            g_cmd.b = b; g_cmd.n = next_hint_node;
+            g_cmd.claim = claim_wanted ? 1 : 0;
         }
+        claim_pending = claim_pending || claim_wanted;
+        claim_wanted = false;
         task_barrier();                                    // B
         SweepCmd cmd;
         cmd.kind = kind; cmd.nAt = uniform_f32(rc.nAt); cmd.nAd = uniform_f32(rc.nAd); cmd.rho = uniform_f32(rc.rho);
         cmd.sp = sp; cmd.sq = sq; cmd.m = m; cmd.naive = naive; cmd.next = -1;
         run_sweep<E, KIND>(pair, cmd, k32, 0, lane);
         task_barrier();                                    // A
-        collect_sums(team, s0, s1);
+        if (kind == kCmdMassSlope) collect_sums<true>(team, s0, s1);
+        else collect_sums<false>(team, s0, s1);
     };
     // W(c) for one c
     auto residual_mass = [&](double cc) __attribute__((always_inline)) -> double {
@@ -1261,7 +1417,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // are teams idle?  Asked now, needed when this task hands on to the next (the leader's business)
     int idle_now = 0;
     if (lead) idle_now = ld_relaxed(&ws.qctl[kCtlIdle]);
-    const bool split_here = METHOD == MPV_METHOD_TRAVERSAL && a.lazy && !resumed && n == tree.split_node;
+    const bool split_here = METHOD == MPV_METHOD_TRAVERSAL && lazy && !resumed && n == uniform_i32(tree.split_node);
     const bool idle_seen = (flags & kFlagIdle) != 0;
 
     // Traversal, only what is needed, and idle teams about: an only child's task is queued
@@ -1269,11 +1425,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // then finds the weight published (or waits a moment for it), so that a chain of nodes
     // takes little more than one task's time.  If the weight turns out to be 0 it gives up.
     bool child_ahead = false;
-    if (METHOD == MPV_METHOD_TRAVERSAL && a.lazy && k == 1 && !split_here && idle_seen) {
-        const int cn = tree.child_list[tree.child_off[n]];
-        if (tree.nchild[cn] > 0) {
+    if (METHOD == MPV_METHOD_TRAVERSAL && lazy && k == 1 && !split_here && idle_seen) {
+        const int cn = child_of(0);
+        if (n_children(cn) > 0) {
             child_ahead = true;
-            if (lead) append_task(tree, ws, tree.cls[cn], b * N + cn);
+            if (lead) append_task(tree, ws, field(node_word(cn), kClass, 1u), b * N + cn);
         }
     }
 
@@ -1308,7 +1464,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             }
         }
         a0 = lane_f64(a0, 0);
-        if (a0_known >= 0.0) a0 = a0_known;
+        if (all_alike(a0_known >= 0.0)) a0 = a0_known;
         a0_known = -1.0;
         // lanes to their wave's largest reference, waves to the workgroup's, members to the team's
         const float Mt_w = wave_max(f.t.mk), Md_w = wave_max(f.d.mk);
@@ -1319,58 +1475,20 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             g_sh.part[0][0] = st_w; g_sh.part[0][1] = sd_w;
         }
         task_barrier();                                    // A: every wave's partials are there
-        un = ch_u[MPV_MAX_CHILDREN];
-        team.seq++;
-        float Mt = g_sh.partf[0][0], Md = g_sh.partf[0][1];
-#pragma unroll
-        for (int w = 1; w < kTaskWaves; ++w) { Mt = fmaxf(Mt, g_sh.partf[w][0]); Md = fmaxf(Md, g_sh.partf[w][1]); }
-        double st = 0.0, sd = 0.0;
-#pragma unroll
-        for (int w = 0; w < kTaskWaves; ++w) {
-            st += g_sh.part[w][0] * static_cast<double>(fast_exp2(g_sh.partf[w][0] - Mt));
-            sd += g_sh.part[w][1] * static_cast<double>(fast_exp2(g_sh.partf[w][1] - Md));
-        }
-        unsigned mine = 0u;
-        switch (lane) {
-            case 0: mine = __float_as_uint(Mt); break;
-            case 1: mine = __float_as_uint(Md); break;
-            case 2: mine = half_of(st, 0); break;
-            case 3: mine = half_of(st, 1); break;
-            case 4: mine = half_of(sd, 0); break;
-            case 5: mine = half_of(sd, 1); break;
-            case 6: mine = half_of(a0, 0); break;
-            case 7: mine = half_of(a0, 1); break;
-            default: break;
-        }
-        exchange_words(team, mine);
-        __builtin_amdgcn_wave_barrier();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        team.dead = g_sh.dead;
-        float MT = OnlineLse::kFloor, MD = OnlineLse::kFloor;
-        for (int m = 0; m < team.size; ++m) {
-            MT = fmaxf(MT, __uint_as_float(g_sh.words[m * kExchWords]));
-            MD = fmaxf(MD, __uint_as_float(g_sh.words[m * kExchWords + 1]));
-        }
-        double ST = 0.0, SD = 0.0;
-        for (int m = 0; m < team.size; ++m) {
-            ST += double_at(g_sh.words, m, 1) * static_cast<double>(fast_exp2(__uint_as_float(g_sh.words[m * kExchWords]) - MT));
-            SD += double_at(g_sh.words, m, 2) * static_cast<double>(fast_exp2(__uint_as_float(g_sh.words[m * kExchWords + 1]) - MD));
-        }
-        const double lg = cold_log2(lane == 1 ? SD : ST);         // both logarithms in one go, a lane each
-        At_ = uniform_f64(static_cast<double>(MT) + lane_f64(lg, 0));
-        Ad_ = uniform_f64(static_cast<double>(MD) + lane_f64(lg, 1));
-        if (METHOD == MPV_METHOD_TRAVERSAL) wa = uniform_f64(double_at(g_sh.words, 0, 3));
+        un = lane_f32(uniforms, n);
+        collect_stats<METHOD == MPV_METHOD_TRAVERSAL>(team, a0, At_, Ad_);
+        if (METHOD == MPV_METHOD_TRAVERSAL) wa = a0;
     }
     RowStat rt, rd;
     rt.A = At_; rd.A = Ad_; rt.m = 0.f; rd.m = 0.f;
 
     // ---- per-child scalars and one residual-mass reduction per child
-    if (METHOD == MPV_METHOD_TRAVERSAL && a.lazy && n != 0 && !(wa > 0.0) && chain_settled == 0ull) {
+    if (METHOD == MPV_METHOD_TRAVERSAL && lazy && n != 0 && !all_alike(wa > 0.0) && chain_settled == 0ull) {
         // queued ahead of its weight, which is 0: the parent has written off the whole subtree.
         // Nothing to do but to pass the news on to an only child queued ahead in turn.
         if (lead) {
             if (child_ahead) {
-                const size_t bc = static_cast<size_t>(b) * N + tree.child_list[tree.child_off[n]];
+                const size_t bc = static_cast<size_t>(b) * N + child_of(0);
                 st_relaxed(reinterpret_cast<unsigned long long*>(&ws.a0[bc]), static_cast<unsigned long long>(__double_as_longlong(0.0)));
             }
             wait_memory();
@@ -1384,10 +1502,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     static_assert(MPV_MAX_CHILDREN <= 32, "one lane per child and row");
     double pq_all;
     {
-        const int j = lane & 31;
-        const bool of_draft = lane >= 32;
-        const float z = j < k ? (of_draft ? ch_zd[j] : ch_zt[j]) : 0.f;
-        pq_all = probability_exp2(static_cast<double>(z) * kd - (of_draft ? Ad_ : At_));
+        pq_all = probability_exp2(static_cast<double>(E::load_one(&logits)) * kd - (lane_here() >= 32 ? Ad_ : At_));
     }
     // test outcomes this task settles, one bit per node at its position in postorder
     unsigned long long settled_bits = 0ull, accepted_bits = 0ull;
@@ -1413,7 +1528,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // (f has a kink where the largest token switches sides and can be nearly flat beyond it:
     // there it takes more).
     double sp_rho = 1.0, sp_W = 1.0;
-    if (METHOD == MPV_METHOD_SPECINFER && a.walk == 3) {
+    if (METHOD == MPV_METHOD_SPECINFER && walk == 3) {
         constexpr double kTol = 3e-8;                 // relative width of the final bracket
         double lo = 1.0, hi = static_cast<double>(k);
         double x = 1.0, fx = 0.0, dfx = 0.0;
@@ -1421,7 +1536,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         for (int it = 0; it < evals; ++it) {
             if (it > 0) {
                 double cand = 0.0;                    // outside the bracket: "no candidate"
-                if (dfx < 0.0) {
+                if (all_alike(dfx < 0.0)) {
                     const double step = -fx / dfx;
                     cand = x + step;
                     if (fabs(step) <= 0.5 * kTol * x) cand = fx > 0.0 ? x * (1.0 + kTol) : x * (1.0 - kTol);
@@ -1444,12 +1559,12 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             sp_W = Wx;
             if (team.dead) break;
             if (it == 0) {
-                if (!(fx > 0.0)) break;               // the root is 1 (also when k = 1)
+                if (!all_alike(fx > 0.0)) break;               // the root is 1 (also when k = 1)
             } else {
-                if (fx > 0.0) lo = x;
-                else if (fx < 0.0) hi = x;
+                if (all_alike(fx > 0.0)) lo = x;
+                else if (all_alike(fx < 0.0)) hi = x;
                 else break;
-                if (hi - lo <= kTol * hi) break;
+                if (all_alike(hi - lo <= kTol * hi)) break;
             }
         }
     }
@@ -1470,7 +1585,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             alpha = 1.0 - int_power(D, k);
         } else if (a.walk == 0) {
             double cc = 0.0, Wc = 1.0;
-            for (int j = 0; j < k && Wc > 0.0 && !team.dead; ++j) {
+            for (int j = 0; j < k && all_alike(Wc > 0.0) && !team.dead; ++j) {
                 cc = uniform_f64(cc + Wc);
                 Wc = residual_mass(cc);
             }
@@ -1508,55 +1623,58 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // a resumed task repeats the arithmetic of the first child (whose task has long run)
         // to get at the residual that follows its rejection
         const bool redone = resumed && j == 0;
-        const int cn = tree.child_list[tree.child_off[n] + j];
+        const unsigned child = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(children), j));
+        const int cn = field(child, kEntry, 63u);
+        const bool inner_child = field(child, 0, 31u) > 0;
         const size_t bc = static_cast<size_t>(b) * N + cn;
-        const int x = ch_tok[j];
         double px = 0.0, qx = 0.0;
-        const bool tok_ok = (x >= 0 && x < V);
+        const bool tok_ok = ((token_ok >> j) & 1ull) != 0ull;
         if (tok_ok) {
             px = lane_f64(pq_all, j);
             qx = lane_f64(pq_all, 32 + j);
         } else if (lead) {
             atomicAdd(&a.counters[MPV_COUNTER_BAD_TOKEN], 1u);
         }
-        const double Px = fmax(px - c * qx, 0.0) / W;     // current distribution at x
+        const double rest = fmax(px - c * qx, 0.0);       // current distribution at x, times W
         double w_child;
         if (METHOD == MPV_METHOD_TRAVERSAL) {
             // block-verification weight recursion (Sec. 3.1) with the current a and P
-            if (!(wa > 0.0) || !(Px > 0.0)) w_child = 0.0;
-            else if (qx > 0.0) w_child = fmin(1.0, wa * Px / qx);
+            if (!all_alike(wa > 0.0 && rest > 0.0)) w_child = 0.0;
+            else if (all_alike(qx > 0.0)) w_child = fmin(1.0, wa * rest / (W * qx));
             else w_child = 1.0;
-        } else if (a.walk == 1) {
+        } else if (walk == 1) {
             // NSS tests nothing (App. B Alg. 1); the estimate wants p(x): the chance that Y ~ p is x
             w_child = px;
-        } else if (a.walk == 3) {
+        } else if (walk == 3) {
             // App. B Alg. 3: accept x if rho* U <= p(x)/q(x)
-            if (qx > 0.0) w_child = fmin(1.0, px / (sp_rho * qx));
+            if (all_alike(qx > 0.0)) w_child = fmin(1.0, px / (sp_rho * qx));
             else w_child = (px > 0.0) ? 1.0 : 0.0;
         } else {
             // App. B Alg. 4: accept x with min(1, p(x)/q(x))
-            if (qx > 0.0) w_child = fmin(1.0, Px / qx);
-            else w_child = (Px > 0.0) ? 1.0 : 0.0;
+            if (all_alike(qx > 0.0)) w_child = fmin(1.0, rest / (W * qx));
+            else w_child = (rest > 0.0) ? 1.0 : 0.0;
         }
         // the same comparison the walk makes
-        const bool child_accepted = static_cast<double>(ch_u[j]) < w_child;
-        const unsigned long long child_bit = 1ull << tree.rank[cn];
+        const double u_child = static_cast<double>(lane_f32(uniforms, cn));
+        // (top-down: as a mask; a scalar branch here makes the compiler copy the loop's end, which costs registers)
+        const bool child_accepted = METHOD == MPV_METHOD_TRAVERSAL ? all_alike(u_child < w_child) : u_child < w_child, child_weight = all_alike(w_child > 0.0);
+        const unsigned long long child_bit = 1ull << field(child, kRank, 63u);
         if (redone) {
         } else if (METHOD == MPV_METHOD_SPECINFER) {
             settled_bits |= child_bit;
-        } else if (tree.nchild[cn] == 0) {
+        } else if (!inner_child) {
             settled_bits |= child_bit;
             if (child_accepted) accepted_bits |= child_bit;
-        } else if (a.lazy && !(w_child > 0.0)) {
+        } else if (lazy && !child_weight) {
             // A child of weight 0 can never be accepted, passes weight 0 to its whole subtree
             // and never provides a bonus distribution: its task (and its subtree's) is not
             // queued, its rows are never read; the whole subtree counts as rejected.
-            const int hi = tree.rank[cn], lo = tree.sub_lo[cn];
+            const int hi = field(child, kRank, 63u), lo = field(child, kLow, 63u);
             const unsigned long long upto = (hi >= 63) ? ~0ull : ((1ull << (hi + 1)) - 1ull);
             settled_bits |= upto & ~((1ull << lo) - 1ull);
         }
         // Traversal: the child's own task is needed unless its weight is 0 (see above)
-        const bool run_child = METHOD == MPV_METHOD_TRAVERSAL && !redone && tree.nchild[cn] > 0 && (w_child > 0.0 || !a.lazy);
+        const bool run_child = METHOD == MPV_METHOD_TRAVERSAL && !redone && inner_child && (child_weight || !lazy);
         const bool first_to_run = run_child && own_child < 0;
         if (first_to_run) {
             // kept for this team if it is the last thing this task finds out and nobody is idle
@@ -1567,11 +1685,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // One more sweep to go at most: time to ask for the next task, unless this team
         // already knows what it will run next (a child's task).
         if (leader && j == k - 1 && !asked && (own_child < 0 || own_given) &&
-            !(METHOD == MPV_METHOD_SPECINFER && a.lazy && child_accepted && tree.nchild[cn] > 0))
+            !(METHOD == MPV_METHOD_SPECINFER && lazy && child_accepted && inner_child))
             ask_ahead();
         if (lead && !redone) {
             if (METHOD == MPV_METHOD_TRAVERSAL) {
-                if (tree.nchild[cn] == 0) {
+                if (!inner_child) {
                     st_shared_f64(&ws.atest[bc], w_child);           // leaves are tested as they are
                 } else {
                     st_relaxed(reinterpret_cast<unsigned long long*>(&ws.a0[bc]), static_cast<unsigned long long>(__double_as_longlong(w_child)));
@@ -1579,11 +1697,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     // no queue) unless some team is idle; every other one is queued now,
                     // while this task goes on with the sweeps that follow.
                     if (run_child && (!first_to_run || own_given) && !child_ahead)
-                        append_task(tree, ws, tree.cls[cn], b * N + cn);      // (waits for the weight's store with its own count)
+                        append_task(tree, ws, field(child, kClass, 1u), b * N + cn);      // (waits for the weight's store with its own count)
                 }
             } else {
                 st_shared_f64(&ws.atest[bc], w_child);
-                if (a.estimate && a.walk == 3) {
+                if (a.estimate && walk == 3) {
                     // App. D, SpecTr Branching: p_res(x), p_res = norm (p - rho* q)_+ (see the search above)
                     const double r = fmax(px - sp_rho * qx, 0.0);
                     st_shared_f64(&ws.aux[bc], sp_W > 0.0 ? fmin(r / sp_W, 1.0) : px);
@@ -1602,12 +1720,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             break;
         }
 
-        if (METHOD == MPV_METHOD_SPECINFER && a.walk >= 2 && !a.estimate && lead &&
-            fabs(w_child - static_cast<double>(ch_u[j])) < 1e-6)
+        if (METHOD == MPV_METHOD_SPECINFER && walk >= 2 && !a.estimate && lead && fabs(w_child - u_child) < 1e-6)
             atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_ACCEPT], 1u);     // (the other rules count these in their walk)
         // SpecInfer moves into the first child it accepts: later children and this node's
         // residual are not needed (the same in every lane: no lane is left behind)
-        if (METHOD == MPV_METHOD_SPECINFER && a.lazy && child_accepted) {
+        if (METHOD == MPV_METHOD_SPECINFER && lazy && child_accepted) {
             next_node = cn;
             if (a.context_node) {
                 // the walk goes on at the node of the accepted entry's context (anything else than a node
@@ -1618,29 +1735,31 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             break;
         }
         // NSS: nothing else to find out here
-        if (METHOD == MPV_METHOD_SPECINFER && a.walk == 1) continue;
+        if (METHOD == MPV_METHOD_SPECINFER && walk == 1) continue;
         // Naive (App. B, Alg. 2) tests the first child only; the token then drawn comes from (p - q)_+
-        if (METHOD == MPV_METHOD_SPECINFER && a.walk == 2 && !a.estimate) {
+        if (METHOD == MPV_METHOD_SPECINFER && walk == 2 && !a.estimate) {
             c = 1.0;
             break;
         }
         // SpecTr tests every child against the same p; its residual is formed once, by the draw
-        if (METHOD == MPV_METHOD_SPECINFER && a.walk == 3) {
+        if (METHOD == MPV_METHOD_SPECINFER && walk == 3) {
             c = sp_rho;
             continue;
         }
 
         // ---- the child (SpecInfer) or its whole subtree (Traversal) is rejected:
         //      P <- norm (a P - q)_+ ,  i.e.  c <- c + W/a ,  W <- W(c)
-        if (METHOD == MPV_METHOD_TRAVERSAL && !(wa > 0.0)) continue;   // (0*P - q)_+ = 0: nothing changes
+        if (METHOD == MPV_METHOD_TRAVERSAL && !all_alike(wa > 0.0)) continue;   // (0*P - q)_+ = 0: nothing changes
         if (team.dead) break;
         const double c2 = uniform_f64(c + W / wa);
         // the task's last sweep, and the team goes on with a child's task: the other waves may ask for its rows
-        if (METHOD == MPV_METHOD_TRAVERSAL && j == k - 1 && own_child >= 0 && !own_given)
-            next_hint = b * N + tree.child_list[tree.child_off[n] + own_child];
+        if (METHOD == MPV_METHOD_TRAVERSAL && j == k - 1 && own_child >= 0 && !own_given) {
+            next_hint_node = child_of(own_child);
+            next_hint = b * N + next_hint_node;
+        }
         const double W2 = residual_mass(c2);
         next_hint = -1;
-        if (W2 > 0.0) {
+        if (all_alike(W2 > 0.0)) {
             if (METHOD == MPV_METHOD_TRAVERSAL) {
                 const double S = (wa / W) * W2;
                 wa = uniform_f64(S / (S + (1.0 - wa)));
@@ -1648,17 +1767,16 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             c = c2;
             W = W2;
         } else {
-            if (METHOD == MPV_METHOD_TRAVERSAL) wa = (wa >= 1.0) ? 1.0 : 0.0;
+            if (METHOD == MPV_METHOD_TRAVERSAL) wa = all_alike(wa >= 1.0) ? 1.0 : 0.0;
             if (lead) atomicAdd(&a.counters[MPV_COUNTER_ZERO_MASS], 1u);
         }
-        if (METHOD == MPV_METHOD_SPECINFER && a.walk == 2) {
+        if (METHOD == MPV_METHOD_SPECINFER && walk == 2) {
             // Naive, estimate (App. D, Naive Branching): p_res(x_i) for every child, p_res = norm (p - q)_+
             // (now c = 1 and W = its mass; p itself if the mass was zero: c = 0, W = 1)
             for (int i = 0; i < k; ++i) {
-                const int ci = tree.child_list[tree.child_off[n] + i];
-                const int xi = ch_tok[i];
+                const int ci = child_of(i);
                 double r = 0.0;
-                if (xi >= 0 && xi < V)
+                if ((token_ok >> i) & 1ull)
                     r = fmax(lane_f64(pq_all, i) - c * lane_f64(pq_all, 32 + i), 0.0) / W;
                 else if (i > 0 && lead)
                     atomicAdd(&a.counters[MPV_COUNTER_BAD_TOKEN], 1u);
@@ -1666,7 +1784,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     st_shared_f64(&ws.aux[static_cast<size_t>(b) * N + ci], r);
                     if (i > 0) st_shared_f64(&ws.atest[static_cast<size_t>(b) * N + ci], 0.0);   // never tested
                 }
-                settled_bits |= 1ull << tree.rank[ci];
+                settled_bits |= 1ull << field(node_word(ci), kRank, 63u);
             }
             break;
         }
@@ -1676,22 +1794,24 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     //      most likely run next (every member works it out by itself, from the same numbers) is
     //      taken up at once: its rows travel while the leader settles what follows from this
     //      task, and while the others wait to hear of it.
-    int likely = -1;
+    next_node = uniform_i32(next_node);
+    int likely_node = -1;
     if (!team.dead) {
         if (METHOD == MPV_METHOD_TRAVERSAL) {
-            if (paused) likely = b * N + tree.child_list[tree.child_off[n]];
-            else if (own_child >= 0 && !own_given) likely = b * N + tree.child_list[tree.child_off[n] + own_child];
-        } else if (a.lazy && next_node >= 0 && tree.nchild[next_node] > 0) {
-            likely = b * N + next_node;
+            if (paused) likely_node = child_of(0);
+            else if (own_child >= 0 && !own_given) likely_node = child_of(own_child);
+        } else if (lazy && next_node >= 0 && n_children(next_node) > 0) {
+            likely_node = next_node;
         }
     }
+    const int likely = likely_node >= 0 ? b * N + likely_node : -1;
     // The team has asked for its next task ahead of time; if the answer is in the mailbox already
     // (and nothing of this task's own can come first) the team is told now and takes the task
     // up, while the leader settles what follows from this one: whatever that produces then goes
     // to the queue instead of being run by this team.  (Not with the token-following rules: a
     // tree can need several draws, the queue has room for one.)
     int taken = -1;
-    if (leader && likely < 0 && !paused && asked && !team.dead && a.walk == 0) {
+    if (leader && likely < 0 && !paused && asked && !team.dead && walk == 0) {
         taken = answer();
         if (taken >= 0) team_announce(team, taken, uniform_i32(idle_now) != 0 ? kFlagIdle : 0);
     }
@@ -1700,7 +1820,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         const int start_now = likely >= 0 ? likely
                             : ((taken >= 0 && !(taken >= B * N && taken < B * N + B) && (!a.per_tree || tree_of(taken) == b)) ? taken : -1);
         if (start_now >= 0) {
-            start_task(view_of(start_now), start_now);
+            start_task(likely >= 0 ? view_at(b, likely_node, false) : view_of(start_now), start_now);
             started = start_now;
         }
         if (likely >= 0) {
@@ -1709,7 +1829,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             // so nothing is announced, nothing waited for, and the outcomes settled here are
             // noted for the first task that goes the long way to publish.  (If another branch
             // settles the tree meanwhile, the chain runs on in vain until it ends.)
-            if (METHOD == MPV_METHOD_TRAVERSAL || a.walk == 0) {
+            if (METHOD == MPV_METHOD_TRAVERSAL || walk == 0) {
                 if (!(METHOD == MPV_METHOD_TRAVERSAL && paused)) {
                     if (lead) {
                         st_shared_f64(&ws.At[bn], rt.A);
@@ -1720,12 +1840,13 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     chain_settled |= settled_bits;
                     chain_accepted |= accepted_bits;
                     if (METHOD == MPV_METHOD_TRAVERSAL && n != 0) {
-                        const unsigned long long own = 1ull << tree.rank[n];
+                        const unsigned long long own = 1ull << field(node_word(n), kRank, 63u);
                         chain_settled |= own;
-                        if (static_cast<double>(un) < wa) chain_accepted |= own;
+                        if (all_alike(static_cast<double>(un) < wa)) chain_accepted |= own;
                     }
                 }
                 if (METHOD == MPV_METHOD_TRAVERSAL) a0_known = own_w;
+                chained = likely_node;
                 task = likely;                            // (flags: as they are)
                 continue;
             }
@@ -1741,7 +1862,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     own_flags = uniform_i32(idle_now) != 0 ? kFlagIdle : 0;
     if (paused) {
         // nothing is settled yet; the first child's task is run next by this team
-        own_task = b * N + tree.child_list[tree.child_off[n]];
+        own_task = b * N + child_of(0);
         team_announce(team, own_task, own_flags);
         if (lane == 0) {
             (void)atomicAdd(&ws.qctl[0], 1);
@@ -1757,10 +1878,10 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         st_shared_f64(&ws.cfin[bn], c);
         if (METHOD == MPV_METHOD_TRAVERSAL && n != 0) st_shared_f64(&ws.atest[bn], wa);
         bool push_sample, settled_tree = false, resume = false;
-        if (METHOD == MPV_METHOD_SPECINFER && a.lazy) {
+        if (METHOD == MPV_METHOD_SPECINFER && lazy) {
             // the walk ends here (no child accepted) or in the accepted leaf
-            push_sample = next_node < 0 || tree.nchild[next_node] == 0;
-            if (a.walk) st_relaxed(&ws.cur[b], next_node >= 0 ? next_node : n);     // where the next token is drawn
+            push_sample = next_node < 0 || n_children(next_node) == 0;
+            if (walk) st_relaxed(&ws.cur[b], next_node >= 0 ? next_node : n);     // where the next token is drawn
             wait_memory();                            // results written through before anything else is started
         } else {
             // Announce the outcomes settled here, then see whether the tree's outcome is settled:
@@ -1770,7 +1891,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             // `acc` is written before `known`, so the acc bits of known nodes are final.  Of
             // the tasks that see a settled tree, the first to flip `decided` starts the sampling.
             if (METHOD == MPV_METHOD_TRAVERSAL && n != 0) {
-                const unsigned long long own = 1ull << tree.rank[n];
+                const unsigned long long own = 1ull << field(node_word(n), kRank, 63u);
                 settled_bits |= own;
                 if (static_cast<double>(un) < wa) accepted_bits |= own;
             }
@@ -1785,7 +1906,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             const unsigned long long acc = ld_relaxed(&ws.acc[b]);
             const int decided_before = ld_relaxed(&ws.decided[b]);      // issued with the load above: one round trip
             bool settled;
-            if (a.lazy) {
+            if (lazy) {
                 const unsigned long long open = ~(known & ~acc);          // not known to be rejected
                 const int first = __ffsll(static_cast<long long>(open)) - 1;   // the root's bit is always set
                 settled = ((known >> first) & 1ull) != 0ull;
@@ -1796,12 +1917,12 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             push_sample = settled && decided_before == 0 && atomicCAS(&ws.decided[b], 0, 1) == 0;
             // only what is needed: once a tree is settled (here or by another task) the rest of
             // its node tasks are pointless
-            settled_tree = a.lazy && (settled || decided_before != 0);
+            settled_tree = lazy && (settled || decided_before != 0);
             // The subtree that was explored first has just turned out to be rejected as a whole
             // (this task supplied its last missing outcome): time for the rest of the node
             // where the tree branches.
-            if (METHOD == MPV_METHOD_TRAVERSAL && a.lazy && tree.split_node >= 0 && !settled_tree &&
-                ((tree.split_mask >> tree.rank[n]) & 1ull) != 0ull) {          // this node lies in that subtree
+            if (METHOD == MPV_METHOD_TRAVERSAL && lazy && tree.split_node >= 0 && !settled_tree &&
+                ((tree.split_mask >> field(node_word(n), kRank, 63u)) & 1ull) != 0ull) {          // this node lies in that subtree
                 const unsigned long long m = tree.split_mask;
                 resume = (known & m) == m && (known_before & m) != m && (acc & m) == 0ull;
             }
@@ -1835,8 +1956,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     } else if (taken >= 0) {
         // (nothing else can follow from a task that has no child of its own to run)
     } else if (METHOD == MPV_METHOD_TRAVERSAL) {
-        if (own_child >= 0 && !own_given && !settled_i) own_task = b * N + tree.child_list[tree.child_off[n] + own_child];
-    } else if (a.lazy && next_node >= 0 && tree.nchild[next_node] > 0) {
+        if (own_child >= 0 && !own_given && !settled_i) own_task = b * N + child_of(own_child);
+    } else if (lazy && next_node >= 0 && n_children(next_node) > 0) {
         own_task = b * N + next_node;
     }
     // the others hear of it at once (they are waiting for the next task by now)
@@ -1848,8 +1969,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         }
         // (cannot happen: a task that settles the tree or completes a subtree has no child left to run)
         if (METHOD == MPV_METHOD_TRAVERSAL && own_child >= 0 && !own_given && !settled_i && (push_sample_i || resume_i)) {
-            const int cn = tree.child_list[tree.child_off[n] + own_child];
-            append_task(tree, ws, tree.cls[cn], b * N + cn);
+            const int cn = child_of(own_child);
+            append_task(tree, ws, field(node_word(cn), kClass, 1u), b * N + cn);
         }
         wait_memory();                                // every new task has been counted
         atomicAdd(&ws.qctl[1], 1);

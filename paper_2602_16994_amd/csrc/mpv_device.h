@@ -605,12 +605,19 @@ struct RetainedPart {
     // Put every load of the kept slots in flight (registers first: they are consumed first).
     // An empty part (nv = 0) loads nothing.
     __device__ __forceinline__ void issue_loads() {
+        issue_register_loads();
+        issue_lds_loads();
+    }
+    __device__ __forceinline__ void issue_register_loads() {
         if (nv <= 0) return;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             rt[j] = load_raw_at_nt(bt, vec_of(j));
             rd[j] = load_raw_at_nt(bd, vec_of(j));
         }
+    }
+    __device__ __forceinline__ void issue_lds_loads() {
+        if (nv <= 0) return;
         const int wave0 = (tid / kWave) * kWave;
 #pragma unroll
         for (int j = 0; j < L; ++j) {
