@@ -99,6 +99,7 @@ struct QueuePlan {
     int32_t teams;                       // teams of the launch (the grid is teams * team_size workgroups)
     int32_t team_size;                   // G: workgroups that share one task
     int32_t part_vecs;                   // 16-byte vectors of a row per member (a multiple of 64)
+    int32_t box_step;                    // words from one team's mailbox to the next
     int32_t same_xcd;                    // members of a team are 8 workgroup numbers apart (one chiplet, its L2)
 };
 
@@ -122,7 +123,7 @@ struct Workspace {
     // [kCtlIdle] teams left waiting after the last round of dispatching (a hint), [kCtlFirst] first tasks
     // counted off, [kCtlTreesDone] trees whose outputs are written
     int32_t* qctl;
-    int32_t* mailbox;    // [teams] kMailboxAbsent until the team has asked for a task, then kMailboxWaiting /
+    int32_t* mailbox;    // [teams], QueuePlan::box_step words apart: kMailboxAbsent until the team has asked for a task, then kMailboxWaiting /
                          // kMailboxSoon, or the task handed to that team
     // Per tree, one bit per node at the node's position in postorder: `known` = the outcome of
     // the node's test is settled, `acc` = it is "accepted" (valid once known).  `decided` = the
@@ -214,10 +215,14 @@ constexpr int kMaxTiles = MPV_MAX_VOCAB / (kWave * 4);
 constexpr int kMailboxWaiting = -1;                  // the team is idle
 constexpr int kMailboxSoon = -2;                     // the team has asked ahead: it will be free shortly
 constexpr int kMailboxAbsent = -3;                   // the team has not asked for anything yet
+constexpr int kMailboxDispatch = -6;                  // the team is handed the dispatcher's lock
+constexpr int kMailboxExit = -7;                      // nothing is left
+constexpr int kMailboxWords = 1024;                   // the mailboxes' memory: as far apart as it allows
 constexpr int kTaskExit = -1;                         // what a leader's wait returns when all is done
 constexpr int kTaskNone = -2;                         // announced to a team that came too late for a first task
 constexpr int kWorkerSlots = 8;                       // mailboxes per dispatcher lane
 constexpr int kMaxTeams = kWave * kWorkerSlots;
+static_assert(kMaxTeams <= kMailboxWords, "a mailbox for every team");
 constexpr int kKindAcceptance = 100;                   // node_task_kernel instantiation for the acceptance rates (see there)
 
 // LDS of node_task_kernel that the functions it calls use as well (file scope, so that they address
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
         const int exch_words = q.teams * q.team_size * 2 * kExchWords;
         for (int w = me; w < exch_words; w += stride) ws.exch[w] = 0ull;
         for (int w = me; w < q.teams * 2; w += stride) ws.team_task[w] = 0ull;
-        for (int w = me; w < q.teams; w += stride) ws.mailbox[w] = kMailboxAbsent;
+        for (int w = me; w < q.teams; w += stride) ws.mailbox[w * q.box_step] = kMailboxAbsent;
     }
     if (n == 0) {
         if (i < MPV_COUNTER_COUNT && !a.keep_counters) a.counters[i] = 0u;
@@ -454,8 +459,12 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
 //   dispatch: a leader that has nothing to do takes the dispatcher lock if it is free and,
 //             with its first wave, hands queued tasks to waiting teams (its own included)
 //             in priority order (class, then age), until it has a task of its own; then it
-//             releases the lock.  Those that find the lock taken poll their mailbox.  If every
-//             team is busy nobody dispatches, and nobody needs to.  Node tasks of trees
+//             passes the lock to a team that is still waiting, or releases it.  Those that find the
+//             lock taken poll their own mailbox and nothing else (the lock and the exit flag only
+//             now and then, should the holder have left at the moment they began to wait): when every
+//             idle team looked at them all the time, their line, which the busy teams need for their
+//             counts, was the bottleneck (200 trees of V = 1500 on 512 teams, Traversal: 338 us, then 273).
+//             If every team is busy nobody dispatches, and nobody needs to.  Node tasks of trees
 //             whose outcome is settled are dropped here when only what is needed is computed.
 //   end:      nothing queued and completed == appended, with appended read before and after
 //             completed and unchanged: no task is queued, handed out or running, so nothing
@@ -525,36 +534,75 @@ __device__ __forceinline__ void tree_done(const Workspace& ws, const Args& a) {
     if (atomicAdd(&ws.qctl[kCtlTreesDone], 1) + 1 == a.B) st_relaxed(&ws.qctl[2], 1);
 }
 
-// One round of dispatching, by a whole wave that holds the lock.  Lane c keeps the head of
-// class c in `head`; lane l looks after the teams l, l + 64, ...  Returns true when
-// everything is finished (the exit flag has been set).
+// What the holder of the dispatcher's lock keeps from round to round.
+struct Dispatcher {
+    int head;             // lane c: head of class c
+    unsigned left;        // which of the lane's teams (lane, lane + 64, ...: a bit each) are still waiting
+    int hint;             // what kCtlIdle says
+    unsigned quiet;       // rounds in which nothing was queued
+    int own;              // the task its own team was given (-1: none)
+    int previous;         // the task it took from its mailbox last
+};
+
+// One round of dispatching, by a whole wave that holds the lock, for team `team`.  Returns true when everything is finished
+// (the exit flag has been set).
+//
+// Latency only: queued tasks wait for it.  Numbers that are the same in every lane are scalars, a lane's place among the
+// waiting ones is a count of bits; all queue entries are asked for before the first is looked at, then all flags (two
+// round trips to memory, not two for every 64 teams).
 __device__ __forceinline__ bool dispatch_round(const QueuePlan& q, const TreeDesc& tree, const Workspace& ws, const Args& a, bool drop_settled,
-                               int& head, long long t_begin) {
-    __shared__ int sh_head[kMaxClasses], sh_before[kMaxClasses + 1];
+                               int team, Dispatcher& d, long long t_begin) {
     const int lane = threadIdx.x;
-    const int workers = q.teams;
+    const int workers = uniform_i32(q.teams);
     // who is waiting, what is queued
-    unsigned waiting = 0u, soon = 0u;
+    int box[kWorkerSlots];
 #pragma unroll
     for (int sl = 0; sl < kWorkerSlots; ++sl) {
-        const int w = lane + kWave * sl;
-        if (w < workers) {
-            const int m = ld_relaxed(&ws.mailbox[w]);
-            if (m == kMailboxWaiting) waiting |= 1u << sl;
-            if (m == kMailboxSoon) soon |= 1u << sl;
-        }
+        box[sl] = kMailboxAbsent;
+        if (sl * kWave < workers && lane + kWave * sl < workers) box[sl] = ld_relaxed(&ws.mailbox[(lane + kWave * sl) * q.box_step]);
     }
     const int tail = (lane <= kMaxClasses) ? ld_relaxed(&ws.qctl[lane < kMaxClasses ? 4 + lane : 2]) : 0;
+    unsigned waiting = 0u, soon = 0u;
+    int idle_others = 0, n_soon = 0;
+    const int self_bit = team / kWave;
+    const bool self_lane = (team & (kWave - 1)) == lane;
+#pragma unroll
+    for (int sl = 0; sl < kWorkerSlots; ++sl) {
+        if (sl * kWave >= workers) continue;
+        if (box[sl] == kMailboxWaiting) waiting |= 1u << sl;
+        if (box[sl] == kMailboxSoon) soon |= 1u << sl;
+        idle_others += __popcll(__ballot(box[sl] == kMailboxWaiting));
+        n_soon += __popcll(__ballot(box[sl] == kMailboxSoon));
+    }
+    d.left = waiting;
+    {   // the holder before may have handed this team a task that it had not seen when it took the lock
+        int in_box = -1;
+#pragma unroll
+        for (int sl = 0; sl < kWorkerSlots; ++sl)
+            if (self_lane && sl == self_bit) in_box = box[sl];
+        in_box = __builtin_amdgcn_readlane(in_box, team & (kWave - 1));
+        if (in_box >= 0 && in_box != d.previous) {
+            d.own = in_box;
+            return false;
+        }
+    }
     if (__builtin_amdgcn_readlane(tail, kMaxClasses) != 0) return true;               // (the exit flag)
-    const int avail = (lane < q.nclass) ? tail - head : 0;
-    const int my_waiting = __popc(waiting), my_soon = __popc(soon);
-    const int waiting_incl = wave_inclusive_scan_i32(my_waiting);
-    const int soon_incl = wave_inclusive_scan_i32(my_soon);
-    const int avail_incl = wave_inclusive_scan_i32(avail);
-    const int total_idle = __shfl(waiting_incl, kWave - 1, kWave);
-    const int total_waiting = total_idle + __shfl(soon_incl, kWave - 1, kWave);
-    const int total_avail = __shfl(avail_incl, kWave - 1, kWave);
-    if (total_avail == 0) {
+    // the dispatcher's own team comes last of the idle ones: it goes on dispatching while there are others
+    const bool mine_waits = self_lane && ((waiting >> self_bit) & 1u);
+    const int self = __ballot(mine_waits) != 0ull ? 1 : 0;
+    if (mine_waits) waiting &= ~(1u << self_bit);
+    idle_others -= self;
+    const int total_idle = idle_others + self, total_waiting = total_idle + n_soon;
+    int first[kMaxClasses], before[kMaxClasses], total_avail = 0;      // class c: where its first entry is, number of that entry
+#pragma unroll
+    for (int c = 0; c < kMaxClasses; ++c) {
+        const int head = __builtin_amdgcn_readlane(d.head, c);
+        first[c] = uniform_i32(tree.class_off[c]) + head;
+        before[c] = total_avail;
+        if (c < q.nclass) total_avail += __builtin_amdgcn_readlane(tail, c) - head;
+    }
+    if (total_avail == 0 && (++d.quiet & 15u) == 0u) {
+        // (the last tree ends the launch, see tree_done: this is for a launch in which something went wrong)
         int done = 0;
         if (lane == 0) {
             const int a1 = ld_relaxed(&ws.qctl[0]);
@@ -577,48 +625,79 @@ __device__ __forceinline__ bool dispatch_round(const QueuePlan& q, const TreeDes
     }
     // how many will still be waiting after this round: tasks look at it to decide whether work
     // that may turn out useless is worth queueing
-    if (lane == 0) st_relaxed(&ws.qctl[kCtlIdle], max(0, total_idle - total_avail));
+    const int still_idle = max(0, total_idle - total_avail);
+    if (lane == 0 && still_idle != d.hint) st_relaxed(&ws.qctl[kCtlIdle], still_idle);
+    d.hint = still_idle;
     if (total_avail == 0 || total_waiting == 0) {
-        __builtin_amdgcn_s_sleep(8);
+        __builtin_amdgcn_s_sleep(4);
         return false;
     }
     // Requester number r gets queued task number r (in class, age order); the idle teams
-    // come first (in lane, slot order), then those that asked ahead.
-    if (lane < q.nclass) { sh_head[lane] = head; sh_before[lane + 1] = avail_incl; }
-    if (lane == 0) sh_before[0] = 0;
-    __builtin_amdgcn_wave_barrier();
-    int r_idle = waiting_incl - my_waiting;
-    int r_soon = total_idle + soon_incl - my_soon;
-    for (int sl = 0; sl < kWorkerSlots; ++sl) {
-        int mine;
-        if ((waiting >> sl) & 1u) mine = r_idle++;
-        else if ((soon >> sl) & 1u) mine = r_soon++;
-        else continue;
-        if (mine >= total_avail) continue;
-        int c = 0;
-        while (mine >= sh_before[c + 1]) ++c;         // ends: mine < total_avail = sh_before[nclass]
-        const int32_t* slot = &ws.queue[tree.class_off[c] + sh_head[c] + (mine - sh_before[c])];
-        int entry = -1;
-        for (int spin = 0; spin < kMaxSpins; ++spin) {          // the entry follows its tail count closely
-            entry = ld_relaxed(slot);
-            if (entry >= 0) break;
-            __builtin_amdgcn_s_sleep(2);
+    // come first, then those that asked ahead.
+    int entry[kWorkerSlots];
+    unsigned served = 0u;
+    {
+        int r_idle = 0, r_soon = total_idle;
+        const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+        for (int sl = 0; sl < kWorkerSlots; ++sl) {
+            entry[sl] = 0;
+            if (sl * kWave >= workers) continue;
+            const bool w = (waiting >> sl) & 1u, s = (soon >> sl) & 1u;
+            const unsigned long long w_mask = __ballot(w), s_mask = __ballot(s);
+            int mine = total_avail;
+            if (w) mine = r_idle + __popcll(w_mask & below);
+            if (s) mine = r_soon + __popcll(s_mask & below);
+            if (mine_waits && sl == self_bit) mine = idle_others;
+            r_idle += __popcll(w_mask);
+            r_soon += __popcll(s_mask);
+            if (mine < total_avail) {
+                int at = first[0] + mine;
+#pragma unroll
+                for (int c = 1; c < kMaxClasses; ++c)
+                    if (c < q.nclass && mine >= before[c]) at = first[c] + (mine - before[c]);
+                entry[sl] = ld_relaxed(&ws.queue[at]);
+                box[sl] = at;
+                served |= 1u << sl;
+            }
         }
-        if (entry < 0) {                              // must never happen: counted as finished, nobody runs it
+    }
+#pragma unroll
+    for (int sl = 0; sl < kWorkerSlots; ++sl) {
+        if (sl * kWave >= workers || !((served >> sl) & 1u)) continue;
+        for (int spin = 0; spin < kMaxSpins && entry[sl] < 0; ++spin) {          // the entry follows its tail count closely
+            __builtin_amdgcn_s_sleep(2);
+            entry[sl] = ld_relaxed(&ws.queue[box[sl]]);
+        }
+    }
+    int settled[kWorkerSlots], own = -1;
+#pragma unroll
+    for (int sl = 0; sl < kWorkerSlots; ++sl) {
+        settled[sl] = 0;
+        if (drop_settled && sl * kWave < workers && ((served >> sl) & 1u) && entry[sl] >= 0 && entry[sl] < a.B * a.N)
+            settled[sl] = ld_relaxed(&ws.decided[entry[sl] / a.N]);
+    }
+#pragma unroll
+    for (int sl = 0; sl < kWorkerSlots; ++sl) {
+        if (sl * kWave >= workers || !((served >> sl) & 1u)) continue;
+        if (entry[sl] < 0) {                          // must never happen: counted as finished, nobody runs it
             atomicAdd(&a.counters[MPV_COUNTER_DEPENDENCY_TIMEOUT], 1u);
             atomicAdd(&ws.qctl[1], 1);
-        } else if (drop_settled && entry < a.B * a.N && ld_relaxed(&ws.decided[entry / a.N]) != 0) {
+        } else if (settled[sl] != 0) {
             atomicAdd(&a.counters[MPV_COUNTER_NODE_TASKS_CANCELLED], 1u);
             atomicAdd(&ws.qctl[1], 1);
         } else {
-            st_relaxed(&ws.mailbox[lane + kWave * sl], entry);
+            st_relaxed(&ws.mailbox[(lane + kWave * sl) * q.box_step], entry[sl]);
+            d.left &= ~(1u << sl);
+            if (mine_waits && sl == self_bit) own = entry[sl];
         }
     }
-    if (lane < q.nclass) {
-        const int before = avail_incl - avail;
-        head += max(0, min(avail, total_waiting - before));
+    d.own = __builtin_amdgcn_readlane(own, team & (kWave - 1));
+#pragma unroll
+    for (int c = 0; c < kMaxClasses; ++c) {
+        const int avail = (c + 1 < kMaxClasses ? before[c + 1] : total_avail) - before[c];
+        if (lane == c) d.head += max(0, min(avail, total_waiting - before[c]));
     }
-    __builtin_amdgcn_wave_barrier();                  // sh_head / sh_before are rewritten next time round
     wait_memory();
     return false;
 }
@@ -636,35 +715,54 @@ __device__ __attribute__((noinline)) int acquire_task(int team_in, int previous_
     const int team = uniform_i32(team_in), previous = uniform_i32(previous_in);
     const bool drop_settled = uniform_i32(drop_settled_in ? 1 : 0) != 0;
     const int lane = threadIdx.x;
-    int32_t* const box = &ws.mailbox[team];
-    for (int spin = 0; spin < kMaxSpins; ++spin) {
+    int32_t* const box = &ws.mailbox[team * q.box_step];
+    for (int spin = 0; spin < 8 * kMaxSpins; ++spin) {        // (the time limit below comes first)
         int t = 0, ex = 0, lk = 1;
         if (lane == 0) {
             // nothing to do any more: from "soon" to "waiting" (unless the answer has arrived)
             t = (spin == 0) ? static_cast<int>(atomicCAS(box, kMailboxSoon, kMailboxWaiting)) : ld_relaxed(box);
-            ex = ld_relaxed(&ws.qctl[2]);
-            lk = ld_relaxed(&ws.qctl[3]);
+            if ((spin & 15) == 0) {
+                ex = ld_relaxed(&ws.qctl[2]);
+                lk = ld_relaxed(&ws.qctl[3]);
+            }
         }
         t = __builtin_amdgcn_readfirstlane(t);
         if (t >= 0 && t != previous) return t;
-        if (__builtin_amdgcn_readfirstlane(ex)) return kTaskExit;
+        if (t == kMailboxExit || __builtin_amdgcn_readfirstlane(ex)) return kTaskExit;
         int got = 0;
-        // (a team whose mailbox is still "absent" cannot be handed anything: it does not dispatch either)
-        if (lane == 0 && lk == 0 && t != kMailboxAbsent) got = (atomicCAS(&ws.qctl[3], 0, 1) == 0) ? 1 : 0;
+        if (t == kMailboxDispatch) {
+            if (lane == 0) st_relaxed(box, kMailboxWaiting);
+            wait_memory();
+            got = 1;
+        } else if (lane == 0 && lk == 0 && t != kMailboxAbsent) {
+            // (a team whose mailbox is still "absent" cannot be handed anything: it does not dispatch either)
+            got = (atomicCAS(&ws.qctl[3], 0, 1) == 0) ? 1 : 0;
+        }
         if (__builtin_amdgcn_readfirstlane(got)) {
-            // the previous holder wrote the heads before it released the lock
-            int head = (lane < q.nclass) ? ld_relaxed(&ws.qctl[4 + kMaxClasses + lane]) : 0;
+            // the previous holder wrote the heads before it passed the lock on
+            Dispatcher d;
+            d.head = (lane < q.nclass) ? ld_relaxed(&ws.qctl[4 + kMaxClasses + lane]) : 0;
+            d.left = d.quiet = 0u;
+            d.hint = d.own = -1;
+            d.previous = previous;
             int result = kTaskExit;
             for (;;) {
-                const bool finished = dispatch_round(q, tree, ws, a, drop_settled, head, t_start);
-                if (finished) break;
-                int mine = (lane == 0) ? ld_relaxed(box) : 0;
-                mine = __builtin_amdgcn_readfirstlane(mine);
-                if (mine >= 0 && mine != previous) { result = mine; break; }
+                if (dispatch_round(q, tree, ws, a, drop_settled, team, d, t_start)) break;
+                if (d.own >= 0) { result = d.own; break; }
             }
-            if (lane < q.nclass) st_relaxed(&ws.qctl[4 + kMaxClasses + lane], head);
+            if (lane < q.nclass) st_relaxed(&ws.qctl[4 + kMaxClasses + lane], d.head);
             wait_memory();
-            if (lane == 0) st_relaxed(&ws.qctl[3], 0);
+            if (result == kTaskExit) {                 // (later ones see the flag)
+                for (int sl = 0; sl < kWorkerSlots; ++sl)
+                    if ((d.left >> sl) & 1u) st_relaxed(&ws.mailbox[(lane + kWave * sl) * q.box_step], kMailboxExit);
+                return result;
+            }
+            const unsigned long long lanes = __ballot(d.left != 0u);
+            if (lanes == 0ull) {
+                if (lane == 0) st_relaxed(&ws.qctl[3], 0);
+            } else if (lane == __ffsll(static_cast<long long>(lanes)) - 1) {
+                st_relaxed(&ws.mailbox[(lane + kWave * (__ffs(static_cast<int>(d.left)) - 1)) * q.box_step], kMailboxDispatch);
+            }
             return result;
         }
         if (wall_clock64() - t_start > kLaunchTimeoutTicks) break;
@@ -1266,7 +1364,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         if (claims) {
             claim_wanted = true;
         } else if (lane == 0) {
-            st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+            st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxSoon);
         }
         asked = true;
     };
@@ -1279,7 +1377,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         claimed = first_task(q, a, uniform_i32(number));
         if (claimed == kTaskNone) {
             claims = false;
-            if (lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+            if (lane == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxSoon);
         }
     };
     // the task that was asked for, if it is there (-1); it is the team's then
@@ -1289,7 +1387,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         if (t == kTaskNone) {
             if (claims) return -1;
             const int previous = uniform_i32(g_loop.previous_task);
-            if (lane == 0) t = ld_relaxed(&ws.mailbox[team.id]);
+            if (lane == 0) t = ld_relaxed(&ws.mailbox[team.id * q.box_step]);
             t = uniform_i32(t);
             if (t < 0 || t == previous) return -1;
             if (lane == 0) g_loop.previous_task = t;
@@ -2076,7 +2174,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 int number = 0;
                 if (lane == 0) number = claim_first(ws);
                 const int t = first_task(q, a, uniform_i32(number));
-                if (t == kTaskNone && lane == 0) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
+                if (t == kTaskNone && lane == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxWaiting);
                 if (team.size == 1) task = t == kTaskNone ? -1 : t;
                 else if (lane < 2) st_relaxed(team.area + 1 + lane, (1ull << 32) | static_cast<unsigned>(lane == 0 ? t : flags));
             }
@@ -2135,7 +2233,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                     claimed = kTaskNone;
                 } else {
                     if (!asked) {
-                        if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxWaiting);
+                        if (threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxWaiting);
                         wait_memory();
                     }
                     task = acquire_task(team.id, previous_task, drop_settled, team.t_start);
@@ -2174,7 +2272,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         if (sampling && leader && !asked) {
             // the walk and the bonus token come next: one sweep or two, then the team is free
             want_claim = claims;
-            if (!claims && threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id], kMailboxSoon);
+            if (!claims && threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxSoon);
             asked = true;
         }
         if (threadIdx.x == 0) {
@@ -2210,7 +2308,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             g_loop.claimed = first_task(q, a, claim_first(ws));
             if (g_loop.claimed == kTaskNone) {
                 g_loop.claims = 0;
-                st_relaxed(&ws.mailbox[g_loop.team.id], kMailboxSoon);
+                st_relaxed(&ws.mailbox[g_loop.team.id * q.box_step], kMailboxSoon);
             }
         }
         // the tree's outcome is settled: walk and bonus token
@@ -2943,14 +3041,13 @@ static size_t carve(const mpv_problem* p, void* base, Workspace* ws) {
     double* at = static_cast<double*>(take(bn * 8));
     int32_t* qu = static_cast<int32_t*>(take(bn * 4));
     int32_t* qc = static_cast<int32_t*>(take(kCtlWords * 4));
-    int32_t* mb = static_cast<int32_t*>(take(kMaxTeams * 4));
+    int32_t* mb = static_cast<int32_t*>(take(kMailboxWords * 4));
     unsigned long long* kn = static_cast<unsigned long long*>(take(static_cast<size_t>(p->B) * 8));
     unsigned long long* ac = static_cast<unsigned long long*>(take(static_cast<size_t>(p->B) * 8));
     int32_t* de = static_cast<int32_t*>(take(static_cast<size_t>(p->B) * 4));
     int32_t* cu = static_cast<int32_t*>(take(static_cast<size_t>(p->B) * 4));
     unsigned long long* ex = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxGrid) * 2 * kExchWords * 8));
     unsigned long long* tt = static_cast<unsigned long long*>(take(static_cast<size_t>(kMaxTeams) * 2 * 8));
-    (void)take(kMaxTeams * 4);                        // (unused: the workspace keeps its size)
     LaunchBlock* la = static_cast<LaunchBlock*>(take(sizeof(LaunchBlock)));
     if (ws) { ws->exch = ex; ws->team_task = tt; ws->launch = la; }
     if (ws) { ws->At = At; ws->Ad = Ad; ws->cfin = cf; ws->aux = ax; ws->a0 = a0; ws->atest = at; ws->queue = qu; ws->qctl = qc; ws->mailbox = mb; ws->known = kn; ws->acc = ac; ws->decided = de; ws->cur = cu; }
@@ -2985,6 +3082,7 @@ static int compute_units() {
 // How a launch is shaped: G workgroups per team so that a member's part of a row fits on chip
 // (kMaxTeam at most: beyond that the rest of a part is re-read in every sweep), as many teams
 // as there can be tasks at once, three workgroups per compute unit at most.
+constexpr int kShortPart = 1024;                      // vectors of a row per member, see launch_shape
 struct Shape { int team_size, teams, part_vecs, same_xcd; };
 
 // Workgroups of a task kernel that one compute unit holds at a time, as the runtime computes it
@@ -3000,8 +3098,10 @@ static int resident_per_cu(K kernel) {
     return n;
 }
 
+// tasks: how many there can be at once;  teams_wanted: parts are made shorter than that for as long as there are so many
+// teams (0: not).
 template <class E>
-static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, int per_cu) {
+static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, int64_t teams_wanted, int per_cu) {
     Shape s;
     const int nvec = (p->V + E::VEC - 1) / E::VEC;
     const int slots = per_cu * compute_units() < kMaxGrid ? per_cu * compute_units() : kMaxGrid;      // workgroups that can be resident
@@ -3013,13 +3113,13 @@ static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, 
     while (g < kMaxTeam && static_cast<long long>(g) * (kPartCapacity + kTaskBlock / 2) < nvec) ++g;
     const int fewest = g;
     while (g < kMaxTeam && slots / (g + 1) >= p->B && static_cast<long long>(g) * 2048 < nvec) ++g;
+    while (teams_wanted > 0 && g < kMaxTeam && slots / (g + 1) >= teams_wanted && static_cast<long long>(g) * kShortPart < nvec) ++g;
     auto teams_of = [&](int size) {
-        int teams = slots / size;
-        if (teams > kMaxTeams) teams = kMaxTeams;
-        if (teams > tasks) teams = tasks;
-        if (teams < 1) teams = 1;
+        const int most = max(1, min(slots / size, kMaxTeams));
+        int teams = max(1, min(most, tasks));
         // workgroup i runs on chiplet i % 8: with a multiple of 8 teams every team can stay on one chiplet
-        return size > 1 && teams >= 8 ? teams - teams % 8 : teams;
+        if (size > 1 && most >= 8) teams = min((teams + 7) / 8 * 8, most - most % 8);
+        return teams;
     };
     // Tasks that do not depend on each other: the size whose rounds take the least time.  A task's own time is
     // a part that no team shortens (exchanges, scalar steps) and one that goes with a member's vectors; the two
@@ -3080,12 +3180,25 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     // although its tasks could be counted too (64 trees of 33 inner nodes, V = 151936, Traversal: 526 us, 410 with teams of
     // 6): probabilities further down a tree are quotients of differences, p - c q over what is left of p, and sums in
     // another order then move single ones by 1e-5 (against 64 bits both are equally far off, up to 5e-5 over 71 such batches).
+    const bool top_down = p->method != MPV_METHOD_TRAVERSAL;
+    // Only what is needed: a top-down walk has one task at a time per tree, and teams without a task only take issue slots
+    // and memory requests from the others (64 trees of V = 32000 in float32: 72.6 us with the 96 teams that tasks could be
+    // queued for, 56.8 with 64; 200 trees of V = 4096: 110 and 72).  Traversal can follow the branches of a tree at the same
+    // time, which pays for about two a tree, and up to 192 teams, beyond which they wait for the dispatcher (200 trees of
+    // V = 1500, 3 branches: 138 us with 200 teams, 149 with 256, 213 with 416, 273 with 512; 2 trees want the 16 more).
+    const int branches = p->B < 176 ? min(2 * p->B + 16, max(p->B, 192)) : max(p->B, 192);
+    const int at_once = !a.lazy ? tasks : min(tasks, top_down ? p->B : branches);
+    // Shorter parts pay as long as every tree (Traversal: four branches of it) still has a team: one tree of V = 32000, top
+    // down, 62 us with parts of 2000 vectors, 57 with 1333, 54 with 1000; 200 trees of V = 16000, Traversal, on fewer teams for it: 182 and 154.
+    const int64_t teams_wanted = !a.lazy ? 0 : top_down ? p->B : 4ll * p->B;
     const int64_t independent = a.estimate == 2 ? static_cast<int64_t>(p->B) * plan.n_internal : 0;
-    const Shape shape = launch_shape<E>(p, tasks, independent, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
+    const Shape shape = launch_shape<E>(p, at_once, independent, teams_wanted, per_cu[a.estimate == 2 ? 2 : (p->method == MPV_METHOD_TRAVERSAL ? 1 : 0)]);
     q.teams = shape.teams;
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
     q.same_xcd = shape.same_xcd;
+    q.box_step = 16;                                   // a cache line each, while there is room for it
+    while (q.teams * q.box_step > kMailboxWords) q.box_step /= 2;
     const bool split = p->method == MPV_METHOD_TRAVERSAL && a.lazy && p->B >= q.teams;
     if (a.per_tree) {
         // (the root of every tree is an inner node, N > 1: what is prequeued is the same for all of them)

@@ -372,6 +372,26 @@ def test_first_tasks_are_counted_off_once(method, B, V, dtype):
     assert np.all((got["bonus_token"] >= 0) & (got["bonus_token"] < V)) and np.all((got["accept_len"] >= 0) & (got["accept_len"] <= 2))
 
 
+@pytest.mark.parametrize("B,V,K,L1,L2", [(2, 1500, 4, 2, 3), (24, 1500, 8, 0, 5), (96, 1500, 4, 2, 3), (96, 16000, 8, 0, 5),
+                                         (200, 1500, 3, 1, 4), (300, 700, 8, 0, 3)])
+def test_branches_are_handed_to_idle_teams(B, V, K, L1, L2):
+    """Traversal with more teams than trees: the branches of a tree are followed at the same time, by teams that
+    wait for the dispatcher, take its place when it finds a task for itself, and are handed a task and the lock by
+    turns.  Every tree is decided (nothing may be left in a mailbox), and as the oracle decides."""
+    announce("idle teams", B, V, K, L1, L2)
+    cfg = workloads.Config("idle_teams", B=B, V=V, K=K, L1=L1, L2=L2, dtype="bf16", T=0.8,
+                           methods=[TV], draft_sigma=2.0, target_sigma=1.0, seed=78)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    got = run_library(inputs, cfg.T, TV, debug=False)
+    assert got["counters"][4] == 0
+    compare_with_oracle(TV, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, max(1, B // 24)), check_debug=False)
+    for _ in range(20):
+        again = run_library(inputs, cfg.T, TV, debug=False)
+        assert again["counters"][4] == 0
+        for key in ("accept_len", "path_nodes", "path_tokens", "bonus_token"):
+            assert np.array_equal(got[key], again[key])
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
