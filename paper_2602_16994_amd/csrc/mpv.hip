@@ -228,11 +228,8 @@ constexpr int kKindAcceptance = 100;                   // node_task_kernel insta
 // LDS of node_task_kernel that the functions it calls use as well (file scope, so that they address
 // it as LDS and not through generic pointers)
 struct TaskShared {
-    double scratch[2 * kTaskWaves];               // block reductions of the stand-alone helpers
     double part[kTaskWaves][4];                   // per-wave partial sums of a team reduction
     float partf[kTaskWaves][2];                   // per-wave reference exponents of the statistics
-    unsigned words[kMaxTeam * kExchWords];        // what the members exchanged last
-    int dead;
 };
 __shared__ TaskShared g_sh;
 // the launch parameters (copied from the workspace at the start of node_task_kernel)
@@ -529,9 +526,11 @@ __device__ __forceinline__ int claim_first(const Workspace& ws) {
 }
 
 // A tree's outputs are written (one lane): with the last one the launch is over, whatever is still
-// queued belongs to settled trees.
-__device__ __forceinline__ void tree_done(const Workspace& ws, const Args& a) {
-    if (atomicAdd(&ws.qctl[kCtlTreesDone], 1) + 1 == a.B) st_relaxed(&ws.qctl[2], 1);
+// queued belongs to settled trees (returns whether it was the last).
+__device__ __forceinline__ bool tree_done(const Workspace& ws, const Args& a) {
+    const bool last = atomicAdd(&ws.qctl[kCtlTreesDone], 1) + 1 == a.B;
+    if (last) st_relaxed(&ws.qctl[2], 1);
+    return last;
 }
 
 // What the holder of the dispatcher's lock keeps from round to round.
@@ -823,47 +822,14 @@ struct LoopState {
     int previous_task;    // last task taken from the mailbox
     int claims;           // leader: there may be first tasks left to count off
     int claimed;          // leader: the first task the team has counted off ahead of time (kTaskNone: none)
+    int finished;         // leader: the team has finished the last tree
+    int kept_task;        // the node task this workgroup finished last (-1: none), its statistics and final state
+    double kept_At, kept_Ad, kept_c;
     int want_claim;       // leader: the second wave is to count off a first task while the team samples
 };
 __shared__ LoopState g_loop;
 constexpr int kNothingHeard = -4;
 constexpr int kNotStarted = -5;           // own_task, every member: the team's first announcement is still to come
-
-// First wave only.  Lane w < kExchWords brings `mine`, its 32 bits of payload.  On return
-// g_sh.words[m * kExchWords + w] holds member m's word w (visible to the other waves after the
-// caller's next barrier) and g_sh.dead says whether a partner failed to answer.
-__device__ __forceinline__ void exchange_words(const Team& t, unsigned mine) {
-    const Workspace& ws = lds_launch().ws;
-    const Args& a = lds_launch().a;
-    const int lane = threadIdx.x;
-    if (t.size == 1) {
-        if (lane < kExchWords) g_sh.words[lane] = mine;
-        if (lane == 0) g_sh.dead = t.dead;
-        return;
-    }
-    unsigned long long* base = t.area + static_cast<size_t>(t.seq & 1u) * t.size * kExchWords;
-    const unsigned long long tag = static_cast<unsigned long long>(t.seq) << 32;
-    if (lane < kExchWords) st_relaxed(base + t.member * kExchWords + lane, tag | mine);
-    int dead = t.dead;
-    for (int w = lane; w < t.size * kExchWords; w += kWave) {
-        unsigned long long v = 0ull;
-        while (!dead) {
-            v = ld_relaxed(base + w);
-            if ((v >> 32) == (tag >> 32)) break;
-            if (wall_clock64() - t.t_start > kLaunchTimeoutTicks) { dead = 1; break; }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        g_sh.words[w] = dead ? 0u : static_cast<unsigned>(v);
-    }
-    const int any_dead = __ballot(dead != 0) != 0ull;
-    if (lane == 0) {
-        g_sh.dead = any_dead;
-        if (any_dead && !t.dead) {
-            atomicAdd(&a.counters[MPV_COUNTER_DEPENDENCY_TIMEOUT], 1u);
-            st_relaxed(&ws.qctl[2], 1);                // everybody leaves at the next occasion
-        }
-    }
-}
 
 // The lane number, for numbers derived from it that are not worth keeping: computed where they are used
 // instead of ahead of the task loop (there they took so many registers that others went to memory).
@@ -930,59 +896,9 @@ __device__ __forceinline__ double row_sum(double v) {
     return v + dpp_f64<0x128>(v);
 }
 
-// All lanes of the workgroup: one exchange of raw words (lane w < kExchWords of the first wave
-// brings `mine`); afterwards every lane may read g_sh.words.
-__device__ __forceinline__ void team_exchange(Team& t, unsigned mine) {
-    t.seq++;
-    __syncthreads();                                  // earlier readers of g_sh.words are done
-    if (threadIdx.x < kWave) exchange_words(t, mine);
-    __syncthreads();
-    t.dead = g_sh.dead;
-}
-
 __device__ __forceinline__ unsigned half_of(double v, int hi) {
     return static_cast<unsigned>(hi ? __double2hiint(v) : __double2loint(v));
 }
-__device__ __forceinline__ double double_at(const unsigned* words, int member, int pair) {
-    return __hiloint2double(static_cast<int>(words[member * kExchWords + 2 * pair + 1]),
-                            static_cast<int>(words[member * kExchWords + 2 * pair]));
-}
-
-// Sums of up to four per-lane values over every lane of every member of the team: wave sums, the
-// four waves and then the members added in a fixed order, so every lane of every member gets the
-// same bits.  Two barriers: wave partials -> (first wave: block total, exchange) -> everybody reads.
-template <int COUNT>
-__device__ __forceinline__ void team_sum(Team& t, double (&v)[COUNT]) {
-    static_assert(COUNT * 2 <= kExchWords && COUNT <= 4, "too many values for one exchange");
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    t.seq++;
-#pragma unroll
-    for (int i = 0; i < COUNT; ++i) {
-        const double w = wave_sum(v[i]);
-        if (lane == 0) g_sh.part[wave][i] = w;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        unsigned mine = 0u;
-        if (lane < 2 * COUNT) {
-            const int i = lane >> 1;
-            double b = g_sh.part[0][i];
-#pragma unroll
-            for (int w = 1; w < kTaskWaves; ++w) b += g_sh.part[w][i];
-            mine = half_of(b, lane & 1);
-        }
-        exchange_words(t, mine);
-    }
-    __syncthreads();
-    t.dead = g_sh.dead;
-#pragma unroll
-    for (int i = 0; i < COUNT; ++i) {
-        double s = 0.0;
-        for (int m = 0; m < t.size; ++m) s += double_at(g_sh.words, m, i);
-        v[i] = uniform_f64(s);
-    }
-}
-
 // The leader tells the others which task it has taken.  Every task announced this way contains at
 // least one exchange, so the leader cannot announce the next before everybody has read this one.
 __device__ __forceinline__ void team_announce(Team& t, int task, int flags) {
@@ -1045,74 +961,16 @@ __device__ __forceinline__ double int_power(double x, int k) {
 
 // task word flags (leader -> members)
 constexpr int kFlagIdle = 1;          // teams were idle after the last round of dispatching
+constexpr int kFlagStopShift = 8;     // a sampling task: the node where the walk stopped, plus one (0: not known)
 
 // (defined below) walk and bonus token of tree b, or one draw of a token-following walk, by the
 // whole team; returns the task that follows from it (-1: none; the same in every lane of every member)
 template <class E, int METHOD>
-__device__ __attribute__((noinline)) int sample_task(int b_in);
+__device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in);
 
 // (defined below) expected block efficiency of tree b from the per-node results, by the first wave
 template <int METHOD>
 __device__ __forceinline__ void estimate_wave(const TreeDesc& tree, const Workspace& ws, const Args& a, int b);
-
-// Softmax statistics of the task's two rows from the lanes' states (sum_v 2^(z_v k32 - mk) against
-// each lane's own reference mk): lanes are brought to their wave's largest reference, waves to the
-// workgroup's, members to the team's; one exchange, which also carries the node's starting weight
-// from the leader (*a0_lds, LDS, written before the call; what the other members pass is ignored).
-// Every lane of every member gets the same bits.
-__device__ __forceinline__ void team_stats(Team& t, const OnlineLse& lt, const OnlineLse& ld, const double* a0_lds,
-                                           double& At, double& Ad, double& a0) {
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    t.seq++;
-    const float Mt_w = wave_max(lt.mk), Md_w = wave_max(ld.mk);
-    const double st_w = wave_sum((lt.s > 0.f) ? static_cast<double>(lt.s * fast_exp2(lt.mk - Mt_w)) : 0.0);
-    const double sd_w = wave_sum((ld.s > 0.f) ? static_cast<double>(ld.s * fast_exp2(ld.mk - Md_w)) : 0.0);
-    if (lane == 0) {
-        g_sh.partf[wave][0] = Mt_w; g_sh.partf[wave][1] = Md_w;
-        g_sh.part[wave][0] = st_w; g_sh.part[wave][1] = sd_w;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        float Mt = g_sh.partf[0][0], Md = g_sh.partf[0][1];
-#pragma unroll
-        for (int w = 1; w < kTaskWaves; ++w) { Mt = fmaxf(Mt, g_sh.partf[w][0]); Md = fmaxf(Md, g_sh.partf[w][1]); }
-        double st = 0.0, sd = 0.0;
-#pragma unroll
-        for (int w = 0; w < kTaskWaves; ++w) {
-            st += g_sh.part[w][0] * static_cast<double>(fast_exp2(g_sh.partf[w][0] - Mt));
-            sd += g_sh.part[w][1] * static_cast<double>(fast_exp2(g_sh.partf[w][1] - Md));
-        }
-        const double a0_mine = *a0_lds;
-        unsigned mine = 0u;
-        switch (lane) {
-            case 0: mine = __float_as_uint(Mt); break;
-            case 1: mine = __float_as_uint(Md); break;
-            case 2: mine = half_of(st, 0); break;
-            case 3: mine = half_of(st, 1); break;
-            case 4: mine = half_of(sd, 0); break;
-            case 5: mine = half_of(sd, 1); break;
-            case 6: mine = half_of(a0_mine, 0); break;
-            case 7: mine = half_of(a0_mine, 1); break;
-            default: break;
-        }
-        exchange_words(t, mine);
-    }
-    __syncthreads();
-    t.dead = g_sh.dead;
-    float MT = OnlineLse::kFloor, MD = OnlineLse::kFloor;
-    for (int m = 0; m < t.size; ++m) {
-        MT = fmaxf(MT, __uint_as_float(g_sh.words[m * kExchWords]));
-        MD = fmaxf(MD, __uint_as_float(g_sh.words[m * kExchWords + 1]));
-    }
-    double ST = 0.0, SD = 0.0;
-    for (int m = 0; m < t.size; ++m) {
-        ST += double_at(g_sh.words, m, 1) * static_cast<double>(fast_exp2(__uint_as_float(g_sh.words[m * kExchWords]) - MT));
-        SD += double_at(g_sh.words, m, 2) * static_cast<double>(fast_exp2(__uint_as_float(g_sh.words[m * kExchWords + 1]) - MD));
-    }
-    At = uniform_f64(static_cast<double>(MT) + cold_log2(ST));
-    Ad = uniform_f64(static_cast<double>(MD) + cold_log2(SD));
-    a0 = uniform_f64(double_at(g_sh.words, 0, 3));
-}
 
 // One node task (or the resumed task of the node where the tree branches), by every member of the
 // team.  A function of its own, not inlined: what it keeps in registers (its part of the row pair)
@@ -1955,9 +1813,21 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     chain_settled = 0ull;
     chain_accepted = 0ull;
 
+    if (!paused && lane == 0) {                       // (a sampling task of this node by this team need not ask memory)
+        g_loop.kept_task = b * N + n;
+        g_loop.kept_At = rt.A; g_loop.kept_Ad = rd.A; g_loop.kept_c = c;
+    }
     // ---- what follows from this task: the leader's business (its first wave's)
     if (!leader) goto task_end;
     own_flags = uniform_i32(idle_now) != 0 ? kFlagIdle : 0;
+    if (METHOD == MPV_METHOD_SPECINFER && lazy && walk == 0 && likely < 0 && taken < 0) {
+        // The walk ends here or in the accepted leaf: the sampling follows at once, by this team, as a part of this task
+        // (nothing is counted, nothing of this node's has to reach memory first: every member has it).
+        own_task = B * N + b;
+        own_flags |= ((next_node >= 0 ? next_node : n) + 1) << kFlagStopShift;
+        team_announce(team, own_task, own_flags);
+        goto task_end;
+    }
     if (paused) {
         // nothing is settled yet; the first child's task is run next by this team
         own_task = b * N + child_of(0);
@@ -1969,7 +1839,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         }
         goto task_end;
     }
-    int push_sample_i = 0, settled_i = 0, resume_i = 0;
+    int push_sample_i = 0, settled_i = 0, resume_i = 0, accepted_at = -1;
     if (lane == 0) {
         st_shared_f64(&ws.At[bn], rt.A);
         st_shared_f64(&ws.Ad[bn], rd.A);
@@ -1993,11 +1863,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 settled_bits |= own;
                 if (static_cast<double>(un) < wa) accepted_bits |= own;
             }
+            if (accepted_bits) (void)atomicOr(&ws.acc[b], accepted_bits);
             wait_memory();                            // results written through before they are announced
-            if (accepted_bits) {
-                (void)atomicOr(&ws.acc[b], accepted_bits);
-                wait_memory();
-            }
             const unsigned long long known_before = atomicOr(&ws.known[b], settled_bits);
             const unsigned long long known = known_before | settled_bits;
             wait_memory();
@@ -2008,6 +1875,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 const unsigned long long open = ~(known & ~acc);          // not known to be rejected
                 const int first = __ffsll(static_cast<long long>(open)) - 1;   // the root's bit is always set
                 settled = ((known >> first) & 1ull) != 0ull;
+                accepted_at = first;
             } else {
                 const unsigned long long all = (N >= 64) ? ~0ull : ((1ull << N) - 1ull);
                 settled = known == all;
@@ -2045,6 +1913,11 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             if (lane == 0) append_task(tree, ws, 0, B * N + b);      // (the results were waited for above)
         } else {
             own_task = B * N + b;
+            // (only what is needed: the outcome is known here, the team need not look it up)
+            int stop = next_node >= 0 ? next_node : n;
+            if (METHOD == MPV_METHOD_TRAVERSAL)
+                stop = __ffsll(static_cast<long long>(__ballot(lane < N && field(nodes, kRank, 63u) == uniform_i32(accepted_at)))) - 1;
+            if (lazy && walk == 0) own_flags |= (stop + 1) << kFlagStopShift;
         }
     } else if (resume_i) {
         // Queued, not run at once: while there are trees that have not been begun, beginning them comes
@@ -2186,6 +2059,8 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 g_loop.claims = task != -1;
                 g_loop.claimed = kTaskNone;
                 g_loop.previous_task = -4;            // none yet
+                g_loop.finished = 0;
+                g_loop.kept_task = -1;
                 g_tree_of = -1;
             }
         }
@@ -2206,6 +2081,8 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         int task = kTaskExit, flags = 0;
         if (team.dead) {
             task = kTaskExit;
+        } else if (leader && uniform_i32(g_loop.finished) != 0) {
+            team_announce(team, task, 0);
         } else if (leader) {
             for (;;) {
                 if (own_task == kNotStarted) {
@@ -2312,9 +2189,19 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             }
         }
         // the tree's outcome is settled: walk and bonus token
-        const int next = sample_task<E, METHOD>(task - a.B * a.N);
-        if (wave == 0 && leader) {
-            if (next >= 0) {                          // a token-following walk goes on
+        const int next = sample_task<E, METHOD>(task - a.B * a.N, (flags >> kFlagStopShift) - 1);
+        if (next < 0 && leader) {
+            // the count of trees is waited for by the second wave, or, if there is nothing to go on with, by the
+            // first, which then knows whether the launch is over
+            const bool by_first = g_loop.claims == 0 && g_loop.claimed == kTaskNone;
+            if (threadIdx.x == (by_first ? 0 : kWave)) {
+                const bool last = tree_done(ws, a);
+                if (by_first && last) g_loop.finished = 1;
+                atomicAdd(&ws.qctl[1], 1);
+            }
+        }
+        if (next >= 0 && wave == 0 && leader) {
+            {                                         // a token-following walk goes on
                 Team team = uniform_struct(g_loop.team);          // (as sample_task left it)
                 team_announce(team, next, flags);
                 if (threadIdx.x == 0) {
@@ -2324,12 +2211,8 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 }
             }
             if (threadIdx.x == 0) {
-                if (next >= 0) {
-                    (void)atomicAdd(&ws.qctl[0], 1);
-                    wait_memory();                    // counted (and the walk's position written) first
-                } else {
-                    tree_done(ws, a);
-                }
+                (void)atomicAdd(&ws.qctl[0], 1);
+                wait_memory();                        // counted (and the walk's position written) first
                 atomicAdd(&ws.qctl[1], 1);
             }
         }
@@ -2501,320 +2384,350 @@ __device__ __forceinline__ void estimate_wave(const TreeDesc& tree, const Worksp
 
 // ------------------------------------------------------------------ bonus sample
 
-// r_v = (p_v - c q_v)_+ up to the common factor 2^-At_lo, for the VEC elements a lane
-// owns in wave tile `tile` (elements [tile * 64 * VEC, (tile + 1) * 64 * VEC); zero beyond V).
-// A vector load when the rows are 16-byte aligned, element loads otherwise.
-template <class E>
-struct ResidualTile {
-    static constexpr int PER_LANE = E::VEC;
-    static constexpr int TILE = kWave * E::VEC;
-    const typename E::T* zt;
-    const typename E::T* zd;
-    int V;
-    bool aligned, use_d;
-    float k32, nAt, nAd, rho;
-
-    __device__ __forceinline__ void load(int tile, int lane, float (&r)[PER_LANE]) const {
-        const int e0 = tile * TILE + lane * PER_LANE;
-        if (aligned && e0 + PER_LANE <= V) {
-            float t[PER_LANE], d[PER_LANE];
-            E::load_vec(zt + e0, t);
-            if (use_d) E::load_vec(zd + e0, d);
-#pragma unroll
-            for (int i = 0; i < PER_LANE; ++i) r[i] = term(t[i], use_d ? d[i] : 0.f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < PER_LANE; ++i) {
-                const int e = e0 + i;
-                r[i] = (e < V) ? term(E::load_one_global(zt + e), use_d ? E::load_one_global(zd + e) : 0.f) : 0.f;
-            }
-        }
-    }
-    __device__ __forceinline__ float term(float t, float d) const {
-        const float et = fast_exp2(fmaf(t, k32, nAt));
-        if (!use_d) return et;
-        const float ed = fast_exp2(fmaf(d, k32, nAd));
-        return fmaxf(fmaf(-rho, ed, et), 0.f);
-    }
-};
-
-
-// tile_sum: kMaxTiles floats of LDS.  Everything it reads from the workspace was written by node
-// tasks of this launch (see st_shared_f64) before the task that started this one was announced.
-// The vocabulary is split among the members in runs of whole wave tiles, in member order; each
-// member adds up the masses of its tiles, one exchange gives everybody every member's total, and
-// the member whose run contains u * R finds the token.
+// The vocabulary is split among the members in runs of whole wave tiles (64 vectors of 16 bytes, counted from the aligned
+// address at or before the row's start, so that rows of any offset are read with vector loads), in member order; tile i of
+// a member's run belongs to wave i % 4.  Each member adds up the masses r_v = (p_v - c q_v)_+ of its tiles (up to the common
+// factor 2^-At_lo), one exchange gives everybody every member's total, and the member whose run contains u * R finds the token.
+// Everything it reads from the workspace was written by node tasks of this launch (see st_shared_f64) before the task
+// that started this one was announced.
+//
+// Latency only (a few microseconds of every tree, or of every step of a token-following walk): the rows are asked for at once
+// and stay in registers (kKeep tiles per wave and row; longer runs are read again), so that a leaf's statistics, the masses
+// and the search for the token share one read; whoever started the task says where the walk stopped (and the team that has just
+// finished that node has its state); the path is recorded by the third wave at the end, and the second adds the tiles up while
+// the first exchanges.  64 trees, V = 128256, an inner node: 7.5 us (12.3 with the rows read up to three times and the walk and
+// the scan in front).  (Whole and partial vectors told apart per lane instead of per tile: half the code, but 36 registers in
+// scratch memory and 3 % slower calls.)
+//
+// stop_in: the node where the walk stopped, -1: not known here (it is worked out from the tests' outcomes).
 template <class E, int METHOD>
-__device__ __attribute__((noinline)) int sample_task(int b_in) {
+__device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
     using T = typename E::T;
+    constexpr int NW = kTaskWaves, VEC = E::VEC, TILE = kWave * VEC, kKeep = 13;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
     const TreeDesc& tree = g_tree;
-    const int b = uniform_i32(b_in);
+    const int b = uniform_i32(b_in), known_stop = uniform_i32(stop_in), walk = uniform_i32(a.walk);
+    const int lane = threadIdx.x & (kWave - 1), wave = uniform_i32(static_cast<int>(threadIdx.x) / kWave);
     float* const tile_sum = reinterpret_cast<float*>(g_rows);
-    Team team = uniform_struct(g_loop.team);           // every lane its copy; they stay alike
-    struct WriteBack {                                 // (after the function's last barrier: nobody reads the old one any more)
-        Team& t;
-        __device__ ~WriteBack() { if (threadIdx.x == 0) g_loop.team = t; }
-    } write_back{team};
-    constexpr int NW = kTaskWaves;
-    constexpr int PER_LANE = ResidualTile<E>::PER_LANE;
-    constexpr int TILE = ResidualTile<E>::TILE;
-    __shared__ int sh_tile;
-    __shared__ double sh_before, sh_local_total;
-
-    __shared__ int sh_stop, sh_next;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    Team team = uniform_struct(g_loop.team);           // every wave its copy; the first wave's counts exchanges
     const bool leader = team.member == 0;
-    const bool lead = leader && threadIdx.x == 0;
-    if (wave == 0) {
-        // where the token is drawn: the node the rule stops in, or the node a token-following
-        // walk has reached
-        const int stop = a.walk ? ld_relaxed(&ws.cur[b]) : walk_wave<METHOD>(tree, ws, a, b, leader);
-        if (lane == 0) { sh_stop = stop; sh_next = -1; }
-    }
-    __syncthreads();
-    const int n = __builtin_amdgcn_readfirstlane(sh_stop);
-    const size_t bn = static_cast<size_t>(b) * a.N + n;
-    const T* zt = static_cast<const T*>(a.zt) + bn * a.V;
-    const T* zd = static_cast<const T*>(a.zd) + bn * a.V;
-    const int V = a.V;
-    const int ntiles = (V + TILE - 1) / TILE;
-    // this member's run of tiles
-    const int per = (ntiles + team.size - 1) / team.size;
-    const int t_lo = min(team.member * per, ntiles), t_hi = min(t_lo + per, ntiles);
-    const int my_tiles = t_hi - t_lo;
+    __shared__ double sh_At, sh_before, sh_target, sh_total;
+    __shared__ int sh_owner, sh_tile, sh_tok, sh_next;
 
-    double At, Ad = 0.0, c = 0.0;
-    if (tree.nchild[n] == 0 || a.walk == 1) {
-        // a leaf (its target row has not been touched yet) or an NSS draw: from p itself
-        RowStatsF<E> f;
-        f.t.init(); f.k32 = a.k32;
-        const int e_lo = t_lo * TILE, e_hi = min(V, t_hi * TILE);
-        if (e_hi > e_lo) sweep_row<E, kTaskBlock, 2 * kTaskUnroll>(zt + e_lo, e_hi - e_lo, f);
-        OnlineLse none; none.init();
-        double unused_d, unused_a0;
-        __shared__ double sh_no_weight;
-        if (threadIdx.x == 0) sh_no_weight = 0.0;
-        team_stats(team, f.t, none, &sh_no_weight, At, unused_d, unused_a0);
-        if (lead) ws.At[bn] = At;
-    } else {
+    // where the token is drawn: the node the rule stops in, or the node a token-following walk has reached
+    const bool told = walk == 0 && known_stop >= 0;
+    int n = known_stop;
+    if (walk) n = ld_relaxed(&ws.cur[b]);
+    else if (!told) n = walk_wave<METHOD>(tree, ws, a, b, leader && wave == 0);
+    n = uniform_i32(n);
+    const size_t bn = static_cast<size_t>(b) * a.N + n;
+    const int V = uniform_i32(a.V);
+    const T* const zt = uniform_ptr(static_cast<const T*>(a.zt)) + bn * V;
+    const T* const zd = uniform_ptr(static_cast<const T*>(a.zd)) + bn * V;
+    const float k32 = uniform_f32(a.k32);
+    // from p itself: a leaf (its target row has not been touched yet) or an NSS draw
+    const bool from_p = uniform_i32(tree.nchild[n]) == 0 || walk == 1;
+    double At = 0.0, Ad = 0.0, c = 0.0;
+    if (!from_p && uniform_i32(g_loop.kept_task) == b * a.N + n) {
+        At = g_loop.kept_At; Ad = g_loop.kept_Ad; c = g_loop.kept_c;
+    } else if (!from_p) {
         At = ld_shared_f64(&ws.At[bn]);
         Ad = ld_shared_f64(&ws.Ad[bn]);
         c = ld_shared_f64(&ws.cfin[bn]);
     }
+    const float u_draw = wave == 0 ? (walk ? as_global(a.draw_uniforms)[bn] : as_global(a.uniforms)[static_cast<size_t>(b) * a.N]) : 0.f;
+    const int k = walk ? uniform_i32(tree.nchild[n]) : 0;
+    int child_token = -1, child = 0;                   // lane j < k: child j
+    if (wave == 0 && lane < k) {
+        child = tree.child_list[tree.child_off[n] + lane];
+        child_token = as_global(a.tokens)[static_cast<size_t>(b) * a.N + child];
+    }
 
-    ResidualTile<E> rt_;
-    rt_.zt = zt; rt_.zd = zd; rt_.V = V;
-    rt_.aligned = ((reinterpret_cast<uintptr_t>(zt) & 15u) == 0);
-    rt_.use_d = (c > 0.0);
-    rt_.k32 = a.k32;
-    if (rt_.use_d) {
+    const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(zt) & 15u) / sizeof(T));      // the same for both rows
+    const int ntiles = (mis + V + TILE - 1) / TILE;
+    const int per = (ntiles + team.size - 1) / team.size;
+    const int t_lo = min(team.member * per, ntiles), t_hi = min(t_lo + per, ntiles);
+    const int my_tiles = t_hi - t_lo;
+    const int cnt = (my_tiles - wave + NW - 1) / NW;   // this wave's tiles: t_lo + wave + NW i
+    uint4 qt[kKeep], qd[kKeep];
+    // 16 bytes of a row; elements before its start and after its end count as masked ones
+    auto load_vec = [&](const T* row, int tile) __attribute__((always_inline)) -> uint4 {
+        const int first = tile * TILE - mis;
+        if (first >= 0 && first + TILE <= V) return load_raw(row + first + lane * VEC);
+        struct alignas(16) { T x[VEC]; } part;
+        const uint4 masked = NegInfVec<E>::v();
+        __builtin_memcpy(&part, &masked, 16);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const int e = first + lane * VEC + i;
+            if (e >= 0 && e < V) part.x[i] = as_global(row)[e];
+        }
+        return __builtin_bit_cast(uint4, part);
+    };
+    auto load_tiles = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j) {
+            if (i0 + j >= cnt) continue;                // (the same in every lane)
+            qt[j] = load_vec(zt, t_lo + wave + NW * (i0 + j));
+            if (!from_p) qd[j] = load_vec(zd, t_lo + wave + NW * (i0 + j));
+        }
+    };
+    load_tiles(0);
+
+    if (from_p) {
+        // ---- the row's statistics first
+        WaveLse<> s;
+        s.init();
+        for (int i0 = 0; i0 < cnt; i0 += kKeep) {
+            if (i0 > 0) load_tiles(i0);
+#pragma unroll
+            for (int j = 0; j < kKeep; ++j) {
+                if (i0 + j >= cnt) continue;
+                float x[VEC];
+                E::unpack(qt[j], x);
+                s.vec(x, k32);
+            }
+        }
+        const double sum = wave_sum(static_cast<double>(s.s));
+        if (lane == 0) {                               // (the second row of collect_stats is not used)
+            g_sh.partf[wave][0] = s.mk; g_sh.partf[wave][1] = 0.f;
+            g_sh.part[wave][0] = sum; g_sh.part[wave][1] = 1.0;
+        }
+        task_barrier();
+        if (wave == 0) {
+            double none = 0.0, unused;
+            collect_stats<false>(team, none, At, unused);
+            if (lane == 0) sh_At = At;
+            if (leader && lane == 0) ws.At[bn] = At;
+        }
+        task_barrier();
+        At = sh_At;
+        if (cnt > kKeep) load_tiles(0);
+    }
+
+    float nAt = -static_cast<float>(At), nAd = 0.f, rho = 0.f;
+    const bool use_d = all_alike(c > 0.0);
+    if (use_d) {
         const ResidualConsts rc = residual_consts(At, Ad, c);
-        rt_.nAt = rc.nAt; rt_.nAd = rc.nAd; rt_.rho = rc.rho;
-    } else {
-        rt_.nAt = -static_cast<float>(At); rt_.nAd = 0.f; rt_.rho = 0.f;
+        nAt = rc.nAt; nAd = rc.nAd; rho = rc.rho;
     }
-
-    // ---- pass 1: mass of every wave tile of this member's run, in vocabulary order
-    //      (tile_sum[i] belongs to tile t_lo + i)
-    {
-        // Whole, aligned tiles are taken U at a time per wave with all their loads issued
-        // before the first use.
-        int t_next = t_lo + wave;
-        constexpr int U = 8;
-        const int whole = min(rt_.aligned ? V / TILE : 0, t_hi);
-        for (; t_next + (U - 1) * NW < whole; t_next += U * NW) {
-            uint4 qt[U], qd[U];
+    nAt = uniform_f32(nAt); nAd = uniform_f32(nAd); rho = uniform_f32(rho);
+    // the masses of a lane's vector
+    auto masses = [&](const uint4& vt, const uint4& vd, float (&r)[VEC]) __attribute__((always_inline)) {
+        float x[VEC];
+        E::unpack(vt, x);
+        if (use_d) {
+            float y[VEC];
+            E::unpack(vd, y);
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int e0 = (t_next + j * NW) * TILE + lane * PER_LANE;
-                qt[j] = load_raw(zt + e0);
-                if (rt_.use_d) qd[j] = load_raw(zd + e0);
-            }
-            float s[U];
+            for (int i = 0; i < VEC; ++i) r[i] = fmaxf(fmaf(-rho, fast_exp2(fmaf(y[i], k32, nAd)), fast_exp2(fmaf(x[i], k32, nAt))), 0.f);
+        } else {
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                float tv[PER_LANE], dv[PER_LANE];
-                E::unpack(qt[j], tv);
-                if (rt_.use_d) E::unpack(qd[j], dv);
-                float ls = 0.f;                       // same order of additions as pass 2
-#pragma unroll
-                for (int i = 0; i < PER_LANE; ++i) ls += rt_.term(tv[i], rt_.use_d ? dv[i] : 0.f);
-                s[j] = ls;
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) s[j] = wave_sum_f32(s[j]);
-            if (lane == 0) {
-#pragma unroll
-                for (int j = 0; j < U; ++j) tile_sum[t_next + j * NW - t_lo] = s[j];
-            }
+            for (int i = 0; i < VEC; ++i) r[i] = fast_exp2(fmaf(x[i], k32, nAt));
         }
-        for (int t = t_next; t < t_hi; t += NW) {
-            float r[PER_LANE];
-            rt_.load(t, lane, r);
-            float ls = 0.f;
+    };
+    auto lane_sum = [&](const float (&r)[VEC]) __attribute__((always_inline)) -> float {
+        float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < PER_LANE; ++i) ls += r[i];
-            const float w = wave_sum_f32(ls);
-            if (lane == 0) tile_sum[t - t_lo] = w;
+        for (int i = 0; i < VEC; ++i) s += r[i];
+        return s;
+    };
+
+    // ---- the mass of every tile of this member's run, in vocabulary order
+    double wave_total = 0.0;
+    for (int i0 = 0; i0 < cnt; i0 += kKeep) {
+        if (i0 > 0) load_tiles(i0);
+        float s[kKeep];
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j) {
+            s[j] = 0.f;
+            if (i0 + j >= cnt) continue;
+            float r[VEC];
+            masses(qt[j], qd[j], r);
+            s[j] = lane_sum(r);
+        }
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j) s[j] = wave_sum_f32(s[j]);              // (side by side)
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j) {
+            if (lane == 0 && i0 + j < cnt) tile_sum[wave + NW * (i0 + j)] = s[j];
+            wave_total += static_cast<double>(s[j]);
         }
     }
-    __syncthreads();
+    if (lane == 0) g_sh.part[wave][0] = wave_total;
+    if (wave == 0) wait_memory();                      // (the node tasks' outcomes, for the path)
+    task_barrier();
 
-    // ---- this member's total (wave 0; each lane owns a run of the member's tiles), then everybody's
+    // ---- everybody's totals (first wave), and meanwhile where this member's tiles lie (second wave: each lane a run of them)
     const int per_lane_tiles = (my_tiles + kWave - 1) / kWave;
     const int l0 = min(lane * per_lane_tiles, my_tiles), l1 = min(l0 + per_lane_tiles, my_tiles);
     double run = 0.0, incl = 0.0;
     if (wave == 0) {
+        const int m = lane & 15;
+        team.seq++;
+        double v = g_sh.part[lane & 3][0];
+        v += dpp_f64<0xB1>(v);
+        v += dpp_f64<0x4E>(v);
+        unsigned got[2] = {half_of(v, 0), half_of(v, 1)};
+        if (team.size > 1) {
+            const int at[2] = {0, 1};
+            note_dead(team, swap_words(team, half_of(v, lane & 1), 2, lane < team.size, at, got));
+        }
+        const double mass = lane < team.size && !team.dead ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) : 0.0;
+        double upto = mass;                            // sums along the row of lanes: member m and those before it
+        upto += dpp_f64<0x111>(upto);
+        upto += dpp_f64<0x112>(upto);
+        upto += dpp_f64<0x114>(upto);
+        upto += dpp_f64<0x118>(upto);
+        const double total = lane_f64(upto, team.size - 1), before = dpp_f64<0x111>(upto);
+        const double target = static_cast<double>(u_draw) * total;
+        // the member whose run contains the target: the first whose running total exceeds it and that has mass;
+        // rounding only: the last one that has mass
+        const unsigned long long hit = __ballot(m == lane && mass > 0.0 && upto > target), any = __ballot(m == lane && mass > 0.0);
+        const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
+        if (lane == 0) {
+            sh_owner = owner;
+            sh_target = target - lane_f64(before, owner);
+            sh_total = total;
+        }
+    } else if (wave == 1) {
         for (int t = l0; t < l1; ++t) run += tile_sum[t];
         incl = wave_inclusive_scan(run);
-        if (lane == kWave - 1) sh_local_total = incl;
     }
-    __syncthreads();
-    const double local_total = sh_local_total;
-    {
-        unsigned mine = 0u;
-        if (threadIdx.x == 0) mine = half_of(local_total, 0);
-        if (threadIdx.x == 1) mine = half_of(local_total, 1);
-        team_exchange(team, mine);
-    }
-    double total = 0.0, before = 0.0;
-    for (int m = 0; m < team.size; ++m) {
-        if (m == team.member) before = total;
-        total += double_at(g_sh.words, m, 0);
-    }
-    const float u_draw = a.walk ? as_global(a.draw_uniforms)[bn] : as_global(a.uniforms)[static_cast<size_t>(b) * a.N];
-    const double target = static_cast<double>(u_draw) * total;
-    // the member whose run contains the target: the first whose running total exceeds it and that
-    // has mass; rounding only: the last one that has mass
-    int owner = -1, last_mass = 0;
-    {
-        double acc = 0.0;
-        for (int m = 0; m < team.size; ++m) {
-            const double tm = double_at(g_sh.words, m, 0);
-            if (tm > 0.0) last_mass = m;
-            if (owner < 0 && tm > 0.0 && acc + tm > target) owner = m;
-            acc += tm;
-        }
-        if (owner < 0) owner = last_mass;
-    }
+    task_barrier();
+    const int owner = uniform_i32(sh_owner);
     const bool mine_it = owner == team.member;
-    const double local_target = target - before;
-
-    // ---- the owner locates the tile that contains the target (wave 0) ...
-    if (mine_it && wave == 0) {
-        const unsigned long long hit = __ballot(incl > local_target && run > 0.0);
-        int lane_owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
-        if (lane_owner < 0) {           // rounding only: last lane that has mass
-            const unsigned long long any = __ballot(run > 0.0);
-            lane_owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
-        }
-        if (lane == lane_owner) {
-            double acc = incl - run;
-            int found = -1, last = l0;
-            double bef = acc;
-            for (int t = l0; t < l1; ++t) {
-                const double ts = tile_sum[t];
-                if (ts > 0.0) last = t;
-                if (found < 0 && acc + ts > local_target && ts > 0.0) { found = t; bef = acc; }
-                acc += ts;
+    if (mine_it) {
+        const double local_target = sh_target;
+        // ---- the tile that contains the target ...
+        if (wave == 1) {
+            const unsigned long long hit = __ballot(incl > local_target && run > 0.0);
+            int lane_owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
+            if (lane_owner < 0) {           // rounding only: last lane that has mass
+                const unsigned long long any = __ballot(run > 0.0);
+                lane_owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
             }
-            if (found < 0) {       // rounding only: last tile of the run that has mass
-                found = last;
-                bef = incl - run;
-                for (int t = l0; t < last; ++t) bef += tile_sum[t];
+            if (lane == lane_owner) {
+                double acc = incl - run;
+                int found = -1, last = l0;
+                double bef = acc;
+                for (int t = l0; t < l1; ++t) {
+                    const double ts = tile_sum[t];
+                    if (ts > 0.0) last = t;
+                    if (found < 0 && acc + ts > local_target && ts > 0.0) { found = t; bef = acc; }
+                    acc += ts;
+                }
+                if (found < 0) {       // rounding only: last tile of the run that has mass
+                    found = last;
+                    bef = incl - run;
+                    for (int t = l0; t < last; ++t) bef += tile_sum[t];
+                }
+                sh_tile = found;
+                sh_before = bef;
             }
-            sh_tile = t_lo + found;
-            sh_before = bef;
         }
-    }
-    __syncthreads();
-
-    // ---- ... and the token inside that tile (wave 0)
-    int tok = 0;
-    if (mine_it && wave == 0) {
-        const int t = sh_tile;
-        const double rem = local_target - sh_before;       // mass to cover inside the tile
-        float r[PER_LANE];
-        rt_.load(t, lane, r);
-        float ls = 0.f;
+        task_barrier();
+        // ---- ... and the token inside that tile, by the wave that has it
+        const int tile = uniform_i32(sh_tile);
+        if (wave == tile % NW) {
+            const double rem = local_target - sh_before;       // mass to cover inside the tile
+            const int slot = tile / NW;
+            uint4 vt = qt[0], vd = qd[0];
+            if (cnt > kKeep) {
+                vt = load_vec(zt, t_lo + tile);
+                if (!from_p) vd = load_vec(zd, t_lo + tile);
+            } else {
 #pragma unroll
-        for (int i = 0; i < PER_LANE; ++i) ls += r[i];
-        const double lsd = static_cast<double>(ls);
-        const double incl2 = wave_inclusive_scan(lsd);
-        const unsigned long long hit = __ballot(incl2 > rem && ls > 0.f);
-        int lane_owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
-        if (lane_owner < 0) {
-            const unsigned long long any = __ballot(ls > 0.f);
-            lane_owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
-        }
-        if (lane == lane_owner) {
-            double acc = incl2 - lsd;
-            int found = -1, last = 0;
-            double lo = acc, hi = acc;
-            for (int i = 0; i < PER_LANE; ++i) {
-                const double ri = static_cast<double>(r[i]);
-                if (ri > 0.0) last = i;
-                if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
-                acc += ri;
+                for (int j = 1; j < kKeep; ++j)
+                    if (slot == j) { vt = qt[j]; vd = qd[j]; }
             }
-            if (found < 0) { found = last; lo = rem; hi = rem; }
-            int tk = t * TILE + lane * PER_LANE + found;
-            if (tk >= V) tk = V - 1;
-            as_global(a.bonus)[b] = tk;
-            sh_tile = tk;                             // (the tile number is no longer needed)
-            const double gap = fmin(fabs(rem - lo), fabs(hi - rem));
-            if (gap < 1e-6 * total) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
+            float r[VEC];
+            masses(vt, vd, r);
+            const float ls = lane_sum(r);
+            const double lsd = static_cast<double>(ls);
+            const double incl2 = wave_inclusive_scan(lsd);
+            const unsigned long long hit = __ballot(incl2 > rem && ls > 0.f);
+            int lane_owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
+            if (lane_owner < 0) {
+                const unsigned long long any = __ballot(ls > 0.f);
+                lane_owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
+            }
+            if (lane == lane_owner) {
+                double acc = incl2 - lsd;
+                int found = -1, last = 0;
+                double lo = acc, hi = acc;
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    const double ri = static_cast<double>(r[i]);
+                    if (ri > 0.0) last = i;
+                    if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
+                    acc += ri;
+                }
+                if (found < 0) { found = last; lo = rem; hi = rem; }
+                int tk = (t_lo + tile) * TILE - mis + lane * VEC + found;
+                if (tk >= V) tk = V - 1;
+                if (tk < 0) tk = 0;
+                as_global(a.bonus)[b] = tk;
+                sh_tok = tk;
+                const double gap = fmin(fabs(rem - lo), fabs(hi - rem));
+                if (gap < 1e-6 * sh_total) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
+            }
         }
     }
-    if (a.walk) {
+    if (told && leader && wave == 2) (void)walk_wave<METHOD>(tree, ws, a, b, true);       // the path
+    int next = -1;
+    if (walk) {
         // Sec. 3.2: if the drawn token is a child's token the walk moves to that child (the
         // first such child in list order), otherwise it ends here.  Everybody needs the token.
-        __syncthreads();
-        {
-            unsigned mine = 0u;
-            if (threadIdx.x == 0 && mine_it) mine = static_cast<unsigned>(sh_tile);
-            team_exchange(team, mine);
-        }
-        tok = static_cast<int>(g_sh.words[owner * kExchWords]);
+        task_barrier();
         if (wave == 0) {
-            const int k = tree.nchild[n];
-            bool same = false;
-            if (lane < k) same = as_global(a.tokens)[static_cast<size_t>(b) * a.N + tree.child_list[tree.child_off[n] + lane]] == tok;
-            const unsigned long long m = __ballot(same);
+            unsigned got[1] = {static_cast<unsigned>(sh_tok)};
+            if (team.size > 1) {
+                team.seq++;
+                const int at[1] = {0};
+                note_dead(team, swap_words(team, got[0], 1, lane == owner, at, got));
+            }
+            const int tok = __builtin_amdgcn_readlane(static_cast<int>(got[0]), owner);
+            const unsigned long long m = __ballot(lane < k && child_token == tok);
+            int to_task = -1;
             if (m) {
-                const int to = tree.child_list[tree.child_off[n] + __ffsll(static_cast<long long>(m)) - 1];
-                if (lane == 0) {
-                    if (leader) st_relaxed(&ws.cur[b], to);
-                    // Naive and SpecTr test children of an inner node before they draw there; NSS and leaves draw at once
-                    sh_next = (a.walk >= 2 && tree.nchild[to] > 0) ? b * a.N + to : a.B * a.N + b;
-                }
+                const int to = __builtin_amdgcn_readlane(child, __ffsll(static_cast<long long>(m)) - 1);
+                if (leader && lane == 0) st_relaxed(&ws.cur[b], to);
+                // Naive and SpecTr test children of an inner node before they draw there; NSS and leaves draw at once
+                to_task = (walk >= 2 && tree.nchild[to] > 0) ? b * a.N + to : a.B * a.N + b;
             } else if (leader) {
                 if (lane == 0) write_path(tree, a, b, n);
                 if (a.dbg_accept && lane < a.N)
                     as_global(a.dbg_accept)[static_cast<size_t>(b) * a.N + lane] =
                         lane == 0 ? 1.f : static_cast<float>(ld_shared_f64(&ws.atest[static_cast<size_t>(b) * a.N + lane]));
             }
+            if (lane == 0) sh_next = to_task;
         }
+        task_barrier();
+        next = uniform_i32(sh_next);
     }
 
     // ---- optional: the normalised distribution itself
     if (a.dbg_resid) {
-        const double inv = 1.0 / total;
+        const double inv = 1.0 / sh_total;
         float* out = a.dbg_resid + static_cast<size_t>(b) * V;
-        for (int t = t_lo + wave; t < t_hi; t += NW) {
-            float r[PER_LANE];
-            rt_.load(t, lane, r);
+        for (int i = 0; i < cnt; ++i) {
+            const int tile = t_lo + wave + NW * i;
+            const uint4 vt = load_vec(zt, tile);
+            uint4 vd = vt;
+            if (!from_p) vd = load_vec(zd, tile);
+            float r[VEC];
+            masses(vt, vd, r);
 #pragma unroll
-            for (int i = 0; i < PER_LANE; ++i) {
-                const int e = t * TILE + lane * PER_LANE + i;
-                if (e < V) out[e] = static_cast<float>(static_cast<double>(r[i]) * inv);
+            for (int v = 0; v < VEC; ++v) {
+                const int e = tile * TILE - mis + lane * VEC + v;
+                if (e >= 0 && e < V) out[e] = static_cast<float>(static_cast<double>(r[v]) * inv);
             }
         }
     }
-    __syncthreads();
-    return sh_next;
+    if (threadIdx.x == 0) g_loop.team = team;          // (the task loop reads it after its barrier)
+    return next;
 }
 
 // ------------------------------------------------------------------ stand-alone row statistics

@@ -392,6 +392,21 @@ def test_branches_are_handed_to_idle_teams(B, V, K, L1, L2):
             assert np.array_equal(got[key], again[key])
 
 
+@pytest.mark.parametrize("V,dtype,B", [(5, "bf16", 3), (63, "f32", 3), (515, "bf16", 3), (1025, "f32", 700), (33001, "bf16", 3),
+                                       (300001, "f32", 2), (524293, "bf16", 2)])
+@pytest.mark.parametrize("method", ALL_METHODS)
+def test_the_draw_reads_rows_of_any_offset(method, V, dtype, B):
+    """The drawn token where rows start at any element of a 16-byte vector, are shorter than one, end inside one, fill a
+    part of a tile, and where a wave has more tiles than it keeps in registers."""
+    announce("draw", METHOD_NAME[method], B, V, dtype)
+    cfg = workloads.Config("draw", B=B, V=V, K=2, L1=0, L2=2, dtype=dtype, T=1.0,
+                           methods=[method], draft_sigma=1.5, target_sigma=1.0, seed=79)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    got = run_library(inputs, cfg.T, method, debug=False)
+    assert got["counters"][4] == 0
+    compare_with_oracle(method, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, max(1, B // 30)), check_debug=False)
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
