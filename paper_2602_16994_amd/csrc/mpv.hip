@@ -1,7 +1,7 @@
 // mpv.hip -- kernels and C ABI of the tree-verification library (gfx950 only).
 //
 // Path of one mpv_verify call (all on the caller's stream):
-//   init_kernel            zero counters, default the per-node results, queue the first tasks
+//   init_kernel            zero counters, default the per-node results, clear queue and team words
 //   node_task_kernel       persistent workgroups of 256 lanes, three per compute unit, grouped in
 //                          TEAMS of G workgroups that take tasks from a queue until none are left.
 //                          A team splits every logit row by vocabulary range: each member keeps its
@@ -788,7 +788,7 @@ __device__ __forceinline__ double ld_shared_f64(const double* p) {
 // ------------------------------------------------------------------ teams
 //
 // The G members of a team run the same task in lockstep on different vocabulary ranges: they
-// execute the same scalar code on the same numbers (exchanged sums are added in member order
+// execute the same scalar code on the same numbers (exchanged sums are added in the same order
 // by every member, so they are bitwise equal everywhere) and therefore take the same branches;
 // side effects (results, queue, counters) are the leader's (member 0).  What the leader alone
 // can know (the task, whether teams are idle, a starting weight) travels with the task word or
@@ -2994,7 +2994,7 @@ static int compute_units() {
 
 // How a launch is shaped: G workgroups per team so that a member's part of a row fits on chip
 // (kMaxTeam at most: beyond that the rest of a part is re-read in every sweep), as many teams
-// as there can be tasks at once, three workgroups per compute unit at most.
+// as there are tasks at once (see launch_all), three workgroups per compute unit at most.
 constexpr int kShortPart = 1024;                      // vectors of a row per member, see launch_shape
 struct Shape { int team_size, teams, part_vecs, same_xcd; };
 
@@ -3114,7 +3114,7 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     while (q.teams * q.box_step > kMailboxWords) q.box_step /= 2;
     const bool split = p->method == MPV_METHOD_TRAVERSAL && a.lazy && p->B >= q.teams;
     if (a.per_tree) {
-        // (the root of every tree is an inner node, N > 1: what is prequeued is the same for all of them)
+        // (the root of every tree is an inner node, N > 1: the first tasks are the same for all of them)
         const int per_chunk = kShapeChunkBytes / p->N;
         for (int b0 = 0; b0 < p->B; b0 += per_chunk) {
             const int trees = min(per_chunk, p->B - b0);
