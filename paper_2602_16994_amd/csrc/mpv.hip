@@ -40,6 +40,7 @@
 
 #include "mpv.h"
 #include "mpv_device.h"
+#include "mpv_exchange.h"
 #include "mpv_nucleus.h"
 
 namespace mpv {
@@ -796,8 +797,8 @@ __device__ __forceinline__ double ld_shared_f64(const double* p) {
 // An exchange: every member writes up to kExchWords words into its own 64-byte line of the
 // team's area, each word tagged with the number of the exchange, and polls the other lines until
 // every word carries that number.  Two areas alternate: a member can be at most one exchange
-// ahead of the slowest (it needs everybody's words of exchange s to finish s), so the words
-// of exchange s are never overwritten before everybody has read them.
+// ahead of the slowest (it needs everybody's words of exchange s to finish s, see exchange_waits),
+// so the words of exchange s are never overwritten before everybody has read them.
 
 struct Team {
     int id, member, size;
@@ -843,17 +844,17 @@ __device__ __forceinline__ int lane_here() {
 // the members' numbers meet in reductions along a row of 16 lanes, and a member's own numbers do not travel.
 // (Through LDS, one member after the other, as the other tasks' still do, the statistics of a team of 8 took
 // 1.15 us from the last word's arrival to the logarithms, now 0.3.)
-static_assert(kMaxTeam <= 16, "a row of lanes holds a team");
+static_assert(kMaxTeam <= kTeamRow, "a row of lanes holds a team");
 
-// Lane l < count sends word l; every lane with `wants` set receives the words at[] of member lane & 15 into
-// got[] (its own are there already).  Returns whether a partner failed to answer.
-template <int COUNT>
-__device__ __forceinline__ int swap_words(const Team& t, unsigned mine, int count, bool wants, const int (&at)[COUNT], unsigned (&got)[COUNT]) {
+// Lane l < count sends word l; the lanes of the first ROWS rows, and those with `also` set, receive the words at[] of member
+// lane & 15 into got[] (a member's own are there already).  Returns whether a partner failed to answer.
+template <int ROWS, int COUNT>
+__device__ __forceinline__ int swap_words(const Team& t, unsigned mine, int count, const int (&at)[COUNT], unsigned (&got)[COUNT], bool also = false) {
     const int lane = lane_here();
-    unsigned long long* const base = t.area + static_cast<size_t>(t.seq & 1u) * t.size * kExchWords;
+    unsigned long long* const base = t.area + static_cast<size_t>(exchange_area(t.seq)) * t.size * kExchWords;
     if (lane < count) st_relaxed(base + t.member * kExchWords + lane, (static_cast<unsigned long long>(t.seq) << 32) | mine);
     int dead = t.dead;
-    if (wants && (lane & 15) != t.member) {
+    if (exchange_waits<ROWS>(lane, t.size, also) && (lane & 15) != t.member) {
         const unsigned long long* const line = base + (lane & 15) * kExchWords;
         for (unsigned spin = 1; !dead; ++spin) {
             unsigned long long v[COUNT];
@@ -1061,7 +1062,7 @@ __device__ __forceinline__ void collect_sums(Team& t, double& s0, double& s1) {
         const unsigned mine = half_of(TWO && (lane & 2) ? other : one, lane & 1);
         unsigned got[2] = {half_of(v, 0), half_of(v, 1)};
         const int at[2] = {2 * row, 2 * row + 1};
-        note_dead(t, swap_words(t, mine, TWO ? 4 : 2, row < (TWO ? 2 : 1) && m < t.size, at, got));
+        note_dead(t, swap_words<TWO ? 2 : 1>(t, mine, TWO ? 4 : 2, at, got));
         v = row_sum(m < t.size && !t.dead ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) : 0.0);
     }
     s0 = lane_f64(v, 0);
@@ -1091,9 +1092,8 @@ __device__ __forceinline__ void collect_stats(Team& t, double& a0, double& At, d
         if (lane < 2) mine = __float_as_uint(lane ? Md : Mt);
         unsigned got[3] = {half_of(s, 0), __float_as_uint(M), half_of(s, 1)};
         if (WEIGHT && row == 2) { got[0] = half_of(a0, 0); got[2] = half_of(a0, 1); }
-        const bool wants = (row < 2 && m < t.size) || (WEIGHT && lane == 32);
         const int at[3] = {2 * row + 2, row < 2 ? row : 6, 2 * row + 3};
-        note_dead(t, swap_words(t, mine, WEIGHT ? 8 : 6, wants, at, got));
+        note_dead(t, swap_words<2>(t, mine, WEIGHT ? 8 : 6, at, got, WEIGHT && lane == 32));
         const bool live = m < t.size && !t.dead;
         const float Mm = live ? __uint_as_float(got[1]) : OnlineLse::kFloor;
         M = row_max(Mm);
@@ -2574,7 +2574,7 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
         unsigned got[2] = {half_of(v, 0), half_of(v, 1)};
         if (team.size > 1) {
             const int at[2] = {0, 1};
-            note_dead(team, swap_words(team, half_of(v, lane & 1), 2, lane < team.size, at, got));
+            note_dead(team, swap_words<1>(team, half_of(v, lane & 1), 2, at, got));
         }
         const double mass = lane < team.size && !team.dead ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) : 0.0;
         double upto = mass;                            // sums along the row of lanes: member m and those before it
@@ -2681,14 +2681,15 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
     int next = -1;
     if (walk) {
         // Sec. 3.2: if the drawn token is a child's token the walk moves to that child (the
-        // first such child in list order), otherwise it ends here.  Everybody needs the token.
+        // first such child in list order), otherwise it ends here.  Everybody needs the token (the owner's word; the
+        // others' say only that they have come this far).
         task_barrier();
         if (wave == 0) {
             unsigned got[1] = {static_cast<unsigned>(sh_tok)};
             if (team.size > 1) {
                 team.seq++;
                 const int at[1] = {0};
-                note_dead(team, swap_words(team, got[0], 1, lane == owner, at, got));
+                note_dead(team, swap_words<1>(team, got[0], 1, at, got));
             }
             const int tok = __builtin_amdgcn_readlane(static_cast<int>(got[0]), owner);
             const unsigned long long m = __ballot(lane < k && child_token == tok);

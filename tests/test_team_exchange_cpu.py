@@ -1,0 +1,91 @@
+"""The exchange between the members of a team (csrc/mpv_exchange.h), modelled on the host: every order in which the
+members of a small team can take their steps, with the kernels' own rules of who waits for whom and which area is written."""
+
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "mpv_exchange.h"
+extern "C" int area_of(unsigned seq) { return static_cast<int>(mpv::exchange_area(seq)); }
+extern "C" int lane_waits(int rows, int lane, int size, int also) {
+    return rows == 1 ? mpv::exchange_waits<1>(lane, size, also != 0) : mpv::exchange_waits<2>(lane, size, also != 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("exchange")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2602_16994_amd", "csrc"),
+                    str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
+    return ctypes.CDLL(str(d / "shim.so"))
+
+
+def a_member_can_miss_a_word(size, exchanges, area_of, waits_for):
+    """Token-following walks, one draw after the other: odd exchanges carry the masses, even ones the drawn token, and a
+    member other than the leader goes on after a token only when the leader has.  True if in some order of the steps a
+    member waits for a word that has been overwritten."""
+    start = (tuple((1, False, 0) for _ in range(size)), tuple((0,) * size for _ in range(2)))
+    seen, todo = {start}, [start]                     # a member: (exchange, word written, partners whose word it has)
+    while todo:
+        members, areas = todo.pop()
+        for m, (seq, written, have) in enumerate(members):
+            if seq > exchanges:
+                continue
+            new_areas, step = areas, None
+            if not written:
+                if m != 0 and seq > 1 and seq % 2 == 1 and members[0][0] < seq:
+                    continue                          # the next draw has not been announced
+                a = area_of(seq)
+                new_areas = tuple(tuple(seq if (i, w) == (a, m) else v for w, v in enumerate(line)) for i, line in enumerate(areas))
+                step = [(seq, True, 1 << m)]
+            else:
+                step, due = [], [p for p in range(size) if waits_for(seq, m, p) and not have >> p & 1]
+                for p in due:
+                    word = areas[area_of(seq)][p]
+                    if word > seq:
+                        return True
+                    if word == seq:
+                        step.append((seq, True, have | 1 << p))
+                if not due:
+                    step = [(seq + 1, False, 0)]
+            for s in step:
+                state = (members[:m] + (s,) + members[m + 1:], new_areas)
+                if state not in seen:
+                    seen.add(state)
+                    todo.append(state)
+    return False
+
+
+@pytest.mark.parametrize("size", [2, 3])
+def test_no_member_misses_a_word(rules, size):
+    assert not a_member_can_miss_a_word(size, 5, rules.area_of, lambda seq, m, p: rules.lane_waits(1, p, size, 0))
+
+
+@pytest.mark.parametrize("size,owner", [(3, 0), (3, 1), (2, 0)])
+def test_the_model_finds_a_token_exchange_that_waits_for_its_owner_alone(rules, size, owner):
+    """(the mistake is in the model's rule: the drawn token comes from one member, and only that one's word is waited for)"""
+    assert a_member_can_miss_a_word(size, 5, rules.area_of, lambda seq, m, p: seq % 2 == 1 or p == owner)
+
+
+@pytest.mark.parametrize("rows", [1, 2])
+def test_every_exchange_waits_for_every_member(rules, rows):
+    for size in range(1, 17):
+        for lane in range(64):
+            expect = lane % 16 < size and lane // 16 < rows
+            assert rules.lane_waits(rows, lane, size, 0) == expect
+            assert rules.lane_waits(rows, lane, size, 1) == (lane % 16 < size)
+
+
+def test_the_kernels_exchange_by_these_rules():
+    with open(os.path.join(ROOT, "paper_2602_16994_amd", "csrc", "mpv.hip")) as f:
+        text = f.read()
+    body = text[text.index("int swap_words("):]
+    body = body[:body.index("\n}\n")]
+    assert "exchange_area(t.seq)" in body and "exchange_waits<ROWS>(lane, t.size, also)" in body
+    assert text.count("swap_words<") == text.count("swap_words") - 1       # no other way to exchange
