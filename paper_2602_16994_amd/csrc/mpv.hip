@@ -2205,6 +2205,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         if (next >= 0 && wave == 0 && leader) {
             {                                         // a token-following walk goes on
                 Team team = uniform_struct(g_loop.team);          // (as sample_task left it)
+                wait_memory();                        // the walk's position, which every member reads when it hears of the task
                 team_announce(team, next, flags);
                 if (threadIdx.x == 0) {
                     g_loop.team = team;
@@ -2214,7 +2215,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             }
             if (threadIdx.x == 0) {
                 (void)atomicAdd(&ws.qctl[0], 1);
-                wait_memory();                        // counted (and the walk's position written) first
+                wait_memory();                        // counted before this one is
                 atomicAdd(&ws.qctl[1], 1);
             }
         }

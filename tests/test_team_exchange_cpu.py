@@ -89,3 +89,15 @@ def test_the_kernels_exchange_by_these_rules():
     body = body[:body.index("\n}\n")]
     assert "exchange_area(t.seq)" in body and "exchange_waits<ROWS>(lane, t.size, also)" in body
     assert text.count("swap_words<") == text.count("swap_words") - 1       # no other way to exchange
+
+
+def test_a_walk_s_position_is_performed_before_the_next_draw_is_announced():
+    """The members read the position from memory when they hear of the task, so the leader waits for its store in between
+    (in the source, not by what a call happens to wait for)."""
+    with open(os.path.join(ROOT, "paper_2602_16994_amd", "csrc", "mpv.hip")) as f:
+        text = f.read()
+    handed_on = text[text.index("const int next = sample_task<E, METHOD>("):]
+    handed_on = handed_on[:handed_on.index("run_node_task<E, KIND>(task, flags);")]
+    assert handed_on.count("team_announce(") == 1
+    before = handed_on[:handed_on.index("team_announce(")]
+    assert "wait_memory();" in before[before.index("next >= 0"):]
