@@ -392,6 +392,19 @@ def test_branches_are_handed_to_idle_teams(B, V, K, L1, L2):
             assert np.array_equal(got[key], again[key])
 
 
+@pytest.mark.parametrize("B", [199, 200, 201, 207, 208])
+def test_the_branching_node_is_split_whatever_the_number_of_trees_modulo_8(B):
+    """No team to spare (teams of several members, as many as trees): a tree's branching node handles its first child first.
+    Teams that are added only to make a multiple of 8 do not count as spare."""
+    announce("split", B)
+    cfg = workloads.Config("split", B=B, V=40000, K=2, L1=0, L2=2, dtype="bf16", T=1.0,
+                           methods=[TV], draft_sigma=1.5, target_sigma=1.0, seed=80)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    got = run_library(inputs, cfg.T, TV, debug=False)
+    assert got["counters"][4] == 0 and got["counters"][7] > 0          # rejected first subtrees: the node's second task
+    compare_with_oracle(TV, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, B // 20), check_debug=False)
+
+
 @pytest.mark.parametrize("V,dtype,B", [(5, "bf16", 3), (63, "f32", 3), (515, "bf16", 3), (1025, "f32", 700), (33001, "bf16", 3),
                                        (300001, "f32", 2), (524293, "bf16", 2)])
 @pytest.mark.parametrize("method", ALL_METHODS)
