@@ -517,7 +517,9 @@ __device__ __forceinline__ void append_task(const TreeDesc& tree, const Workspac
 __device__ __forceinline__ int first_task(const QueuePlan& q, const Args& a, int h) {
     if (h >= q.init_total) return kTaskNone;
     if (q.root_is_leaf) return a.B * a.N + h;
-    return (h % a.B) * a.N + q.init_node[h / a.B];
+    int trees = uniform_i32(a.B);                     // (its reciprocal is not kept across tasks)
+    asm volatile("" : "+s"(trees));
+    return (h % trees) * a.N + q.init_node[h / trees];
 }
 // Counts off one first task (one lane).  The address is made a lane's own: for one that is the same in every lane the
 // compiler adds the lanes up first and waits for the result at once; here it is waited for where it is used.
@@ -833,11 +835,15 @@ __shared__ LoopState g_loop;
 constexpr int kNothingHeard = -4;
 constexpr int kNotStarted = -5;           // own_task, every member: the team's first announcement is still to come
 
-// The lane number, for numbers derived from it that are not worth keeping: computed where they are used
-// instead of ahead of the task loop (there they took so many registers that others went to memory).
+// The lane number, for numbers derived from it that are not worth keeping: computed where they are used, from nothing
+// that would have to be kept, instead of ahead of the task loop (there they took so many registers that others went to
+// private memory, and a reload waits for every row in flight).  With this in estimate_wave and in the words of the task's
+// announcement too, and two more numbers computed where they are used (first_task, the children's exponent), the node
+// tasks' loop has no private-memory access: 256 trees of 41 nodes, V = 151936, Traversal 452 -> 441 us, 64 trees of 15
+// nodes, V = 128256, SpecInfer 83 -> 80, one tree of V = 1500, Traversal 61 -> 56.
 __device__ __forceinline__ int lane_here() {
-    int lane = threadIdx.x & (kWave - 1);
-    asm volatile("" : "+v"(lane));
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
     return lane;
 }
 
@@ -906,9 +912,9 @@ __device__ __forceinline__ unsigned half_of(double v, int hi) {
 __device__ __forceinline__ void team_announce(Team& t, int task, int flags) {
     t.tseq++;
     if (t.size == 1) return;
-    if (threadIdx.x < 2) {
+    if (const int half = lane_here(); half < 2) {
         const unsigned long long tag = static_cast<unsigned long long>(t.tseq) << 32;
-        st_relaxed(t.task_word + threadIdx.x, tag | static_cast<unsigned>(threadIdx.x == 0 ? task : flags));
+        st_relaxed(t.task_word + half, tag | static_cast<unsigned>(half == 0 ? task : flags));
     }
 }
 // The others wait for it (first wave; returns the same in every lane).  kTaskExit on a timeout.
@@ -919,8 +925,8 @@ __device__ __forceinline__ int team_listen(Team& t, int& flags, const Workspace&
     t.tseq++;
     unsigned long long v = 0ull;
     int ok = 1;
-    if (threadIdx.x < 2) {
-        const unsigned long long* const word = (FIRST ? t.area + 1 : t.task_word) + threadIdx.x;
+    if (const int half = lane_here(); half < 2) {
+        const unsigned long long* const word = (FIRST ? t.area + 1 : t.task_word) + half;
         for (unsigned spin = 1;; ++spin) {
             // (the exit flag is looked at rarely: its line is the one that the first tasks are counted on)
             const int leave = FIRST && (spin & 31u) == 0u ? ld_relaxed(&ws.qctl[2]) : 0;
@@ -1459,7 +1465,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     static_assert(MPV_MAX_CHILDREN <= 32, "one lane per child and row");
     double pq_all;
     {
-        pq_all = probability_exp2(static_cast<double>(E::load_one(&logits)) * kd - (lane_here() >= 32 ? Ad_ : At_));
+        float k_here = k32;                           // (widened here: as a double it is not kept across tasks)
+        asm volatile("" : "+s"(k_here));
+        pq_all = probability_exp2(static_cast<double>(E::load_one(&logits)) * static_cast<double>(k_here) - (lane_here() >= 32 ? Ad_ : At_));
     }
     // test outcomes this task settles, one bit per node at its position in postorder
     unsigned long long settled_bits = 0ull, accepted_bits = 0ull;
@@ -2314,7 +2322,7 @@ __device__ __forceinline__ int walk_wave(const TreeDesc& tree, const Workspace& 
 template <int METHOD>
 __device__ __forceinline__ void estimate_wave(const TreeDesc& tree, const Workspace& ws, const Args& a, int b) {
     __shared__ double sh_v[MPV_MAX_NODES], sh_w[MPV_MAX_NODES];
-    const int n = threadIdx.x & (kWave - 1);
+    const int n = lane_here();
     const size_t base = static_cast<size_t>(b) * a.N;
     const bool live = n < a.N;
     double reach = 0.0;
