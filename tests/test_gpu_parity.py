@@ -357,19 +357,30 @@ def test_more_trees_than_workgroups_delayed_tree(method):
 
 @pytest.mark.parametrize("B,V,dtype", [(511, 64, "f32"), (512, 64, "f32"), (513, 64, "f32"),       # 512 teams of one
                                        (47, 40000, "bf16"), (97, 40000, "bf16"), (257, 40000, "bf16")])   # teams of several
-@pytest.mark.parametrize("method", [SI, TV, NSS])
-def test_first_tasks_are_counted_off_once(method, B, V, dtype):
+@pytest.mark.parametrize("method,L2", [(SI, 2), (SI, 1), (TV, 2), (TV, 1), (NSS, 2)])
+def test_first_tasks_are_counted_off_once(method, L2, B, V, dtype):
     """As many trees as teams, one less, one more, and more: a team's first task comes with its last
     member, the further ones are asked for ahead of time, from a node task or while a token is sampled.
-    Every tree must get its outcome, and a tree's node tasks run once."""
-    announce("first tasks", METHOD_NAME[method], B, V)
-    cfg = workloads.Config("first_tasks", B=B, V=V, K=2, L1=0, L2=2, dtype=dtype, T=1.0,
+    Every tree must get its outcome, and a tree's node tasks run once: a top-down walk's are those of the inner nodes it
+    comes to, NSS has none, and Traversal's are the root's where that is the only inner node (L2 = 1; with more it
+    depends on which branches are followed at the same time)."""
+    announce("first tasks", METHOD_NAME[method], B, V, L2)
+    cfg = workloads.Config("first_tasks", B=B, V=V, K=2, L1=0, L2=L2, dtype=dtype, T=1.0,
                            methods=[method], draft_sigma=1.5, target_sigma=1.0, seed=77)
     inputs = workloads.make_inputs(cfg, "cuda")
     got = run_library(inputs, cfg.T, method, debug=False)
-    assert got["counters"][4] == 0 and got["counters"][5] <= 3 * B
+    assert got["counters"][4] == 0 and got["counters"][7] <= B
+    tasks = int(got["counters"][5])
+    if method == SI:
+        assert tasks == int(np.minimum(got["accept_len"] + 1, L2).sum())
+    elif method == NSS:
+        assert tasks == 0
+    elif L2 == 1:
+        assert tasks == B
+    else:
+        assert B <= tasks <= 3 * B
     compare_with_oracle(method, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, max(1, B // 40)), check_debug=False)
-    assert np.all((got["bonus_token"] >= 0) & (got["bonus_token"] < V)) and np.all((got["accept_len"] >= 0) & (got["accept_len"] <= 2))
+    assert np.all((got["bonus_token"] >= 0) & (got["bonus_token"] < V)) and np.all((got["accept_len"] >= 0) & (got["accept_len"] <= L2))
 
 
 @pytest.mark.parametrize("B,V,K,L1,L2", [(2, 1500, 4, 2, 3), (24, 1500, 8, 0, 5), (96, 1500, 4, 2, 3), (96, 16000, 8, 0, 5),
