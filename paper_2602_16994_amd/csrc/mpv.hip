@@ -465,10 +465,11 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
 //             counts, was the bottleneck (200 trees of V = 1500 on 512 teams, Traversal: 338 us, then 273).
 //             If every team is busy nobody dispatches, and nobody needs to.  Node tasks of trees
 //             whose outcome is settled are dropped here when only what is needed is computed.
-//   end:      nothing queued and completed == appended, with appended read before and after
-//             completed and unchanged: no task is queued, handed out or running, so nothing
-//             can be appended any more; the dispatching leader sets the exit flag.  A
-//             task's appends are performed before its completed++.
+//   end:      whoever finishes the last tree (acceptance rates: the last task) sets the exit flag, see tree_done; what
+//             is still queued then belongs to settled trees.  As a fallback, for a launch in which something went wrong,
+//             the dispatcher looks in every 16th round without a queued task whether completed == appended, with
+//             appended read before and after completed and unchanged: no task is queued, handed out or running, so
+//             nothing can be appended any more.  A task's appends are performed before its completed++.
 // A team may also run a task it has produced itself straight away (counted in appended,
 // never queued).  Every wait is bounded.  Only the leader (member 0) of a team talks to the queue.
 
@@ -849,7 +850,7 @@ __device__ __forceinline__ int lane_here() {
 
 // The node task's exchanges (first wave only) stay in registers: lane 16 r + m looks after member m, so that
 // the members' numbers meet in reductions along a row of 16 lanes, and a member's own numbers do not travel.
-// (Through LDS, one member after the other, as the other tasks' still do, the statistics of a team of 8 took
+// The sampling task's go the same way.  (Through LDS, one member after the other, the statistics of a team of 8 took
 // 1.15 us from the last word's arrival to the logarithms, now 0.3.)
 static_assert(kMaxTeam <= kTeamRow, "a row of lanes holds a team");
 
@@ -2236,8 +2237,9 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
 
 // ------------------------------------------------------------------ walk
 //
-// The uniform-dependent part of SpecInfer and Traversal, run by the first wave of every member of
-// the sampling team (they all need the stopping node; the leader records the path): lane n compares u[n] with the probability node n is tested with
+// The uniform-dependent part of SpecInfer and Traversal.  Where the task says in which node the walk stopped, only the
+// leader's third wave does it, to record the path; else every wave of the sampling team does (they all need the stopping
+// node; the leader's first records the path).  Lane n compares u[n] with the probability node n is tested with
 // (which does not depend on the uniforms), the 64 outcomes become a bit mask, and
 // the walk itself is a few scalar steps over that mask.
 //   SpecInfer (Sec. 3.2 walk + App. B Alg. 4): from the root, move to the first
@@ -2511,7 +2513,6 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
             double none = 0.0, unused;
             collect_stats<false>(team, none, At, unused);
             if (lane == 0) sh_At = At;
-            if (leader && lane == 0) ws.At[bn] = At;
         }
         task_barrier();
         At = sh_At;
@@ -3112,7 +3113,7 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     // queued for, 56.8 with 64; 200 trees of V = 4096: 110 and 72).  Traversal can follow the branches of a tree at the same
     // time, which pays for about two a tree, and up to 192 teams, beyond which they wait for the dispatcher (200 trees of
     // V = 1500, 3 branches: 138 us with 200 teams, 149 with 256, 213 with 416, 273 with 512; 2 trees want the 16 more).
-    const int branches = p->B < 176 ? min(2 * p->B + 16, max(p->B, 192)) : max(p->B, 192);
+    const int branches = min(2 * p->B + 16, max(p->B, 192));       // (B * (N + 2) is at most 2^30)
     const int at_once = !a.lazy ? tasks : min(tasks, top_down ? p->B : branches);
     // Shorter parts pay as long as every tree (Traversal: four branches of it) still has a team: one tree of V = 32000, top
     // down, 62 us with parts of 2000 vectors, 57 with 1333, 54 with 1000; 200 trees of V = 16000, Traversal, on fewer teams for it: 182 and 154.
