@@ -321,7 +321,10 @@ __device__ __forceinline__ void sweep_row(const typename E::T* __restrict__ z, i
 struct OnlineLse {
     // The reference starts at a huge negative but finite value, so that a row (or a
     // vector) of -inf logits needs no special case: fma(-inf, k, big) = -inf -> 2^-inf = 0.
-    static constexpr float kFloor = -1e30f;
+    // It never lies below that value: a reference is rounded to float, an exponent's argument measured against it is off by as
+    // much, and beyond 2^31 that is 2^128, an infinity, which times the 2^-huge of the next reference is no number (a
+    // lane, or a wave, whose first logits are masked with -1e10 or -1e30).  Logits below it weigh nothing, as -inf does.
+    static constexpr float kFloor = -0x1p31f;
     float m, mk, s;
     __device__ __forceinline__ void init() { m = -INFINITY; mk = kFloor; s = 0.f; }
     // The reference follows the running maximum only in steps: it is moved when the

@@ -311,14 +311,14 @@ struct NucleusCollect {
     NucleusShared<BLOCK>& sh;
     float k32, span;        // span: of what is listed, in units of the logits
     int first;              // the wave's run of the list starts here
-    float mz, mk;           // the reference: mk = mz * k32 (the same in every lane of the wave)
+    float mz, mk;           // the reference: mk = mz * k32, kFloor at least (the same in every lane of the wave)
     float top;              // the largest logit of any wave, as far as this one knows
     float cut, thr;         // listed: logits >= cut; a vector whose terms add up to less than thr has none
     float s;                // this lane's mass, in units of the reference
     int n;                  // tokens listed by this wave (more than fit: too many)
     __device__ __forceinline__ void init(float k, float top, int wave) {
         k32 = k; span = kNucleusSpan / k; first = wave * kNucleusPerWave;
-        mz = top; mk = top > -INFINITY ? top * k : OnlineLse::kFloor;
+        mz = top; mk = fmaxf(top * k, OnlineLse::kFloor);
         s = 0.f; n = 0;
         set_cut(top);
     }
@@ -329,7 +329,7 @@ struct NucleusCollect {
     }
     __device__ __forceinline__ void set_cut(float largest) {
         top = largest;
-        const bool none = !(top > -INFINITY) || n > kNucleusPerWave;     // nothing but -inf so far, or no room left
+        const bool none = !(top * k32 > OnlineLse::kFloor) || n > kNucleusPerWave;     // nothing but masked logits so far, or no room left
         cut = none ? INFINITY : top - span;
         // (0.98: the rounding of the terms; 0.9: a logit above the reference must always be noticed)
         thr = none ? 0.9f : fminf(0.9f, 0.98f * fast_exp2(fmaf(cut, k32, -mk)));
@@ -352,7 +352,7 @@ struct NucleusCollect {
 #pragma unroll
             for (int i = 1; i < COUNT; ++i) lm = fmaxf(lm, a[i]);
             if (__builtin_amdgcn_ballot_w64(lm > mz) != 0ull) {        // a new largest logit
-                const float nz = wave_max(lm), nmk = nz * k32;
+                const float nz = wave_max(lm), nmk = fmaxf(nz * k32, OnlineLse::kFloor);
                 s *= fast_exp2(mk - nmk);
                 mz = nz; mk = nmk;
                 v = terms(a);
@@ -490,7 +490,7 @@ __global__ __launch_bounds__(BLOCK) void nucleus_kernel(const typename E::T* in,
             p.mass = lane == 0 ? part : 0.0; p.below = -INFINITY; p.above = INFINITY; p.count = 0;
             want = static_cast<double>(top_p) * block_total<BLOCK>(p, sh).mass * kNucleusUnit;
         }
-        if (row_max > -INFINITY) {                            // (a row of -inf only has nothing to drop)
+        if (row_max * k32 > OnlineLse::kFloor) {              // (a row of masked logits only has nothing to drop)
             // what is within the span of the maximum moves to the front of the list
             const float cut0 = row_max - kNucleusSpan / k32;
             int listed = 0;

@@ -358,3 +358,26 @@ def test_one_wave_or_four_find_the_same_threshold():
             assert torch.equal(a[:1024], b)
         # (upper sets of neighbouring values differ by 1e-3 of the mass)
         assert check_rows(z[:12], 1.0, top_p, few[0][:12], few[1][:12], few[2][:12]) == 0
+
+
+@pytest.mark.parametrize("dtype,V,lead", [(torch.float32, 50001, 16384), (torch.float32, 6003, 4096), (torch.float32, 2000, 1),
+                                          (torch.bfloat16, 100003, 32768), (torch.bfloat16, 4001, 3000)])
+@pytest.mark.parametrize("mask", [-1e10, -1e30, float(torch.finfo(torch.bfloat16).min)])
+def test_masked_tokens_of_any_low_logit(dtype, V, lead, mask):
+    """Tokens masked by a large negative logit instead of -inf: before the first token that counts, after the last, in
+    between, and rows of nothing else (nothing is dropped there)."""
+    announce("nucleus masked", dtype, V, lead, mask)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V + 1)
+    z = torch.randn(7, V, generator=gen, device="cuda") * 3.0
+    z[:3, :lead] = mask
+    z[1:5, -(V // 10):] = mask
+    z[4:6][torch.rand(2, V, generator=gen, device="cuda") < 0.5] = mask
+    z[6] = mask
+    z = z.to(dtype)
+    for T, top_p in ((1.0, 0.9), (0.7, 0.99)):
+        masked, thr, kept = mpv.mpv_nucleus_mask(z, T, top_p)
+        torch.cuda.synchronize()
+        near = check_rows(z[:6], T, top_p, masked[:6], thr[:6], kept[:6])
+        assert near <= 1
+        assert torch.equal(masked[6], z[6]) and int(kept[6]) == V

@@ -516,3 +516,38 @@ def test_fill_uniforms_matches_the_documented_generator():
         got = mpv.mpv_fill_uniforms(seed, count).cpu().numpy()
         want = orc.uniforms_from_seed(seed, count)
         assert got.dtype == np.float32 and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("mask", [-3e9, -1e10, -1e30, float(np.finfo(np.float32).min), -np.inf])
+@pytest.mark.parametrize("method", ALL_METHODS)
+def test_masked_tokens_of_any_low_logit(method, mask):
+    """float32 rows with tokens masked by a large negative logit: whole waves of them at the front (a wave's first vector),
+    the padding at the end, single ones in between, and rows whose first element before the aligned vectors is one."""
+    announce("masked", METHOD_NAME[method], mask)
+    cfg = workloads.Config("masked", B=12, V=2102, K=2, L1=1, L2=2, dtype="f32", T=0.8,
+                           methods=[method], draft_sigma=1.5, target_sigma=1.0, seed=81)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    off = torch.rand(cfg.V, generator=torch.Generator().manual_seed(5)) < 0.3
+    off[:700] = True
+    off[-90:] = True
+    off[1500] = False
+    for rows, n in ((inputs["target"], 3), (inputs["draft"], 5)):
+        few = off.clone()
+        few[700::n] = True                                    # (the two rows do not mask the same tokens)
+        few[1500] = False
+        rows[:, :, few] = mask
+        rows[3:5, :, 1:] = torch.where(rows[3:5, :, 1:] == mask, torch.randn_like(rows[3:5, :, 1:]), rows[3:5, :, 1:])
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    for n in range(1, cfg.N):
+        q = torch.softmax(inputs["draft"][:, cfg.parent[n]] / cfg.T, dim=-1)
+        inputs["tokens"][:, n] = torch.multinomial(q, 1, generator=gen).squeeze(1).to(torch.int32)
+    host = workloads.to_host(inputs)
+    for debug in (True, False):
+        got = run_library(inputs, cfg.T, method, debug)
+        assert got["counters"][4] == 0
+        compare_with_oracle(method, host, cfg.T, got, check_debug=debug)
+    rows = inputs["draft"].view(-1, cfg.V)
+    out = mpv.mpv_row_stats(rows, cfg.T).cpu().numpy().astype(np.float64)
+    z = rows.double().cpu()
+    assert np.array_equal(out[:, 0], z.max(dim=1).values.numpy())
+    np.testing.assert_allclose(out[:, 1], torch.logsumexp((z - z.max(dim=1, keepdim=True).values) / cfg.T, dim=1).numpy(), atol=1e-5)
