@@ -317,8 +317,8 @@ __device__ __forceinline__ void load_shape(const unsigned long long* shapes, int
 }
 
 // Before, a batch was one launch pair per run of consecutive equal shapes, each a dependent chain of
-// tasks with most of the chip idle: 64 trees of 22 shapes, V = 128256, SpecInfer 3.6 ms, now 0.112 ms;
-// 256 trees of 162 shapes, V = 151936, Traversal 22.2 ms, now 0.515 ms.
+// tasks with most of the chip idle: 64 trees of 22 shapes, V = 128256, SpecInfer 3.6 ms, now 0.092 ms;
+// 256 trees of 162 shapes, V = 151936, Traversal 22.2 ms, now 0.51 ms.
 //
 // Parent arrays travel to the device as kernel arguments (a byte per node): no copy that could
 // synchronise, no host memory that has to outlive the call, and a captured graph holds them.
@@ -3051,7 +3051,7 @@ static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, 
     // Tasks that do not depend on each other: the size whose rounds take the least time.  A task's own time is
     // a part that no team shortens (exchanges, scalar steps) and one that goes with a member's vectors; the two
     // are equal at about 1900 vectors (22 us a task with parts of 1 900, 30 with 3 165).  64 trees of 33 inner
-    // nodes, V = 151936: 670 us with 72 teams of 10, 497 with 128 of 6; but 4 such trees of V = 262144 are three
+    // nodes, V = 151936: 670 us with 72 teams of 10, 497 with 128 of 6 (392 by now); but 4 such trees of V = 262144 are three
     // rounds either way, 91 us with teams of 16, 97 with teams of 11.  (The constant is SpecInfer's in bf16 at V = 151936;
     // with the others the sizes it gives are faster too than those that the trees give: SpecTr 791 -> 609 us, NSS
     // 822 -> 628, Naive 783 -> 598; 24 trees of V = 100003 in float32, 12 inner nodes: 137 -> 98, 150 -> 109, 146 -> 106.)
@@ -3104,8 +3104,8 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
     // Tasks that do not depend on each other: every node's for the acceptance rates.  (A rate is 1 less a mass: with other
     // parts, so sums in another order, it moves by 7e-7 at most.)  Block efficiency keeps the size that the trees give,
-    // although its tasks could be counted too (64 trees of 33 inner nodes, V = 151936, Traversal: 526 us, 410 with teams of
-    // 6): probabilities further down a tree are quotients of differences, p - c q over what is left of p, and sums in
+    // although its tasks could be counted too (64 trees of 33 inner nodes, V = 151936, Traversal: 485 us, 399 with teams of
+    // 6; SpecInfer 523 and 421): probabilities further down a tree are quotients of differences, p - c q over what is left of p, and sums in
     // another order then move single ones by 1e-5 (against 64 bits both are equally far off, up to 5e-5 over 71 such batches).
     const bool top_down = p->method != MPV_METHOD_TRAVERSAL;
     // Only what is needed: a top-down walk has one task at a time per tree, and teams without a task only take issue slots
