@@ -81,7 +81,8 @@ extern "C" {
 #define MPV_METHOD_NAIVE     3
 #define MPV_METHOD_SPECTR    4
 
-#define MPV_DTYPE_F32  0      /* IEEE binary32 logits                      */
+#define MPV_DTYPE_F32  0      /* IEEE binary32 logits: finite, or -inf for a token of probability zero.  A
+                               * logit z with z log2(e)/T below -2^31 (a mask of -1e10) counts as -inf. */
 #define MPV_DTYPE_BF16 1      /* bfloat16 logits (upper half of binary32).  Finite values must lie
                                * within +-65504; magnitudes below 2^-14 are used to within 2^-25
                                * (an error of log2(e)/T * 2^-25 in the exponent of e^(z/T): nothing
