@@ -496,6 +496,9 @@ __device__ __forceinline__ unsigned atomicAdd(unsigned* p, unsigned v) {
 __device__ __forceinline__ unsigned long long atomicOr(unsigned long long* p, unsigned long long v) {
     return __hip_atomic_fetch_or(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ unsigned long long atomicAdd(unsigned long long* p, unsigned long long v) {
+    return __hip_atomic_fetch_add(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ int atomicCAS(int* p, int expected, int desired) {
     __hip_atomic_compare_exchange_strong(as_global(p), &expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
@@ -806,6 +809,7 @@ __device__ __forceinline__ double ld_shared_f64(const double* p) {
 
 struct Team {
     int id, member, size;
+    int one_chiplet;                 // all members run on one chiplet: what they tell each other stays in its L2 (st_team)
     unsigned seq;                    // exchanges done
     unsigned tseq;                   // task words seen
     unsigned long long* area;        // [2][size][kExchWords]
@@ -813,6 +817,20 @@ struct Team {
     long long t_start;               // wall clock at the start of the launch
     int dead;                        // a partner never answered: results are invalid, every wait is skipped
 };
+
+// What the members of a team tell each other.  Loads of device scope are served by the chiplet's L2, past the first-level
+// caches; so where every member runs on one chiplet (checked as they arrive, by the hardware's own number: teams are laid
+// out for it, but nothing promises where a workgroup runs) the words need not go any further than that L2 either, which
+// a store of workgroup scope says.  A store of device scope writes through to memory and takes the line out of
+// the L2, and every reader waits for memory: an exchange between 2 / 6 / 12 / 16 workgroups with nothing else to do took
+// 0.68 / 0.70 / 0.84 / 1.02 us with it and takes 0.35 / 0.40 / 0.43 / 0.44.  (64 trees of V = 128256, Traversal, 139 -> 133 us a
+// call; 32 of V = 262144 on teams of 16, SpecInfer, 79 -> 73; 256 of V = 151936, Traversal, 447 -> 433.)
+__device__ __forceinline__ void st_team(const Team& t, unsigned long long* p, unsigned long long v) {
+    if (t.one_chiplet) __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else st_relaxed(p, v);
+}
+static_assert(kMaxTeam < (1 << kArrivedBits), "the counts of a team's arrivals fit their fields");
+__device__ __forceinline__ int chiplet_here() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15; }      // (HW_REG_XCC_ID, 4 bits)
 
 // What a workgroup carries from task to task, kept in LDS: the functions that run the tasks are
 // not inlined, and state handed to them by reference would live in each lane's private memory.
@@ -860,7 +878,7 @@ template <int ROWS, int COUNT>
 __device__ __forceinline__ int swap_words(const Team& t, unsigned mine, int count, const int (&at)[COUNT], unsigned (&got)[COUNT], bool also = false) {
     const int lane = lane_here();
     unsigned long long* const base = t.area + static_cast<size_t>(exchange_area(t.seq)) * t.size * kExchWords;
-    if (lane < count) st_relaxed(base + t.member * kExchWords + lane, (static_cast<unsigned long long>(t.seq) << 32) | mine);
+    if (lane < count) st_team(t, base + t.member * kExchWords + lane, (static_cast<unsigned long long>(t.seq) << 32) | mine);
     int dead = t.dead;
     if (exchange_waits<ROWS>(lane, t.size, also) && (lane & 15) != t.member) {
         const unsigned long long* const line = base + (lane & 15) * kExchWords;
@@ -908,6 +926,11 @@ __device__ __forceinline__ double row_sum(double v) {
 __device__ __forceinline__ unsigned half_of(double v, int hi) {
     return static_cast<unsigned>(hi ? __double2hiint(v) : __double2loint(v));
 }
+// task word flags (leader -> members)
+constexpr int kFlagIdle = 1;          // teams were idle after the last round of dispatching
+constexpr int kFlagOneChiplet = 2;    // the first announcement: every member runs on one chiplet
+constexpr int kFlagStopShift = 8;     // a sampling task: the node where the walk stopped, plus one (0: not known)
+
 // The leader tells the others which task it has taken.  Every task announced this way contains at
 // least one exchange, so the leader cannot announce the next before everybody has read this one.
 __device__ __forceinline__ void team_announce(Team& t, int task, int flags) {
@@ -915,7 +938,7 @@ __device__ __forceinline__ void team_announce(Team& t, int task, int flags) {
     if (t.size == 1) return;
     if (const int half = lane_here(); half < 2) {
         const unsigned long long tag = static_cast<unsigned long long>(t.tseq) << 32;
-        st_relaxed(t.task_word + half, tag | static_cast<unsigned>(half == 0 ? task : flags));
+        st_team(t, t.task_word + half, tag | static_cast<unsigned>(half == 0 ? task : flags));
     }
 }
 // The others wait for it (first wave; returns the same in every lane).  kTaskExit on a timeout.
@@ -940,6 +963,10 @@ __device__ __forceinline__ int team_listen(Team& t, int& flags, const Workspace&
     const int all_ok = __ballot(!ok) == 0ull;
     const int task = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned>(v)), 0);
     flags = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned>(v)), 1);
+    if (FIRST) {
+        t.one_chiplet = all_ok && (flags & kFlagOneChiplet) != 0 ? 1 : 0;
+        flags &= ~kFlagOneChiplet;
+    }
     return all_ok ? task : kTaskExit;
 }
 
@@ -968,9 +995,6 @@ __device__ __forceinline__ double int_power(double x, int k) {
     return r;
 }
 
-// task word flags (leader -> members)
-constexpr int kFlagIdle = 1;          // teams were idle after the last round of dispatching
-constexpr int kFlagStopShift = 8;     // a sampling task: the node where the walk stopped, plus one (0: not known)
 
 // (defined below) walk and bonus token of tree b, or one draw of a token-following walk, by the
 // whole team; returns the task that follows from it (-1: none; the same in every lane of every member)
@@ -2038,7 +2062,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             team.id = i / team.size;
             team.member = i % team.size;
         }
-        team.seq = 0u; team.tseq = 0u; team.dead = 0;
+        team.seq = 0u; team.tseq = 0u; team.dead = 0; team.one_chiplet = 0;
         team.area = ws.exch + static_cast<size_t>(team.id) * 2 * team.size * kExchWords;
         team.task_word = ws.team_task + static_cast<size_t>(team.id) * 2;
         team.t_start = wall_clock64();
@@ -2048,10 +2072,13 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             // The last member to arrive counts off the team's first task and tells the others; if there is
             // none left it opens the team's mailbox: from then on the dispatcher may hand it tasks.
             const int flags = q.spare ? kFlagIdle : 0;
-            int task = kNotStarted, n_arrived = 1;
+            int task = kNotStarted, n_arrived = 1, n_here = 0;
             if (team.size > 1) {
-                if (lane == 0) n_arrived = atomicAdd(reinterpret_cast<int*>(team.area), 1) + 1;
-                n_arrived = uniform_i32(n_arrived);
+                const int on = chiplet_here();
+                unsigned long long so_far = arrival_of(on);
+                if (lane == 0) so_far += atomicAdd(team.area, so_far);
+                n_arrived = uniform_i32(arrived(so_far));
+                n_here = uniform_i32(arrived_on(so_far, on));
             }
             if (n_arrived == team.size) {
                 int number = 0;
@@ -2059,7 +2086,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 const int t = first_task(q, a, uniform_i32(number));
                 if (t == kTaskNone && lane == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxWaiting);
                 if (team.size == 1) task = t == kTaskNone ? -1 : t;
-                else if (lane < 2) st_relaxed(team.area + 1 + lane, (1ull << 32) | static_cast<unsigned>(lane == 0 ? t : flags));
+                else if (lane < 2) st_relaxed(team.area + 1 + lane, (1ull << 32) | static_cast<unsigned>(lane == 0 ? t : flags | (n_here == team.size ? kFlagOneChiplet : 0)));
             }
             if (lane == 0) {
                 g_loop.team = team;

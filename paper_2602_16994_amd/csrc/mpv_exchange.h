@@ -22,4 +22,16 @@ constexpr bool exchange_waits(int lane, int size, bool also) {
     return (lane & (kTeamRow - 1)) < size && (lane < ROWS * kTeamRow || also);
 }
 
+// The word in which a team's members count themselves as they start: how many there are, and how many on each chiplet.
+// Members on chiplets that it has no field for are nobody's neighbours.
+constexpr int kArrivedOn = 8, kArrivedBits = 5, kChiplets = 8;
+static_assert(kArrivedOn + kChiplets * kArrivedBits <= 64, "the counts of a team's arrivals fit a word");
+constexpr unsigned long long arrival_of(int chiplet) {
+    return 1ull + (chiplet < kChiplets ? 1ull << (kArrivedOn + kArrivedBits * chiplet) : 0ull);
+}
+constexpr int arrived(unsigned long long word) { return static_cast<int>(word & ((1ull << kArrivedOn) - 1ull)); }
+constexpr int arrived_on(unsigned long long word, int chiplet) {
+    return chiplet < kChiplets ? static_cast<int>((word >> (kArrivedOn + kArrivedBits * chiplet)) & ((1ull << kArrivedBits) - 1ull)) : 0;
+}
+
 }  // namespace mpv

@@ -11,6 +11,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "mpv_exchange.h"
 extern "C" int area_of(unsigned seq) { return static_cast<int>(mpv::exchange_area(seq)); }
+extern "C" unsigned long long arrival(int chiplet) { return mpv::arrival_of(chiplet); }
+extern "C" int count(unsigned long long word) { return mpv::arrived(word); }
+extern "C" int count_on(unsigned long long word, int chiplet) { return mpv::arrived_on(word, chiplet); }
 extern "C" int lane_waits(int rows, int lane, int size, int also) {
     return rows == 1 ? mpv::exchange_waits<1>(lane, size, also != 0) : mpv::exchange_waits<2>(lane, size, also != 0);
 }
@@ -80,6 +83,20 @@ def test_every_exchange_waits_for_every_member(rules, rows):
             expect = lane % 16 < size and lane // 16 < rows
             assert rules.lane_waits(rows, lane, size, 0) == expect
             assert rules.lane_waits(rows, lane, size, 1) == (lane % 16 < size)
+
+
+@pytest.mark.parametrize("size", [2, 15, 16])
+def test_a_team_on_one_chiplet_is_told_from_one_that_is_not(rules, size):
+    """The last to arrive sees every member on its own chiplet, or not: also with one member elsewhere, or on a chiplet that
+    the word has no field for (16 is the largest team, 0..15 what the hardware's number can be)."""
+    rules.arrival.restype = ctypes.c_ulonglong
+    rules.count.argtypes = [ctypes.c_ulonglong]
+    rules.count_on.argtypes = [ctypes.c_ulonglong, ctypes.c_int]
+    for on in range(16):
+        for other in range(16):
+            word = (size - 1) * rules.arrival(on) + rules.arrival(other)
+            assert rules.count(word) == size
+            assert (rules.count_on(word, other) == size) == (on == other and on < 8)
 
 
 def test_the_kernels_exchange_by_these_rules():
