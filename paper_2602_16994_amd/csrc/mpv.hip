@@ -103,6 +103,7 @@ struct QueuePlan {
     int32_t box_step;                    // words from one team's mailbox to the next
     int32_t same_xcd;                    // members of a team are 8 workgroup numbers apart (one chiplet, its L2)
     int32_t spare;                       // teams are left over from the start (not counting those that whole chiplets add)
+    int32_t draw_here;                   // top-down rules: node tasks draw the tokens themselves, from the part on chip (see launch_all)
 };
 
 constexpr int kMaxTeam = 16;                          // workgroups per team, at most
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
     {   // team words: every sequence number starts at 0, nobody has arrived
         const int exch_words = q.teams * q.team_size * 2 * kExchWords;
         for (int w = me; w < exch_words; w += stride) ws.exch[w] = 0ull;
-        for (int w = me; w < q.teams * 2; w += stride) ws.team_task[w] = 0ull;
+        for (int w = me; w < kMaxTeams * 2; w += stride) ws.team_task[w] = 0ull;
         for (int w = me; w < q.teams; w += stride) ws.mailbox[w * q.box_step] = kMailboxAbsent;
     }
     if (n == 0) {
@@ -1001,6 +1002,10 @@ __device__ __forceinline__ double int_power(double x, int k) {
 template <class E, int METHOD>
 __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in);
 
+// (defined below) draws of a top-down walk of tree b, from node n on; returns the task that follows (-1: none)
+template <class E>
+__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in);
+
 // (defined below) expected block efficiency of tree b from the per-node results, by the first wave
 template <int METHOD>
 __device__ __forceinline__ void estimate_wave(const TreeDesc& tree, const Workspace& ws, const Args& a, int b);
@@ -1035,6 +1040,7 @@ constexpr int kCmdDone = 0;          // the task is over
 constexpr int kCmdMass = 1;          // sum (p - rho q)_+
 constexpr int kCmdMassSlope = 2;     // the same and sum_{p > rho q} rho q       (SpecTr's root search)
 constexpr int kCmdAcceptance = 3;    // the NSS / Naive acceptance-rate sum      (acceptance rates only)
+constexpr int kCmdTiles = 6;         // a draw from the pair on chip comes next: the masses of its tiles (top-down rules)
 
 struct SweepCmd {
     int kind;
@@ -1049,6 +1055,15 @@ struct SweepCmd {
 };
 __shared__ SweepCmd g_cmd;
 __shared__ int g_claim_number;
+// A draw (see draw_walk).
+struct DrawShared {
+    float tile[kDrawTiles];          // the masses of this member's tiles, in units of 2^(g_sh.partf of the wave)
+    float nAt, nAd, rho;             // a pair: the constants they were weighed with
+    int pending, b, n, row;          // the node task that has just ended has come to this draw: tree, node, from a target row alone
+    int owner, in_tile, token, next;
+    double rem, total;               // of the tile that holds the target: mass to cover inside it; the whole row's, in the same unit
+};
+__shared__ DrawShared g_draw;
 
 // One sweep over the part on chip as the command says; the wave's partial sums go to g_sh.part.
 template <class E, int KIND, class PAIR>
@@ -1137,6 +1152,12 @@ __device__ __forceinline__ void collect_stats(Team& t, double& a0, double& At, d
     Ad = lane_f64(A, 16);
 }
 
+// the wave that has tile t of a draw (see PartDraw; the elements at the row's ends are the first wave's)
+__device__ __forceinline__ int draw_wave(int t) { return t == 0 ? 0 : (t - 1) % kTaskWaves; }
+
+template <class E> using TaskPart = RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs>;
+template <class E> using TaskDraw = PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs>;
+
 template <class E, int KIND>
 __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_in) {
     using T = typename E::T;
@@ -1147,6 +1168,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // within it made plain batches of many trees slower (Naive, 204 trees of V = 7872: 246 us, 237 without); Traversal
     // has no such cost, and going back would make 256 trees of V = 151936 slower (538 us, 531).
     constexpr bool kShapeInTask = !ACCEPT && METHOD == MPV_METHOD_TRAVERSAL;
+    constexpr bool DRAWS = KIND == MPV_METHOD_SPECINFER;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
     const QueuePlan& q = lds_launch().q;
@@ -1191,6 +1213,12 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
 
     // ---- the part of the pair this member keeps on chip while a task runs
     RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs> pair;
+    auto weigh_tiles = [&](float nAt, float nAd, float rho) __attribute__((always_inline)) {
+        TaskDraw<E> d(pair);
+        d.f.init(k32, nAt, nAd, rho);
+        d.weigh_pair(g_draw.tile, wave, lane);
+        if (lane == 0) g_sh.partf[wave][0] = 0.f;
+    };
 
     if (wave != 0) {
         // ---- a sweeping wave does what the first wave commands: it takes up a task (loads its
@@ -1226,6 +1254,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     g_sh.partf[wave][0] = Mt_w; g_sh.partf[wave][1] = Md_w;
                     g_sh.part[wave][0] = st_w; g_sh.part[wave][1] = sd_w;
                 }
+            } else if (DRAWS && kind == kCmdTiles) {
+                weigh_tiles(uniform_f32(cmd.nAt), uniform_f32(cmd.nAd), uniform_f32(cmd.rho));
             } else {
                 const bool claims_now = wave == 1 && uniform_i32(cmd.claim) != 0;
                 int claim_number = 0;
@@ -1348,6 +1378,15 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     unsigned long long chain_settled = 0ull, chain_accepted = 0ull;
     double a0_known = -1.0;
     int chained = -1;                                 // the node of the task handed on to (same tree)
+    // Walks draw their tokens in draw_walk, which is called next; a pair's tiles are weighed here, where it is on chip.
+    const int draws = DRAWS ? uniform_i32(q.draw_here) : 0;
+    // (Known to be the same each time, the compiler makes paths of their own of it, which take 140 registers to private memory.)
+    auto draw_here = [&]() __attribute__((always_inline)) {
+        if constexpr (!DRAWS) return false;
+        int x = draws;
+        asm volatile("" : "+s"(x));
+        return x != 0;
+    };
     // One node task after the other, for as long as the team knows its next one itself (the task
     // a node task hands to its own team: a child's, or the rest of the node where the tree
     // branches): no way back through the task loop, no queue in between.
@@ -1689,7 +1728,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                     if (run_child && (!first_to_run || own_given) && !child_ahead)
                         append_task(tree, ws, field(child, kClass, 1u), b * N + cn);      // (waits for the weight's store with its own count)
                 }
-            } else {
+            } else if (!draw_here()) {
                 st_shared_f64(&ws.atest[bc], w_child);
                 if (a.estimate && walk == 3) {
                     // App. D, SpecTr Branching: p_res(x), p_res = norm (p - rho* q)_+ (see the search above)
@@ -1710,8 +1749,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             break;
         }
 
-        if (METHOD == MPV_METHOD_SPECINFER && walk >= 2 && !a.estimate && lead && fabs(w_child - u_child) < 1e-6)
-            atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_ACCEPT], 1u);     // (the other rules count these in their walk)
+        if (METHOD == MPV_METHOD_SPECINFER && (walk >= 2 || draw_here()) && !a.estimate && lead && fabs(w_child - u_child) < 1e-6)
+            atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_ACCEPT], 1u);     // (else these are counted by the walk)
         // SpecInfer moves into the first child it accepts: later children and this node's
         // residual are not needed (the same in every lane: no lane is left behind)
         if (METHOD == MPV_METHOD_SPECINFER && lazy && child_accepted) {
@@ -1785,6 +1824,34 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     //      taken up at once: its rows travel while the leader settles what follows from this
     //      task, and while the others wait to hear of it.
     next_node = uniform_i32(next_node);
+    if (DRAWS && draw_here() && (next_node < 0 || n_children(next_node) == 0)) {
+        // The walk has come to its draw, at this node or at the accepted leaf: every member knows, nothing is announced.
+        const bool row = next_node >= 0;
+        if (!row) {
+            const ResidualConsts rc = cold_residual_consts(At_, Ad_, c);
+            if (lane == 0) { g_cmd.kind = kCmdTiles; g_cmd.nAt = rc.nAt; g_cmd.nAd = rc.nAd; g_cmd.rho = rc.rho; }
+            task_barrier();                                // B
+            weigh_tiles(uniform_f32(rc.nAt), uniform_f32(rc.nAd), uniform_f32(rc.rho));
+            if (lane == 0) { g_draw.nAt = rc.nAt; g_draw.nAd = rc.nAd; g_draw.rho = rc.rho; }
+            task_barrier();                                // A
+        }
+        settle_claim();
+        bool want_claim = false;
+        if (leader && !asked) {
+            want_claim = claims;
+            if (!claims && lane == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxSoon);
+            asked = true;
+        }
+        if (lane == 0) {
+            g_draw.pending = 1;
+            g_draw.b = b;
+            g_draw.n = row ? next_node : n;
+            g_draw.row = row ? 1 : 0;
+            g_loop.want_claim = want_claim ? 1 : 0;
+        }
+        own_task = -1; own_flags = 0;
+        goto task_end;
+    }
     int likely_node = -1;
     if (!team.dead) {
         if (METHOD == MPV_METHOD_TRAVERSAL) {
@@ -1819,8 +1886,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             // so nothing is announced, nothing waited for, and the outcomes settled here are
             // noted for the first task that goes the long way to publish.  (If another branch
             // settles the tree meanwhile, the chain runs on in vain until it ends.)
-            if (METHOD == MPV_METHOD_TRAVERSAL || walk == 0) {
-                if (!(METHOD == MPV_METHOD_TRAVERSAL && paused)) {
+            if (METHOD == MPV_METHOD_TRAVERSAL || walk == 0 || draw_here()) {
+                if (!draw_here() && !(METHOD == MPV_METHOD_TRAVERSAL && paused)) {
                     if (lead) {
                         st_shared_f64(&ws.At[bn], rt.A);
                         st_shared_f64(&ws.Ad[bn], rd.A);
@@ -1988,6 +2055,8 @@ task_end:
     if (leader) {
         next = own_task;
         next_flags = own_flags;
+    } else if (DRAWS && draw_here()) {
+        next = kNothingHeard;                              // (a draw comes next, what follows it is announced in the task loop)
     } else {
         next = team_listen(team, next_flags, ws);
     }
@@ -2002,9 +2071,9 @@ task_end:
     }
     if (!node_next) {
         settle_claim();
-        if (lane == 0) g_cmd.kind = kCmdDone;
-        task_barrier();                                    // B: the other waves leave
+        // (before the others leave: with a draw to come the second wave counts off a first task for the leader then)
         if (lane == 0) {
+            g_cmd.kind = kCmdDone;
             g_loop.team = team;
             g_loop.asked = asked ? 1 : 0;
             g_loop.claims = claims ? 1 : 0;
@@ -2012,6 +2081,7 @@ task_end:
             g_loop.own_task = next;                       // (already announced to, or heard by, the team)
             g_loop.own_flags = next_flags;
         }
+        task_barrier();                                    // B: the other waves leave
         return;
     }
     task = next;
@@ -2064,7 +2134,8 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         }
         team.seq = 0u; team.tseq = 0u; team.dead = 0; team.one_chiplet = 0;
         team.area = ws.exch + static_cast<size_t>(team.id) * 2 * team.size * kExchWords;
-        team.task_word = ws.team_task + static_cast<size_t>(team.id) * 2;
+        // (a line holds the words of eight teams: of one chiplet, like everything that stays in its L2)
+        team.task_word = ws.team_task + static_cast<size_t>(q.same_xcd ? (team.id % 8) * (kMaxTeams / 8) + team.id / 8 : team.id) * 2;
         team.t_start = wall_clock64();
         leader = team.member == 0;
         if (wave == 0) {
@@ -2098,6 +2169,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
                 g_loop.previous_task = -4;            // none yet
                 g_loop.finished = 0;
                 g_loop.kept_task = -1;
+                g_draw.pending = 0;
                 g_tree_of = -1;
             }
         }
@@ -2182,10 +2254,10 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             if (task == kTaskNone) task = team_listen(team, flags, ws);
             own_task = kNothingHeard;
         }
-        const bool sampling = task != kTaskExit && task >= a.B * a.N && task < a.B * a.N + a.B && !(ACCEPT || a.estimate);
+        const bool samples = task != kTaskExit && task >= a.B * a.N && task < a.B * a.N + a.B && !(ACCEPT || a.estimate);
         if (!ACCEPT && a.per_tree && task != kTaskExit) load_shape(reinterpret_cast<const unsigned long long*>(ws.aux), a.N, tree_of_task(task, a.B, a.N));
         bool want_claim = false;
-        if (sampling && leader && !asked) {
+        if (samples && leader && !asked) {
             // the walk and the bonus token come next: one sweep or two, then the team is free
             want_claim = claims;
             if (!claims && threadIdx.x == 0) st_relaxed(&ws.mailbox[team.id * q.box_step], kMailboxSoon);
@@ -2206,7 +2278,29 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
     __syncthreads();
     const int task = uniform_i32(sh_task), flags = uniform_i32(sh_flags);
     if (task == kTaskExit) break;
-    if (task >= a.B * a.N && task < a.B * a.N + a.B) {
+    const bool sampling = task >= a.B * a.N && task < a.B * a.N + a.B;
+    const bool draw_here = KIND == MPV_METHOD_SPECINFER && uniform_i32(q.draw_here) != 0;
+    // the leader's second wave, when the first is busy with a walk's end
+    auto claim_ahead = [&]() __attribute__((always_inline)) {
+        if (leader && threadIdx.x == kWave && g_loop.want_claim) {
+            g_loop.claimed = first_task(q, a, claim_first(ws));
+            if (g_loop.claimed == kTaskNone) {
+                g_loop.claims = 0;
+                st_relaxed(&ws.mailbox[g_loop.team.id * q.box_step], kMailboxSoon);
+            }
+        }
+    };
+    // A walk is over.  The count of trees is waited for by the second wave, or, if there is nothing to go on with, by the
+    // first, which then knows whether the launch is over.
+    auto count_tree = [&]() __attribute__((always_inline)) {
+        const bool by_first = g_loop.claims == 0 && g_loop.claimed == kTaskNone;
+        if (threadIdx.x == (by_first ? 0 : kWave)) {
+            const bool last = tree_done(ws, a);
+            if (by_first && last) g_loop.finished = 1;
+            atomicAdd(&ws.qctl[1], 1);
+        }
+    };
+    if (sampling && !draw_here) {
         if (ACCEPT || a.estimate) {
             // no walk in these modes (there are no uniforms): scalar work of the leader's first
             // wave alone, whichever way the task came
@@ -2220,25 +2314,10 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
             }
             continue;
         }
-        if (leader && threadIdx.x == kWave && g_loop.want_claim) {          // (the first wave is busy with the walk)
-            g_loop.claimed = first_task(q, a, claim_first(ws));
-            if (g_loop.claimed == kTaskNone) {
-                g_loop.claims = 0;
-                st_relaxed(&ws.mailbox[g_loop.team.id * q.box_step], kMailboxSoon);
-            }
-        }
+        claim_ahead();
         // the tree's outcome is settled: walk and bonus token
         const int next = sample_task<E, METHOD>(task - a.B * a.N, (flags >> kFlagStopShift) - 1);
-        if (next < 0 && leader) {
-            // the count of trees is waited for by the second wave, or, if there is nothing to go on with, by the
-            // first, which then knows whether the launch is over
-            const bool by_first = g_loop.claims == 0 && g_loop.claimed == kTaskNone;
-            if (threadIdx.x == (by_first ? 0 : kWave)) {
-                const bool last = tree_done(ws, a);
-                if (by_first && last) g_loop.finished = 1;
-                atomicAdd(&ws.qctl[1], 1);
-            }
-        }
+        if (next < 0 && leader) count_tree();
         if (next >= 0 && wave == 0 && leader) {
             {                                         // a token-following walk goes on
                 Team team = uniform_struct(g_loop.team);          // (as sample_task left it)
@@ -2258,7 +2337,18 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         }
         continue;
     }
-    run_node_task<E, KIND>(task, flags);
+    if (!sampling) run_node_task<E, KIND>(task, flags);
+    if constexpr (KIND == MPV_METHOD_SPECINFER) {
+        if (!draw_here || !(sampling || uniform_i32(g_draw.pending) != 0)) continue;
+        // the walk has come to a draw: the node task's that has just ended, or its first step
+        claim_ahead();
+        const int next = draw_walk<E>(sampling ? task - a.B * a.N : g_draw.b, sampling ? 0 : g_draw.n, sampling ? 1 : g_draw.row);
+        if (next < 0 && leader) count_tree();
+        if (threadIdx.x == 0) {
+            g_draw.pending = 0;
+            if (next >= 0) { g_loop.own_task = next; g_loop.own_flags = 0; }          // every member knows: it is not announced
+        }
+    }
     }   // task loop
 }
 
@@ -2771,6 +2861,154 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
     return next;
 }
 
+// ------------------------------------------------------------------ draws of the top-down rules
+//
+// The end of every top-down walk, and every step of a token-following one, by the whole team.  Either the node task that has
+// just ended has weighed the tiles of its pair, which it had on chip (the walk stops at its node), or the token comes from p at
+// a leaf (NSS: at any node): then the target row is asked for here, once, straight into LDS, and every wave weighs its
+// tiles against its own largest logit, so that the row's sum and the members' shares of it are one exchange, not two, and no
+// logarithm.  The member whose part holds the target finds the tile, and the wave that has it the token; a pair's tile is
+// read again for that (2 KB: the registers that held it are gone, and keeping them took others from the sweeps).
+//
+// Latency only.  Before, a walk that had come to its end left the node task, was sent back through the task loop to
+// sample_task, which read the rows once more, and for a leaf had two exchanges: 64 trees of V = 128256 on teams of 12,
+// from the last test to the token 12 us (an inner node) and 16 (a leaf), now 6 and 7 (call: 88 -> 82 us; 32 of V = 262144:
+// 73 -> 63; 37 of V = 50001, SpecTr: 87 -> 79; 186 of V = 1974, Naive: 96 -> 58).  sample_task stays for Traversal, whose walk
+// stops at a node that another team may have had, for parts of more slots than are kept, and for the debug outputs.
+//
+// Returns the task that follows (-1: the walk is over; the same in every lane of every member).
+
+// The token inside the tile that holds the target, by the wave that has it.
+template <class E>
+__device__ __forceinline__ void draw_find(const TaskDraw<E>& d, bool row, int b, int wave, int lane) {
+    const Args& a = lds_launch().a;
+    bool near = false;
+    const int tok = d.find(uniform_i32(g_draw.in_tile), row, lane, g_draw.rem, g_draw.total, near);
+    if (tok >= 0) {
+        as_global(a.bonus)[b] = tok;
+        g_draw.token = tok;
+        if (near) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
+    }
+}
+
+// First wave, when every wave has weighed its tiles: who has the target (u times the mass of the whole row), and in which tile.
+__device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
+    const int lane = lane_here();
+    // this workgroup's tiles, lane t that of tile t, in units of 2^unit
+    const float unit = fmaxf(fmaxf(g_sh.partf[0][0], g_sh.partf[1][0]), fmaxf(g_sh.partf[2][0], g_sh.partf[3][0]));
+    const float of_wave = fast_exp2(g_sh.partf[draw_wave(lane)][0] - unit);
+    const double in_tile = lane < 2 + kTaskWaves * slots ? static_cast<double>(g_draw.tile[lane]) * static_cast<double>(of_wave) : 0.0;
+    const double incl = wave_inclusive_scan(in_tile), own = lane_f64(incl, kWave - 1);
+    unsigned got[3] = {half_of(own, 0), half_of(own, 1), __float_as_uint(unit)};
+    team.seq++;
+    if (team.size > 1) {
+        const int at[3] = {0, 1, 2};
+        note_dead(team, swap_words<1>(team, lane < 2 ? half_of(own, lane & 1) : __float_as_uint(unit), 3, at, got));
+    }
+    const bool live = lane < team.size && !team.dead;
+    const float of_m = live ? __uint_as_float(got[2]) : OnlineLse::kFloor, team_unit = lane_f32(row_max(of_m), 0);
+    const double mass = live ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) * static_cast<double>(fast_exp2(of_m - team_unit)) : 0.0;
+    double upto = mass;                                // sums along the row of lanes: member m and those before it
+    upto += dpp_f64<0x111>(upto);
+    upto += dpp_f64<0x112>(upto);
+    upto += dpp_f64<0x114>(upto);
+    upto += dpp_f64<0x118>(upto);
+    const double total = lane_f64(upto, team.size - 1), target = static_cast<double>(u) * total;
+    // the first member whose running total exceeds the target and that has mass; rounding only: the last one that has mass
+    const unsigned long long hit = __ballot(mass > 0.0 && upto > target), any = __ballot(mass > 0.0);
+    const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
+    if (lane == 0) g_draw.owner = owner;
+    if (owner != team.member) return;
+    const double scale = static_cast<double>(fast_exp2(unit - team_unit));          // (this member has mass, or nobody has)
+    const double here = (target - lane_f64(dpp_f64<0x111>(upto), owner)) / scale;
+    const unsigned long long hit_t = __ballot(in_tile > 0.0 && incl > here), any_t = __ballot(in_tile > 0.0);
+    const int tile = hit_t ? __ffsll(static_cast<long long>(hit_t)) - 1 : any_t ? 63 - __clzll(static_cast<long long>(any_t)) : 1;
+    if (lane == tile) {
+        const double of_tile = static_cast<double>(of_wave);
+        g_draw.in_tile = tile;
+        g_draw.rem = (here - (incl - in_tile)) / of_tile;
+        g_draw.total = total / scale / of_tile;
+    }
+}
+
+template <class E>
+__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in) {
+    using T = typename E::T;
+    const Args& a = lds_launch().a;
+    const Workspace& ws = lds_launch().ws;
+    const TreeDesc& tree = g_tree;
+    (void)ws;
+    const int b = uniform_i32(b_in), walk = uniform_i32(a.walk), N = uniform_i32(a.N), V = uniform_i32(a.V);
+    const int lane = threadIdx.x & (kWave - 1), wave = uniform_i32(static_cast<int>(threadIdx.x) / kWave);
+    const int part_vecs = uniform_i32(lds_launch().q.part_vecs);
+    int n = uniform_i32(n_in);
+    bool row = uniform_i32(row_in) != 0;
+    Team team = uniform_struct(g_loop.team);           // every wave its copy; the first wave's counts exchanges
+    const bool leader = team.member == 0;
+    const size_t at = static_cast<size_t>(b) * N;
+    const T* const zt0 = uniform_ptr(static_cast<const T*>(a.zt)) + at * V;
+    const T* const zd0 = uniform_ptr(static_cast<const T*>(a.zd)) + at * V;
+    TaskPart<E> part;
+    TaskDraw<E> d(part);
+    d.k32 = uniform_f32(a.k32);
+    int next = -1;
+    for (;;) {
+        const size_t off = static_cast<size_t>(n) * V;
+        part.setup(zt0 + off, zd0 + off, V, g_rows, g_rows + kLdsVecs * kTaskBlock, threadIdx.x, team.member, team.size, part_vecs);
+        const int k = walk ? uniform_i32(tree.nchild[n]) : 0;
+        float u = 0.f;
+        int child = 0, child_token = -1;               // lane j < k: child j
+        if (wave == 0) {                               // (asked for ahead of the row)
+            u = walk ? as_global(a.draw_uniforms)[at + n] : as_global(a.uniforms)[at];
+            if (lane < k) {
+                child = tree.child_list[tree.child_off[n] + lane];
+                child_token = as_global(a.tokens)[at + child];
+            }
+        }
+        if (row) {
+            d.weigh_row(g_draw.tile, wave, lane);
+            if (lane == 0) g_sh.partf[wave][0] = d.mk;
+        } else {
+            d.f.init(d.k32, uniform_f32(g_draw.nAt), uniform_f32(g_draw.nAd), uniform_f32(g_draw.rho));
+        }
+        task_barrier();
+        if (wave == 0) draw_owner(team, part.nslots, u);
+        else if (wave == 2 && leader && k == 0) write_path(tree, a, b, n);          // (the walk ends here)
+        task_barrier();
+        if (uniform_i32(g_draw.owner) == team.member && wave == draw_wave(uniform_i32(g_draw.in_tile))) draw_find<E>(d, row, b, wave, lane);
+        if (k == 0) break;
+        // Sec. 3.2: if the drawn token is a child's token the walk moves to that child (the first such child in list order),
+        // otherwise it ends here.  Everybody needs the token (the owner's word; the others' say only that they have come
+        // this far).
+        task_barrier();
+        if (wave == 0) {
+            unsigned got[1] = {static_cast<unsigned>(g_draw.token)};
+            team.seq++;
+            if (team.size > 1) {
+                const int word[1] = {0};
+                note_dead(team, swap_words<1>(team, got[0], 1, word, got));
+            }
+            const int tok = __builtin_amdgcn_readlane(static_cast<int>(got[0]), uniform_i32(g_draw.owner));
+            const unsigned long long m = __ballot(lane < k && child_token == tok);
+            int to = -1;
+            if (m != 0ull && !team.dead) to = __builtin_amdgcn_readlane(child, __ffsll(static_cast<long long>(m)) - 1);
+            else if (leader && lane == 0) write_path(tree, a, b, n);
+            if (lane == 0) g_draw.next = to;
+        }
+        task_barrier();
+        n = uniform_i32(g_draw.next);
+        if (n < 0) break;
+        // Naive and SpecTr test children of an inner node before they draw there; NSS and leaves draw at once
+        if (walk >= 2 && uniform_i32(tree.nchild[n]) > 0) {
+            next = b * N + n;
+            break;
+        }
+        row = true;
+    }
+    if (threadIdx.x == 0) g_loop.team = team;          // (the task loop reads it after its barrier)
+    return next;
+}
+
 // ------------------------------------------------------------------ stand-alone row statistics
 
 template <class E>
@@ -3151,6 +3389,9 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
     q.same_xcd = shape.same_xcd;
+    // Where the last slot of a part is kept, or is the one that a sweep reads again; longer parts are drawn from by sample_task,
+    // like the calls with debug outputs of the draw (64 trees of V = 128256, SpecInfer: 88 us by it, 82 by draw_walk).
+    q.draw_here = top_down && a.lazy && !a.estimate && !a.dbg_accept && !a.dbg_resid && q.part_vecs <= kPartCapacity + kTaskBlock ? 1 : 0;
     q.box_step = 16;                                   // a cache line each, while there is room for it
     while (q.teams * q.box_step > kMailboxWords) q.box_step /= 2;
     // (The few teams that launch_shape adds to fill whole chiplets are not meant: with them in the comparison the branching

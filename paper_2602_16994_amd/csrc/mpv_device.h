@@ -905,4 +905,184 @@ struct ResidualMassRawF {
     __device__ __forceinline__ double total() const { return 2.0 * (static_cast<double>(acc0) + static_cast<double>(acc1)); }
 };
 
+// ---------------------------------------------------------------- drawing a token from the part on chip
+//
+// The draw (inverse CDF in vocabulary order) of a part that is on chip, of a pair after its sweeps or of a target row alone,
+// goes by tiles: slot s of wave w, 64 vectors that follow each other in the vocabulary.  Tile 0 holds the elements before
+// the aligned vectors, tile 1 + 4 s + w is slot s of wave w, and the elements after the vectors are the last one.
+constexpr int kDrawTiles = 64;                            // a lane of the first wave looks after each
+
+// The masses of one vector's elements, in one of two units.  A pair: half of (e_t - rho e_d)_+ as the residual sweeps add it
+// up.  A row: 2^(z k32 - mk), mk the wave's reference.  A row alone lies in LDS, where the loops over its slots need not be
+// unrolled (the task functions are larger than the instruction cache as they are).
+template <class E, int BLOCK, int R, int L>
+struct PartDraw {
+    using P = RetainedPart<E, BLOCK, R, L>;
+    static constexpr int VEC = E::VEC, NW = BLOCK / kWave, kSlots = R + L + 1;      // (the last is not kept: see ask_overflow)
+    static_assert(2 + NW * kSlots <= kDrawTiles && R == L, "a lane per tile; a row alone takes the draft's share of the LDS too");
+    P& p;
+    ResidualMassRawF<E> f;            // a pair: its constants
+    float k32, mk;                    // a row: its reference
+    __device__ __forceinline__ PartDraw(P& p_) : p(p_) {}
+
+    // ---- a target row alone: slot s at lt[s][lane], as stored
+    __device__ __forceinline__ void ask_row(uint4& more) {
+        const int wave0 = (p.tid / kWave) * kWave;
+        for (int s = 0; s < min(p.nslots, R + L); ++s)
+            load_to_lds_16B(p.bt + static_cast<size_t>(p.vec_of(s)) * VEC, p.lt + s * BLOCK + wave0);
+        more = NegInfVec<E>::v();
+        if (p.has_overflow()) more = load_raw_at(p.bt, p.vec_of(R + L));
+    }
+    __device__ __forceinline__ uint4 row_vector(int s, const uint4& more) const { return s < R + L ? p.lt[s * BLOCK + p.tid] : more; }
+    __device__ __forceinline__ void row_masses(int s, const uint4& v, float (&r)[VEC]) const {
+        float x[VEC];
+        E::unpack(v, x);
+        const float ref = p.inside(s) ? -mk : -INFINITY;           // (past the end: no mass)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) r[i] = fast_exp2(fmaf(x[i], k32, ref));
+    }
+    // ---- a pair
+    __device__ __forceinline__ void pair_masses(const uint4& a, const uint4& d, bool kept, float (&r)[VEC]) const {
+        float x[VEC], y[VEC];
+        E::unpack(a, x);
+        E::unpack(d, y);
+        if (kept) { E::unpack_kept(a, x); E::unpack_kept(d, y); }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) r[i] = f.term(x[i], y[i]);
+    }
+    // slot s >= R: kept in LDS, or read again
+    __device__ __forceinline__ void pair_vectors(int s, uint4& a, uint4& d) const {
+        if (s < R + L) {
+            a = p.lt[(s - R) * BLOCK + p.tid];
+            d = p.ld[(s - R) * BLOCK + p.tid];
+        } else {
+            p.ask_overflow(a, d);
+            if (!p.inside(s)) { a = NegInfVec<E>::v(); d = a; }
+        }
+    }
+    // this lane's element before / after the aligned vectors
+    template <bool ROW>
+    __device__ __forceinline__ float edge(bool last) const {
+        const int e = last ? p.tail0 + p.tid : p.tid;
+        float a = -INFINITY, b = -INFINITY;
+        if (last ? p.last_part && e < p.V : p.first_part && e < p.head) {
+            a = E::load_one_global(p.zt + e);
+            if (!ROW) b = E::load_one_global(p.zd + e);
+        }
+        return ROW ? a : f.term(a, b);
+    }
+    __device__ __forceinline__ static float sum(const float (&r)[VEC]) {
+        float t0 = r[0], t1 = r[1];
+#pragma unroll
+        for (int i = 2; i < VEC; i += 2) { t0 += r[i]; t1 += r[i + 1]; }
+        return t0 + t1;
+    }
+
+    // the masses of this wave's tiles (the first wave's lanes hold the elements at the row's ends: fewer than a vector's)
+    __device__ __forceinline__ void weigh_pair(float* tile, int wave, int lane) const {
+        float mine = 0.f;                                 // lane s: slot s
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            if (s < p.nslots) {
+                float r[VEC];
+                pair_masses(p.rt[s], p.rd[s], true, r);
+                const float of_tile = wave_sum_f32(sum(r));
+                if (lane == s) mine = of_tile;
+            }
+            __builtin_amdgcn_sched_barrier(0);            // (slots side by side take registers that there are not)
+        }
+        for (int s = R; s < p.nslots; ++s) {
+            uint4 a, d;
+            pair_vectors(s, a, d);
+            float r[VEC];
+            pair_masses(a, d, s < R + L, r);
+            const float of_tile = wave_sum_f32(sum(r));
+            if (lane == s) mine = of_tile;
+        }
+        if (lane < p.nslots) tile[1 + NW * lane + wave] = mine;
+        if (wave == 0) {
+            const float first = wave_sum_f32(edge<false>(false)), last = wave_sum_f32(edge<false>(true));
+            if (lane == 0) { tile[0] = first; tile[1 + NW * p.nslots] = last; }
+        }
+    }
+    // a row, asked for here; mk: the largest exponent of this wave's share
+    __device__ __forceinline__ void weigh_row(float* tile, int wave, int lane) {
+        uint4 more;
+        ask_row(more);
+        const float before = edge<true>(false), after = edge<true>(true);
+        float m = fmaxf(before, after);
+        for (int s = 0; s < p.nslots; ++s) {
+            float x[VEC];
+            E::unpack(row_vector(s, more), x);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) m = fmaxf(m, x[i]);       // (a lane past the end holds the part's last vector)
+        }
+        mk = fmaxf(wave_max(m) * k32, OnlineLse::kFloor);
+        float mine = 0.f;
+        for (int s = 0; s < p.nslots; ++s) {
+            float r[VEC];
+            row_masses(s, row_vector(s, more), r);
+            const float of_tile = wave_sum_f32(sum(r));
+            if (lane == s) mine = of_tile;
+        }
+        if (lane < p.nslots) tile[1 + NW * lane + wave] = mine;
+        if (wave == 0) {
+            const float first = wave_sum_f32(fast_exp2(fmaf(before, k32, -mk))), last = wave_sum_f32(fast_exp2(fmaf(after, k32, -mk)));
+            if (lane == 0) { tile[0] = first; tile[1 + NW * p.nslots] = last; }
+        }
+    }
+    // The token in which the running mass of tile t passes `rem`, by the wave that has the tile; near: whether it lies within
+    // 1e-6 of the total from one of the token's own ends.  (Rounding only: the last one that has mass.)  Returned in one lane,
+    // -1 in the others.  A pair's vectors are read again, as stored.
+    __device__ __forceinline__ int find(int t, bool row, int lane, double rem, double total, bool& near) const {
+        float r[VEC];
+        int first = 0, step = VEC;                        // token of the lane's first element: first + lane * step
+        if (t == 0 || t == 1 + NW * p.nslots) {
+#pragma unroll
+            for (int i = 1; i < VEC; ++i) r[i] = 0.f;
+            r[0] = row ? fast_exp2(fmaf(edge<true>(t != 0), k32, -mk)) : edge<false>(t != 0);
+            first = t ? p.tail0 : 0;
+            step = 1;
+        } else {
+            const int s = (t - 1) / NW;
+            uint4 a, d;
+            if (row && s < R + L) {
+                a = p.lt[s * BLOCK + p.tid];
+            } else {
+                a = load_raw_at(p.bt, p.vec_of(s));
+                if (!row) d = load_raw_at(p.bd, p.vec_of(s));
+            }
+            if (row) {
+                row_masses(s, a, r);
+            } else {
+                if (!p.inside(s)) { a = NegInfVec<E>::v(); d = a; }
+                pair_masses(a, d, false, r);
+            }
+            first = p.head + (p.v0 + (t - 1) * kWave) * VEC;
+        }
+        const float ls = sum(r);
+        const double lsd = static_cast<double>(ls), incl = wave_inclusive_scan(lsd);
+        const unsigned long long hit = __ballot(incl > rem && ls > 0.f);
+        int owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
+        if (owner < 0) {
+            const unsigned long long any = __ballot(ls > 0.f);
+            owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
+        }
+        if (lane != owner) return -1;
+        double acc = incl - lsd;
+        int found = -1, last = 0;
+        double lo = acc, hi = acc;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const double ri = static_cast<double>(r[i]);
+            if (ri > 0.0) last = i;
+            if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
+            acc += ri;
+        }
+        if (found < 0) { found = last; lo = rem; hi = rem; }
+        near = fmin(fabs(rem - lo), fabs(hi - rem)) < 1e-6 * total;
+        return min(max(first + lane * step + found, 0), p.V - 1);
+    }
+};
+
 }  // namespace mpv

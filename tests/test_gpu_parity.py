@@ -431,6 +431,20 @@ def test_the_draw_reads_rows_of_any_offset(method, V, dtype, B):
     compare_with_oracle(method, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, max(1, B // 30)), check_debug=False)
 
 
+@pytest.mark.parametrize("V,dtype,B", [
+    (24576, "bf16", 400), (24577, "bf16", 400), (25601, "bf16", 400),     # one member: 12 slots full, one more, half of it
+    (12287, "f32", 400),
+    (425984, "bf16", 2), (425992, "bf16", 2),                             # 16 members: the 13th slot full; one vector too many
+])
+@pytest.mark.parametrize("method", ALL_METHODS[:1] + ALL_METHODS[2:])
+def test_the_draw_at_the_edges_of_what_is_kept(method, V, dtype, B):
+    """Top-down rules draw from the part that a workgroup keeps: at its last slot, at the one that is read again, and
+    beyond them, where the rows are read once more by the other way (which the debug run takes everywhere)."""
+    cfg = workloads.Config("kept edges", B=B, V=V, K=2, L1=0, L2=1, dtype=dtype, T=0.9, methods=[method], draft_sigma=1.0, target_sigma=0.7, seed=97 + V)
+    rep, _ = run_case(cfg, method, trees=range(min(B, 12)))
+    assert rep["trees"] == min(B, 12)
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
