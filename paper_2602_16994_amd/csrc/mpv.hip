@@ -103,6 +103,7 @@ struct QueuePlan {
     int32_t box_step;                    // words from one team's mailbox to the next
     int32_t same_xcd;                    // members of a team are 8 workgroup numbers apart (one chiplet, its L2)
     int32_t spare;                       // teams are left over from the start (not counting those that whole chiplets add)
+    int32_t ahead;                       // a part leaves the LDS free: the rows that will likely be next are asked for there (see launch_all)
     int32_t draw_here;                   // top-down rules: node tasks draw the tokens themselves, from the part on chip (see launch_all)
 };
 
@@ -227,6 +228,8 @@ constexpr int kWorkerSlots = 8;                       // mailboxes per dispatche
 constexpr int kMaxTeams = kWave * kWorkerSlots;
 static_assert(kMaxTeams <= kMailboxWords, "a mailbox for every team");
 constexpr int kKindAcceptance = 100;                   // node_task_kernel instantiation for the acceptance rates (see there)
+constexpr int kKindShort = 200;                        // top-down rules, parts that the registers hold (short_part_kernel)
+constexpr int method_of(int kind) { return kind == kKindAcceptance || kind == kKindShort ? MPV_METHOD_SPECINFER : kind; }
 
 // LDS of node_task_kernel that the functions it calls use as well (file scope, so that they address
 // it as LDS and not through generic pointers)
@@ -1004,7 +1007,7 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in);
 
 // (defined below) draws of a top-down walk of tree b, from node n on; returns the task that follows (-1: none)
 template <class E>
-__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in);
+__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in, int there_in);
 
 // (defined below) expected block efficiency of tree b from the per-node results, by the first wave
 template <int METHOD>
@@ -1049,6 +1052,8 @@ struct SweepCmd {
     int m, naive;                    // acceptance sweep: exponent, which formula (kCmdTask: m = the task)
     int claim;                       // a sweep: the second wave counts off a first task meanwhile (g_claim_number)
     int b, n;                        // kCmdTask: its tree and node;  a sweep: n = the node of `next`, in the same tree
+    int ahead, ahead_row;            // kCmdTask: the node of this tree whose rows are asked for when its first sweep is over (-1: none;
+                                     // ahead_row: only the target's, for a draw), by the waves that then wait
     int next;                        // a sweep: the task this team goes on with when the sweep was the
                                      // current task's last (-1: not known); each wave asks for its share
                                      // of that task's rows as soon as it is done with its share of the sweep
@@ -1059,6 +1064,7 @@ __shared__ int g_claim_number;
 struct DrawShared {
     float tile[kDrawTiles];          // the masses of this member's tiles, in units of 2^(g_sh.partf of the wave)
     float nAt, nAd, rho;             // a pair: the constants they were weighed with
+    int there;                       // the row lies in LDS already (RetainedPart::ask_ahead)
     int pending, b, n, row;          // the node task that has just ended has come to this draw: tree, node, from a target row alone
     int owner, in_tile, token, next;
     double rem, total;               // of the tile that holds the target: mass to cover inside it; the whole row's, in the same unit
@@ -1069,7 +1075,7 @@ __shared__ DrawShared g_draw;
 template <class E, int KIND, class PAIR>
 __device__ __forceinline__ void run_sweep(PAIR& pair, const SweepCmd& cmd, float k32, int wave, int lane) {
     constexpr bool ACCEPT = KIND == kKindAcceptance;
-    constexpr bool SLOPE = KIND != MPV_METHOD_TRAVERSAL;      // SpecTr's search exists in the top-down kernels only
+    constexpr bool SLOPE = method_of(KIND) != MPV_METHOD_TRAVERSAL;      // SpecTr's search exists in the top-down kernels only
     double s0 = 0.0, s1 = 0.0;
     if (SLOPE && cmd.kind == kCmdMassSlope) {
         ResidualMassSlopeRawF<E> f;
@@ -1161,14 +1167,14 @@ template <class E> using TaskDraw = PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs>;
 template <class E, int KIND>
 __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_in) {
     using T = typename E::T;
-    constexpr bool ACCEPT = KIND == kKindAcceptance;
-    constexpr int METHOD = ACCEPT ? MPV_METHOD_SPECINFER : KIND;
+    constexpr bool ACCEPT = KIND == kKindAcceptance, SHORT = KIND == kKindShort;
+    constexpr int METHOD = method_of(KIND);
     // Trees with shapes of their own: a task of another tree has its tables loaded here (Traversal), or it goes back to the
     // task loop, which loads them.  The top-down rules run this function through its whole length for SpecTr, and the loads
     // within it made plain batches of many trees slower (Naive, 204 trees of V = 7872: 246 us, 237 without); Traversal
     // has no such cost, and going back would make 256 trees of V = 151936 slower (538 us, 531).
     constexpr bool kShapeInTask = !ACCEPT && METHOD == MPV_METHOD_TRAVERSAL;
-    constexpr bool DRAWS = KIND == MPV_METHOD_SPECINFER;
+    constexpr bool DRAWS = !ACCEPT && METHOD == MPV_METHOD_SPECINFER;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
     const QueuePlan& q = lds_launch().q;
@@ -1212,9 +1218,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     };
 
     // ---- the part of the pair this member keeps on chip while a task runs
-    RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs> pair;
+    RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs, SHORT> pair;
     auto weigh_tiles = [&](float nAt, float nAd, float rho) __attribute__((always_inline)) {
-        TaskDraw<E> d(pair);
+        PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs, SHORT> d(pair);
         d.f.init(k32, nAt, nAd, rho);
         d.weigh_pair(g_draw.tile, wave, lane);
         if (lane == 0) g_sh.partf[wave][0] = 0.f;
@@ -1224,11 +1230,13 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // ---- a sweeping wave does what the first wave commands: it takes up a task (loads its
         //      share of the pair and runs the statistics sweep) or sweeps once more
         int asked_for = -1;                               // the task whose rows this wave has asked for already
+        int ahead = -1;                                   // the task whose rows are in LDS
         auto take_up = [&](int t, const NodeView& nv) __attribute__((always_inline)) {
             int tid_l = threadIdx.x;
             asm volatile("" : "+v"(tid_l));     // per-task copy: nothing derived from it is kept across tasks
             pair.setup(nv.zt, nv.zd, V, lds_t, lds_d, tid_l, member, team_size, part_vecs);
-            pair.issue_loads();
+            if (!SHORT || t != ahead) pair.issue_loads();
+            ahead = -1;
             asked_for = t;
         };
         for (;;) {
@@ -1236,11 +1244,15 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             const SweepCmd cmd = g_cmd;
             const int kind = uniform_i32(cmd.kind);
             if (kind == kCmdDone) {
-                if (asked_for >= 0) wait_memory();        // (asked for in vain: nothing may land in LDS after this)
+                if (SHORT || asked_for >= 0) wait_memory();        // (asked for in vain, or for the draw: nothing may land in LDS after this)
                 return;
             }
             if (kind == kCmdTask) {
                 const int t = uniform_i32(cmd.m);
+                if (SHORT) {                              // what has been asked for ahead is there, or at least out of the way:
+                    wait_memory();                        // each wave waits for its own, then all of them for each other
+                    task_barrier();                       // C
+                }
                 if (asked_for != t) take_up(t, view_at(cmd.b, cmd.n, false));
                 asked_for = -1;
                 PairStatsRawF<E, ACCEPT> f;
@@ -1262,10 +1274,19 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 if (claims_now && lane == 0) claim_number = claim_first(ws);
                 run_sweep<E, KIND>(pair, cmd, k32, wave, lane);
                 if (claims_now && lane == 0) g_claim_number = claim_number;
-                const int nx = uniform_i32(cmd.next);
+                const int nx = uniform_i32(cmd.next);       // (Traversal only)
                 if (nx >= 0) take_up(nx, view_at(cmd.b, cmd.n, false));     // this wave's slots are free again: the next task's rows
             }
             task_barrier();                                // A: this wave's partial sums are there
+            if (SHORT && kind == kCmdTask && uniform_i32(cmd.ahead) >= 0) {
+                // every wave has its vectors in registers: the LDS is free
+                const NodeView nx = view_at(cmd.b, cmd.ahead, false);
+                TaskPart<E> then;
+                then.setup(nx.zt, nx.zd, V, lds_t, lds_d, threadIdx.x, member, team_size, part_vecs);
+                const bool row = uniform_i32(cmd.ahead_row) != 0;
+                then.ask_ahead(wave - 1, kTaskWaves - 1, !row);
+                ahead = row ? -1 : uniform_i32(cmd.b) * N + uniform_i32(cmd.ahead);
+            }
         }
     }
 
@@ -1340,11 +1361,40 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     };
     load_tables();
     auto gather = [&](int from_lane, int v) __attribute__((always_inline)) { return __builtin_amdgcn_ds_bpermute(from_lane << 2, v); };
+    // Walks draw their tokens in draw_walk, which is called next; a pair's tiles are weighed here, where it is on chip.
+    const int draws = DRAWS ? uniform_i32(q.draw_here) : 0;
+    // (Known to be the same each time, the compiler makes paths of their own of it, which take 140 registers to private memory.)
+    auto draw_here = [&]() __attribute__((always_inline)) {
+        if constexpr (!DRAWS) return false;
+        int x = draws;
+        asm volatile("" : "+s"(x));
+        return x != 0;
+    };
+    // The rows asked for ahead (see start_task): their node, -1: none; only a leaf's target row; the task they belong to.
+    int ahead_node = -1, ahead_task = -1;
+    bool ahead_row = false, there = false;            // (there: of the task under way: its rows were there when it was taken up)
     // Takes a task up: the other waves are told, this wave's share of the pair is asked for, then the children's logits
     // (tokens and uniforms once per tree, so that nothing waits for a load that depends on a load).
     auto start_task = [&](const NodeView& v, int t) __attribute__((always_inline)) {
+        const bool ready = SHORT && t == ahead_task;
+        if (SHORT) {
+            // What comes next if it is accepted: the first child (its rows, or a leaf's target row).
+            ahead_node = -1;
+            ahead_row = false;
+            if (uniform_i32(q.ahead) != 0) {
+                const int first = field(node_word(field(node_word(v.n), kOff, 63u)), kEntry, 63u);
+                const bool inner = n_children(first) > 0;
+                if (inner || draw_here()) {
+                    ahead_node = first;
+                    ahead_row = !inner;
+                }
+            }
+            ahead_task = ahead_node >= 0 && !ahead_row ? v.b * N + ahead_node : -1;
+            if (lane == 0) { g_cmd.ahead = ahead_node; g_cmd.ahead_row = ahead_row ? 1 : 0; }
+        }
         if (lane == 0) { g_cmd.kind = kCmdTask; g_cmd.m = t; g_cmd.b = v.b; g_cmd.n = v.n; }
         task_barrier();                                    // B: the other waves take the task up
+        if (SHORT) task_barrier();                         // C: the LDS is theirs to write
         int tid_l = threadIdx.x;
         asm volatile("" : "+v"(tid_l));     // per-task copy: nothing derived from it is kept across tasks
         pair.setup(v.zt, v.zd, V, lds_t, lds_d, tid_l, member, team_size, part_vecs);
@@ -1359,7 +1409,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             tokens = as_global(a.tokens)[at];
             if (!a.estimate) uniforms = as_global(a.uniforms)[at];
         }
-        pair.issue_loads();
+        there = ready;
+        if (!ready) pair.issue_loads();
         // (lanes read each other's registers here, not LDS: the compiler would wait for the loads that go there)
         const int own = lane_here(), j = own & 31, k = n_children(v.n);
         const int child = field(static_cast<unsigned>(gather(field(node_word(v.n), kOff, 63u) + j, static_cast<int>(nodes))), kEntry, 63u);
@@ -1378,15 +1429,6 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     unsigned long long chain_settled = 0ull, chain_accepted = 0ull;
     double a0_known = -1.0;
     int chained = -1;                                 // the node of the task handed on to (same tree)
-    // Walks draw their tokens in draw_walk, which is called next; a pair's tiles are weighed here, where it is on chip.
-    const int draws = DRAWS ? uniform_i32(q.draw_here) : 0;
-    // (Known to be the same each time, the compiler makes paths of their own of it, which take 140 registers to private memory.)
-    auto draw_here = [&]() __attribute__((always_inline)) {
-        if constexpr (!DRAWS) return false;
-        int x = draws;
-        asm volatile("" : "+s"(x));
-        return x != 0;
-    };
     // One node task after the other, for as long as the team knows its next one itself (the task
     // a node task hands to its own team: a child's, or the rest of the node where the tree
     // branches): no way back through the task loop, no queue in between.
@@ -1474,7 +1516,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         if (wants_a0) bits = ld_relaxed(reinterpret_cast<const unsigned long long*>(&ws.a0[bn]));
         PairStatsRawF<E, ACCEPT> f;
         f.t.init(); f.d.init(); f.k32 = k32;
-        pair.first_pass(f);
+        pair.first_pass(f, there);
         f.t.finish(); f.d.finish();
         double a0 = 1.0;
         if (wants_a0) {
@@ -1847,6 +1889,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             g_draw.b = b;
             g_draw.n = row ? next_node : n;
             g_draw.row = row ? 1 : 0;
+            g_draw.there = row && ahead_row && ahead_node == next_node ? 1 : 0;
             g_loop.want_claim = want_claim ? 1 : 0;
         }
         own_task = -1; own_flags = 0;
@@ -2090,17 +2133,13 @@ task_end:
 }
 
 
-// (disable_tail_calls: a call marked as a possible tail call makes the compiler treat the callee
-// as one that must preserve registers for its caller, and the task functions, which use nearly
-// all of them, would save and restore dozens per call in private memory)
 template <class E, int KIND>
-__global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
-void node_task_kernel(const LaunchBlock* __restrict__ launch) {
-    // KIND: MPV_METHOD_SPECINFER (all top-down rules) or MPV_METHOD_TRAVERSAL, or kKindAcceptance: the
+__device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch) {
+    // KIND: MPV_METHOD_SPECINFER (all top-down rules) or MPV_METHOD_TRAVERSAL, kKindShort (top-down rules), or kKindAcceptance: the
     // top-down kernel reduced to what the acceptance rates need (an instantiation of its own, so that
     // its extra sweeps do not weigh on the register allocation of the verification kernels)
     constexpr bool ACCEPT = KIND == kKindAcceptance;
-    constexpr int METHOD = ACCEPT ? MPV_METHOD_SPECINFER : KIND;
+    constexpr int METHOD = method_of(KIND);
     __shared__ int sh_task, sh_flags;
     // The launch parameters and the tree tables are read from LDS, copied there from the
     // workspace (init_kernel put them there): as kernel arguments, handed on by reference or
@@ -2279,7 +2318,7 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
     const int task = uniform_i32(sh_task), flags = uniform_i32(sh_flags);
     if (task == kTaskExit) break;
     const bool sampling = task >= a.B * a.N && task < a.B * a.N + a.B;
-    const bool draw_here = KIND == MPV_METHOD_SPECINFER && uniform_i32(q.draw_here) != 0;
+    const bool draw_here = !ACCEPT && METHOD == MPV_METHOD_SPECINFER && uniform_i32(q.draw_here) != 0;
     // the leader's second wave, when the first is busy with a walk's end
     auto claim_ahead = [&]() __attribute__((always_inline)) {
         if (leader && threadIdx.x == kWave && g_loop.want_claim) {
@@ -2338,11 +2377,11 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
         continue;
     }
     if (!sampling) run_node_task<E, KIND>(task, flags);
-    if constexpr (KIND == MPV_METHOD_SPECINFER) {
+    if constexpr (!ACCEPT && METHOD == MPV_METHOD_SPECINFER) {
         if (!draw_here || !(sampling || uniform_i32(g_draw.pending) != 0)) continue;
         // the walk has come to a draw: the node task's that has just ended, or its first step
         claim_ahead();
-        const int next = draw_walk<E>(sampling ? task - a.B * a.N : g_draw.b, sampling ? 0 : g_draw.n, sampling ? 1 : g_draw.row);
+        const int next = draw_walk<E>(sampling ? task - a.B * a.N : g_draw.b, sampling ? 0 : g_draw.n, sampling ? 1 : g_draw.row, sampling ? 0 : g_draw.there);
         if (next < 0 && leader) count_tree();
         if (threadIdx.x == 0) {
             g_draw.pending = 0;
@@ -2351,6 +2390,24 @@ void node_task_kernel(const LaunchBlock* __restrict__ launch) {
     }
     }   // task loop
 }
+
+// (disable_tail_calls: a call marked as a possible tail call makes the compiler treat the callee
+// as one that must preserve registers for its caller, and the task functions, which use nearly
+// all of them, would save and restore dozens per call in private memory)
+template <class E, int KIND>
+__global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
+void node_task_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, KIND>(launch); }
+
+// The top-down rules on parts that the registers hold (six vectors of a row per lane).  Their rows come through the LDS, and
+// as soon as the first sweep has taken them from there the second to fourth wave ask for the rows of the first child,
+// which is where the walk goes on if it is accepted (for a leaf, the target row, for the draw): they travel while the
+// first wave exchanges sums and works out whether it is.  Without slots in LDS and beyond them the task function is
+// little more than half as long (68 KB, 113 in bf16; the instruction cache of two compute units has 64).  64 trees of V = 128256,
+// SpecInfer: a link of the chain 9.2 -> 8.3 us; calls: 37 trees of V = 50001, SpecTr, 79 -> 73 us, 2 of V = 1143 74 -> 64, 186 of V = 1974, Naive,
+// 61 -> 56, 26 of V = 5093, SpecInfer, 48 -> 46.  Traversal gained nothing by it (94 trees of V = 8515: 151 us, 157 with).
+template <class E>
+__global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
+void short_part_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, kKindShort>(launch); }
 
 // ------------------------------------------------------------------ walk
 //
@@ -2932,7 +2989,7 @@ __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
 }
 
 template <class E>
-__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in) {
+__device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_in, int there_in) {
     using T = typename E::T;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
@@ -2942,7 +2999,7 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
     const int lane = threadIdx.x & (kWave - 1), wave = uniform_i32(static_cast<int>(threadIdx.x) / kWave);
     const int part_vecs = uniform_i32(lds_launch().q.part_vecs);
     int n = uniform_i32(n_in);
-    bool row = uniform_i32(row_in) != 0;
+    bool row = uniform_i32(row_in) != 0, there = uniform_i32(there_in) != 0;
     Team team = uniform_struct(g_loop.team);           // every wave its copy; the first wave's counts exchanges
     const bool leader = team.member == 0;
     const size_t at = static_cast<size_t>(b) * N;
@@ -2952,6 +3009,7 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
     TaskDraw<E> d(part);
     d.k32 = uniform_f32(a.k32);
     int next = -1;
+    task_barrier();                                    // (every wave has waited for what it had asked for ahead)
     for (;;) {
         const size_t off = static_cast<size_t>(n) * V;
         part.setup(zt0 + off, zd0 + off, V, g_rows, g_rows + kLdsVecs * kTaskBlock, threadIdx.x, team.member, team.size, part_vecs);
@@ -2966,7 +3024,7 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
             }
         }
         if (row) {
-            d.weigh_row(g_draw.tile, wave, lane);
+            d.weigh_row(g_draw.tile, wave, lane, there);
             if (lane == 0) g_sh.partf[wave][0] = d.mk;
         } else {
             d.f.init(d.k32, uniform_f32(g_draw.nAt), uniform_f32(g_draw.nAd), uniform_f32(g_draw.rho));
@@ -3004,6 +3062,7 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
             break;
         }
         row = true;
+        there = false;
     }
     if (threadIdx.x == 0) g_loop.team = team;          // (the task loop reads it after its barrier)
     return next;
@@ -3364,7 +3423,7 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     }
     for (int c = 0; c <= q.nclass; ++c) tree.class_off[c] = q.off[c];
     const int tasks = q.off[q.nclass];
-    static const int per_cu[3] = {resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>),
+    static const int per_cu[3] = {min(resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>), resident_per_cu(short_part_kernel<E>)),
                                   resident_per_cu(node_task_kernel<E, MPV_METHOD_TRAVERSAL>),
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
     // Tasks that do not depend on each other: every node's for the acceptance rates.  (A rate is 1 less a mass: with other
@@ -3389,6 +3448,12 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
     q.same_xcd = shape.same_xcd;
+    // Up to four slots; six for SpecTr, which sweeps a part about seven times for one load.  With more the chip is full of teams
+    // and loads, and what is asked for in vain holds the others up (64 trees of V = 128256, parts of 1 344 vectors: SpecInfer 73.2 us
+    // by the other kernel, 74.9 by this, SpecTr 186 and 182; 64 of V = 32000, parts of 512: 65.2 and 62.9).
+    const bool short_part = top_down && a.estimate != 2 && q.part_vecs <= (a.walk == 3 ? kRegVecs : 4) * kTaskBlock;
+    // (a walk's rows are asked for ahead only where just what it needs is computed)
+    q.ahead = short_part && a.lazy ? 1 : 0;
     // Where the last slot of a part is kept, or is the one that a sweep reads again; longer parts are drawn from by sample_task,
     // like the calls with debug outputs of the draw (64 trees of V = 128256, SpecInfer: 88 us by it, 82 by draw_walk).
     q.draw_here = top_down && a.lazy && !a.estimate && !a.dbg_accept && !a.dbg_resid && q.part_vecs <= kPartCapacity + kTaskBlock ? 1 : 0;
@@ -3434,7 +3499,8 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
         if (a.estimate == 2) {
             launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, kKindAcceptance>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         } else if (p->method != MPV_METHOD_TRAVERSAL) {      // NSS, Naive and SpecTr are variants of the top-down kernel
-            launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_SPECINFER>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
+            launch(MPV_KERNEL_NODE_TASK, short_part ? short_part_kernel<E> : node_task_kernel<E, MPV_METHOD_SPECINFER>, grid, block, s,
+                   const_cast<const LaunchBlock*>(ws.launch));
         } else {
             launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_TRAVERSAL>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         }

@@ -548,7 +548,10 @@ template <class E> struct NegInfVec;
 template <> struct NegInfVec<ElemF32> { static __device__ __forceinline__ uint4 v() { return make_uint4(0xff800000u, 0xff800000u, 0xff800000u, 0xff800000u); } };
 template <> struct NegInfVec<ElemBF16> { static __device__ __forceinline__ uint4 v() { return make_uint4(0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u); } };
 
-template <class E, int BLOCK, int R, int L>
+// STAGED: a part of R slots at most.  It is kept in registers alone, and its rows come through the LDS, which is free from the
+// first sweep's end on: rows that are likely to be next can be asked for long before they are.  (No load into registers,
+// from one place or another: the compiler would wait for them where the two ways meet.)
+template <class E, int BLOCK, int R, int L, bool STAGED = false>
 struct RetainedPart {
     using T = typename E::T;
     static constexpr int VEC = E::VEC;
@@ -608,8 +611,12 @@ struct RetainedPart {
     // Put every load of the kept slots in flight (registers first: they are consumed first).
     // An empty part (nv = 0) loads nothing.
     __device__ __forceinline__ void issue_loads() {
-        issue_register_loads();
-        issue_lds_loads();
+        if constexpr (STAGED) {
+            ask_staged();
+        } else {
+            issue_register_loads();
+            issue_lds_loads();
+        }
     }
     __device__ __forceinline__ void issue_register_loads() {
         if (nv <= 0) return;
@@ -631,9 +638,29 @@ struct RetainedPart {
         }
     }
 
+    // Staged: vector i of a part lies at lt[i] and ld[i].  ask_ahead: all of them, by wave `which` of `of` that do this.
+    __device__ __forceinline__ void ask_ahead(int which, int of, bool draft_too) const {
+        const int lane = tid & (kWave - 1);
+        for (int c = which; c * kWave < nv; c += of) {
+            const size_t at = static_cast<size_t>(v0 + min(c * kWave + lane, nv - 1)) * VEC;
+            load_to_lds_16B(bt + at, lt + c * kWave);
+            if (draft_too) load_to_lds_16B(bd + at, ld + c * kWave);
+        }
+    }
+    // ... the wave's own
+    __device__ __forceinline__ void ask_staged() const {
+        const int wave0 = (tid / kWave) * kWave;
+        for (int s = 0; s < nslots; ++s) {
+            const size_t at = static_cast<size_t>(vec_of(s)) * VEC;
+            load_to_lds_16B(bt + at, lt + s * BLOCK + wave0);
+            load_to_lds_16B(bd + at, ld + s * BLOCK + wave0);
+        }
+    }
+
     // slots beyond what is kept: read from memory, CH loads in flight
     template <class F>
     __device__ __forceinline__ void streamed(F& f) const {
+        if constexpr (STAGED) return;
         constexpr int CH = 2;
         for (int s = R + L + 1; s < nslots; s += CH) {
             uint4 a[CH], d[CH];
@@ -656,7 +683,7 @@ struct RetainedPart {
     // One slot beyond the kept ones (a part slightly too large) is asked for when a sweep starts
     // and used when it ends: its memory latency hides behind the kept slots.  More than that is
     // streamed two slots at a time (streamed()).
-    __device__ __forceinline__ bool has_overflow() const { return nslots > R + L; }      // (the same in every lane)
+    __device__ __forceinline__ bool has_overflow() const { return !STAGED && nslots > R + L; }      // (the same in every lane)
     __device__ __forceinline__ void ask_overflow(uint4& a, uint4& d) const {
         a = load_raw_at(bt, vec_of(R + L));
         d = load_raw_at(bd, vec_of(R + L));
@@ -667,8 +694,10 @@ struct RetainedPart {
         f.vec(a, d);
     }
 
+    // (there: staged rows that the caller has waited for)
     template <class F>
-    __device__ __forceinline__ void first_pass(F& f) {
+    __device__ __forceinline__ void first_pass(F& f, bool there = false) {
+        if (STAGED && !there) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (the compiler does not see what lands in LDS)
         edges(f);
         if (nv <= 0) return;
         uint4 oa, od;
@@ -677,6 +706,7 @@ struct RetainedPart {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             if (j < nslots) {
+                if constexpr (STAGED) { rt[j] = lt[j * BLOCK + tid]; rd[j] = ld[j * BLOCK + tid]; }
                 if (!full_slot(j)) {
                     if (!inside(j)) { rt[j] = NegInfVec<E>::v(); rd[j] = NegInfVec<E>::v(); }
                 }
@@ -693,7 +723,7 @@ struct RetainedPart {
             }
         }
 #pragma unroll
-        for (int j = 0; j < L; ++j) {
+        for (int j = 0; j < (STAGED ? 0 : L); ++j) {
             if (R + j < nslots) {
                 uint4 a = lt[j * BLOCK + tid], d = ld[j * BLOCK + tid];
                 bool padded = false;
@@ -728,7 +758,7 @@ struct RetainedPart {
         const bool overflow = has_overflow();
         if (overflow) ask_overflow(oa, od);
 #pragma unroll
-        for (int j = 0; j < L; ++j) {
+        for (int j = 0; j < (STAGED ? 0 : L); ++j) {
             if (R + j < nslots) f.vec_kept(lt[j * BLOCK + tid], ld[j * BLOCK + tid]);
         }
 #pragma unroll
@@ -915,9 +945,9 @@ constexpr int kDrawTiles = 64;                            // a lane of the first
 // The masses of one vector's elements, in one of two units.  A pair: half of (e_t - rho e_d)_+ as the residual sweeps add it
 // up.  A row: 2^(z k32 - mk), mk the wave's reference.  A row alone lies in LDS, where the loops over its slots need not be
 // unrolled (the task functions are larger than the instruction cache as they are).
-template <class E, int BLOCK, int R, int L>
+template <class E, int BLOCK, int R, int L, bool STAGED = false>
 struct PartDraw {
-    using P = RetainedPart<E, BLOCK, R, L>;
+    using P = RetainedPart<E, BLOCK, R, L, STAGED>;
     static constexpr int VEC = E::VEC, NW = BLOCK / kWave, kSlots = R + L + 1;      // (the last is not kept: see ask_overflow)
     static_assert(2 + NW * kSlots <= kDrawTiles && R == L, "a lane per tile; a row alone takes the draft's share of the LDS too");
     P& p;
@@ -933,13 +963,17 @@ struct PartDraw {
         more = NegInfVec<E>::v();
         if (p.has_overflow()) more = load_raw_at(p.bt, p.vec_of(R + L));
     }
-    __device__ __forceinline__ uint4 row_vector(int s, const uint4& more) const { return s < R + L ? p.lt[s * BLOCK + p.tid] : more; }
+    __device__ __forceinline__ uint4 row_vector(int s, uint4 more) const {
+        if (s < R + L) more = p.lt[s * BLOCK + p.tid];
+        const bool in = p.inside(s);                               // (past the part's end there may lie anything)
+        const uint4 none = NegInfVec<E>::v();
+        return make_uint4(in ? more.x : none.x, in ? more.y : none.y, in ? more.z : none.z, in ? more.w : none.w);
+    }
     __device__ __forceinline__ void row_masses(int s, const uint4& v, float (&r)[VEC]) const {
         float x[VEC];
         E::unpack(v, x);
-        const float ref = p.inside(s) ? -mk : -INFINITY;           // (past the end: no mass)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) r[i] = fast_exp2(fmaf(x[i], k32, ref));
+        for (int i = 0; i < VEC; ++i) r[i] = fast_exp2(fmaf(x[i], k32, -mk));
     }
     // ---- a pair
     __device__ __forceinline__ void pair_masses(const uint4& a, const uint4& d, bool kept, float (&r)[VEC]) const {
@@ -991,7 +1025,7 @@ struct PartDraw {
             }
             __builtin_amdgcn_sched_barrier(0);            // (slots side by side take registers that there are not)
         }
-        for (int s = R; s < p.nslots; ++s) {
+        for (int s = R; !STAGED && s < p.nslots; ++s) {
             uint4 a, d;
             pair_vectors(s, a, d);
             float r[VEC];
@@ -1006,16 +1040,17 @@ struct PartDraw {
         }
     }
     // a row, asked for here; mk: the largest exponent of this wave's share
-    __device__ __forceinline__ void weigh_row(float* tile, int wave, int lane) {
-        uint4 more;
-        ask_row(more);
+    // (there: it lies in LDS already, see ask_ahead)
+    __device__ __forceinline__ void weigh_row(float* tile, int wave, int lane, bool there) {
+        uint4 more = NegInfVec<E>::v();
+        if (!there) ask_row(more);
         const float before = edge<true>(false), after = edge<true>(true);
         float m = fmaxf(before, after);
         for (int s = 0; s < p.nslots; ++s) {
             float x[VEC];
             E::unpack(row_vector(s, more), x);
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) m = fmaxf(m, x[i]);       // (a lane past the end holds the part's last vector)
+            for (int i = 0; i < VEC; ++i) m = fmaxf(m, x[i]);
         }
         mk = fmaxf(wave_max(m) * k32, OnlineLse::kFloor);
         float mine = 0.f;
@@ -1045,19 +1080,15 @@ struct PartDraw {
             step = 1;
         } else {
             const int s = (t - 1) / NW;
-            uint4 a, d;
-            if (row && s < R + L) {
-                a = p.lt[s * BLOCK + p.tid];
-            } else {
-                a = load_raw_at(p.bt, p.vec_of(s));
-                if (!row) d = load_raw_at(p.bd, p.vec_of(s));
+            uint4 a = NegInfVec<E>::v(), d = a;
+            if (!row || s >= R + L) {
+                if (p.inside(s)) {
+                    a = load_raw_at(p.bt, p.vec_of(s));
+                    if (!row) d = load_raw_at(p.bd, p.vec_of(s));
+                }
             }
-            if (row) {
-                row_masses(s, a, r);
-            } else {
-                if (!p.inside(s)) { a = NegInfVec<E>::v(); d = a; }
-                pair_masses(a, d, false, r);
-            }
+            if (row) row_masses(s, row_vector(s, a), r);
+            else pair_masses(a, d, false, r);
             first = p.head + (p.v0 + (t - 1) * kWave) * VEC;
         }
         const float ls = sum(r);

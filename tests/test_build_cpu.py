@@ -30,3 +30,12 @@ def test_the_task_kernels_keep_their_registers(tmp_path):
     for name, k in task_kernels.items():
         assert k[".vgpr_count"] <= 168, name
         assert k[".vgpr_spill_count"] <= 5 and k[".private_segment_fixed_size"] <= 48, name
+
+
+@pytest.mark.skipif(not os.path.exists(f"{LLVM}/clang-offload-bundler"), reason="no LLVM tools of ROCm")
+def test_so_do_the_kernels_for_short_parts(tmp_path):
+    short = {n: k for n, k in kernels_of(mpv.lib_path(), tmp_path).items() if "short_part_kernel" in n}
+    assert len(short) == 2
+    for name, k in short.items():
+        assert k[".vgpr_count"] <= 168, name
+        assert k[".vgpr_spill_count"] <= 5 and k[".private_segment_fixed_size"] <= 48, name

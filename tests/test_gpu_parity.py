@@ -432,6 +432,8 @@ def test_the_draw_reads_rows_of_any_offset(method, V, dtype, B):
 
 
 @pytest.mark.parametrize("V,dtype,B", [
+    (8192, "bf16", 400), (8200, "bf16", 400),                             # one member: 4 slots (SpecTr: 6), the most of the short kernel;
+    (12287, "bf16", 400), (12288, "bf16", 400), (12296, "bf16", 400),     # one vector more
     (24576, "bf16", 400), (24577, "bf16", 400), (25601, "bf16", 400),     # one member: 12 slots full, one more, half of it
     (12287, "f32", 400),
     (425984, "bf16", 2), (425992, "bf16", 2),                             # 16 members: the 13th slot full; one vector too many
