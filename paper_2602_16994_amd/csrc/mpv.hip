@@ -21,6 +21,8 @@
 //                            tree: the uniform-dependent walk, then the team draws the bonus
 //                            token by inverse CDF from the residual of the stopping node.
 //                            (NSS, Naive, SpecTr: one per draw of the token-following walk.)
+//                          The top-down rules draw as a part of the walk instead (draw_walk), from the part on chip.
+//   short_part_kernel      the same for top-down rules whose parts the registers hold
 // mpv_verify_merged (a shape per tree) adds shape_kernel, which works out every tree's tables.
 // mpv_block_efficiency and mpv_acceptance_rates run the same kernels with every node task and
 // no uniforms (see Args::estimate); mpv_nucleus_mask is a kernel of its own (mpv_nucleus.h).
@@ -1363,7 +1365,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     auto gather = [&](int from_lane, int v) __attribute__((always_inline)) { return __builtin_amdgcn_ds_bpermute(from_lane << 2, v); };
     // Walks draw their tokens in draw_walk, which is called next; a pair's tiles are weighed here, where it is on chip.
     const int draws = DRAWS ? uniform_i32(q.draw_here) : 0;
-    // (Known to be the same each time, the compiler makes paths of their own of it, which take 140 registers to private memory.)
+    // (If it knew that this is the same each time, the compiler would make paths of their own of it, which take 140 registers to private memory.)
     auto draw_here = [&]() __attribute__((always_inline)) {
         if constexpr (!DRAWS) return false;
         int x = draws;
