@@ -410,7 +410,7 @@ __global__ __launch_bounds__(kInitBlock) void init_kernel(LaunchBlock block) {
         int* dst = reinterpret_cast<int*>(ws.launch);
         for (int w = me; w < static_cast<int>(sizeof(LaunchBlock) / sizeof(int)); w += stride) dst[w] = src[w];
     }
-    {   // team words: every sequence number starts at 0, nobody has arrived
+    {   // team words: no exchange has been written (their numbers are above 0), nobody has arrived
         const int exch_words = q.teams * q.team_size * 2 * kExchWords;
         for (int w = me; w < exch_words; w += stride) ws.exch[w] = 0ull;
         for (int w = me; w < kMaxTeams * 2; w += stride) ws.team_task[w] = 0ull;
@@ -815,8 +815,7 @@ __device__ __forceinline__ double ld_shared_f64(const double* p) {
 
 struct Team {
     int id, member, size;
-    int one_chiplet;                 // all members run on one chiplet: what they tell each other stays in its L2 (st_team)
-    unsigned seq;                    // exchanges done
+    unsigned seq;                    // number of the last exchange; whether the team runs on one chiplet (before_first_exchange)
     unsigned tseq;                   // task words seen
     unsigned long long* area;        // [2][size][kExchWords]
     unsigned long long* task_word;   // [2]
@@ -832,7 +831,7 @@ struct Team {
 // 0.68 / 0.70 / 0.84 / 1.02 us with it and takes 0.35 / 0.40 / 0.43 / 0.44.  (64 trees of V = 128256, Traversal, 139 -> 133 us a
 // call; 32 of V = 262144 on teams of 16, SpecInfer, 79 -> 73; 256 of V = 151936, Traversal, 447 -> 433.)
 __device__ __forceinline__ void st_team(const Team& t, unsigned long long* p, unsigned long long v) {
-    if (t.one_chiplet) __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (on_one_chiplet(t.seq)) __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     else st_relaxed(p, v);
 }
 static_assert(kMaxTeam < (1 << kArrivedBits), "the counts of a team's arrivals fit their fields");
@@ -970,7 +969,7 @@ __device__ __forceinline__ int team_listen(Team& t, int& flags, const Workspace&
     const int task = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned>(v)), 0);
     flags = __builtin_amdgcn_readlane(static_cast<int>(static_cast<unsigned>(v)), 1);
     if (FIRST) {
-        t.one_chiplet = all_ok && (flags & kFlagOneChiplet) != 0 ? 1 : 0;
+        t.seq = before_first_exchange(all_ok && (flags & kFlagOneChiplet) != 0);
         flags &= ~kFlagOneChiplet;
     }
     return all_ok ? task : kTaskExit;
@@ -2173,7 +2172,7 @@ __device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch
             team.id = i / team.size;
             team.member = i % team.size;
         }
-        team.seq = 0u; team.tseq = 0u; team.dead = 0; team.one_chiplet = 0;
+        team.seq = before_first_exchange(false); team.tseq = 0u; team.dead = 0;
         team.area = ws.exch + static_cast<size_t>(team.id) * 2 * team.size * kExchWords;
         // (a line holds the words of eight teams: of one chiplet, like everything that stays in its L2)
         team.task_word = ws.team_task + static_cast<size_t>(q.same_xcd ? (team.id % 8) * (kMaxTeams / 8) + team.id / 8 : team.id) * 2;

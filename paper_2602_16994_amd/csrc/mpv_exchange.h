@@ -23,7 +23,9 @@ constexpr bool exchange_waits(int lane, int size, bool also) {
 }
 
 // The word in which a team's members count themselves as they start: how many there are, and how many on each chiplet.
-// Members on chiplets that it has no field for are nobody's neighbours.
+// Members on chiplets that it has no field for are nobody's neighbours.  It is word 0 of the first member's line in area 0
+// and stays there until exchange words overwrite it; so the numbers of exchanges, which tell a word that has been written from
+// one that has not (an exchange's number is the upper half of its words), begin above everything its upper half can hold.
 constexpr int kArrivedOn = 8, kArrivedBits = 5, kChiplets = 8;
 static_assert(kArrivedOn + kChiplets * kArrivedBits <= 64, "the counts of a team's arrivals fit a word");
 constexpr unsigned long long arrival_of(int chiplet) {
@@ -33,5 +35,12 @@ constexpr int arrived(unsigned long long word) { return static_cast<int>(word & 
 constexpr int arrived_on(unsigned long long word, int chiplet) {
     return chiplet < kChiplets ? static_cast<int>((word >> (kArrivedOn + kArrivedBits * chiplet)) & ((1ull << kArrivedBits) - 1ull)) : 0;
 }
+
+// The number before a team's first exchange.  The top bit says for the whole launch that the team runs on one chiplet (a
+// word of its own for that is one more scalar register through the task loops).  Even: the first exchange uses area 1, as the
+// team's first task is announced in area 0, which the next one overwrites only when everybody has read it.
+constexpr unsigned before_first_exchange(bool one_chiplet) { return one_chiplet ? 1u << 31 : 1u << 16; }
+constexpr bool on_one_chiplet(unsigned seq) { return (seq >> 31) != 0u; }
+static_assert(kArrivedOn + kChiplets * kArrivedBits - 32 <= 16, "an exchange's number is above the upper half of the arrival word");
 
 }  // namespace mpv

@@ -14,6 +14,18 @@ extern "C" int area_of(unsigned seq) { return static_cast<int>(mpv::exchange_are
 extern "C" unsigned long long arrival(int chiplet) { return mpv::arrival_of(chiplet); }
 extern "C" int count(unsigned long long word) { return mpv::arrived(word); }
 extern "C" int count_on(unsigned long long word, int chiplet) { return mpv::arrived_on(word, chiplet); }
+extern "C" unsigned before_first(int one_chiplet) { return mpv::before_first_exchange(one_chiplet != 0); }
+extern "C" int on_one(unsigned seq) { return mpv::on_one_chiplet(seq) ? 1 : 0; }
+// the largest upper half of the arrival word, over every placement of up to `most` members from chiplet `from` on (16: of any other)
+static unsigned highest(unsigned long long word, int from, int most) {
+    unsigned top = static_cast<unsigned>(word >> 32);
+    for (int c = from; c <= mpv::kChiplets && most > 0; ++c) {
+        const unsigned t = highest(word + mpv::arrival_of(c), c, most - 1);
+        top = t > top ? t : top;
+    }
+    return top;
+}
+extern "C" unsigned highest_arrival(int most) { return highest(0, 0, most); }
 extern "C" int lane_waits(int rows, int lane, int size, int also) {
     return rows == 1 ? mpv::exchange_waits<1>(lane, size, also != 0) : mpv::exchange_waits<2>(lane, size, also != 0);
 }
@@ -97,6 +109,27 @@ def test_a_team_on_one_chiplet_is_told_from_one_that_is_not(rules, size):
             word = (size - 1) * rules.arrival(on) + rules.arrival(other)
             assert rules.count(word) == size
             assert (rules.count_on(word, other) == size) == (on == other and on < 8)
+
+
+def test_no_arrival_word_passes_for_an_exchange(rules):
+    """The members' count lies where exchange words are written later: whatever chiplets up to 16 members run on, its upper half
+    is not the number of any exchange (one on chiplet 5 and one on 4 made it 2, the number of the first exchange there)."""
+    for f in (rules.before_first, rules.highest_arrival):
+        f.restype = ctypes.c_uint32
+    rules.on_one.argtypes = [ctypes.c_uint32]
+    top = rules.highest_arrival(16)
+    assert top >= 2                                   # (numbers that begin at 1 would be among them)
+    for one in (0, 1):
+        first, last = rules.before_first(one), rules.before_first(one) + 10 ** 9      # (more exchanges than two seconds hold)
+        assert top < first and last < 2 ** 32 and rules.area_of(ctypes.c_uint32(first + 1)) == 1
+        assert rules.on_one(first) == rules.on_one(last) == one
+
+
+def test_the_kernels_number_exchanges_by_these_rules():
+    with open(os.path.join(ROOT, "paper_2602_16994_amd", "csrc", "mpv.hip")) as f:
+        text = f.read()
+    starts = [line.strip() for line in text.split("\n") if ".seq = " in line]
+    assert len(starts) == 2 and all(".seq = before_first_exchange(" in line for line in starts), starts
 
 
 def test_the_kernels_exchange_by_these_rules():
