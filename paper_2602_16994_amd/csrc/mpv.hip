@@ -993,6 +993,14 @@ __device__ __forceinline__ double cold_log2(double x) { return log2(x); }
 __device__ __forceinline__ ResidualConsts cold_residual_consts(double At, double Ad, double c) { return residual_consts(At, Ad, c); }
 // a comparison of numbers that are the same in every lane: a scalar branch, not a masked one
 __device__ __forceinline__ bool all_alike(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
+// The constants that a draw weighs a pair with.  c = 0 (nothing has been taken away from p): the draft row is left out, as
+// one that is masked throughout has no partition, and 0 times one of its terms would be no number.
+__device__ __forceinline__ ResidualConsts draw_consts(double At, double Ad, double c) {
+    const bool use_d = all_alike(c > 0.0);
+    ResidualConsts r = residual_consts(At, use_d ? Ad : 0.0, use_d ? c : 0.0);
+    if (!use_d) r.nAd = -INFINITY;
+    return r;
+}
 // x^k for a small whole k
 __device__ __forceinline__ double int_power(double x, int k) {
     double r = 1.0;
@@ -1871,7 +1879,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // The walk has come to its draw, at this node or at the accepted leaf: every member knows, nothing is announced.
         const bool row = next_node >= 0;
         if (!row) {
-            const ResidualConsts rc = cold_residual_consts(At_, Ad_, c);
+            const ResidualConsts rc = draw_consts(At_, Ad_, c);
             if (lane == 0) { g_cmd.kind = kCmdTiles; g_cmd.nAt = rc.nAt; g_cmd.nAd = rc.nAd; g_cmd.rho = rc.rho; }
             task_barrier();                                // B
             weigh_tiles(uniform_f32(rc.nAt), uniform_f32(rc.nAd), uniform_f32(rc.rho));

@@ -447,6 +447,25 @@ def test_the_draw_at_the_edges_of_what_is_kept(method, V, dtype, B):
     assert rep["trees"] == min(B, 12)
 
 
+@pytest.mark.parametrize("V,dtype", [(1000, "f32"), (5003, "bf16"), (20000, "bf16"), (131072, "f32")])
+def test_a_draft_row_without_any_token_leaves_the_target_row_to_draw_from(V, dtype):
+    """The draft row is masked throughout and so is the child's token in the target row: the child is rejected, no mass
+    can be taken from p, and the token is drawn from p."""
+    announce("masked draft row", V, dtype)
+    B = 8
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    target = torch.randn(B, 2, V, generator=gen, device="cuda").mul_(2.0)
+    target[:, 0, 7] = float("-inf")
+    draft = torch.full((B, 2, V), float("-inf"), device="cuda")
+    inputs = dict(parent=[-1, 0], tokens=torch.full((B, 2), 7, dtype=torch.int32, device="cuda"), uniforms=torch.rand(B, 2, generator=gen, device="cuda"),
+                  target=target.to(torch.float32 if dtype == "f32" else torch.bfloat16), draft=draft.to(torch.float32 if dtype == "f32" else torch.bfloat16))
+    got = run_library(inputs, 1.0, SI, debug=False)
+    assert got["counters"][4] == 0 and np.all(got["accept_len"] == 0)
+    for b in range(B):
+        token, gap = orc.sample_index(orc.softmax_T(inputs["target"][b, 0].float().cpu().numpy(), 1.0), float(inputs["uniforms"][b, 0]))
+        assert gap < 1e-6 or got["bonus_token"][b] == token
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
