@@ -2988,7 +2988,8 @@ __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
     const double scale = static_cast<double>(fast_exp2(unit - team_unit));          // (this member has mass, or nobody has)
     const double here = (target - lane_f64(dpp_f64<0x111>(upto), owner)) / scale;
     const unsigned long long hit_t = __ballot(in_tile > 0.0 && incl > here), any_t = __ballot(in_tile > 0.0);
-    const int tile = hit_t ? __ffsll(static_cast<long long>(hit_t)) - 1 : any_t ? 63 - __clzll(static_cast<long long>(any_t)) : 1;
+    // (no mass anywhere: token 0, as in sample_task)
+    const int tile = hit_t ? __ffsll(static_cast<long long>(hit_t)) - 1 : any_t ? 63 - __clzll(static_cast<long long>(any_t)) : 0;
     if (lane == tile) {
         const double of_tile = static_cast<double>(of_wave);
         g_draw.in_tile = tile;

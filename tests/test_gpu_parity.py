@@ -466,6 +466,23 @@ def test_a_draft_row_without_any_token_leaves_the_target_row_to_draw_from(V, dty
         assert gap < 1e-6 or got["bonus_token"][b] == token
 
 
+@pytest.mark.parametrize("V,dtype", [(1003, "f32"), (1003, "bf16"), (20011, "bf16")])
+@pytest.mark.parametrize("method", [NAIVE, SPECTR])
+def test_a_draw_without_any_mass_is_the_same_with_and_without_debug_outputs(method, V, dtype):
+    """Equal rows and a child's token that is masked in both: the child is rejected and (p - q)_+ has no mass.  Rows start at
+    any element of a 16-byte vector."""
+    announce("no mass", METHOD_NAME[method], V, dtype)
+    B = 12
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    rows = torch.randn(B, 2, V, generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    rows[:, 0, 9] = float("-inf")
+    inputs = dict(parent=[-1, 0], tokens=torch.full((B, 2), 9, dtype=torch.int32, device="cuda"), target=rows, draft=rows.clone(),
+                  uniforms=torch.rand(B, 2, generator=gen, device="cuda"), draw_uniforms=torch.rand(B, 2, generator=gen, device="cuda"))
+    with_outputs, lean = run_library(inputs, 1.0, method), run_library(inputs, 1.0, method, debug=False)
+    assert lean["counters"][4] == 0 and np.all(lean["accept_len"] == 0)
+    assert np.array_equal(lean["bonus_token"], with_outputs["bonus_token"])
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
