@@ -11,7 +11,7 @@ import torch
 import paper_2602_16994_amd as mpv
 import workloads
 from oracle import mpv_oracle as orc
-from tests.parity_util import check_properties, compare_with_oracle, result_to_host
+from tests.parity_util import SUM_REL_ERR, check_properties, compare_with_oracle, result_to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -481,6 +481,39 @@ def test_a_draw_without_any_mass_is_the_same_with_and_without_debug_outputs(meth
     with_outputs, lean = run_library(inputs, 1.0, method), run_library(inputs, 1.0, method, debug=False)
     assert lean["counters"][4] == 0 and np.all(lean["accept_len"] == 0)
     assert np.array_equal(lean["bonus_token"], with_outputs["bonus_token"])
+
+
+@pytest.mark.parametrize("method,V,B", [(SI, 4096, 64), (SI, 65536, 24), (NAIVE, 65536, 100), (SI, 131072, 100)])
+def test_a_draw_weighs_p_against_q_no_worse_than_its_terms_are(method, V, B):
+    """Partitions between 2^63 and 2^64, where a float that is lowered by one loses its last bit: p and q, alike to 1e-4 in the
+    first half of the row and to 2e-3 in the second, then differ by 2.6e-6 too much or too little, and a draw from
+    (p - q)_+ in the first half lands 2.6 % off.  Allowed: the rounding of rho (2^-24) and what the sums are off by
+    (SUM_REL_ERR), over 1e-4."""
+    announce("p against q", METHOD_NAME[method], V, B)
+    near = 1e-4
+    rng = np.random.default_rng(V + B)
+    base = rng.standard_normal((B, V))
+    base += ((63.0 + rng.uniform(0.05, 0.95, B)) * np.log(2.0) - np.log(np.sum(np.exp(base), axis=1)))[:, None]
+    apart = rng.choice([-1.0, 1.0], (B, V)) * np.where(np.arange(V) < V // 2, near, 2e-3)
+    apart[:, V - 1] = -8.0                            # the child's token: rejected
+    draft, target = base.astype(np.float32), (base + apart).astype(np.float32)
+    uniforms = np.full((B, 2), 0.99, dtype=np.float32)
+    cdfs = []
+    for b in range(B):
+        r = np.maximum(orc.softmax_T(target[b], 1.0) - orc.softmax_T(draft[b], 1.0), 0.0)
+        cdfs.append(np.cumsum(r) / np.sum(r))
+        uniforms[b, 0] = 0.5 * cdfs[b][V // 2 - 1]
+    rows = lambda x: torch.from_numpy(np.stack([x, x], axis=1)).cuda()
+    inputs = dict(parent=[-1, 0], tokens=torch.full((B, 2), V - 1, dtype=torch.int32, device="cuda"), target=rows(target), draft=rows(draft),
+                  uniforms=torch.from_numpy(uniforms).cuda(), draw_uniforms=torch.from_numpy(uniforms).cuda())
+    got = run_library(inputs, 1.0, method, debug=False)
+    assert got["counters"][4] == 0 and np.all(got["accept_len"] == 0)
+    off = []
+    for b in range(B):
+        t, u = int(got["bonus_token"][b]), float(uniforms[b, 0])
+        off.append(max(0.0, (cdfs[b][t - 1] if t else 0.0) - u, u - cdfs[b][t]) / u)
+    print("[report] off by at most", max(off), flush=True)
+    assert max(off) <= (2.0 ** -24 + SUM_REL_ERR) / near
 
 
 def test_out_of_range_tokens_are_counted_not_followed():
