@@ -2957,13 +2957,16 @@ __device__ __forceinline__ void draw_find(const TaskDraw<E>& d, bool row, int b,
     }
 }
 
+// 2^(from - to) of two whole numbers, exactly
+__device__ __forceinline__ double unit_ratio(float from, float to) { return ldexp(1.0, static_cast<int>(fmaxf(from - to, -4096.f))); }
+
 // First wave, when every wave has weighed its tiles: who has the target (u times the mass of the whole row), and in which tile.
 __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
     const int lane = lane_here();
     // this workgroup's tiles, lane t that of tile t, in units of 2^unit
     const float unit = fmaxf(fmaxf(g_sh.partf[0][0], g_sh.partf[1][0]), fmaxf(g_sh.partf[2][0], g_sh.partf[3][0]));
-    const float of_wave = fast_exp2(g_sh.partf[draw_wave(lane)][0] - unit);
-    const double in_tile = lane < 2 + kTaskWaves * slots ? static_cast<double>(g_draw.tile[lane]) * static_cast<double>(of_wave) : 0.0;
+    const double of_wave = unit_ratio(g_sh.partf[draw_wave(lane)][0], unit);
+    const double in_tile = lane < 2 + kTaskWaves * slots ? static_cast<double>(g_draw.tile[lane]) * of_wave : 0.0;
     const double incl = wave_inclusive_scan(in_tile), own = lane_f64(incl, kWave - 1);
     unsigned got[3] = {half_of(own, 0), half_of(own, 1), __float_as_uint(unit)};
     team.seq++;
@@ -2973,7 +2976,7 @@ __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
     }
     const bool live = lane < team.size && !team.dead;
     const float of_m = live ? __uint_as_float(got[2]) : OnlineLse::kFloor, team_unit = lane_f32(row_max(of_m), 0);
-    const double mass = live ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) * static_cast<double>(fast_exp2(of_m - team_unit)) : 0.0;
+    const double mass = live ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) * unit_ratio(of_m, team_unit) : 0.0;
     double upto = mass;                                // sums along the row of lanes: member m and those before it
     upto += dpp_f64<0x111>(upto);
     upto += dpp_f64<0x112>(upto);
@@ -2985,16 +2988,15 @@ __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
     const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
     if (lane == 0) g_draw.owner = owner;
     if (owner != team.member) return;
-    const double scale = static_cast<double>(fast_exp2(unit - team_unit));          // (this member has mass, or nobody has)
+    const double scale = unit_ratio(unit, team_unit);          // (this member has mass, or nobody has)
     const double here = (target - lane_f64(dpp_f64<0x111>(upto), owner)) / scale;
     const unsigned long long hit_t = __ballot(in_tile > 0.0 && incl > here), any_t = __ballot(in_tile > 0.0);
     // (no mass anywhere: token 0, as in sample_task)
     const int tile = hit_t ? __ffsll(static_cast<long long>(hit_t)) - 1 : any_t ? 63 - __clzll(static_cast<long long>(any_t)) : 0;
     if (lane == tile) {
-        const double of_tile = static_cast<double>(of_wave);
         g_draw.in_tile = tile;
-        g_draw.rem = (here - (incl - in_tile)) / of_tile;
-        g_draw.total = total / scale / of_tile;
+        g_draw.rem = (here - (incl - in_tile)) / of_wave;
+        g_draw.total = total / scale / of_wave;
     }
 }
 

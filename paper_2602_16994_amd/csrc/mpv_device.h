@@ -1045,7 +1045,9 @@ struct PartDraw {
             if (lane == 0) { tile[0] = first; tile[1 + NW * p.nslots] = last; }
         }
     }
-    // a row, asked for here; mk: the largest exponent of this wave's share
+    // a row, asked for here; mk: the largest exponent of this wave's share, rounded up to a whole number (the tiles of waves
+    // and members are then brought to one unit by powers of two, exactly: a float 2^x is off by 1e-7, and so would be all of
+    // a wave's share)
     // (there: it lies in LDS already, see ask_ahead)
     __device__ __forceinline__ void weigh_row(float* tile, int wave, int lane, bool there) {
         uint4 more = NegInfVec<E>::v();
@@ -1058,7 +1060,7 @@ struct PartDraw {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) m = fmaxf(m, x[i]);
         }
-        mk = fmaxf(wave_max(m) * k32, OnlineLse::kFloor);
+        mk = ceilf(fmaxf(wave_max(m) * k32, OnlineLse::kFloor));
         float mine = 0.f;
         for (int s = 0; s < p.nslots; ++s) {
             float r[VEC];

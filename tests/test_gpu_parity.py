@@ -516,6 +516,35 @@ def test_a_draw_weighs_p_against_q_no_worse_than_its_terms_are(method, V, B):
     assert max(off) <= (2.0 ** -24 + SUM_REL_ERR) / near
 
 
+def test_a_draw_at_a_leaf_weighs_its_waves_exactly_against_each_other():
+    """Two tokens in the shares of two waves, ten apart: where the draw goes from one to the other is found to a float of u.
+    Each token's mass is off by one v_exp_f32 (2^-24 or a little less), the rest is exact: 1e-7 in the mean square over the
+    rows (with a float 2^(difference of the waves' references) between them, 2.5e-7)."""
+    announce("leaf, two waves")
+    V, rows, steps = 1024, 96, np.arange(-16, 17)
+    # a temperature whose log2(e)/T is a float
+    T = min((np.float32(0.9 + i * 1e-5) for i in range(20000)), key=lambda t: abs(float(np.float32(np.log2(np.e) / float(t))) * float(t) / np.log2(np.e) - 1.0))
+    rng = np.random.default_rng(5)
+    a, gap = rng.uniform(-4.0, 4.0, rows).astype(np.float32), rng.uniform(9.0, 11.0, rows).astype(np.float32)
+    z = np.full((rows, V), -np.inf, dtype=np.float32)
+    z[:, 300], z[:, 900] = a, a + gap                 # (64 vectors of 4 elements per wave: the second wave's and the fourth's)
+    step = np.array([orc.softmax_T(z[r, [300, 900]], float(T))[0] for r in range(rows)])
+    at = step.astype(np.float32).view(np.int32)
+    u = (at[:, None] + steps[None, :]).astype(np.int32).view(np.float32)
+    B = u.size
+    target = torch.from_numpy(np.repeat(z, len(steps), axis=0)).cuda().view(B, 1, V)
+    inputs = dict(parent=[-1], tokens=torch.zeros(B, 1, dtype=torch.int32, device="cuda"), target=target, draft=target,
+                  uniforms=torch.from_numpy(np.ascontiguousarray(u).reshape(B, 1)).cuda())
+    got = run_library(inputs, float(T), SI, debug=False)
+    assert got["counters"][4] == 0
+    first = (got["bonus_token"].reshape(rows, len(steps)) == 300).sum(axis=1)          # u below the step: the first token
+    assert np.all((first > 0) & (first < len(steps)))
+    found = np.array([0.5 * (float(u[r, first[r] - 1]) + float(u[r, first[r]])) for r in range(rows)])
+    off = np.sqrt(np.mean((found / step - 1.0) ** 2))
+    print("[report] off by", off, "at most", np.max(np.abs(found / step - 1.0)), flush=True)
+    assert off <= 1e-7
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
