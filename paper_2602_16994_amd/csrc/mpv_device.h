@@ -1053,6 +1053,7 @@ struct PartDraw {
         uint4 more = NegInfVec<E>::v();
         if (!there) ask_row(more);
         const float before = edge<true>(false), after = edge<true>(true);
+        if (!there) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (the compiler does not see what lands in LDS)
         float m = fmaxf(before, after);
         for (int s = 0; s < p.nslots; ++s) {
             float x[VEC];

@@ -39,3 +39,15 @@ def test_so_do_the_kernels_for_short_parts(tmp_path):
     for name, k in short.items():
         assert k[".vgpr_count"] <= 168, name
         assert k[".vgpr_spill_count"] <= 5 and k[".private_segment_fixed_size"] <= 48, name
+
+
+def test_rows_that_go_straight_to_lds_are_waited_for_before_they_are_read():
+    """The compiler does not tie a read of LDS to the load that brings the row there: the source waits in between, and not only
+    by what other loads there happen to need."""
+    with open(os.path.join(os.path.dirname(mpv.lib_path()), "csrc", "mpv_device.h")) as f:
+        text = f.read()
+    for function, ask, read in (("void weigh_row(", "ask_row(", "row_vector("), ("void first_pass(", "first_pass(", "lt[")):
+        body = text[text.index(function):]
+        body = body[:body.index("\n    }\n")]
+        before = body[body.index(ask):body.index(read)]
+        assert "!there) asm volatile(\"s_waitcnt vmcnt(0)\"" in before, function
