@@ -2864,7 +2864,7 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
                 int tk = (t_lo + tile) * TILE - mis + lane * VEC + found;
                 if (tk >= V) tk = V - 1;
                 if (tk < 0) tk = 0;
-                as_global(a.bonus)[b] = tk;
+                if (k == 0) as_global(a.bonus)[b] = tk;          // (once in a walk, see draw_find)
                 sh_tok = tk;
                 const double gap = fmin(fabs(rem - lo), fabs(hi - rem));
                 if (gap < 1e-6 * sh_total) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
@@ -2894,7 +2894,10 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
                 // Naive and SpecTr test children of an inner node before they draw there; NSS and leaves draw at once
                 to_task = (walk >= 2 && tree.nchild[to] > 0) ? b * a.N + to : a.B * a.N + b;
             } else if (leader) {
-                if (lane == 0) write_path(tree, a, b, n);
+                if (lane == 0) {
+                    as_global(a.bonus)[b] = tok;
+                    write_path(tree, a, b, n);
+                }
                 if (a.dbg_accept && lane < a.N)
                     as_global(a.dbg_accept)[static_cast<size_t>(b) * a.N + lane] =
                         lane == 0 ? 1.f : static_cast<float>(ld_shared_f64(&ws.atest[static_cast<size_t>(b) * a.N + lane]));
@@ -2905,8 +2908,8 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
         next = uniform_i32(sh_next);
     }
 
-    // ---- optional: the normalised distribution itself
-    if (a.dbg_resid) {
+    // ---- optional: the normalised distribution itself (of the walk's last draw; a member's share of it differs from row to row)
+    if (a.dbg_resid && next < 0) {
         const double inv = 1.0 / sh_total;
         float* out = a.dbg_resid + static_cast<size_t>(b) * V;
         for (int i = 0; i < cnt; ++i) {
@@ -2944,14 +2947,16 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
 //
 // Returns the task that follows (-1: the walk is over; the same in every lane of every member).
 
-// The token inside the tile that holds the target, by the wave that has it.
+// The token inside the tile that holds the target, by the wave that has it.  last: the walk ends with this draw.  (The bonus
+// token is written once in a walk: several members' stores to one word, from different chiplets or with nothing that
+// orders them, can leave any of them there.)
 template <class E>
-__device__ __forceinline__ void draw_find(const TaskDraw<E>& d, bool row, int b, int wave, int lane) {
+__device__ __forceinline__ void draw_find(const TaskDraw<E>& d, bool row, bool last, int b, int wave, int lane) {
     const Args& a = lds_launch().a;
     bool near = false;
     const int tok = d.find(uniform_i32(g_draw.in_tile), row, lane, g_draw.rem, g_draw.total, near);
     if (tok >= 0) {
-        as_global(a.bonus)[b] = tok;
+        if (last) as_global(a.bonus)[b] = tok;
         g_draw.token = tok;
         if (near) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
     }
@@ -3045,7 +3050,7 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
         if (wave == 0) draw_owner(team, part.nslots, u);
         else if (wave == 2 && leader && k == 0) write_path(tree, a, b, n);          // (the walk ends here)
         task_barrier();
-        if (uniform_i32(g_draw.owner) == team.member && wave == draw_wave(uniform_i32(g_draw.in_tile))) draw_find<E>(d, row, b, wave, lane);
+        if (uniform_i32(g_draw.owner) == team.member && wave == draw_wave(uniform_i32(g_draw.in_tile))) draw_find<E>(d, row, k == 0, b, wave, lane);
         if (k == 0) break;
         // Sec. 3.2: if the drawn token is a child's token the walk moves to that child (the first such child in list order),
         // otherwise it ends here.  Everybody needs the token (the owner's word; the others' say only that they have come
@@ -3062,7 +3067,10 @@ __device__ __attribute__((noinline)) int draw_walk(int b_in, int n_in, int row_i
             const unsigned long long m = __ballot(lane < k && child_token == tok);
             int to = -1;
             if (m != 0ull && !team.dead) to = __builtin_amdgcn_readlane(child, __ffsll(static_cast<long long>(m)) - 1);
-            else if (leader && lane == 0) write_path(tree, a, b, n);
+            else if (leader && lane == 0) {
+                as_global(a.bonus)[b] = tok;
+                write_path(tree, a, b, n);
+            }
             if (lane == 0) g_draw.next = to;
         }
         task_barrier();
@@ -3187,6 +3195,7 @@ struct Plan {
     int nclass;
     int64_t class_tasks[kMaxClasses];      // tasks a class can ever hold, over the batch
     const int32_t* shapes;                 // HOST [B,N]: a parent array per tree, checked; null: every tree is `tree`
+    bool teams_apart = false;              // tests only (mpv_test_verify_teams_apart)
 };
 
 // What the checks of one parent array find out.
@@ -3459,7 +3468,7 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     q.teams = shape.teams;
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
-    q.same_xcd = shape.same_xcd;
+    q.same_xcd = plan.teams_apart ? 0 : shape.same_xcd;
     // Up to four slots; six for SpecTr, which sweeps a part about seven times for one load.  With more the chip is full of teams
     // and loads, and what is asked for in vain holds the others up (64 trees of V = 128256, parts of 1 344 vectors: SpecInfer 73.2 us
     // by the other kernel, 74.9 by this, SpecTr 186 and 182; 64 of V = 32000, parts of 512: 65.2 and 62.9).
@@ -3603,7 +3612,7 @@ int mpv_workspace_bytes(const mpv_problem* problem, size_t* out) {
 static int verify_with_workspace(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                                  size_t workspace_bytes, void* hip_stream, bool part_of_batch = false,
                                  bool keep_counters = false, const int32_t* context_node = nullptr,
-                                 const int32_t* shapes = nullptr);
+                                 const int32_t* shapes = nullptr, bool teams_apart = false);
 
 // Only what the rule needs is computed: nobody has asked for per-node outputs.
 static bool only_what_is_needed(const mpv_problem* p, const mpv_buffers* buf) {
@@ -3614,6 +3623,13 @@ static bool only_what_is_needed(const mpv_problem* p, const mpv_buffers* buf) {
 int mpv_verify(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                size_t workspace_bytes, void* hip_stream) {
     return verify_with_workspace(problem, buf, workspace, workspace_bytes, hip_stream);
+}
+
+// For tests, not in the header: mpv_verify with the members of a team on different chiplets (consecutive workgroups), where
+// they exchange words at device scope.  No other call can choose this layout, and nothing but the layout differs.
+int mpv_test_verify_teams_apart(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
+                                size_t workspace_bytes, void* hip_stream) {
+    return verify_with_workspace(problem, buf, workspace, workspace_bytes, hip_stream, false, false, nullptr, nullptr, true);
 }
 
 int mpv_verify_static(const mpv_problem* problem, const mpv_buffers* buf, void* hip_stream) {
@@ -3629,10 +3645,11 @@ int mpv_verify_static(const mpv_problem* problem, const mpv_buffers* buf, void* 
 
 static int verify_with_workspace(const mpv_problem* problem, const mpv_buffers* buf, void* workspace,
                                  size_t workspace_bytes, void* hip_stream, bool part_of_batch, bool keep_counters,
-                                 const int32_t* context_node, const int32_t* shapes) {
+                                 const int32_t* context_node, const int32_t* shapes, bool teams_apart) {
     mpv::Plan plan;
     const int rc = mpv::validate(problem, &plan);
     if (rc != MPV_OK) return rc;
+    plan.teams_apart = teams_apart;
     if (shapes) {
         memset(plan.class_tasks, 0, sizeof(plan.class_tasks));
         mpv::TreeScan scan;

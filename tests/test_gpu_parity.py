@@ -545,6 +545,29 @@ def test_a_draw_at_a_leaf_weighs_its_waves_exactly_against_each_other():
     assert off <= 1e-7
 
 
+@pytest.mark.parametrize("V,dtype,B,members", [(20000, "bf16", 300, 2), (12500, "f32", 100, 4), (60000, "bf16", 90, 8), (50001, "bf16", 37, 7), (262144, "bf16", 2, 16)])
+@pytest.mark.parametrize("method", ALL_METHODS)
+def test_teams_whose_members_are_on_different_chiplets(method, V, dtype, B, members, monkeypatch):
+    """Consecutive workgroups run on different chiplets: a team of them counts its members there and exchanges words at device
+    scope, which no launch of the library chooses.  (members: of the top-down rules' teams.  K = 3, trunk 1, chains of 2: draws, branches and drawn tokens that are followed;
+    the drafted tokens of a tree come from a few, so that they are.)"""
+    announce("teams apart", METHOD_NAME[method], B, V, dtype, members)
+    lib = mpv.binding.load_library()
+    apart = lib.mpv_test_verify_teams_apart
+    apart.restype, apart.argtypes = lib.mpv_verify.restype, lib.mpv_verify.argtypes
+    cfg = workloads.Config("apart", B=B, V=V, K=3, L1=1, L2=2, dtype=dtype, T=0.8,
+                           methods=[method], draft_sigma=3.0, target_sigma=1.0, seed=83 + V)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    together = [run_library(inputs, cfg.T, method, debug=debug) for debug in (True, False)]
+    monkeypatch.setattr(lib, "mpv_verify", apart)
+    for expect, debug in zip(together, (True, False)):
+        got = run_library(inputs, cfg.T, method, debug=debug)
+        assert got["counters"][4] == 0
+        for key in ("accept_len", "path_nodes", "path_tokens", "bonus_token") + (("accept_prob", "final_residual") if debug else ()):
+            assert np.array_equal(got[key], expect[key]), key                        # (the same parts, the same order of additions)
+    compare_with_oracle(method, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, max(1, B // 10)), check_debug=False)
+
+
 def test_out_of_range_tokens_are_counted_not_followed():
     announce("bad tokens")
     cfg = workloads.Config("badtok", B=3, V=500, K=2, L1=0, L2=2, dtype="f32", T=1.0,
