@@ -22,7 +22,8 @@
 //                            token by inverse CDF from the residual of the stopping node.
 //                            (NSS, Naive, SpecTr: one per draw of the token-following walk.)
 //                          The top-down rules draw as a part of the walk instead (draw_walk), from the part on chip.
-//   short_part_kernel      the same for top-down rules whose parts the registers hold
+//   walk_kernel, short_part_kernel, staged_part_kernel    the same for walks of the top-down rules, and for parts that the
+//                          registers hold (with draws, and without)
 // mpv_verify_merged (a shape per tree) adds shape_kernel, which works out every tree's tables.
 // mpv_block_efficiency and mpv_acceptance_rates run the same kernels with every node task and
 // no uniforms (see Args::estimate); mpv_nucleus_mask is a kernel of its own (mpv_nucleus.h).
@@ -105,8 +106,6 @@ struct QueuePlan {
     int32_t box_step;                    // words from one team's mailbox to the next
     int32_t same_xcd;                    // members of a team are 8 workgroup numbers apart (one chiplet, its L2)
     int32_t spare;                       // teams are left over from the start (not counting those that whole chiplets add)
-    int32_t ahead;                       // a part leaves the LDS free: the rows that will likely be next are asked for there (see launch_all)
-    int32_t draw_here;                   // top-down rules: node tasks draw the tokens themselves, from the part on chip (see launch_all)
 };
 
 constexpr int kMaxTeam = 16;                          // workgroups per team, at most
@@ -230,8 +229,10 @@ constexpr int kWorkerSlots = 8;                       // mailboxes per dispatche
 constexpr int kMaxTeams = kWave * kWorkerSlots;
 static_assert(kMaxTeams <= kMailboxWords, "a mailbox for every team");
 constexpr int kKindAcceptance = 100;                   // node_task_kernel instantiation for the acceptance rates (see there)
-constexpr int kKindShort = 200;                        // top-down rules, parts that the registers hold (short_part_kernel)
-constexpr int method_of(int kind) { return kind == kKindAcceptance || kind == kKindShort ? MPV_METHOD_SPECINFER : kind; }
+constexpr int kKindWalk = 200;                         // top-down rules, walks that draw their tokens themselves (walk_kernel)
+constexpr int kKindShort = 300;                        // ... on parts that the registers hold (short_part_kernel)
+constexpr int kKindShortAll = 400;                     // such parts without draws: every node's task, estimates (staged_part_kernel)
+constexpr int method_of(int kind) { return kind >= kKindAcceptance ? MPV_METHOD_SPECINFER : kind; }
 
 // LDS of node_task_kernel that the functions it calls use as well (file scope, so that they address
 // it as LDS and not through generic pointers)
@@ -1061,8 +1062,8 @@ struct SweepCmd {
     int m, naive;                    // acceptance sweep: exponent, which formula (kCmdTask: m = the task)
     int claim;                       // a sweep: the second wave counts off a first task meanwhile (g_claim_number)
     int b, n;                        // kCmdTask: its tree and node;  a sweep: n = the node of `next`, in the same tree
-    int ahead, ahead_row;            // kCmdTask: the node of this tree whose rows are asked for when its first sweep is over (-1: none;
-                                     // ahead_row: only the target's, for a draw), by the waves that then wait
+    int ahead, ahead_row;            // kCmdTask: the node of this tree whose rows are asked for when its first sweep is over
+                                     // (ahead_row: only the target's, for a draw), by the waves that then wait (short_part_kernel)
     int next;                        // a sweep: the task this team goes on with when the sweep was the
                                      // current task's last (-1: not known); each wave asks for its share
                                      // of that task's rows as soon as it is done with its share of the sweep
@@ -1176,14 +1177,14 @@ template <class E> using TaskDraw = PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs>;
 template <class E, int KIND>
 __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_in) {
     using T = typename E::T;
-    constexpr bool ACCEPT = KIND == kKindAcceptance, SHORT = KIND == kKindShort;
+    constexpr bool ACCEPT = KIND == kKindAcceptance, SHORT = KIND == kKindShort, STAGED = SHORT || KIND == kKindShortAll;
     constexpr int METHOD = method_of(KIND);
     // Trees with shapes of their own: a task of another tree has its tables loaded here (Traversal), or it goes back to the
     // task loop, which loads them.  The top-down rules run this function through its whole length for SpecTr, and the loads
     // within it made plain batches of many trees slower (Naive, 204 trees of V = 7872: 246 us, 237 without); Traversal
     // has no such cost, and going back would make 256 trees of V = 151936 slower (538 us, 531).
     constexpr bool kShapeInTask = !ACCEPT && METHOD == MPV_METHOD_TRAVERSAL;
-    constexpr bool DRAWS = !ACCEPT && METHOD == MPV_METHOD_SPECINFER;
+    constexpr bool DRAWS = KIND == kKindWalk || SHORT;
     const Args& a = lds_launch().a;
     const Workspace& ws = lds_launch().ws;
     const QueuePlan& q = lds_launch().q;
@@ -1227,9 +1228,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     };
 
     // ---- the part of the pair this member keeps on chip while a task runs
-    RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs, SHORT> pair;
+    RetainedPart<E, kTaskBlock, kRegVecs, kLdsVecs, STAGED> pair;
     auto weigh_tiles = [&](float nAt, float nAd, float rho) __attribute__((always_inline)) {
-        PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs, SHORT> d(pair);
+        PartDraw<E, kTaskBlock, kRegVecs, kLdsVecs, STAGED> d(pair);
         d.f.init(k32, nAt, nAd, rho);
         d.weigh_pair(g_draw.tile, wave, lane);
         if (lane == 0) g_sh.partf[wave][0] = 0.f;
@@ -1287,7 +1288,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 if (nx >= 0) take_up(nx, view_at(cmd.b, cmd.n, false));     // this wave's slots are free again: the next task's rows
             }
             task_barrier();                                // A: this wave's partial sums are there
-            if (SHORT && kind == kCmdTask && uniform_i32(cmd.ahead) >= 0) {
+            if (SHORT && kind == kCmdTask) {
                 // every wave has its vectors in registers: the LDS is free
                 const NodeView nx = view_at(cmd.b, cmd.ahead, false);
                 TaskPart<E> then;
@@ -1348,7 +1349,8 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     };
     // What the scalar steps look up is kept in registers, a node (or a child) per lane: read from LDS or memory
     // one after the other, when needed, it was most of the time between the sweeps.
-    const int lazy = uniform_i32(a.lazy), walk = uniform_i32(a.walk);
+    const int lazy = DRAWS ? 1 : uniform_i32(a.lazy), walk = uniform_i32(a.walk);
+    auto estimate = [&]() __attribute__((always_inline)) { return !DRAWS && a.estimate != 0; };
     unsigned nodes = 0u;                              // the tree's tables, lane n: see below
     int tokens = -1;                                  // lane n: token and uniform of node n
     float uniforms = 2.f;
@@ -1371,11 +1373,10 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     load_tables();
     auto gather = [&](int from_lane, int v) __attribute__((always_inline)) { return __builtin_amdgcn_ds_bpermute(from_lane << 2, v); };
     // Walks draw their tokens in draw_walk, which is called next; a pair's tiles are weighed here, where it is on chip.
-    const int draws = DRAWS ? uniform_i32(q.draw_here) : 0;
-    // (If it knew that this is the same each time, the compiler would make paths of their own of it, which take 140 registers to private memory.)
+    // (On long parts, what the compiler knows makes paths of their own, which take dozens of registers to private memory.)
     auto draw_here = [&]() __attribute__((always_inline)) {
-        if constexpr (!DRAWS) return false;
-        int x = draws;
+        if constexpr (!DRAWS || SHORT) return DRAWS;
+        int x = 1;
         asm volatile("" : "+s"(x));
         return x != 0;
     };
@@ -1388,17 +1389,9 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         const bool ready = SHORT && t == ahead_task;
         if (SHORT) {
             // What comes next if it is accepted: the first child (its rows, or a leaf's target row).
-            ahead_node = -1;
-            ahead_row = false;
-            if (uniform_i32(q.ahead) != 0) {
-                const int first = field(node_word(field(node_word(v.n), kOff, 63u)), kEntry, 63u);
-                const bool inner = n_children(first) > 0;
-                if (inner || draw_here()) {
-                    ahead_node = first;
-                    ahead_row = !inner;
-                }
-            }
-            ahead_task = ahead_node >= 0 && !ahead_row ? v.b * N + ahead_node : -1;
+            ahead_node = field(node_word(field(node_word(v.n), kOff, 63u)), kEntry, 63u);
+            ahead_row = n_children(ahead_node) == 0;
+            ahead_task = !ahead_row ? v.b * N + ahead_node : -1;
             if (lane == 0) { g_cmd.ahead = ahead_node; g_cmd.ahead_row = ahead_row ? 1 : 0; }
         }
         if (lane == 0) { g_cmd.kind = kCmdTask; g_cmd.m = t; g_cmd.b = v.b; g_cmd.n = v.n; }
@@ -1416,7 +1409,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         if (new_tree) {
             const size_t at = static_cast<size_t>(v.b) * N + min(lane_here(), N - 1);
             tokens = as_global(a.tokens)[at];
-            if (!a.estimate) uniforms = as_global(a.uniforms)[at];
+            if (!estimate()) uniforms = as_global(a.uniforms)[at];
         }
         there = ready;
         if (!ready) pair.issue_loads();
@@ -1781,7 +1774,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
                 }
             } else if (!draw_here()) {
                 st_shared_f64(&ws.atest[bc], w_child);
-                if (a.estimate && walk == 3) {
+                if (estimate() && walk == 3) {
                     // App. D, SpecTr Branching: p_res(x), p_res = norm (p - rho* q)_+ (see the search above)
                     const double r = fmax(px - sp_rho * qx, 0.0);
                     st_shared_f64(&ws.aux[bc], sp_W > 0.0 ? fmin(r / sp_W, 1.0) : px);
@@ -1800,7 +1793,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
             break;
         }
 
-        if (METHOD == MPV_METHOD_SPECINFER && (walk >= 2 || draw_here()) && !a.estimate && lead && fabs(w_child - u_child) < 1e-6)
+        if (METHOD == MPV_METHOD_SPECINFER && (walk >= 2 || draw_here()) && !estimate() && lead && fabs(w_child - u_child) < 1e-6)
             atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_ACCEPT], 1u);     // (else these are counted by the walk)
         // SpecInfer moves into the first child it accepts: later children and this node's
         // residual are not needed (the same in every lane: no lane is left behind)
@@ -1817,7 +1810,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
         // NSS: nothing else to find out here
         if (METHOD == MPV_METHOD_SPECINFER && walk == 1) continue;
         // Naive (App. B, Alg. 2) tests the first child only; the token then drawn comes from (p - q)_+
-        if (METHOD == MPV_METHOD_SPECINFER && walk == 2 && !a.estimate) {
+        if (METHOD == MPV_METHOD_SPECINFER && walk == 2 && !estimate()) {
             c = 1.0;
             break;
         }
@@ -2057,7 +2050,7 @@ __device__ __attribute__((noinline)) void run_node_task(int task_in, int flags_i
     // no waiting): the sampling if this task settled the tree, else the first child that needs
     // its own task (Traversal) or the accepted child (SpecInfer).  The other children are queued.
     if (push_sample_i) {
-        if (!ACCEPT && a.estimate) {
+        if (!ACCEPT && estimate()) {
             // the expected block efficiency instead of a walk: scalar work over the tree's
             // per-node results, done here and now by this wave (there are no uniforms to walk with)
             estimate_wave<METHOD>(tree, ws, a, b);
@@ -2144,10 +2137,10 @@ task_end:
 
 template <class E, int KIND>
 __device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch) {
-    // KIND: MPV_METHOD_SPECINFER (all top-down rules) or MPV_METHOD_TRAVERSAL, kKindShort (top-down rules), or kKindAcceptance: the
+    // KIND: MPV_METHOD_TRAVERSAL; the top-down rules: MPV_METHOD_SPECINFER, kKindWalk, kKindShort, kKindShortAll; or kKindAcceptance: the
     // top-down kernel reduced to what the acceptance rates need (an instantiation of its own, so that
     // its extra sweeps do not weigh on the register allocation of the verification kernels)
-    constexpr bool ACCEPT = KIND == kKindAcceptance;
+    constexpr bool ACCEPT = KIND == kKindAcceptance, DRAWS = KIND == kKindWalk || KIND == kKindShort;
     constexpr int METHOD = method_of(KIND);
     __shared__ int sh_task, sh_flags;
     // The launch parameters and the tree tables are read from LDS, copied there from the
@@ -2327,7 +2320,6 @@ __device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch
     const int task = uniform_i32(sh_task), flags = uniform_i32(sh_flags);
     if (task == kTaskExit) break;
     const bool sampling = task >= a.B * a.N && task < a.B * a.N + a.B;
-    const bool draw_here = !ACCEPT && METHOD == MPV_METHOD_SPECINFER && uniform_i32(q.draw_here) != 0;
     // the leader's second wave, when the first is busy with a walk's end
     auto claim_ahead = [&]() __attribute__((always_inline)) {
         if (leader && threadIdx.x == kWave && g_loop.want_claim) {
@@ -2348,7 +2340,7 @@ __device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch
             atomicAdd(&ws.qctl[1], 1);
         }
     };
-    if (sampling && !draw_here) {
+    if (!DRAWS && sampling) {
         if (ACCEPT || a.estimate) {
             // no walk in these modes (there are no uniforms): scalar work of the leader's first
             // wave alone, whichever way the task came
@@ -2386,8 +2378,8 @@ __device__ __forceinline__ void run_tasks(const LaunchBlock* __restrict__ launch
         continue;
     }
     if (!sampling) run_node_task<E, KIND>(task, flags);
-    if constexpr (!ACCEPT && METHOD == MPV_METHOD_SPECINFER) {
-        if (!draw_here || !(sampling || uniform_i32(g_draw.pending) != 0)) continue;
+    if constexpr (DRAWS) {
+        if (!sampling && uniform_i32(g_draw.pending) == 0) continue;
         // the walk has come to a draw: the node task's that has just ended, or its first step
         claim_ahead();
         const int next = draw_walk<E>(sampling ? task - a.B * a.N : g_draw.b, sampling ? 0 : g_draw.n, sampling ? 1 : g_draw.row, sampling ? 0 : g_draw.there);
@@ -2407,16 +2399,31 @@ template <class E, int KIND>
 __global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
 void node_task_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, KIND>(launch); }
 
-// The top-down rules on parts that the registers hold (six vectors of a row per lane).  Their rows come through the LDS, and
+// The top-down rules where walks draw their tokens themselves (draw_walk) and nothing but the walks runs: neither estimates nor
+// debug outputs.  Kernels apart: with the draws, which it never uses, in its code and a question for them at every step
+// node_task_kernel took 22.5 us for the block efficiency of one tree of V = 6784 in float32 (NSS) and 65 for 41 trees of V = 4480
+// (Naive), without 21.2 and 60; and what a walk never uses taken out here, 32 trees of V = 262144, SpecInfer, take 66.2 us (67.8
+// before), 241 of V = 6295 63 (64.8), 200 of V = 136256, SpecTr, 168.5 (170.4).
+template <class E>
+__global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
+void walk_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, kKindWalk>(launch); }
+
+// The same on parts that the registers hold (six vectors of a row per lane).  Their rows come through the LDS, and
 // as soon as the first sweep has taken them from there the second to fourth wave ask for the rows of the first child,
 // which is where the walk goes on if it is accepted (for a leaf, the target row, for the draw): they travel while the
 // first wave exchanges sums and works out whether it is.  Without slots in LDS and beyond them the task function is
-// little more than half as long (68 KB, 113 in bf16; the instruction cache of two compute units has 64).  64 trees of V = 128256,
+// little more than half as long (65 KB, 108 in bf16; the instruction cache of two compute units has 64).  64 trees of V = 128256,
 // SpecInfer: a link of the chain 9.2 -> 8.3 us; calls: 37 trees of V = 50001, SpecTr, 79 -> 73 us, 2 of V = 1143 74 -> 64, 186 of V = 1974, Naive,
-// 61 -> 56, 26 of V = 5093, SpecInfer, 48 -> 46.  Traversal gained nothing by it (94 trees of V = 8515: 151 us, 157 with).
+// 61 -> 54, 26 of V = 5093, SpecInfer, 48 -> 46.  Traversal gained nothing by it (94 trees of V = 8515: 151 us, 157 with).
 template <class E>
 __global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
 void short_part_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, kKindShort>(launch); }
+
+// Estimates and debug outputs of the top-down rules on such parts: nothing is asked for ahead, and the shorter function alone is
+// worth it (block efficiency of 212 trees of V = 1474, NSS: 156 us by node_task_kernel, 145 by this; 178 of V = 2475, SpecInfer: 122, 114).
+template <class E>
+__global__ __launch_bounds__(kTaskBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) __attribute__((disable_tail_calls))
+void staged_part_kernel(const LaunchBlock* __restrict__ launch) { run_tasks<E, kKindShortAll>(launch); }
 
 // ------------------------------------------------------------------ walk
 //
@@ -3444,7 +3451,8 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     }
     for (int c = 0; c <= q.nclass; ++c) tree.class_off[c] = q.off[c];
     const int tasks = q.off[q.nclass];
-    static const int per_cu[3] = {min(resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>), resident_per_cu(short_part_kernel<E>)),
+    static const int per_cu[3] = {min(min(resident_per_cu(node_task_kernel<E, MPV_METHOD_SPECINFER>), resident_per_cu(staged_part_kernel<E>)),
+                                      min(resident_per_cu(walk_kernel<E>), resident_per_cu(short_part_kernel<E>))),
                                   resident_per_cu(node_task_kernel<E, MPV_METHOD_TRAVERSAL>),
                                   resident_per_cu(node_task_kernel<E, kKindAcceptance>)};
     // Tasks that do not depend on each other: every node's for the acceptance rates.  (A rate is 1 less a mass: with other
@@ -3469,15 +3477,14 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
     q.team_size = shape.team_size;
     q.part_vecs = shape.part_vecs;
     q.same_xcd = plan.teams_apart ? 0 : shape.same_xcd;
+    // Walks draw their tokens themselves where the last slot of a part is kept, or is the one that a sweep reads again; longer
+    // parts are drawn from by sample_task, like the calls with debug outputs of the draw (64 trees of V = 128256, SpecInfer: 88 us by it, 82
+    // by draw_walk).
+    const bool draws = top_down && a.lazy && !a.estimate && !a.dbg_accept && !a.dbg_resid && q.part_vecs <= kPartCapacity + kTaskBlock;
     // Up to four slots; six for SpecTr, which sweeps a part about seven times for one load.  With more the chip is full of teams
     // and loads, and what is asked for in vain holds the others up (64 trees of V = 128256, parts of 1 344 vectors: SpecInfer 73.2 us
     // by the other kernel, 74.9 by this, SpecTr 186 and 182; 64 of V = 32000, parts of 512: 65.2 and 62.9).
     const bool short_part = top_down && a.estimate != 2 && q.part_vecs <= (a.walk == 3 ? kRegVecs : 4) * kTaskBlock;
-    // (a walk's rows are asked for ahead only where just what it needs is computed)
-    q.ahead = short_part && a.lazy ? 1 : 0;
-    // Where the last slot of a part is kept, or is the one that a sweep reads again; longer parts are drawn from by sample_task,
-    // like the calls with debug outputs of the draw (64 trees of V = 128256, SpecInfer: 88 us by it, 82 by draw_walk).
-    q.draw_here = top_down && a.lazy && !a.estimate && !a.dbg_accept && !a.dbg_resid && q.part_vecs <= kPartCapacity + kTaskBlock ? 1 : 0;
     q.box_step = 16;                                   // a cache line each, while there is room for it
     while (q.teams * q.box_step > kMailboxWords) q.box_step /= 2;
     // (The few teams that launch_shape adds to fill whole chiplets are not meant: with them in the comparison the branching
@@ -3519,9 +3526,10 @@ static int launch_all(const mpv_problem* p, const Plan& plan, const Workspace& w
         const dim3 grid(static_cast<unsigned>(q.teams * q.team_size)), block(kTaskBlock);
         if (a.estimate == 2) {
             launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, kKindAcceptance>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
-        } else if (p->method != MPV_METHOD_TRAVERSAL) {      // NSS, Naive and SpecTr are variants of the top-down kernel
-            launch(MPV_KERNEL_NODE_TASK, short_part ? short_part_kernel<E> : node_task_kernel<E, MPV_METHOD_SPECINFER>, grid, block, s,
-                   const_cast<const LaunchBlock*>(ws.launch));
+        } else if (p->method != MPV_METHOD_TRAVERSAL) {      // NSS, Naive and SpecTr are variants of the top-down kernels
+            launch(MPV_KERNEL_NODE_TASK, draws ? (short_part ? short_part_kernel<E> : walk_kernel<E>)
+                                               : (short_part ? staged_part_kernel<E> : node_task_kernel<E, MPV_METHOD_SPECINFER>),
+                   grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         } else {
             launch(MPV_KERNEL_NODE_TASK, node_task_kernel<E, MPV_METHOD_TRAVERSAL>, grid, block, s, const_cast<const LaunchBlock*>(ws.launch));
         }

@@ -41,6 +41,17 @@ def test_so_do_the_kernels_for_short_parts(tmp_path):
         assert k[".vgpr_spill_count"] <= 5 and k[".private_segment_fixed_size"] <= 48, name
 
 
+@pytest.mark.skipif(not os.path.exists(f"{LLVM}/clang-offload-bundler"), reason="no LLVM tools of ROCm")
+@pytest.mark.parametrize("kernel", ["walk_kernel", "staged_part_kernel"])
+def test_so_do_the_kernels_of_walks_and_of_short_parts_without_draws(tmp_path, kernel):
+    """(Estimates and debug outputs run without the code of the draws, walks without that of the estimates.)"""
+    found = {n: k for n, k in kernels_of(mpv.lib_path(), tmp_path).items() if kernel in n}
+    assert len(found) == 2
+    for name, k in found.items():
+        assert k[".vgpr_count"] <= 168, name
+        assert k[".vgpr_spill_count"] <= 5 and k[".private_segment_fixed_size"] <= 48, name
+
+
 def test_rows_that_go_straight_to_lds_are_waited_for_before_they_are_read():
     """The compiler does not tie a read of LDS to the load that brings the row there: the source waits in between, and not only
     by what other loads there happen to need."""

@@ -104,6 +104,13 @@ def test_more_trees_than_workgroups_ragged_vocabulary(method):
     run_case(workloads.scaled(workloads.CONFIGS["v128k_delayed"], B=300, V=1003, dtype="f32"), method)
 
 
+@pytest.mark.parametrize("V,dtype", [(8192, "bf16"), (8200, "bf16"), (12288, "bf16"), (12296, "bf16"), (4099, "f32"), (6151, "f32")])
+@pytest.mark.parametrize("method", [SI, NSS, NAIVE, SPECTR])
+def test_parts_at_the_edge_of_what_the_registers_hold(method, V, dtype):
+    # one member: 4 slots (SpecTr: 6), one vector more; float32 rows that start at any address
+    run_case(workloads.Config("register edges", B=6, V=V, K=3, L1=1, L2=2, dtype=dtype, T=0.9, methods=[method], draft_sigma=1.5, target_sigma=0.8, seed=V), method)
+
+
 def small_vocabulary_inputs(parent, B, V, seed, dtype=torch.float32):
     """Rows N(0, 1.5^2) + noise, tokens uniform over a small vocabulary: equal-token siblings are frequent."""
     gen = torch.Generator(device="cuda")
