@@ -831,8 +831,12 @@ struct Team {
 // the L2, and every reader waits for memory: an exchange between 2 / 6 / 12 / 16 workgroups with nothing else to do took
 // 0.68 / 0.70 / 0.84 / 1.02 us with it and takes 0.35 / 0.40 / 0.43 / 0.44.  (64 trees of V = 128256, Traversal, 139 -> 133 us a
 // call; 32 of V = 262144 on teams of 16, SpecInfer, 79 -> 73; 256 of V = 151936, Traversal, 447 -> 433.)
+// (uniform_i32, and the rare side of the wait in swap_words marked as rare: the choice is one scalar branch then, not a masked
+// one.  The code of a task is longer than the instruction cache, so that calls of single-member teams, which exchange
+// nothing, paid for it: 35 trees of V = 1216, block efficiency, Traversal, 206 us before there was a choice, 211, now 207; 104 of
+// V = 1152 170, 177, 170; 5 of V = 2737, a call, 48.6, 49.7, 49.2.)
 __device__ __forceinline__ void st_team(const Team& t, unsigned long long* p, unsigned long long v) {
-    if (on_one_chiplet(t.seq)) __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (on_one_chiplet(static_cast<unsigned>(uniform_i32(static_cast<int>(t.seq))))) __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     else st_relaxed(p, v);
 }
 static_assert(kMaxTeam < (1 << kArrivedBits), "the counts of a team's arrivals fit their fields");
@@ -899,7 +903,7 @@ __device__ __forceinline__ int swap_words(const Team& t, unsigned mine, int coun
                 got[i] = static_cast<unsigned>(v[i]);
             }
             if (there) break;
-            if ((spin & 31u) == 0u && wall_clock64() - t.t_start > kLaunchTimeoutTicks) dead = 1;
+            if (__builtin_expect((spin & 31u) == 0u, 0) && wall_clock64() - t.t_start > kLaunchTimeoutTicks) dead = 1;
             __builtin_amdgcn_s_sleep(1);
         }
     }
