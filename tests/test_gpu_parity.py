@@ -447,6 +447,25 @@ def test_the_draw_at_the_edges_of_what_is_kept(method, V, dtype, B):
     assert rep["trees"] == min(B, 12)
 
 
+@pytest.mark.parametrize("V,dtype", [(8192, "bf16"), (8200, "bf16"), (8195, "bf16"), (12287, "bf16"), (12288, "bf16"), (12296, "bf16"), (4095, "f32"), (6145, "f32")])
+@pytest.mark.parametrize("method", ALL_METHODS[:1] + ALL_METHODS[2:])
+def test_a_child_s_rows_asked_for_ahead_at_the_edges_of_what_the_registers_hold(method, V, dtype):
+    """Parts of 4 slots (SpecTr: 6), the most of the kernel that asks for the first child's pair while its parent is tested, and
+    one vector to either side: walks on through an inner first child (taken up from where it lies), through the second
+    (what was asked for is overwritten) or neither.  Rows of a child start at other offsets than their parent's."""
+    announce("ahead edges", METHOD_NAME[method], V, dtype)
+    B = 400
+    cfg = workloads.Config("ahead edges", B=B, V=V, K=2, L1=0, L2=2, dtype=dtype, T=0.9, methods=[method], draft_sigma=2.5, target_sigma=1.0, seed=101 + V)
+    inputs = workloads.make_inputs(cfg, "cuda")
+    got = run_library(inputs, cfg.T, method, debug=False)
+    assert got["counters"][4] == 0
+    compare_with_oracle(method, workloads.to_host(inputs), cfg.T, got, trees=range(0, B, 4), check_debug=False)
+    if method != NSS:                                 # (which tests nothing and asks for rows as it comes to them)
+        through = lambda child, length: np.any((got["path_nodes"][:, 0] == child) & (got["accept_len"] == length))
+        assert through(1, 1) and through(1, 2) and np.any(got["accept_len"] == 0)
+        assert method == NAIVE or (through(3, 1) and through(3, 2))          # (Naive comes to the second child by its draws alone)
+
+
 @pytest.mark.parametrize("V,dtype", [(1000, "f32"), (5003, "bf16"), (20000, "bf16"), (131072, "f32")])
 def test_a_draft_row_without_any_token_leaves_the_target_row_to_draw_from(V, dtype):
     """The draft row is masked throughout and so is the child's token in the target row: the child is rejected, no mass
