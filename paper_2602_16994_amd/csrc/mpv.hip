@@ -2592,6 +2592,23 @@ __device__ __forceinline__ void estimate_wave(const TreeDesc& tree, const Worksp
 
 // ------------------------------------------------------------------ bonus sample
 
+// The member whose share of a row contains u times the mass of all, lane m < team.size holding member m's mass (the others
+// 0): the first whose running total exceeds it and that has mass; rounding only: the last one that has mass.  into: how far
+// the target lies into that member's share.
+__device__ __forceinline__ int member_at(const Team& team, double mass, float u, double& into, double& total) {
+    double upto = mass;                                // sums along the row of lanes: member m and those before it
+    upto += dpp_f64<0x111>(upto);
+    upto += dpp_f64<0x112>(upto);
+    upto += dpp_f64<0x114>(upto);
+    upto += dpp_f64<0x118>(upto);
+    total = lane_f64(upto, team.size - 1);
+    const double target = static_cast<double>(u) * total;
+    const unsigned long long hit = __ballot(mass > 0.0 && upto > target), any = __ballot(mass > 0.0);
+    const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
+    into = target - lane_f64(dpp_f64<0x111>(upto), owner);
+    return owner;
+}
+
 // The vocabulary is split among the members in runs of whole wave tiles (64 vectors of 16 bytes, counted from the aligned
 // address at or before the row's start, so that rows of any offset are read with vector loads), in member order; tile i of
 // a member's run belongs to wave i % 4.  Each member adds up the masses r_v = (p_v - c q_v)_+ of its tiles (up to the common
@@ -2771,7 +2788,6 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
     const int l0 = min(lane * per_lane_tiles, my_tiles), l1 = min(l0 + per_lane_tiles, my_tiles);
     double run = 0.0, incl = 0.0;
     if (wave == 0) {
-        const int m = lane & 15;
         team.seq++;
         double v = g_sh.part[lane & 3][0];
         v += dpp_f64<0xB1>(v);
@@ -2782,20 +2798,11 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
             note_dead(team, swap_words<1>(team, half_of(v, lane & 1), 2, at, got));
         }
         const double mass = lane < team.size && !team.dead ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) : 0.0;
-        double upto = mass;                            // sums along the row of lanes: member m and those before it
-        upto += dpp_f64<0x111>(upto);
-        upto += dpp_f64<0x112>(upto);
-        upto += dpp_f64<0x114>(upto);
-        upto += dpp_f64<0x118>(upto);
-        const double total = lane_f64(upto, team.size - 1), before = dpp_f64<0x111>(upto);
-        const double target = static_cast<double>(u_draw) * total;
-        // the member whose run contains the target: the first whose running total exceeds it and that has mass;
-        // rounding only: the last one that has mass
-        const unsigned long long hit = __ballot(m == lane && mass > 0.0 && upto > target), any = __ballot(m == lane && mass > 0.0);
-        const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
+        double in_run, total;
+        const int owner = member_at(team, mass, u_draw, in_run, total);
         if (lane == 0) {
             sh_owner = owner;
-            sh_target = target - lane_f64(before, owner);
+            sh_target = in_run;
             sh_total = total;
         }
     } else if (wave == 1) {
@@ -2851,34 +2858,13 @@ __device__ __attribute__((noinline)) int sample_task(int b_in, int stop_in) {
             }
             float r[VEC];
             masses(vt, vd, r);
-            const float ls = lane_sum(r);
-            const double lsd = static_cast<double>(ls);
-            const double incl2 = wave_inclusive_scan(lsd);
-            const unsigned long long hit = __ballot(incl2 > rem && ls > 0.f);
-            int lane_owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
-            if (lane_owner < 0) {
-                const unsigned long long any = __ballot(ls > 0.f);
-                lane_owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
-            }
-            if (lane == lane_owner) {
-                double acc = incl2 - lsd;
-                int found = -1, last = 0;
-                double lo = acc, hi = acc;
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    const double ri = static_cast<double>(r[i]);
-                    if (ri > 0.0) last = i;
-                    if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
-                    acc += ri;
-                }
-                if (found < 0) { found = last; lo = rem; hi = rem; }
-                int tk = (t_lo + tile) * TILE - mis + lane * VEC + found;
-                if (tk >= V) tk = V - 1;
-                if (tk < 0) tk = 0;
+            bool near = false;
+            const int found = element_at(r, lane_sum(r), lane, rem, sh_total, near);
+            if (found >= 0) {
+                const int tk = min(max((t_lo + tile) * TILE - mis + lane * VEC + found, 0), V - 1);
                 if (k == 0) as_global(a.bonus)[b] = tk;          // (once in a walk, see draw_find)
                 sh_tok = tk;
-                const double gap = fmin(fabs(rem - lo), fabs(hi - rem));
-                if (gap < 1e-6 * sh_total) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
+                if (near) atomicAdd(&a.counters[MPV_COUNTER_NEAR_TIE_BONUS], 1u);
             }
         }
     }
@@ -2993,19 +2979,12 @@ __device__ __forceinline__ void draw_owner(Team& team, int slots, float u) {
     const bool live = lane < team.size && !team.dead;
     const float of_m = live ? __uint_as_float(got[2]) : OnlineLse::kFloor, team_unit = lane_f32(row_max(of_m), 0);
     const double mass = live ? __hiloint2double(static_cast<int>(got[1]), static_cast<int>(got[0])) * unit_ratio(of_m, team_unit) : 0.0;
-    double upto = mass;                                // sums along the row of lanes: member m and those before it
-    upto += dpp_f64<0x111>(upto);
-    upto += dpp_f64<0x112>(upto);
-    upto += dpp_f64<0x114>(upto);
-    upto += dpp_f64<0x118>(upto);
-    const double total = lane_f64(upto, team.size - 1), target = static_cast<double>(u) * total;
-    // the first member whose running total exceeds the target and that has mass; rounding only: the last one that has mass
-    const unsigned long long hit = __ballot(mass > 0.0 && upto > target), any = __ballot(mass > 0.0);
-    const int owner = hit ? __ffsll(static_cast<long long>(hit)) - 1 : any ? 63 - __clzll(static_cast<long long>(any)) : 0;
+    double in_part, total;
+    const int owner = member_at(team, mass, u, in_part, total);
     if (lane == 0) g_draw.owner = owner;
     if (owner != team.member) return;
     const double scale = unit_ratio(unit, team_unit);          // (this member has mass, or nobody has)
-    const double here = (target - lane_f64(dpp_f64<0x111>(upto), owner)) / scale;
+    const double here = in_part / scale;
     const unsigned long long hit_t = __ballot(in_tile > 0.0 && incl > here), any_t = __ballot(in_tile > 0.0);
     // (no mass anywhere: token 0, as in sample_task)
     const int tile = hit_t ? __ffsll(static_cast<long long>(hit_t)) - 1 : any_t ? 63 - __clzll(static_cast<long long>(any_t)) : 0;

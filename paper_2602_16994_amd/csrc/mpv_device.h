@@ -941,6 +941,36 @@ struct ResidualMassRawF {
     __device__ __forceinline__ double total() const { return 2.0 * (static_cast<double>(acc0) + static_cast<double>(acc1)); }
 };
 
+// ---------------------------------------------------------------- drawing a token
+//
+// The element at which the running mass of a wave's vectors (lane after lane, `of_lane` the sum of a lane's masses) passes
+// `rem`; rounding only: the last one that has mass.  Returned in its lane, -1 in the others.  near: `rem` lies within 1e-6 of
+// `total` from one of the element's own ends.
+template <int VEC>
+__device__ __forceinline__ int element_at(const float (&r)[VEC], float of_lane, int lane, double rem, double total, bool& near) {
+    const double mine = static_cast<double>(of_lane), incl = wave_inclusive_scan(mine);
+    const unsigned long long hit = __ballot(incl > rem && of_lane > 0.f);
+    int owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
+    if (owner < 0) {
+        const unsigned long long any = __ballot(of_lane > 0.f);
+        owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
+    }
+    if (lane != owner) return -1;
+    double acc = incl - mine;
+    int found = -1, last = 0;
+    double lo = acc, hi = acc;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+        const double ri = static_cast<double>(r[i]);
+        if (ri > 0.0) last = i;
+        if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
+        acc += ri;
+    }
+    if (found < 0) { found = last; lo = rem; hi = rem; }
+    near = fmin(fabs(rem - lo), fabs(hi - rem)) < 1e-6 * total;
+    return found;
+}
+
 // ---------------------------------------------------------------- drawing a token from the part on chip
 //
 // The draw (inverse CDF in vocabulary order) of a part that is on chip, of a pair after its sweeps or of a target row alone,
@@ -1100,28 +1130,8 @@ struct PartDraw {
             else pair_masses(a, d, false, r);
             first = p.head + (p.v0 + (t - 1) * kWave) * VEC;
         }
-        const float ls = sum(r);
-        const double lsd = static_cast<double>(ls), incl = wave_inclusive_scan(lsd);
-        const unsigned long long hit = __ballot(incl > rem && ls > 0.f);
-        int owner = hit ? (__ffsll(static_cast<long long>(hit)) - 1) : -1;
-        if (owner < 0) {
-            const unsigned long long any = __ballot(ls > 0.f);
-            owner = any ? (63 - __clzll(static_cast<long long>(any))) : 0;
-        }
-        if (lane != owner) return -1;
-        double acc = incl - lsd;
-        int found = -1, last = 0;
-        double lo = acc, hi = acc;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            const double ri = static_cast<double>(r[i]);
-            if (ri > 0.0) last = i;
-            if (found < 0 && ri > 0.0 && acc + ri > rem) { found = i; lo = acc; hi = acc + ri; }
-            acc += ri;
-        }
-        if (found < 0) { found = last; lo = rem; hi = rem; }
-        near = fmin(fabs(rem - lo), fabs(hi - rem)) < 1e-6 * total;
-        return min(max(first + lane * step + found, 0), p.V - 1);
+        const int found = element_at(r, sum(r), lane, rem, total, near);
+        return found < 0 ? -1 : min(max(first + lane * step + found, 0), p.V - 1);
     }
 };
 
