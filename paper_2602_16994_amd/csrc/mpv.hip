@@ -7,7 +7,8 @@
 //                          A team splits every logit row by vocabulary range: each member keeps its
 //                          part of the task's (target, draft) row pair on chip (registers + LDS),
 //                          and every V-wide sum is a local partial plus one exchange of a few
-//                          words between the members (through memory; about a microsecond).
+//                          words between the members (through the L2 of their chiplet, 0.4 us; through
+//                          memory, 0.7 to 1, where they are not on one).
 //                          Node task, one per (tree, internal node) the rule needs:
 //                            softmax statistics of the node's target and draft rows, then,
 //                            for each child in list order, the probability the child is
@@ -3344,7 +3345,7 @@ static int compute_units() {
 // How a launch is shaped: G workgroups per team so that a member's part of a row fits on chip
 // (kMaxTeam at most: beyond that the rest of a part is re-read in every sweep), as many teams
 // as there are tasks at once (see launch_all), three workgroups per compute unit at most.
-constexpr int kShortPart = 1024;                      // vectors of a row per member, see launch_shape
+constexpr int kWantedPart = 1024;                     // vectors of a row per member where there are members to spare, see launch_shape
 struct Shape { int team_size, teams, part_vecs, same_xcd; };
 
 // Workgroups of a task kernel that one compute unit holds at a time, as the runtime computes it
@@ -3375,7 +3376,7 @@ static Shape launch_shape(const mpv_problem* p, int tasks, int64_t independent, 
     while (g < kMaxTeam && static_cast<long long>(g) * (kPartCapacity + kTaskBlock / 2) < nvec) ++g;
     const int fewest = g;
     while (g < kMaxTeam && slots / (g + 1) >= p->B && static_cast<long long>(g) * 2048 < nvec) ++g;
-    while (teams_wanted > 0 && g < kMaxTeam && slots / (g + 1) >= teams_wanted && static_cast<long long>(g) * kShortPart < nvec) ++g;
+    while (teams_wanted > 0 && g < kMaxTeam && slots / (g + 1) >= teams_wanted && static_cast<long long>(g) * kWantedPart < nvec) ++g;
     auto teams_of = [&](int size) {
         const int most = max(1, min(slots / size, kMaxTeams));
         int teams = max(1, min(most, tasks));

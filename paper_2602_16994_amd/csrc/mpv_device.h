@@ -898,7 +898,7 @@ struct AcceptanceF {
     }
 };
 
-// The node task's form of it.  Both exponents are lowered by one, so that every term is below
+// The node task's form of it.  Both exponents are lowered by one (exactly, see rounded_partition), so that every term is below
 // 1 and "(x)_+" can be the clamp to [0, 1] that the multiply-add applies to its own result (one
 // instruction less per element); total() undoes the halving.
 // BY_VECTOR (acceptance rates): added as AcceptanceF adds.
