@@ -832,7 +832,7 @@ struct Team {
 // the L2, and every reader waits for memory: an exchange between 2 / 6 / 12 / 16 workgroups with nothing else to do took
 // 0.68 / 0.70 / 0.84 / 1.02 us with it and takes 0.35 / 0.40 / 0.43 / 0.44.  (64 trees of V = 128256, Traversal, 139 -> 133 us a
 // call; 32 of V = 262144 on teams of 16, SpecInfer, 79 -> 73; 256 of V = 151936, Traversal, 447 -> 433.)
-// (uniform_i32, and the rare side of the wait in swap_words marked as rare: the choice is one scalar branch then, not a masked
+// (uniform_i32, and the rare side of an exchange's wait marked as rare: the choice is one scalar branch then, not a masked
 // one.  The code of a task is longer than the instruction cache, so that calls of single-member teams, which exchange
 // nothing, paid for it: 35 trees of V = 1216, block efficiency, Traversal, 206 us before there was a choice, 211, now 207; 104 of
 // V = 1152 170, 177, 170; 5 of V = 2737, a call, 48.6, 49.7, 49.2.)
